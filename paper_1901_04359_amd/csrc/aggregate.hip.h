@@ -13,6 +13,11 @@ constexpr int kAggMaxP = 1024;         // workers, at most
 constexpr int kAggRangeLog2 = 13;
 static_assert((1 << kAggRangeLog2) == kAggRange, "range size");
 
+constexpr int kFewP = 32;              // k_scatter_mean_few: one bit of a word per worker
+constexpr int kFewRange = 4096;        // its dense elements per block: half a range of the bounds
+constexpr int kFewBlock = 512;
+static_assert(kAggRange % kFewRange == 0, "a block's elements lie in one range");
+
 // bounds[g][b] = number of entries of worker g's (index-ascending) k-set with index below
 // b * kAggRange, for b = 0 .. nranges: the slices that k_scatter_mean's blocks take.  One
 // binary search per bound; the searches of neighbouring bounds share their first probes.
@@ -153,6 +158,113 @@ __global__ __launch_bounds__(kBlock) void k_scatter_mean(
         }
     } else {
         for (uint32_t i = t; i < span; i += kBlock) out[i] = acc[i] / divisor;
+    }
+}
+
+// The same for at most 32 workers.  What bounded k_scatter_mean was latency: with a bid per
+// element its 74 KB of LDS leave two blocks of four waves per CU, and every round of bids costs
+// three barriers.  Here a block owns kFewRange elements (33 KB: four blocks of eight waves per
+// CU) and, instead of a bid, keeps per element the set of workers of the batch that hold it, one
+// bit each: an entry's turn is the number of lower workers in that set, so turns need one barrier
+// each and no vote.  A block reads its whole 8192-element range's entries and drops those of the
+// other half: P * k entries read twice, against m elements written once.
+__global__ __launch_bounds__(kFewBlock) void k_scatter_mean_few(
+        const uint32_t* __restrict__ loc_idx, const float* __restrict__ loc_val, uint32_t P,
+        uint32_t k, uint32_t m, const uint32_t* __restrict__ bounds, uint32_t nranges,
+        float divisor, float* __restrict__ dense) {
+    constexpr int kEpt = 4;
+    constexpr uint32_t kParts = kAggRange / kFewRange;
+    __shared__ __align__(16) float acc[kFewRange];
+    __shared__ __align__(16) uint32_t who[kFewRange];      // workers of the batch that hold the element
+    __shared__ uint32_t s_lo[kFewP];                       // first entry of worker g inside the range
+    __shared__ uint32_t s_off[kFewP + 1];                  // entries of workers < g inside the range
+    __shared__ uint32_t s_last;                            // last turn of the batch
+    const uint32_t t = threadIdx.x;
+    const uint32_t range = blockIdx.x / kParts;
+    const uint32_t base = range * (uint32_t)kAggRange + (blockIdx.x % kParts) * (uint32_t)kFewRange;
+    if (base >= m) return;                                 // block-uniform
+    const uint32_t span = m - base < (uint32_t)kFewRange ? m - base : (uint32_t)kFewRange;
+    if (t < (uint32_t)kWave) {
+        uint32_t lo = 0, hi = 0;
+        if (t < P) {
+            const uint32_t* bg = bounds + (size_t)t * (nranges + 1) + range;
+            lo = bg[0];
+            hi = bg[1];
+            // always lo <= hi <= k for a sorted set; keeps every access in bounds for any other
+            if (hi > k) hi = k;
+            if (lo > hi) lo = hi;
+        }
+        const uint32_t incl = wave_incl_scan(hi - lo);
+        if (t < P) {
+            s_lo[t] = lo;
+            s_off[t + 1] = incl;
+        }
+        if (t == 0) { s_off[0] = 0u; s_last = 0u; }
+    }
+    for (uint32_t i = 4 * t; i < (uint32_t)kFewRange; i += 4 * kFewBlock) {
+        *reinterpret_cast<float4*>(&acc[i]) = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+        *reinterpret_cast<uint4*>(&who[i]) = make_uint4(0u, 0u, 0u, 0u);
+    }
+    __syncthreads();
+    const uint32_t total = s_off[P];
+    for (uint32_t c0 = 0; c0 < total; c0 += kFewBlock * kEpt) {
+        uint32_t ei[kEpt], eg[kEpt];
+        float ev[kEpt];
+        bool mine[kEpt];
+#pragma unroll
+        for (int u = 0; u < kEpt; ++u) {
+            const uint32_t e = c0 + u * kFewBlock + t;
+            mine[u] = e < total;
+            ei[u] = 0; eg[u] = 0; ev[u] = 0.0f;
+            if (mine[u]) {
+                uint32_t lo = 0, hi = P;                   // the last g with s_off[g] <= e
+                while (hi - lo > 1) {
+                    const uint32_t mid = (lo + hi) >> 1;
+                    if (s_off[mid] <= e) lo = mid; else hi = mid;
+                }
+                const size_t j = (size_t)lo * k + s_lo[lo] + (e - s_off[lo]);
+                eg[u] = lo;
+                ei[u] = loc_idx[j] - base;
+                ev[u] = loc_val[j];
+            }
+        }
+#pragma unroll
+        for (int u = 0; u < kEpt; ++u) {
+            mine[u] = mine[u] && ei[u] < (uint32_t)kFewRange;      // not the other half's
+            if (mine[u]) atomicOr(&who[ei[u]], 1u << eg[u]);
+        }
+        __syncthreads();
+        uint32_t turn[kEpt], last = 0;
+#pragma unroll
+        for (int u = 0; u < kEpt; ++u) {
+            turn[u] = mine[u] ? (uint32_t)__popc(who[ei[u]] & ((1u << eg[u]) - 1u)) : 0u;
+            last = turn[u] > last ? turn[u] : last;
+        }
+        if (last) atomicMax(&s_last, last);
+        __syncthreads();
+        last = s_last;
+        for (uint32_t r = 0; r <= last; ++r) {             // block-uniform
+            if (r) __syncthreads();
+#pragma unroll
+            for (int u = 0; u < kEpt; ++u)
+                if (mine[u] && turn[u] == r) acc[ei[u]] = acc[ei[u]] + ev[u];
+        }
+        // (every turn has been worked out before the barrier above: the sets can be cleared)
+#pragma unroll
+        for (int u = 0; u < kEpt; ++u)
+            if (mine[u]) who[ei[u]] = 0u;
+        __syncthreads();
+        if (t == 0) s_last = 0u;                           // read by all, set again behind a barrier
+    }
+    float* out = dense + base;                             // 16-byte aligned: base is a multiple of kFewRange
+    if (span == (uint32_t)kFewRange) {
+        for (uint32_t i = 4 * t; i < (uint32_t)kFewRange; i += 4 * kFewBlock) {
+            const float4 a = *reinterpret_cast<const float4*>(&acc[i]);
+            *reinterpret_cast<float4*>(out + i) =
+                make_float4(a.x / divisor, a.y / divisor, a.z / divisor, a.w / divisor);
+        }
+    } else {
+        for (uint32_t i = t; i < span; i += kFewBlock) out[i] = acc[i] / divisor;
     }
 }
 

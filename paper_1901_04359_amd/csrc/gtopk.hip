@@ -931,8 +931,14 @@ int gtopk_topk_allreduce(const uint32_t* loc_idx, const float* loc_val, int32_t 
     uint32_t* bounds = reinterpret_cast<uint32_t*>(ws);
     hipLaunchKernelGGL(k_slice_bounds, dim3(ceil_div(nranges + 1, kBlock), (uint32_t)P), dim3(kBlock),
                        0, st, loc_idx, (uint32_t)k, nranges, bounds);
-    hipLaunchKernelGGL(k_scatter_mean, dim3(nranges), dim3(kBlock), 0, st, loc_idx, loc_val,
-                       (uint32_t)P, (uint32_t)k, (uint32_t)m, bounds, nranges, (float)P, dense);
+    // up to 32 workers' turns at an element fit a word
+    if (P <= kFewP)
+        hipLaunchKernelGGL(k_scatter_mean_few, dim3(nranges * (kAggRange / kFewRange)), dim3(kFewBlock), 0, st,
+                           loc_idx, loc_val, (uint32_t)P, (uint32_t)k, (uint32_t)m, bounds, nranges, (float)P,
+                           dense);
+    else
+        hipLaunchKernelGGL(k_scatter_mean, dim3(nranges), dim3(kBlock), 0, st, loc_idx, loc_val,
+                           (uint32_t)P, (uint32_t)k, (uint32_t)m, bounds, nranges, (float)P, dense);
     return launch_status();
 }
 
