@@ -207,6 +207,13 @@ __global__ __launch_bounds__(kFewBlock) void k_scatter_mean_few(
     }
     __syncthreads();
     const uint32_t total = s_off[P];
+    if (total == 0u) {                                     // nobody holds anything here (block-uniform)
+        for (uint32_t i = 4 * t; i < span; i += 4 * kFewBlock) {
+            if (i + 4 <= span) *reinterpret_cast<float4*>(dense + base + i) = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+            else for (uint32_t j = i; j < span; ++j) dense[base + j] = 0.0f;
+        }
+        return;
+    }
     for (uint32_t c0 = 0; c0 < total; c0 += kFewBlock * kEpt) {
         uint32_t ei[kEpt], eg[kEpt];
         float ev[kEpt];
