@@ -122,7 +122,19 @@ uint32_t groups_for(uint32_t sets) {
 }
 
 constexpr uint64_t kInlineFinishMax = 1u << 20;  // sets up to this many slots: no k_finish
-constexpr uint32_t kUnionPathMinK = 131072;      // sets above this size take k_union_path
+// Which union: one entry per thread with a search of its own (k_union: short chains, latency) or eight
+// slots per thread cut by output position (k_union_path: less work per slot, throughput).  Sets above
+// kUnionPathMinK take the latter; smaller ones do once the launch holds enough entries to be bound
+// by throughput.  A merge call in us, k_union / k_union_path, for batches of 1, 4 and 16 pairs:
+//   k = 100,000   28.5 / 29.6   41.0 / 39.2   73.6 / 58.2
+//   k =  50,000   26.3 / 28.0   32.2 / 33.2   58.0 / 52.0
+//   k =  25,000        -        29.0 / 31.0   43.2 / 42.6
+constexpr uint32_t kUnionPathMinK = 131072;
+constexpr uint64_t kUnionPathMinEntries = 3u << 17;      // of one operand, all pairs together
+constexpr uint32_t kUnionPathFewK = 16384;               // at least four tiles per pair
+inline bool union_by_path(uint32_t k, uint32_t batch) {
+    return k > kUnionPathMinK || (k >= kUnionPathFewK && (uint64_t)k * batch >= kUnionPathMinEntries);
+}
 constexpr int kUnionPathEpt = 8;
 constexpr int kUnionHistBlock = 1024;           // threads per block of the union that also histograms
 constexpr uint32_t kUnionCutsMinK = 1u << 19;   // sets above this size: cut points in a kernel of their own
@@ -559,10 +571,10 @@ void do_merge_batch(const uint32_t* a_idx, const float* a_val, const uint32_t* b
     ss.T_out = out_min;
     // The union runs in blocks as large as the histogram kernel's and counts the first digits
     // of the keys it produces, so the select below starts at its second kernel.
-    // small sets: one entry of either operand per thread (latency);
-    // large sets: cut by output position, eight slots per thread (throughput); for the
+    // small sets: one entry of either operand per thread (latency); large sets, or many: cut by
+    // output position, eight slots per thread (throughput), see union_by_path; for the
     // largest the blocks' cut points come from a kernel of their own
-    if (k <= kUnionPathMinK)
+    if (!union_by_path(k, batch))
         hipLaunchKernelGGL((k_union<1, kUnionHistBlock, true>), dim3(ceil_div(k, kUnionHistBlock), batch),
                            dim3(kUnionHistBlock), 0, st, a_idx, a_val, b_idx, b_val, k, in_stride, w.m_idx,
                            w.m_val, w.m_stride, zp, zw, src, ss);

@@ -1,0 +1,24 @@
+"""Parity at the sizes where the library changes kernels, against the CPU oracle, bit for bit."""
+import numpy as np
+import pytest
+
+from oracle import gtopk_oracle as orc
+from paper_1901_04359_amd import workloads as W
+from tests.gpu_harness import bits_equal, first_diff, say
+from tests.test_gpu_parity import run_merge
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("kind", ["gauss", "ties", "cancel"])
+@pytest.mark.parametrize("k,batch", [(16_383, 25), (16_384, 24), (24_577, 16), (24_575, 16)])
+def test_merge_batches_at_the_unions_border(kind, k, batch):
+    """Either side of the batch sizes at which a merge's union is cut by output position."""
+    m = 200_003
+    idx, val = W.ksets(2 * batch, k, m, seed=k + batch, overlap=0.4, value_kind=kind)
+    say(f"merge batches: kind={kind} k={k} batch={batch}")
+    gi, gv = run_merge(idx[0::2].copy(), val[0::2].copy(), idx[1::2].copy(), val[1::2].copy(), k)
+    for b in range(batch):
+        oi, ov = orc.merge(idx[2 * b], val[2 * b], idx[2 * b + 1], val[2 * b + 1], k)
+        assert np.array_equal(gi[b], oi), f"b={b} idx: {first_diff(gi[b], oi)}"
+        assert bits_equal(gv[b], ov), f"b={b} val: {first_diff(gv[b], ov)}"
