@@ -214,7 +214,7 @@ struct StepWs {
     uint32_t* ord_idx;     // [P][cap] candidates in index order
     float* ord_val;
     SelState sel;          // P sets
-    uint32_t cap, nchunks;
+    uint32_t cap, nchunks, chunk_log2;
     uint32_t Lc, gcand;    // candidate list: slots per group, groups
     uint32_t Ld, gdense;   // dense row: slots per group, groups
     // tree
@@ -255,15 +255,69 @@ static bool run_groups(int64_t m, uint32_t k) {
 }
 // (the few-launch path takes a smaller sample: one block per worker reads it)
 constexpr double kSampleMean = 256.0, kSampleMinTiles = 4096.0;
-constexpr double kSmallSampleMean = 16.0, kSmallSampleMinTiles = 128.0;
-SamplePlan plan_sample(int64_t m, uint32_t k, double sample_mean = kSampleMean,
-                       double min_tiles = kSampleMinTiles);
+constexpr double kSmallSampleMean = 16.0, kSmallSampleMin = 8192.0;
+SamplePlan plan_sample(int64_t m, uint32_t k, uint32_t tile, double sample_mean, double min_elements);
+
+// Medium problems: rows so short that the three launches in front of the pass (clear, k_sample,
+// k_sample_pick) weigh as much as it does, and a sample that one block per worker reads in one or two
+// rounds is enough: k_small_sample then does all three.  A step, three launches / one, in us:
+//   m = 200,000  P = 8  k = 20,000   131 -> 99       m = 100,000  P = 2  k = 1000    60 -> 50
+//   m = 1 M      P = 4  k = 1000      88 -> 77       m = 2 M      P = 32 k = 2000   277 -> 270
+// (the first two include what their shorter chunks give, see pass_chunk_log2).  A larger sample in one
+// block loses: 65,536 elements at m = 8 M, P = 4, k = 8000 take the step from 148 to 161 us.
+constexpr uint64_t kMidElements = 1ull << 26;            // of all rows together
+constexpr double kMidSampleMin = 16384.0, kMidSampleMax = 32768.0;
+// Expected sample rank of the k-th key.  At rank 16 the threshold keeps 2.5 k candidates on average with
+// a spread of a sixth; a list of 3 k + 8192 entries has room for that only while k is in the
+// thousands.  At rank 64 it keeps 1.7 k +- an eighth.
+static double mid_sample_mean(uint32_t k) { return k <= 4096u ? 16.0 : 64.0; }
+static bool mid_problem(int64_t m, uint32_t k, uint64_t P) {
+    return (uint64_t)m * P <= kMidElements && mid_sample_mean(k) * (double)m <= kMidSampleMax * (double)k &&
+           !merge_filtered(k) && !small_problem(m, k, (int64_t)P);
+}
+static SamplePlan plan_row_sample(int64_t m, uint32_t k, uint64_t P) {
+    return mid_problem(m, k, P) ? plan_sample(m, k, kMidSampleTile, mid_sample_mean(k), kMidSampleMin)
+                                : plan_sample(m, k, kSampleTile, kSampleMean, kSampleMinTiles * kSampleTile);
+}
+
+// Elements per block of the pass = per run of candidates: 2^15, less
+//   - where that gives fewer than 1024 blocks: a block that has a CU to itself reads at some 60 GB/s;
+//   - at densities from 0.6 % on (runs selected where they lie): a run is compacted, walked and
+//     emitted by one block or wave, and hot layers make some runs ten times as long as others.
+//     Shorter runs even that out until the blocks' fixed price in the emit outweighs it.
+// Measured, a step in us with chunks of 2^15 / 2^14 / 2^13 elements:
+//   m = 5 M   P = 8   k = 1 M      502 / 451 / 449      m = 2 M  P = 32  k = 400,000   780 / 675 / 661
+//   m = 5 M   P = 8   k = 50,000   210 /  -  / 195      m = 5 M  P = 32  k = 50,000    550 / 538 /  -
+//   m = 14 M  P = 16  k = 1.4 M   1282 / 1229 / 1245    m = 14 M P = 16  k = 140,000   645 / 688 /  -
+//   m = 25.6 M P = 32 k = 1.85 M  3616 / 3950 /  -      (k = 6.4 M: 6607 / 6775)
+static uint32_t pass_chunk_log2(int64_t m, uint32_t k, uint64_t P) {
+    const bool few = (uint64_t)m * P <= kMidElements;
+    const double rho = (double)k / (double)m;
+    const uint64_t most = rho >= 0.05 ? 16384 : (rho >= 0.006 ? 10240 : 0);      // blocks, all workers
+    uint32_t l = kChunkLog2;
+    while (l > 12 && ceil_div((uint64_t)m + 3, 1u << (l - 1)) <= (uint32_t)kMaxGroups &&
+           ((few && P * ceil_div((uint64_t)m + 3, 1u << l) < 1024) ||
+            (l > 13 && P * ceil_div((uint64_t)m + 3, 1u << (l - 1)) <= most)))
+        --l;
+    return l;
+}
 
 StepWs carve_step(void* ws, int64_t m, uint32_t k, uint32_t P) {
     Carver c{reinterpret_cast<char*>(ws)};
     StepWs s;
     s.cap = cand_capacity(m, k);
-    s.nchunks = ceil_div((uint64_t)m + 3, kChunk);      // a row may start up to 3 elements into a chunk
+    s.chunk_log2 = pass_chunk_log2(m, k, P);
+    s.nchunks = ceil_div((uint64_t)m + 3, 1u << s.chunk_log2);      // a row may start up to 3 elements into a chunk
+    const bool mid = mid_problem(m, k, P);
+    // The tables per chunk of medium problems are sized for the smallest chunks, so that the workspace of
+    // given k and P never shrinks as m grows, whatever the chunks: at most 28 bytes for each of
+    // 2048 chunks, and no sample histogram (64 KB per worker).
+    uint32_t table = s.nchunks;
+    if (mid) {
+        table = ceil_div((uint64_t)m + 3, 4096);
+        if (table > (uint32_t)kMaxGroups) table = (uint32_t)kMaxGroups;
+        if (table < s.nchunks) table = s.nchunks;
+    }
     {
         uint32_t g = kLocalTargetBlocks / P;
         g = g < 32 ? 32 : (g > (uint32_t)kMaxGroups ? (uint32_t)kMaxGroups : g);
@@ -276,20 +330,28 @@ StepWs carve_step(void* ws, int64_t m, uint32_t k, uint32_t P) {
     s.gdense = P == 1 ? (uint32_t)kMaxGroups : 1024u;
     s.Ld = group_slots_for((uint64_t)m, s.gdense);
     s.gdense = ceil_div((uint64_t)m, s.Ld);
-    s.samp_hist = c.take<uint32_t>((size_t)P * kSampleBins);
+    s.samp_hist = c.take<uint32_t>(mid ? 0 : (size_t)P * kSampleBins);
     s.cand_count = c.take<uint32_t>(P);
     s.tspec = c.take<uint32_t>(P);
     s.cand_idx = c.take<uint32_t>((size_t)P * s.cap);
     s.cand_val = c.take<float>((size_t)P * s.cap);
     // (the few-launch path for small problems cuts a row into runs of 4096 elements)
     const uint32_t nruns_small = small_problem(m, k, P) ? ceil_div((uint64_t)m + 3, kSmallChunk) : 0u;
-    s.run_table = c.take<uint2>((size_t)P * (s.nchunks > nruns_small ? s.nchunks : nruns_small));
-    s.run_off = c.take<uint32_t>((size_t)P * s.nchunks);
+    if (table < nruns_small) table = nruns_small;
+    // the sample histogram is dead when the pass writes its runs: short tables lie in its place
+    if (!mid && table <= (uint32_t)kMaxGroups) {
+        static_assert(kMaxGroups * (sizeof(uint2) + sizeof(uint32_t)) <= kSampleBins * sizeof(uint32_t), "fits");
+        s.run_table = reinterpret_cast<uint2*>(s.samp_hist);
+        s.run_off = s.samp_hist + (size_t)P * table * 2;
+    } else {
+        s.run_table = c.take<uint2>((size_t)P * table);
+        s.run_off = c.take<uint32_t>((size_t)P * table);
+    }
     s.ord_idx = c.take<uint32_t>((size_t)P * s.cap);
     s.ord_val = c.take<float>((size_t)P * s.cap);
     {
         uint32_t g = s.gcand > s.gdense ? s.gcand : s.gdense;
-        if (run_groups(m, k) && s.nchunks > g) g = s.nchunks;      // one group per run
+        if (run_groups(m, k) && table > g) g = table;      // one group per run
         s.sel = carve_select(c, P, s.cap, g, /*with_dense_hist=*/true);
     }
     const size_t pairs = P > 1 ? P / 2 : 1;
@@ -327,12 +389,16 @@ ZeroJob zero_job(uint32_t* p0 = nullptr, size_t n0 = 0, uint32_t* p1 = nullptr, 
     return ZeroJob{{p0, p1, p2, p3, p4, nullptr}, {n0, n1, n2, n3, n4, 0}};
 }
 
-void zero_async(hipStream_t st, const ZeroJob& job) {
+// blocks that clear the longest array of the job, `words` words each, at most 1024
+uint32_t zero_blocks(const ZeroJob& job, uint32_t words) {
     size_t n = 0;
     for (int a = 0; a < kZeroSlots; ++a) n = job.n[a] > n ? job.n[a] : n;
-    if (n == 0) return;
-    uint32_t blocks = (uint32_t)((n + 1023) / 1024 > 1024 ? 1024 : (n + 1023) / 1024);
-    hipLaunchKernelGGL(k_zero_u32, dim3(blocks ? blocks : 1), dim3(256), 0, st, job);
+    return (uint32_t)((n + words - 1) / words > 1024 ? 1024 : (n + words - 1) / words);
+}
+
+void zero_async(hipStream_t st, const ZeroJob& job) {
+    const uint32_t blocks = zero_blocks(job, 1024);
+    if (blocks) hipLaunchKernelGGL(k_zero_u32, dim3(blocks), dim3(256), 0, st, job);
 }
 
 // how a batch of sets is walked and emitted
@@ -385,21 +451,20 @@ void run_select(const Src& src, const SelState& ss0, const SelGrid& gr, uint32_t
 // (and then that worker is merely selected from its dense row).
 // sample_mean: expected sample rank of the k-th key, at least.  min_tiles: spread (with
 // 4096, a layer of 1 % of the row still gets ~40 tiles).
-SamplePlan plan_sample(int64_t m, uint32_t k, double sample_mean, double min_tiles) {
+SamplePlan plan_sample(int64_t m, uint32_t k, uint32_t tile, double sample_mean, double min_elements) {
     SamplePlan p;
     double want = sample_mean * (double)m / (double)k;
-    if (want < min_tiles * kSampleTile) want = min_tiles * kSampleTile;
+    if (want < min_elements) want = min_elements;
     if (want >= (double)m) {
-        p.tile_stride = kSampleTile;
+        p.tile_stride = tile;
     } else {
-        const uint64_t tiles = (uint64_t)(want / kSampleTile) + 1;
+        const uint64_t tiles = (uint64_t)(want / tile) + 1;
         const uint64_t ts = (uint64_t)m / tiles;
-        p.tile_stride = (uint32_t)(ts < (uint64_t)kSampleTile ? kSampleTile : ts);
+        p.tile_stride = (uint32_t)(ts < (uint64_t)tile ? tile : ts);
     }
     p.n_tiles = ceil_div((uint64_t)m, p.tile_stride);
     const uint64_t last = (uint64_t)m - (uint64_t)(p.n_tiles - 1) * p.tile_stride;
-    const uint64_t sampled = (uint64_t)(p.n_tiles - 1) * kSampleTile +
-                             (last < (uint64_t)kSampleTile ? last : (uint64_t)kSampleTile);
+    const uint64_t sampled = (uint64_t)(p.n_tiles - 1) * tile + (last < tile ? last : tile);
     if (sampled >= (uint64_t)m) {
         p.target = k;                        // the "sample" is the whole row: exact count
     } else {
@@ -429,7 +494,7 @@ bool pass_histograms(int64_t m, uint32_t k) {
 // the candidate lists (or dense rows) of the P workers as the select kernels' source
 CandSrc cand_source(const float* rows, int64_t stride, int64_t m, uint32_t k, const StepWs& w,
                     bool producer_hist, bool no_bounds, uint32_t* thr_state = nullptr) {
-    return CandSrc{rows, stride, (uint32_t)m, k, w.cap, w.nchunks, w.Lc, w.Ld,
+    return CandSrc{rows, stride, (uint32_t)m, k, w.cap, w.nchunks, w.chunk_log2, w.Lc, w.Ld,
                    w.cand_idx, w.cand_val, w.cand_count, w.tspec, w.run_table, w.run_off,
                    w.ord_idx, w.ord_val, producer_hist, no_bounds, reinterpret_cast<uint4*>(thr_state)};
 }
@@ -443,41 +508,57 @@ SelGrid local_grid(const StepWs& w, uint32_t P) {
     return SelGrid{P, gx, gx, (uint64_t)w.cap, false};
 }
 
+template <bool HIST>
+void launch_pass(const float* grad, float* residual, int64_t m, int64_t stride, uint32_t P, const StepWs& w,
+                 hipStream_t st) {
+    const dim3 grid(w.nchunks, P), block(kSBlock);
+#define GTOPK_PASS(ITERS)                                                                                   \
+    hipLaunchKernelGGL((k_accum_filter<HIST, ITERS>), grid, block, 0, st, grad, residual, (uint32_t)m,     \
+                       stride, w.tspec, w.cand_idx, w.cand_val, w.cap, w.cand_count, w.run_table, w.nchunks, \
+                       w.sel.hist)
+    static_assert(kIters == 16, "a chunk of 2^15 elements per block of 16 float4 per lane");
+    switch (w.chunk_log2) {
+        case 12: GTOPK_PASS(2); break;
+        case 13: GTOPK_PASS(4); break;
+        case 14: GTOPK_PASS(8); break;
+        default: GTOPK_PASS(16); break;
+    }
+#undef GTOPK_PASS
+}
+
 // `zero_rows`: store +0.0 at the selected entries (the stand-alone call); gtopk_step
-// passes false and settles the rows in k_restore_fused.  `pre_cleared`: the caller has
-// already cleared this call's counters and histograms.
+// passes false and settles the rows in k_restore_fused.  `job`: what the call needs cleared before
+// its select, the candidate counters among it.
 int do_local_select(const float* grad, float* residual, int64_t m, int64_t stride, uint32_t P,
                     uint32_t k, uint32_t* out_idx, float* out_val, const StepWs& w, bool zero_rows,
-                    bool pre_cleared, hipStream_t st, void* const* events = nullptr,
+                    const ZeroJob& job, hipStream_t st, void* const* events = nullptr,
                     uint32_t* thr_state = nullptr) {
-    // workers whose threshold is carried over from the previous call skip the sampling (both
+    // workers whose threshold is carried over from the previous call skip the sampling (the
     // kernels are launched all the same: who samples is decided on the device)
     const uint4* carry = reinterpret_cast<const uint4*>(thr_state);
-    if (!pre_cleared)
-        zero_async(st, zero_job(w.samp_hist, (size_t)(w.tspec - w.samp_hist), w.sel.hist,
-                                select_clear_words(w.sel)));
-
-    const SamplePlan sp = plan_sample(m, k);
-    uint32_t sblocks = ceil_div(sp.n_tiles, (kSampleBlock / kSampleTile) * 8);
-    // about 256 blocks in all: every block flushes its own 16384-bin histogram with atomics
-    const uint32_t sb_max = P >= 64 ? 4u : (P <= 16 ? 16u : 256u / P);
-    if (sblocks > sb_max) sblocks = sb_max;
-    if (sblocks < 1) sblocks = 1;
-    hipLaunchKernelGGL(k_sample, dim3(sblocks, P), dim3(kSampleBlock), 0, st, grad, residual,
-                       (uint32_t)m, stride, sp.tile_stride, sp.n_tiles, w.samp_hist, carry);
-    hipLaunchKernelGGL(k_sample_pick, dim3(P), dim3(kSampleBlock), 0, st, w.samp_hist, sp.target,
-                       w.tspec, carry);
+    const SamplePlan sp = plan_row_sample(m, k, P);
+    if (mid_problem(m, k, P)) {
+        const uint32_t zblocks = zero_blocks(job, 4 * kSmallBlock);
+        hipLaunchKernelGGL((k_small_sample<kMidSampleTile, true>), dim3(P + zblocks), dim3(kSmallBlock), 0, st, grad, residual,
+                           (uint32_t)m, stride, P, sp.tile_stride, sp.n_tiles, sp.target, w.tspec, w.cand_count,
+                           carry, job);
+    } else {
+        zero_async(st, job);
+        uint32_t sblocks = ceil_div(sp.n_tiles, (kSampleBlock / kSampleTile) * 8);
+        // about 256 blocks in all: every block flushes its own 16384-bin histogram with atomics
+        const uint32_t sb_max = P >= 64 ? 4u : (P <= 16 ? 16u : 256u / P);
+        if (sblocks > sb_max) sblocks = sb_max;
+        if (sblocks < 1) sblocks = 1;
+        hipLaunchKernelGGL(k_sample, dim3(sblocks, P), dim3(kSampleBlock), 0, st, grad, residual,
+                           (uint32_t)m, stride, sp.tile_stride, sp.n_tiles, w.samp_hist, carry);
+        hipLaunchKernelGGL(k_sample_pick, dim3(P), dim3(kSampleBlock), 0, st, w.samp_hist, sp.target,
+                           w.tspec, carry);
+    }
     mark_stage(1, events, st);
 
     const bool producer_hist = pass_histograms(m, k);
-    if (producer_hist)
-        hipLaunchKernelGGL(k_accum_filter<true>, dim3(w.nchunks, P), dim3(kSBlock), 0, st, grad,
-                           residual, (uint32_t)m, stride, w.tspec, w.cand_idx, w.cand_val, w.cap,
-                           w.cand_count, w.run_table, w.nchunks, w.sel.hist);
-    else
-        hipLaunchKernelGGL(k_accum_filter<false>, dim3(w.nchunks, P), dim3(kSBlock), 0, st, grad,
-                           residual, (uint32_t)m, stride, w.tspec, w.cand_idx, w.cand_val, w.cap,
-                           w.cand_count, w.run_table, w.nchunks, w.sel.hist);
+    if (producer_hist) launch_pass<true>(grad, residual, m, stride, P, w, st);
+    else launch_pass<false>(grad, residual, m, stride, P, w, st);
     mark_stage(2, events, st);
 
     const CandSrc src = cand_source(residual, stride, m, k, w, producer_hist, false, thr_state);
@@ -718,8 +799,10 @@ int gtopk_local_select(const float* grad, float* residual, int64_t m, int64_t st
         return GTOPK_EALIGN;
     const StepWs w = carve_step(ws, m, (uint32_t)k, (uint32_t)P);
     if (ws_bytes < w.bytes) return GTOPK_EWORKSPACE;
-    return do_local_select(grad, residual, m, stride, (uint32_t)P, (uint32_t)k, out_idx, out_val, w,
-                           true, false, (hipStream_t)stream);
+    return do_local_select(grad, residual, m, stride, (uint32_t)P, (uint32_t)k, out_idx, out_val, w, true,
+                           zero_job(w.samp_hist, (size_t)(w.tspec - w.samp_hist), w.sel.hist,
+                                    select_clear_words(w.sel)),
+                           (hipStream_t)stream);
 }
 
 int gtopk_merge(const uint32_t* a_idx, const float* a_val, const uint32_t* b_idx, const float* b_val,
@@ -789,10 +872,10 @@ static int step_impl(const float* grad, float* residual, int64_t m, int64_t stri
     float* lv = loc_val ? loc_val : w.loc_val;
     if (!events && !thr_state && small_problem(m, k, P)) {
         // one block per worker samples, picks the threshold and clears the candidate counter
-        const SamplePlan sp = plan_sample(m, (uint32_t)k, kSmallSampleMean, kSmallSampleMinTiles);
-        hipLaunchKernelGGL(k_small_sample, dim3(P), dim3(kSmallBlock), 0, st, grad, residual,
-                           (uint32_t)m, stride, sp.tile_stride, sp.n_tiles, sp.target, w.tspec,
-                           w.cand_count);
+        const SamplePlan sp = plan_sample(m, (uint32_t)k, kSampleTile, kSmallSampleMean, kSmallSampleMin);
+        hipLaunchKernelGGL((k_small_sample<kSampleTile, false>), dim3(P), dim3(kSmallBlock), 0, st, grad, residual,
+                           (uint32_t)m, stride, (uint32_t)P, sp.tile_stride, sp.n_tiles, sp.target, w.tspec,
+                           w.cand_count, (const uint4*)nullptr, ZeroJob{});
         // small blocks: one run per 4096 elements (the run table was carved for that many)
         const uint32_t nruns = ceil_div((uint64_t)m + 3, kSmallChunk);
         hipLaunchKernelGGL((k_accum_filter<false, kSmallIters>), dim3(nruns, P), dim3(kSBlock), 0, st,
@@ -808,11 +891,11 @@ static int step_impl(const float* grad, float* residual, int64_t m, int64_t stri
     mark_stage(0, events, st);
     // one clear for everything this step needs zeroed: the sampler's histograms and the
     // candidate counters; both selects' histograms and tickets; the global-set bitmap
-    zero_async(st, zero_job(w.samp_hist, (size_t)(w.tspec - w.samp_hist), w.sel.hist,
-                            select_clear_words(w.sel), w.mrg.sel.hist, select_clear_words(w.mrg.sel),
-                            w.mrg.sel_alt.hist, w.mrg.alt_clear_words, w.gbits, w.gbits_words));
+    const ZeroJob job = zero_job(w.samp_hist, (size_t)(w.tspec - w.samp_hist), w.sel.hist,
+                                 select_clear_words(w.sel), w.mrg.sel.hist, select_clear_words(w.mrg.sel),
+                                 w.mrg.sel_alt.hist, w.mrg.alt_clear_words, w.gbits, w.gbits_words);
     int rc = do_local_select(grad, residual, m, stride, (uint32_t)P, (uint32_t)k, li, lv, w, false,
-                             true, st, events, thr_state);
+                             job, st, events, thr_state);
     if (rc != GTOPK_OK) return rc;
     mark_stage(3, events, st);
     rc = do_tree(li, lv, w.sel.T, (uint32_t)P, (uint32_t)k, g_idx, g_val, w, w.gbits, true, st);
@@ -1020,10 +1103,10 @@ int gtopk_probe_stream(const float* a, float* b, int64_t n, int32_t mode, float*
 
 int gtopk_debug_plan(int64_t m, int32_t k, int32_t P, uint32_t* plan) {
     if (!plan || !sizes_ok(m, k, P)) return GTOPK_EINVAL;
-    const SamplePlan sp = plan_sample(m, (uint32_t)k);
+    const SamplePlan sp = plan_row_sample(m, (uint32_t)k, (uint64_t)P);
     plan[0] = sp.tile_stride;
     plan[1] = sp.n_tiles;
-    plan[2] = (uint32_t)kSampleTile;
+    plan[2] = (uint32_t)(mid_problem(m, (uint32_t)k, (uint64_t)P) ? kMidSampleTile : kSampleTile);
     plan[3] = sp.target;
     plan[4] = cand_capacity(m, (uint32_t)k);
     plan[5] = pass_histograms(m, (uint32_t)k) ? 1u : 0u;
@@ -1038,7 +1121,7 @@ int gtopk_debug_plan(int64_t m, int32_t k, int32_t P, uint32_t* plan) {
         plan[14] = mp.target;
     }
     if (plan[6]) {
-        const SamplePlan ss = plan_sample(m, (uint32_t)k, kSmallSampleMean, kSmallSampleMinTiles);
+        const SamplePlan ss = plan_sample(m, (uint32_t)k, kSampleTile, kSmallSampleMean, kSmallSampleMin);
         plan[8] = ss.tile_stride;
         plan[9] = ss.n_tiles;
         plan[10] = ss.target;

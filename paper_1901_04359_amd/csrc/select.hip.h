@@ -69,7 +69,7 @@ struct SelState {
 
 // Local select: the candidate list of worker s, or - when the speculative threshold
 // left fewer than k candidates or more than the list holds - the worker's dense row.
-// The streaming pass leaves the candidates as one run per 32768-element chunk of the row,
+// The streaming pass leaves the candidates as one run per chunk of the row,
 // in index order inside a run, the runs in the order in which the blocks reserved them
 // (run_table[w][chunk] = first slot, count); one extra block of k_hist scans the run
 // counts (run_off[w][chunk] = first logical position of the run), and k_bucket's walk
@@ -88,6 +88,7 @@ struct CandSrc {
     const float* res;
     int64_t stride;
     uint32_t m, k, cap, nchunks;
+    uint32_t chunk_log2;                  // elements per chunk of the streaming pass
     uint32_t Lc, Ld;                      // slots per group: candidate list / dense row
     const uint32_t* cand_idx;             // [P][cap] runs in reservation order
     const float* cand_val;
@@ -208,9 +209,9 @@ struct CandSrc {
     }
     __device__ uint32_t logical(int s, bool dn, uint32_t p, uint32_t idx) const {
         if (dn) return p;
-        // the streaming pass cuts a row into chunks at multiples of 32768 of idx + head
+        // the streaming pass cuts a row into chunks at multiples of 2^chunk_log2 of idx + head
         const uint32_t head = (uint32_t)(((int64_t)s * stride) & 3);
-        uint32_t chunk = (idx + head) >> kChunkLog2;
+        uint32_t chunk = (idx + head) >> chunk_log2;
         if (chunk >= nchunks) chunk = nchunks - 1;       // never for a list the pass wrote
         const size_t r = (size_t)s * nchunks + chunk;
         const uint32_t lp = run_off[r] + (p - run_table[r].x);
@@ -250,7 +251,7 @@ struct CandSrc {
 // the groups are the runs themselves - group g of worker s is the run of chunk g, where the
 // streaming pass left it - so nothing is copied into index order: the walk of k_bucket
 // reads a run's values only, the emit reads the run's indices and values in place.  Runs
-// differ in length (0 .. 32768 entries); with hundreds of runs per worker the blocks even
+// differ in length (0 .. a chunk's elements); with hundreds of runs per worker the blocks even
 // out.  A worker that falls back to its dense row is handled as in CandSrc.
 // kWaveGroups: every WAVE of a block of k_bucket / k_emit takes a run of its own (a block
 // per run spends its time on the block's fixed chain of dependent loads, not on the run).
@@ -273,7 +274,7 @@ struct RunSrc : CandSrc {
     __device__ uint32_t group_of(int s, bool dn, uint32_t p, uint32_t idx) const {
         if (dn) return p / Ld;
         const uint32_t head = (uint32_t)(((int64_t)s * stride) & 3);
-        const uint32_t chunk = (idx + head) >> kChunkLog2;
+        const uint32_t chunk = (idx + head) >> chunk_log2;
         return chunk < nchunks ? chunk : nchunks - 1;          // likewise
     }
     __device__ bool fetch_ord(int s, bool dn, uint32_t p, uint32_t& idx, uint32_t& bits) const {

@@ -25,7 +25,8 @@ constexpr int kSmallMaxEntries = 4096;       // P * k, at most
 constexpr int kSmallMaxK = 512;
 constexpr int kSmallMaxP = 64;
 constexpr int kSmallRankList = 2048;         // candidate lists up to here: selection by one wave
-constexpr int kSmallSampleUnroll = 16;       // tiles a wave of the sampler keeps in flight
+constexpr int kMidSampleTile = 16;           // elements per tile where it serves rows of millions of elements
+constexpr int kSmallSampleUnroll = 16;       // tiles that each of its groups of lanes keeps in flight
 
 // Sum / maximum / minimum of v over the 64 lanes of the wave (every lane takes part; the
 // result is uniform): butterfly steps inside each row of 16 lanes, then the four row
@@ -161,34 +162,51 @@ __device__ __forceinline__ void wave_select_any(const uint32_t* keys, uint32_t n
 // speculative threshold of one worker in one block
 // ---------------------------------------------------------------------------------
 
-// Worker w = blockIdx.x.  Sample tile t covers [t*tile_stride, t*tile_stride + 64) of the
-// accumulated row (clipped to m), one wave per tile; the block histograms the keys of all
+// Worker w = blockIdx.x.  Sample tile t covers [t*tile_stride, t*tile_stride + TILE) of the
+// accumulated row (clipped to m), TILE lanes per tile; the block histograms the keys of all
 // tiles in LDS and stores the lower edge of the bucket at which the count from the top
 // reaches `target`.  It also clears the worker's candidate counter for the streaming pass
-// that follows in stream order.
+// that follows in stream order.  GENERAL, in front of the general kernels: blocks from P on clear
+// what the rest of the step needs cleared (`job`), and a worker whose threshold is carried over
+// (`carry`, see k_sample) takes that.
+template <int TILE, bool GENERAL>
 __global__ __launch_bounds__(kSmallBlock) void k_small_sample(
         const float* __restrict__ grad, const float* __restrict__ res, uint32_t m, int64_t stride,
-        uint32_t tile_stride, uint32_t n_tiles, uint32_t target, uint32_t* __restrict__ tspec,
-        uint32_t* __restrict__ cand_count) {
+        uint32_t P, uint32_t tile_stride, uint32_t n_tiles, uint32_t target, uint32_t* __restrict__ tspec,
+        uint32_t* __restrict__ cand_count, const uint4* __restrict__ carry, ZeroJob job) {
     constexpr int kT = kSmallBlock;
     __shared__ uint32_t h[kSampleBins];
     __shared__ uint32_t s_wave[kT / kWave];
     __shared__ uint32_t s_out[3];
-    const int w = blockIdx.x;
     const uint32_t t = threadIdx.x;
+    if (GENERAL && blockIdx.x >= P) {
+        const size_t step = (size_t)(gridDim.x - P) * kT, first = (size_t)(blockIdx.x - P) * kT + t;
+#pragma unroll
+        for (int a = 0; a < kZeroSlots; ++a)
+            for (size_t i = first; i < job.n[a]; i += step) job.p[a][i] = 0u;
+        return;
+    }
+    const int w = blockIdx.x;
     if (t == 0) cand_count[w] = 0u;
+    if (GENERAL && carry) {
+        const uint4 c = carry[w];
+        if (c.x == 2u) {                             // block-uniform
+            if (t == 0) tspec[w] = c.w;
+            return;
+        }
+    }
     for (int b = t; b < kSampleBins; b += kT) h[b] = 0u;
     __syncthreads();
     const float* g = grad + (int64_t)w * stride;
     const float* r = res + (int64_t)w * stride;
-    const uint32_t wave = t / kWave, el = t % kWave;
-    constexpr uint32_t kWaves = kT / kWave;
-    for (uint32_t t0 = wave; t0 < n_tiles; t0 += kWaves * kSmallSampleUnroll) {
+    const uint32_t sub = t / TILE, el = t % TILE;
+    constexpr uint32_t kTiles = kT / TILE;         // tiles the block takes side by side
+    for (uint32_t t0 = sub; t0 < n_tiles; t0 += kTiles * kSmallSampleUnroll) {
         float gv[kSmallSampleUnroll], rv[kSmallSampleUnroll];
         bool ok[kSmallSampleUnroll];
 #pragma unroll
         for (int u = 0; u < kSmallSampleUnroll; ++u) {
-            const uint32_t tile = t0 + (uint32_t)u * kWaves;
+            const uint32_t tile = t0 + (uint32_t)u * kTiles;
             const uint64_t q = (uint64_t)tile * tile_stride + el;
             ok[u] = tile < n_tiles && q < m;
             gv[u] = ok[u] ? g[q] : 0.0f;

@@ -5,7 +5,7 @@ import pytest
 from oracle import gtopk_oracle as orc
 from paper_1901_04359_amd import workloads as W
 from tests.gpu_harness import bits_equal, first_diff, say
-from tests.test_gpu_parity import run_merge
+from tests.test_gpu_parity import _check_two_iterations, run_merge
 
 pytestmark = pytest.mark.gpu
 
@@ -22,3 +22,21 @@ def test_merge_batches_at_the_unions_border(kind, k, batch):
         oi, ov = orc.merge(idx[2 * b], val[2 * b], idx[2 * b + 1], val[2 * b + 1], k)
         assert np.array_equal(gi[b], oi), f"b={b} idx: {first_diff(gi[b], oi)}"
         assert bits_equal(gv[b], ov), f"b={b} val: {first_diff(gv[b], ov)}"
+
+
+@pytest.mark.parametrize("kind", ["gauss", "ties"])
+@pytest.mark.parametrize("P,m,k,pad,tile", [
+    (2, 33_001, 900, 1, 16),             # 4096-element chunks, runs selected in place
+    (4, 900_001, 4000, 0, 16),           # 4096, runs put into index order
+    (4, 1_500_003, 300_000, 3, 16),      # 4096, a dense selection
+    (8, 1_100_003, 5000, 2, 16),         # 8192
+    (16, 1_048_581, 5000, 0, 16),        # 16384
+    (2, 3_000_001, 4500, 5, 64),         # the large sample, whose histogram's place the run tables take
+])
+def test_step_at_every_chunk_size(P, m, k, pad, tile, kind):
+    """Medium rows: the one-block sampler (tiles of 16) and each size of the pass's chunks, on
+    rows of ragged length and alignment."""
+    from paper_1901_04359_amd import binding as B
+    plan = B.gtopk_debug_plan(m, k, P)
+    assert plan["tile_len"] == tile and plan["small_path"] == 0
+    _check_two_iterations(P, m, k, kind, pad, "chunk sizes")
