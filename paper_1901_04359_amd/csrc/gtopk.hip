@@ -508,12 +508,12 @@ SelGrid local_grid(const StepWs& w, uint32_t P) {
     return SelGrid{P, gx, gx, (uint64_t)w.cap, false};
 }
 
-template <bool HIST>
+template <bool HIST, bool SUM>
 void launch_pass(const float* grad, float* residual, int64_t m, int64_t stride, uint32_t P, const StepWs& w,
                  hipStream_t st) {
     const dim3 grid(w.nchunks, P), block(kSBlock);
 #define GTOPK_PASS(ITERS)                                                                                   \
-    hipLaunchKernelGGL((k_accum_filter<HIST, ITERS>), grid, block, 0, st, grad, residual, (uint32_t)m,     \
+    hipLaunchKernelGGL((k_accum_filter<HIST, ITERS, SUM>), grid, block, 0, st, grad, residual, (uint32_t)m,     \
                        stride, w.tspec, w.cand_idx, w.cand_val, w.cap, w.cand_count, w.run_table, w.nchunks, \
                        w.sel.hist)
     static_assert(kIters == 16, "a chunk of 2^15 elements per block of 16 float4 per lane");
@@ -526,22 +526,23 @@ void launch_pass(const float* grad, float* residual, int64_t m, int64_t stride, 
 #undef GTOPK_PASS
 }
 
-// `zero_rows`: store +0.0 at the selected entries (the stand-alone call); gtopk_step
-// passes false and settles the rows in k_restore_fused.  `job`: what the call needs cleared before
-// its select, the candidate counters among it.
-int do_local_select(const float* grad, float* residual, int64_t m, int64_t stride, uint32_t P,
-                    uint32_t k, uint32_t* out_idx, float* out_val, const StepWs& w, bool zero_rows,
-                    const ZeroJob& job, hipStream_t st, void* const* events = nullptr,
-                    uint32_t* thr_state = nullptr) {
+// The speculative thresholds of P rows and the pass that filters them; before that, clears what
+// `job` says (the candidate counters among it).  SUM: the rows are residual + grad, the sums replace the
+// residual; else the rows are `residual` as it stands, nothing is written to it.  Returns whether the
+// pass has histogrammed its candidates.
+template <bool SUM>
+bool filter_rows(const float* grad, float* residual, int64_t m, int64_t stride, uint32_t P, uint32_t k,
+                 const StepWs& w, const ZeroJob& job, hipStream_t st, void* const* events = nullptr,
+                 uint32_t* thr_state = nullptr) {
     // workers whose threshold is carried over from the previous call skip the sampling (the
     // kernels are launched all the same: who samples is decided on the device)
     const uint4* carry = reinterpret_cast<const uint4*>(thr_state);
     const SamplePlan sp = plan_row_sample(m, k, P);
     if (mid_problem(m, k, P)) {
         const uint32_t zblocks = zero_blocks(job, 4 * kSmallBlock);
-        hipLaunchKernelGGL((k_small_sample<kMidSampleTile, true>), dim3(P + zblocks), dim3(kSmallBlock), 0, st, grad, residual,
-                           (uint32_t)m, stride, P, sp.tile_stride, sp.n_tiles, sp.target, w.tspec, w.cand_count,
-                           carry, job);
+        hipLaunchKernelGGL((k_small_sample<kMidSampleTile, true, SUM>), dim3(P + zblocks), dim3(kSmallBlock), 0,
+                           st, grad, residual, (uint32_t)m, stride, P, sp.tile_stride, sp.n_tiles, sp.target,
+                           w.tspec, w.cand_count, carry, job);
     } else {
         zero_async(st, job);
         uint32_t sblocks = ceil_div(sp.n_tiles, (kSampleBlock / kSampleTile) * 8);
@@ -549,7 +550,7 @@ int do_local_select(const float* grad, float* residual, int64_t m, int64_t strid
         const uint32_t sb_max = P >= 64 ? 4u : (P <= 16 ? 16u : 256u / P);
         if (sblocks > sb_max) sblocks = sb_max;
         if (sblocks < 1) sblocks = 1;
-        hipLaunchKernelGGL(k_sample, dim3(sblocks, P), dim3(kSampleBlock), 0, st, grad, residual,
+        hipLaunchKernelGGL((k_sample<SUM>), dim3(sblocks, P), dim3(kSampleBlock), 0, st, grad, residual,
                            (uint32_t)m, stride, sp.tile_stride, sp.n_tiles, w.samp_hist, carry);
         hipLaunchKernelGGL(k_sample_pick, dim3(P), dim3(kSampleBlock), 0, st, w.samp_hist, sp.target,
                            w.tspec, carry);
@@ -557,10 +558,20 @@ int do_local_select(const float* grad, float* residual, int64_t m, int64_t strid
     mark_stage(1, events, st);
 
     const bool producer_hist = pass_histograms(m, k);
-    if (producer_hist) launch_pass<true>(grad, residual, m, stride, P, w, st);
-    else launch_pass<false>(grad, residual, m, stride, P, w, st);
+    if (producer_hist) launch_pass<true, SUM>(grad, residual, m, stride, P, w, st);
+    else launch_pass<false, SUM>(grad, residual, m, stride, P, w, st);
     mark_stage(2, events, st);
+    return producer_hist;
+}
 
+// `zero_rows`: store +0.0 at the selected entries (the stand-alone call); gtopk_step
+// passes false and settles the rows in k_restore_fused.  `job`: what the call needs cleared before
+// its select, the candidate counters among it.
+int do_local_select(const float* grad, float* residual, int64_t m, int64_t stride, uint32_t P,
+                    uint32_t k, uint32_t* out_idx, float* out_val, const StepWs& w, bool zero_rows,
+                    const ZeroJob& job, hipStream_t st, void* const* events = nullptr,
+                    uint32_t* thr_state = nullptr) {
+    const bool producer_hist = filter_rows<true>(grad, residual, m, stride, P, k, w, job, st, events, thr_state);
     const CandSrc src = cand_source(residual, stride, m, k, w, producer_hist, false, thr_state);
     // the histogram kernel always runs: where the pass has counted its candidates it serves
     // only the workers that came back with fewer than k of them
@@ -873,7 +884,7 @@ static int step_impl(const float* grad, float* residual, int64_t m, int64_t stri
     if (!events && !thr_state && small_problem(m, k, P)) {
         // one block per worker samples, picks the threshold and clears the candidate counter
         const SamplePlan sp = plan_sample(m, (uint32_t)k, kSampleTile, kSmallSampleMean, kSmallSampleMin);
-        hipLaunchKernelGGL((k_small_sample<kSampleTile, false>), dim3(P), dim3(kSmallBlock), 0, st, grad, residual,
+        hipLaunchKernelGGL((k_small_sample<kSampleTile, false, true>), dim3(P), dim3(kSmallBlock), 0, st, grad, residual,
                            (uint32_t)m, stride, (uint32_t)P, sp.tile_stride, sp.n_tiles, sp.target, w.tspec,
                            w.cand_count, (const uint4*)nullptr, ZeroJob{});
         // small blocks: one run per 4096 elements (the run table was carved for that many)
@@ -1037,6 +1048,18 @@ int gtopk_topk_allreduce(const uint32_t* loc_idx, const float* loc_val, int32_t 
     return launch_status();
 }
 
+// Whether the dense top-k filters its row by a sampled threshold first, as the local selection does,
+// and selects from the candidates, instead of reading the whole row in each of its three kernels (54 + 56
+// + 58 us at m = 25,557,032; now sample 9 + 5, pass 22, select 27).  A call in us, three reads / filtered,
+// on rows of which a tenth (the last line: all) is non-zero:
+//   m = 200,001     k = 200     26.4 / 27.7     k = 4000        29.3 / 28.5
+//   m = 500,000     k = 500     32.9 / 30.8     k = 30,000      37.7 / 30.8
+//   m = 4,000,001   k = 4000    59.1 / 40.6     k = 240,000     68.8 / 45.0
+//   m = 25,557,032  k = 25,557  180.7 / 63.6    k = 1,533,421  244.4 / 96.6
+//   m = 25,557,032  k = 6.4 M   881.9 / 174.9   k = 23 M       392.4 / 361.3
+// A row with fewer than k non-zeros is read three times as before (212 -> 228 us at the fourth size).
+static bool dense_topk_filters(int64_t m) { return m >= ((int64_t)1 << 19); }
+
 int gtopk_dense_topk(const float* dense, int64_t m, int32_t k, uint32_t* g_idx, float* g_val,
                      void* ws, size_t ws_bytes, void* stream) {
     if (!dense || !g_idx || !g_val || !ws) return GTOPK_EINVAL;
@@ -1046,12 +1069,19 @@ int gtopk_dense_topk(const float* dense, int64_t m, int32_t k, uint32_t* g_idx, 
     const StepWs w = carve_step(ws, m, (uint32_t)k, 1);
     if (ws_bytes < w.bytes) return GTOPK_EWORKSPACE;
     hipStream_t st = (hipStream_t)stream;
-    // a candidate count of zero makes the select read the dense row itself
-    zero_async(st, zero_job(w.samp_hist, (size_t)(w.tspec - w.samp_hist), w.sel.hist, select_clear_words(w.sel)));
-    const CandSrc src = cand_source(dense, m, m, (uint32_t)k, w, false, /*no_bounds=*/true);
-    // one set, always read as a dense row: the grids follow the row's groups; without a
-    // lower bound of the k-th key the list can be long, so large rows are finished once
-    const SelGrid gr{1, w.gdense, w.gdense, (uint64_t)m, m > ((int64_t)1 << 20)};
+    const ZeroJob job = zero_job(w.samp_hist, (size_t)(w.tspec - w.samp_hist), w.sel.hist,
+                                 select_clear_words(w.sel));
+    const bool filter = dense_topk_filters(m);
+    bool producer_hist = false;
+    if (filter)
+        producer_hist = filter_rows<false>(nullptr, const_cast<float*>(dense), m, m, 1, (uint32_t)k, w, job, st);
+    else
+        zero_async(st, job);       // a candidate count of zero makes the select read the dense row itself
+    const CandSrc src = cand_source(dense, m, m, (uint32_t)k, w, producer_hist, /*no_bounds=*/!filter);
+    // one set: the grids follow the dense row's groups (a row whose sample misled is read as one);
+    // without a lower bound of the k-th key the list can be long, so large rows are finished once
+    const uint32_t gx = filter && w.gcand > w.gdense ? w.gcand : w.gdense;
+    const SelGrid gr{1, gx, gx, (uint64_t)m, m > ((int64_t)1 << 20)};
     run_select<CandSrc, false>(src, w.sel, gr, (uint32_t)k, g_idx, g_val, (int64_t)k, 1.0f, nullptr, st);
     return launch_status();
 }

@@ -168,8 +168,8 @@ __device__ __forceinline__ void wave_select_any(const uint32_t* keys, uint32_t n
 // reaches `target`.  It also clears the worker's candidate counter for the streaming pass
 // that follows in stream order.  GENERAL, in front of the general kernels: blocks from P on clear
 // what the rest of the step needs cleared (`job`), and a worker whose threshold is carried over
-// (`carry`, see k_sample) takes that.
-template <int TILE, bool GENERAL>
+// (`carry`, see k_sample) takes that.  !SUM: the row is res alone, grad is not read.
+template <int TILE, bool GENERAL, bool SUM>
 __global__ __launch_bounds__(kSmallBlock) void k_small_sample(
         const float* __restrict__ grad, const float* __restrict__ res, uint32_t m, int64_t stride,
         uint32_t P, uint32_t tile_stride, uint32_t n_tiles, uint32_t target, uint32_t* __restrict__ tspec,
@@ -209,12 +209,14 @@ __global__ __launch_bounds__(kSmallBlock) void k_small_sample(
             const uint32_t tile = t0 + (uint32_t)u * kTiles;
             const uint64_t q = (uint64_t)tile * tile_stride + el;
             ok[u] = tile < n_tiles && q < m;
-            gv[u] = ok[u] ? g[q] : 0.0f;
+            gv[u] = SUM && ok[u] ? g[q] : 0.0f;
             rv[u] = ok[u] ? r[q] : 0.0f;
         }
 #pragma unroll
-        for (int u = 0; u < kSmallSampleUnroll; ++u)
-            if (ok[u]) atomicAdd(&h[(__float_as_uint(rv[u] + gv[u]) & kAbs) >> kSampleShift], 1u);
+        for (int u = 0; u < kSmallSampleUnroll; ++u) {
+            const uint32_t bin = (__float_as_uint(SUM ? rv[u] + gv[u] : rv[u]) & kAbs) >> kSampleShift;
+            if (ok[u] && (SUM || bin != 0u)) atomicAdd(&h[bin], 1u);      // (see k_sample)
+        }
     }
     __syncthreads();
     constexpr int kPer = kSampleBins / kT;

@@ -8,7 +8,8 @@ namespace gtopk {
 
 // Sample tile t of a row covers [t*tile_stride, t*tile_stride + 64) (clipped to m): one
 // wave per tile.  A block of 1024 threads takes sixteen tiles per round and keeps four
-// rounds of loads in flight.
+// rounds of loads in flight.  (SUM: the row is res + grad; else it is res alone, grad is not read.)
+template <bool SUM>
 __global__ __launch_bounds__(kSampleBlock) void k_sample(
         const float* __restrict__ grad, const float* __restrict__ res, uint32_t m, int64_t stride,
         uint32_t tile_stride, uint32_t n_tiles, uint32_t* __restrict__ samp_hist,
@@ -32,14 +33,17 @@ __global__ __launch_bounds__(kSampleBlock) void k_sample(
             const uint64_t t = t0 + (uint64_t)u * tiles_per_round;
             const uint64_t q = t * tile_stride + el;
             ok[u] = t < n_tiles && q < m;
-            gv[u] = ok[u] ? g[q] : 0.0f;
+            gv[u] = SUM && ok[u] ? g[q] : 0.0f;
             rv[u] = ok[u] ? r[q] : 0.0f;
         }
 #pragma unroll
         for (int u = 0; u < kUnroll; ++u) {
             if (ok[u]) {
-                const uint32_t key = __float_as_uint(rv[u] + gv[u]) & kAbs;
-                atomicAdd(&h[key >> kSampleShift], 1u);
+                const uint32_t key = __float_as_uint(SUM ? rv[u] + gv[u] : rv[u]) & kAbs;
+                // (a row that is not summed is mostly zeros, all lanes on one counter; the lowest
+                // bin's count makes no difference: whether the pick ends in it or finds too few
+                // entries above it, the threshold is 0)
+                if (SUM || (key >> kSampleShift) != 0u) atomicAdd(&h[key >> kSampleShift], 1u);
             }
         }
     }
@@ -95,7 +99,9 @@ __global__ __launch_bounds__(kSampleBlock) void k_sample_pick(
 // (what the select's histogram kernel would read back), through an LDS histogram: one
 // global atomic per non-empty bin.  (One global atomic per candidate is as good where the
 // candidates are spread evenly, and far worse where they crowd into a few blocks.)
-template <bool HIST, int ITERS = kIters>
+// !SUM (the dense top-k): the row is `res` as it stands: grad is not read and nothing is stored to the
+// row.  Half the bytes per block of the sum's pass and no writes: 22 us at m = 25,557,032 = 4.6 TB/s.
+template <bool HIST, int ITERS = kIters, bool SUM = true>
 __global__ __launch_bounds__(kSBlock) void k_accum_filter(
         const float* __restrict__ grad, float* __restrict__ res, uint32_t m, int64_t stride,
         const uint32_t* __restrict__ tspec, uint32_t* __restrict__ cand_idx,
@@ -118,6 +124,9 @@ __global__ __launch_bounds__(kSBlock) void k_accum_filter(
     float* r = res + (int64_t)w * stride - head;
     const uint32_t vend = head + m;          // <= 2^31 + 3
     const uint32_t ts = tspec[w];
+    // a sample without enough entries above the lowest bin (fewer than k non-zeros): nothing to filter by.
+    // The counter stays 0 and the select reads the row itself (block-uniform).
+    if (!SUM && ts == 0u) return;
     // chunk < ceil((m + 3) / 32768), so none of the offsets below wraps
     constexpr uint32_t kSpan = ITERS * 4 * kWave;            // elements per wave
     const uint32_t wbase = chunk * (kSpan * (uint32_t)kWaves) + wave * kSpan;
@@ -129,14 +138,17 @@ __global__ __launch_bounds__(kSBlock) void k_accum_filter(
 #pragma unroll
         for (int i = 0; i < ITERS; ++i) {
             const uint32_t v = wbase + i * 256 + lane * 4;
-            gv[i] = __builtin_nontemporal_load(reinterpret_cast<const floatx4*>(g + v));
+            if (SUM) gv[i] = __builtin_nontemporal_load(reinterpret_cast<const floatx4*>(g + v));
             rv[i] = __builtin_nontemporal_load(reinterpret_cast<const floatx4*>(r + v));
         }
 #pragma unroll
         for (int i = 0; i < ITERS; ++i) {
             const uint32_t v = wbase + i * 256 + lane * 4;
-            const floatx4 s = rv[i] + gv[i];          // four independent fp32 adds
-            __builtin_nontemporal_store(s, reinterpret_cast<floatx4*>(r + v));
+            floatx4 s = rv[i];
+            if (SUM) {
+                s = rv[i] + gv[i];                    // four independent fp32 adds
+                __builtin_nontemporal_store(s, reinterpret_cast<floatx4*>(r + v));
+            }
             a[i][0] = s.x; a[i][1] = s.y; a[i][2] = s.z; a[i][3] = s.w;
         }
     } else {
@@ -144,17 +156,22 @@ __global__ __launch_bounds__(kSBlock) void k_accum_filter(
         for (int i = 0; i < ITERS; ++i) {
             const uint32_t v = wbase + i * 256 + lane * 4;
             if (v >= head && v + 4 <= vend) {
-                const floatx4 s = *reinterpret_cast<const floatx4*>(r + v) +
-                                  *reinterpret_cast<const floatx4*>(g + v);
-                *reinterpret_cast<floatx4*>(r + v) = s;
+                floatx4 s = *reinterpret_cast<const floatx4*>(r + v);
+                if (SUM) {
+                    s = s + *reinterpret_cast<const floatx4*>(g + v);
+                    *reinterpret_cast<floatx4*>(r + v) = s;
+                }
                 a[i][0] = s.x; a[i][1] = s.y; a[i][2] = s.z; a[i][3] = s.w;
             } else {
 #pragma unroll
                 for (int e = 0; e < 4; ++e) {
                     float s = 0.0f;
                     if (v + e >= head && v + e < vend) {
-                        s = r[v + e] + g[v + e];
-                        r[v + e] = s;
+                        s = r[v + e];
+                        if (SUM) {
+                            s = s + g[v + e];
+                            r[v + e] = s;
+                        }
                     }
                     a[i][e] = s;
                 }

@@ -40,3 +40,47 @@ def test_step_at_every_chunk_size(P, m, k, pad, tile, kind):
     plan = B.gtopk_debug_plan(m, k, P)
     assert plan["tile_len"] == tile and plan["small_path"] == 0
     _check_two_iterations(P, m, k, kind, pad, "chunk sizes")
+
+
+@pytest.mark.parametrize("kind", ["gauss", "sparse", "ties", "zeros", "special", "hidden"])
+@pytest.mark.parametrize("m,k", [
+    ((1 << 19) - 1, 700),                # read as it stands
+    (1 << 19, 700),                      # filtered
+    ((1 << 20) + 1, 300_000),            # the select finished once per set
+    (1_500_003, 1_500_003),              # everything selected
+    (3_000_001, 1000),                   # the large sample
+    (3_000_001, 4500),                   # chunks whose runs the pass histograms
+    (3_000_001, 200_000),
+])
+def test_dense_topk_filtered(m, k, kind):
+    """Rows that are filtered before the selection, and rows whose filter has nothing to go by (fewer
+    than k non-zeros, masses of ties, the largest entries where the sample does not look)."""
+    import torch
+    from paper_1901_04359_amd import binding as B
+    rng = np.random.default_rng(m + k)
+    d = rng.standard_normal(m).astype(np.float32)
+    if kind == "sparse":
+        d[rng.random(m) < 0.9] = 0.0
+    elif kind == "ties":
+        d = np.round(d).astype(np.float32)
+    elif kind == "zeros":                # -0.0 among them
+        d *= np.float32(0.0)
+        at = rng.choice(m, max(1, k // 2), replace=False)
+        d[at] = rng.standard_normal(at.size).astype(np.float32)
+    elif kind == "special":
+        for j, x in enumerate([np.inf, -np.inf, 1e-45, -1e-45, -0.0, 3.4e38, np.nan]):
+            d[rng.integers(0, m, 5)] = np.float32(x)
+    elif kind == "hidden":               # large entries everywhere but in the sampled tiles, then the reverse
+        plan = B.gtopk_debug_plan(m, k, 1)
+        at = np.arange(m) % plan["tile_stride"] < plan["tile_len"]
+        d = np.where(at if k % 8 else ~at, d * np.float32(100.0), d).astype(np.float32)
+    say(f"dense top-k: m={m} k={k} kind={kind}")
+    row = torch.from_numpy(d).cuda()
+    gi = torch.zeros(k, dtype=torch.int32, device="cuda")
+    gv = torch.zeros(k, device="cuda")
+    B.gtopk_dense_topk(row, k, gi, gv, B.alloc_workspace(m, k, 1))
+    oi, ov = orc.dense_topk(d, k)
+    gi, gv = gi.cpu().numpy().view(np.uint32), gv.cpu().numpy()
+    assert np.array_equal(gi, oi), first_diff(gi, oi)
+    assert bits_equal(gv, ov), first_diff(gv, ov)
+    assert bits_equal(row.cpu().numpy(), d), "the row was written to"
