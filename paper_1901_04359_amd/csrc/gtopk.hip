@@ -401,6 +401,31 @@ void zero_async(hipStream_t st, const ZeroJob& job) {
     if (blocks) hipLaunchKernelGGL(k_zero_u32, dim3(blocks), dim3(256), 0, st, job);
 }
 
+inline uint32_t min_key_blocks(uint32_t k) {
+    const uint32_t b = ceil_div(k, 16 * kMinKeyBlock);
+    return b < 1 ? 1 : (b > 64 ? 64 : b);
+}
+
+// Smallest keys of `sets` sets (rows of v0, or of v0 and v1 in turn) into out; clears what `job` says.
+// Sets up to kMinKeyWholeK: in one launch, a block per set.  A merge call in us, clear and several
+// blocks per set / one launch:  1 pair  k = 200: 19.9 / 17.7   k = 16,000: 23.6 / 21.7   k = 32,000: 26.6 / 26.8
+// 16 pairs  k = 200: 21.2 / 19.3   k = 16,000: 31.6 / 29.7   k = 65,000: 52.8 / 65.9
+constexpr uint32_t kMinKeyWholeK = 16384;
+void find_min_keys(const float* v0, const float* v1, int64_t stride, uint32_t k, uint32_t sets, uint32_t* out,
+                   ZeroJob job, hipStream_t st) {
+    if (k <= kMinKeyWholeK && sets <= 32767u) {              // (at most 65535 rows of blocks)
+        const uint32_t zblocks = zero_blocks(job, 4 * kMinKeyBlock);
+        hipLaunchKernelGGL(k_set_min_key<true>, dim3(1, sets + zblocks), dim3(kMinKeyBlock), 0, st, v0, v1, stride, k,
+                           sets, out, job);
+    } else {
+        job.p[kZeroSlots - 1] = out;
+        job.n[kZeroSlots - 1] = sets;
+        zero_async(st, job);
+        hipLaunchKernelGGL(k_set_min_key<false>, dim3(min_key_blocks(k), sets), dim3(kMinKeyBlock), 0, st, v0, v1,
+                           stride, k, sets, out, ZeroJob{});
+    }
+}
+
 // how a batch of sets is walked and emitted
 struct SelGrid {
     uint32_t sets;
@@ -618,11 +643,6 @@ inline MergeSamplePlan plan_merge_sample(uint32_t k) {
     return p;
 }
 
-inline uint32_t min_key_blocks(uint32_t k) {
-    const uint32_t b = ceil_div(k, 8192);
-    return b < 1 ? 1 : (b > 64 ? 64 : b);
-}
-
 // Lanes per cut point by the number of cut points of the launch (see k_union_cuts).  Measured
 // for sets of 1.9 M and 6.4 M entries, in us for (25 k, 12.5 k, 6.2 k, 3.1 k, 1.6 k) and
 // (7.3 k, 3.6 k, 1.8 k, 0.9 k, 0.45 k) cut points:
@@ -733,14 +753,15 @@ int do_tree(const uint32_t* loc_idx, const float* loc_val, const uint32_t* loc_m
                            g_idx, g_val, divisor, gbits);
         return launch_status();
     }
+    ZeroJob job = zero_job();
     if (!pre_cleared)
-        zero_async(st, zero_job(w.mrg.sel.hist, select_clear_words(w.mrg.sel), w.mrg.sel_alt.hist,
-                                w.mrg.alt_clear_words, w.mrg.inv_min, P));
+        job = zero_job(w.mrg.sel.hist, select_clear_words(w.mrg.sel), w.mrg.sel_alt.hist, w.mrg.alt_clear_words);
     bool inverted = false;
-    if (!loc_min) {
+    if (loc_min) {
+        zero_async(st, job);
+    } else {
         // sets from the caller: find their smallest keys, the first round's lower bounds
-        hipLaunchKernelGGL(k_set_min_key, dim3(min_key_blocks(k), P), dim3(kBlock), 0, st, loc_val,
-                           (const float*)nullptr, (int64_t)k, k, w.mrg.inv_min);
+        find_min_keys(loc_val, nullptr, (int64_t)k, k, P, w.mrg.inv_min, job, st);
         loc_min = w.mrg.inv_min;
         inverted = true;
     }
@@ -829,9 +850,8 @@ int gtopk_merge(const uint32_t* a_idx, const float* a_val, const uint32_t* b_idx
     const MergeWs w = carve_merge(c, (uint32_t)k, (size_t)batch);
     if (ws_bytes < w.bytes) return GTOPK_EWORKSPACE;
     hipStream_t st = (hipStream_t)stream;
-    zero_async(st, zero_job(w.sel.hist, select_clear_words(w.sel), w.inv_min, 2 * (size_t)batch));
-    hipLaunchKernelGGL(k_set_min_key, dim3(min_key_blocks((uint32_t)k), 2 * (uint32_t)batch),
-                       dim3(kBlock), 0, st, a_val, b_val, in_stride, (uint32_t)k, w.inv_min);
+    find_min_keys(a_val, b_val, in_stride, (uint32_t)k, 2 * (uint32_t)batch, w.inv_min,
+                  zero_job(w.sel.hist, select_clear_words(w.sel)), st);
     do_merge_batch<false>(a_idx, a_val, b_idx, b_val, (uint32_t)k, (uint32_t)batch, in_stride,
                           out_idx, out_val, out_stride, w, 0, w.inv_min, true, nullptr, 1.0f, nullptr,
                           st);

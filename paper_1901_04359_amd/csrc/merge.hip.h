@@ -541,19 +541,43 @@ __global__ __launch_bounds__(kSampleBlock) void k_merge_sample(
     }
 }
 
+constexpr int kMinKeyBlock = 1024;
 // Smallest key of each k-set, for sets that did not come out of a select of this library:
 // out[s] = max over the set of (0x7fffffff - key), by atomic maximum onto a zeroed word.
 // Set s is row s of v0 (v1 == NULL), or row s/2 of v0 (s even) / v1 (s odd).
-__global__ __launch_bounds__(kBlock) void k_set_min_key(
-        const float* __restrict__ v0, const float* __restrict__ v1, int64_t stride, uint32_t k,
-        uint32_t* __restrict__ out) {
-    __shared__ uint32_t s_wave[kBlock / kWave];
+// WHOLE: one block per set (grid.x == 1), which stores the word without needing it zeroed, and
+// further blocks (set index from `sets` on) that clear what the merge needs cleared (`job`).
+// Bound by latency: sixteen loads of a thread are in flight together.
+template <bool WHOLE>
+__global__ __launch_bounds__(kMinKeyBlock) void k_set_min_key(
+        const float* __restrict__ v0, const float* __restrict__ v1, int64_t stride, uint32_t k, uint32_t sets,
+        uint32_t* __restrict__ out, ZeroJob job) {
+    __shared__ uint32_t s_wave[kMinKeyBlock / kWave];
     const uint32_t s = blockIdx.y;
+    if (WHOLE && s >= sets) {
+        const size_t step = (size_t)(gridDim.y - sets) * kMinKeyBlock;
+        const size_t first = (size_t)(s - sets) * kMinKeyBlock + threadIdx.x;
+#pragma unroll
+        for (int a = 0; a < kZeroSlots; ++a)
+            for (size_t i = first; i < job.n[a]; i += step) job.p[a][i] = 0u;
+        return;
+    }
     const float* v = v1 ? ((s & 1) ? v1 : v0) + (int64_t)(s >> 1) * stride : v0 + (int64_t)s * stride;
+    constexpr int kEpt = 16;
     uint32_t best = 0;
-    for (uint32_t i = blockIdx.x * kBlock + threadIdx.x; i < k; i += gridDim.x * kBlock) {
-        const uint32_t inv = kAbs - (__float_as_uint(v[i]) & kAbs);
-        best = inv > best ? inv : best;
+    for (uint64_t i0 = (uint64_t)blockIdx.x * (kMinKeyBlock * kEpt); i0 < k;
+         i0 += (uint64_t)gridDim.x * (kMinKeyBlock * kEpt)) {
+        uint32_t x[kEpt];
+#pragma unroll
+        for (int j = 0; j < kEpt; ++j) {
+            const uint64_t i = i0 + j * kMinKeyBlock + threadIdx.x;
+            x[j] = i < k ? __float_as_uint(v[i]) : kAbs;              // the largest key: changes nothing
+        }
+#pragma unroll
+        for (int j = 0; j < kEpt; ++j) {
+            const uint32_t inv = kAbs - (x[j] & kAbs);
+            best = inv > best ? inv : best;
+        }
     }
 #pragma unroll
     for (int d = 32; d >= 1; d >>= 1) {
@@ -563,8 +587,9 @@ __global__ __launch_bounds__(kBlock) void k_set_min_key(
     if (lane_id() == 0) s_wave[threadIdx.x / kWave] = best;
     __syncthreads();
     if (threadIdx.x == 0) {
-        for (int w = 1; w < kBlock / kWave; ++w) best = s_wave[w] > best ? s_wave[w] : best;
-        atomicMax(&out[s], best);
+        for (int w = 1; w < kMinKeyBlock / kWave; ++w) best = s_wave[w] > best ? s_wave[w] : best;
+        if (WHOLE) out[s] = best;
+        else atomicMax(&out[s], best);
     }
 }
 

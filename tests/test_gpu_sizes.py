@@ -84,3 +84,20 @@ def test_dense_topk_filtered(m, k, kind):
     assert np.array_equal(gi, oi), first_diff(gi, oi)
     assert bits_equal(gv, ov), first_diff(gv, ov)
     assert bits_equal(row.cpu().numpy(), d), "the row was written to"
+
+
+@pytest.mark.parametrize("k", [1, 1023, 16_384, 16_385])
+@pytest.mark.parametrize("batch", [1, 3])
+def test_merge_smallest_keys(k, batch):
+    """Either side of the set size up to which one block finds a set's smallest key; the smallest
+    key lies at either end of the set, or is 0."""
+    m = 40_000
+    idx, val = W.ksets(2 * batch, k, m, seed=k, overlap=0.5, value_kind="gauss")
+    val[0, 0] = val[1, -1] = np.float32(1e-6)
+    val[-1, -1] = np.float32(-0.0)
+    say(f"merge smallest keys: k={k} batch={batch}")
+    gi, gv = run_merge(idx[0::2].copy(), val[0::2].copy(), idx[1::2].copy(), val[1::2].copy(), k)
+    for b in range(batch):
+        oi, ov = orc.merge(idx[2 * b], val[2 * b], idx[2 * b + 1], val[2 * b + 1], k)
+        assert np.array_equal(gi[b], oi), f"b={b} idx: {first_diff(gi[b], oi)}"
+        assert bits_equal(gv[b], ov), f"b={b} val: {first_diff(gv[b], ov)}"
