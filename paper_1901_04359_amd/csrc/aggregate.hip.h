@@ -14,8 +14,8 @@ constexpr int kAggRangeLog2 = 13;
 static_assert((1 << kAggRangeLog2) == kAggRange, "range size");
 
 constexpr int kFewP = 32;              // k_scatter_mean_few: one bit of a word per worker
-constexpr int kFewRange = 4096;        // its dense elements per block: half a range of the bounds
-constexpr int kFewBlock = 512;
+constexpr int kFewRange = 2048;        // its dense elements per block: a quarter of a range of the bounds
+constexpr int kFewBlock = 256;
 static_assert(kAggRange % kFewRange == 0, "a block's elements lie in one range");
 
 // bounds[g][b] = number of entries of worker g's (index-ascending) k-set with index below
@@ -163,11 +163,15 @@ __global__ __launch_bounds__(kBlock) void k_scatter_mean(
 
 // The same for at most 32 workers.  What bounded k_scatter_mean was latency: with a bid per
 // element its 74 KB of LDS leave two blocks of four waves per CU, and every round of bids costs
-// three barriers.  Here a block owns kFewRange elements (33 KB: four blocks of eight waves per
-// CU) and, instead of a bid, keeps per element the set of workers of the batch that hold it, one
-// bit each: an entry's turn is the number of lower workers in that set, so turns need one barrier
-// each and no vote.  A block reads its whole 8192-element range's entries and drops those of the
-// other half: P * k entries read twice, against m elements written once.
+// three barriers.  Here a block owns kFewRange elements (17 KB) and, instead of a bid, keeps per
+// element the set of workers of the batch that hold it, one bit each: an entry's turn is the number
+// of lower workers in that set, so turns need one barrier each and no vote.  The workers' entries crowd
+// into a few ranges (the layers with large gradients), and the blocks of those take as long as the
+// launch: a quarter of a range per block shortens them, and each finds its part of every worker's
+// entries by two searches inside the range's bounds.  The average of 32 workers at m = 25,557,032 in us,
+// k_scatter_mean / blocks of 4096 that read the whole range / 2048 / 1024 elements:
+//   k = 25,557  103 / 63 / 50 / 50     k = 255,570  291 / 174 / 135 / 122     the same in one layer  131 / 80 / 76 / 108
+// and at m = 61,100,840, k = 61,101 (many empty ranges)  89 / 52 / 51 / 74.
 __global__ __launch_bounds__(kFewBlock) void k_scatter_mean_few(
         const uint32_t* __restrict__ loc_idx, const float* __restrict__ loc_val, uint32_t P,
         uint32_t k, uint32_t m, const uint32_t* __restrict__ bounds, uint32_t nranges,
@@ -185,15 +189,25 @@ __global__ __launch_bounds__(kFewBlock) void k_scatter_mean_few(
     if (base >= m) return;                                 // block-uniform
     const uint32_t span = m - base < (uint32_t)kFewRange ? m - base : (uint32_t)kFewRange;
     if (t < (uint32_t)kWave) {
+        // lane g: where the block's part of worker g's entries in the range starts; lane 32 + g: where it ends
+        const uint32_t g = t % (uint32_t)kFewP;
         uint32_t lo = 0, hi = 0;
-        if (t < P) {
-            const uint32_t* bg = bounds + (size_t)t * (nranges + 1) + range;
+        if (g < P) {
+            const uint32_t* bg = bounds + (size_t)g * (nranges + 1) + range;
             lo = bg[0];
             hi = bg[1];
             // always lo <= hi <= k for a sorted set; keeps every access in bounds for any other
             if (hi > k) hi = k;
             if (lo > hi) lo = hi;
+            const uint32_t first = t < (uint32_t)kFewP ? base : base + (uint32_t)kFewRange;
+            const uint32_t* set = loc_idx + (size_t)g * k;
+            while (lo < hi) {
+                const uint32_t mid = (lo + hi) >> 1;
+                if (set[mid] < first) lo = mid + 1; else hi = mid;
+            }
         }
+        hi = (uint32_t)__shfl_xor((int)lo, kFewP);
+        if (t >= (uint32_t)kFewP || hi < lo) hi = lo;      // (hi < lo: not a sorted set)
         const uint32_t incl = wave_incl_scan(hi - lo);
         if (t < P) {
             s_lo[t] = lo;

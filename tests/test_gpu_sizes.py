@@ -101,3 +101,27 @@ def test_merge_smallest_keys(k, batch):
         oi, ov = orc.merge(idx[2 * b], val[2 * b], idx[2 * b + 1], val[2 * b + 1], k)
         assert np.array_equal(gi[b], oi), f"b={b} idx: {first_diff(gi[b], oi)}"
         assert bits_equal(gv[b], ov), f"b={b} val: {first_diff(gv[b], ov)}"
+
+
+@pytest.mark.parametrize("m", [2047, 2048, 2049, 8191, 8193, 30_001])
+@pytest.mark.parametrize("P", [1, 31, 32])
+def test_dense_average_of_crowded_blocks(m, P):
+    """Up to 32 workers whose entries fill whole blocks of the dense average and their borders."""
+    import torch
+    from paper_1901_04359_amd import binding as B
+    k = max(1, m // 2)
+    rng = np.random.default_rng(m + P)
+    idx = np.stack([np.sort(rng.choice(m, k, replace=False)) for _ in range(P)]).astype(np.uint32)
+    idx[0] = np.arange(m - k, m)         # a run up to the row's end, across every border before it
+    idx[P - 1] = np.arange(k)
+    val = rng.standard_normal((P, k)).astype(np.float32)
+    say(f"dense average: m={m} P={P}")
+    dense = torch.full((m,), 7.0, device="cuda")
+    B.gtopk_topk_allreduce(torch.from_numpy(idx.view(np.int32)).cuda(), torch.from_numpy(val).cuda(), P, k, dense,
+                           B.alloc_allreduce_workspace(m, P))
+    exp = np.zeros(m, dtype=np.float32)
+    for w in range(P):                   # rank order, one fp32 add each
+        exp[idx[w]] += val[w]
+    exp /= np.float32(P)
+    got = dense.cpu().numpy()
+    assert bits_equal(got, exp), first_diff(got, exp)
