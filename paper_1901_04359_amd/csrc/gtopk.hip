@@ -402,7 +402,7 @@ void zero_async(hipStream_t st, const ZeroJob& job) {
 }
 
 inline uint32_t min_key_blocks(uint32_t k) {
-    const uint32_t b = ceil_div(k, 16 * kMinKeyBlock);
+    const uint32_t b = ceil_div(k, 8 * kMinKeyBlock);
     return b < 1 ? 1 : (b > 64 ? 64 : b);
 }
 
