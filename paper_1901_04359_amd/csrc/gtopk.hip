@@ -59,8 +59,9 @@ struct Carver {
 };
 
 // hist .. hist_dense are carved back to back so that one clear covers them
+// with_finish: the select may be finished by k_finish, which needs the groups' offsets
 SelState carve_select(Carver& c, size_t sets, uint32_t list_cap, uint32_t maxgroups,
-                      bool with_dense_hist = false) {
+                      bool with_dense_hist = false, bool with_finish = true) {
     SelState s;
     s.hist = c.take<uint32_t>(sets * kHistBins);
     s.list_cnt = c.take<uint32_t>(sets);
@@ -75,8 +76,8 @@ SelState carve_select(Carver& c, size_t sets, uint32_t list_cap, uint32_t maxgro
     s.need = c.take<uint32_t>(sets);
     s.T_out = nullptr;
     s.list = c.take<uint2>(sets * list_cap);
-    s.off_gt = c.take<uint32_t>(sets * maxgroups);
-    s.off_eq = c.take<uint32_t>(sets * maxgroups);
+    s.off_gt = with_finish ? c.take<uint32_t>(sets * maxgroups) : nullptr;
+    s.off_eq = with_finish ? c.take<uint32_t>(sets * maxgroups) : nullptr;
     s.list_cap = list_cap;
     s.maxgroups = maxgroups;
     s.seg_list = 0u;
@@ -352,7 +353,9 @@ StepWs carve_step(void* ws, int64_t m, uint32_t k, uint32_t P) {
     {
         uint32_t g = s.gcand > s.gdense ? s.gcand : s.gdense;
         if (run_groups(m, k) && table > g) g = table;      // one group per run
-        s.sel = carve_select(c, P, s.cap, g, /*with_dense_hist=*/true);
+        // (only the dense top-k, one row, is ever finished by k_finish: see local_grid.  Without the
+        // offsets the groups of short chunks fit in where the fewer groups of long ones were.)
+        s.sel = carve_select(c, P, s.cap, g, /*with_dense_hist=*/true, /*with_finish=*/P == 1);
     }
     const size_t pairs = P > 1 ? P / 2 : 1;
     s.mrg = carve_merge(c, k, pairs);
