@@ -205,8 +205,9 @@ MergeWs carve_merge(Carver& c, uint32_t k, size_t pairs) {
 
 struct StepWs {
     // local select
-    uint32_t* samp_hist;   // [P][16384]    } cleared together
-    uint32_t* cand_count;  // [P]           }
+    uint32_t* samp_hist;   // [P][16384] or NULL: not needed  } cleared before
+    uint32_t* cand_count;  // [P]                             } every selection
+    size_t samp_words;
     uint32_t* tspec;       // [P] speculative threshold of the streaming pass
     uint32_t* cand_idx;    // [P][cap] candidates as the streaming pass left them (runs)
     float* cand_val;
@@ -272,7 +273,9 @@ constexpr double kMidSampleMin = 16384.0, kMidSampleMax = 32768.0;
 // a spread of a sixth; a list of 3 k + 8192 entries has room for that only while k is in the
 // thousands.  At rank 64 it keeps 1.7 k +- an eighth.
 static double mid_sample_mean(uint32_t k) { return k <= 4096u ? 16.0 : 64.0; }
+// Rows no longer than the smallest sample are one, whatever k and P are.
 static bool mid_problem(int64_t m, uint32_t k, uint64_t P) {
+    if ((double)m <= kMidSampleMin) return true;
     return (uint64_t)m * P <= kMidElements && mid_sample_mean(k) * (double)m <= kMidSampleMax * (double)k &&
            !merge_filtered(k) && !small_problem(m, k, (int64_t)P);
 }
@@ -309,16 +312,6 @@ StepWs carve_step(void* ws, int64_t m, uint32_t k, uint32_t P) {
     s.cap = cand_capacity(m, k);
     s.chunk_log2 = pass_chunk_log2(m, k, P);
     s.nchunks = ceil_div((uint64_t)m + 3, 1u << s.chunk_log2);      // a row may start up to 3 elements into a chunk
-    const bool mid = mid_problem(m, k, P);
-    // The tables per chunk of medium problems are sized for the smallest chunks, so that the workspace of
-    // given k and P never shrinks as m grows, whatever the chunks: at most 28 bytes for each of
-    // 2048 chunks, and no sample histogram (64 KB per worker).
-    uint32_t table = s.nchunks;
-    if (mid) {
-        table = ceil_div((uint64_t)m + 3, 4096);
-        if (table > (uint32_t)kMaxGroups) table = (uint32_t)kMaxGroups;
-        if (table < s.nchunks) table = s.nchunks;
-    }
     {
         uint32_t g = kLocalTargetBlocks / P;
         g = g < 32 ? 32 : (g > (uint32_t)kMaxGroups ? (uint32_t)kMaxGroups : g);
@@ -331,31 +324,31 @@ StepWs carve_step(void* ws, int64_t m, uint32_t k, uint32_t P) {
     s.gdense = P == 1 ? (uint32_t)kMaxGroups : 1024u;
     s.Ld = group_slots_for((uint64_t)m, s.gdense);
     s.gdense = ceil_div((uint64_t)m, s.Ld);
-    s.samp_hist = c.take<uint32_t>(mid ? 0 : (size_t)P * kSampleBins);
     s.cand_count = c.take<uint32_t>(P);
     s.tspec = c.take<uint32_t>(P);
     s.cand_idx = c.take<uint32_t>((size_t)P * s.cap);
     s.cand_val = c.take<float>((size_t)P * s.cap);
-    // (the few-launch path for small problems cuts a row into runs of 4096 elements)
-    const uint32_t nruns_small = small_problem(m, k, P) ? ceil_div((uint64_t)m + 3, kSmallChunk) : 0u;
-    if (table < nruns_small) table = nruns_small;
-    // the sample histogram is dead when the pass writes its runs: short tables lie in its place
-    if (!mid && table <= (uint32_t)kMaxGroups) {
-        static_assert(kMaxGroups * (sizeof(uint2) + sizeof(uint32_t)) <= kSampleBins * sizeof(uint32_t), "fits");
-        s.run_table = reinterpret_cast<uint2*>(s.samp_hist);
-        s.run_off = s.samp_hist + (size_t)P * table * 2;
-    } else {
-        s.run_table = c.take<uint2>((size_t)P * table);
-        s.run_off = c.take<uint32_t>((size_t)P * table);
-    }
+    // The run tables are sized for the shortest chunks (the few-launch path's among them): how long the chunks
+    // are changes in steps with m and k, and a workspace should serve shorter rows and smaller k too
+    // (a density that comes down; a tree, whose rows are m = k).
+    uint32_t table = ceil_div((uint64_t)m + 3, 4096);
+    static_assert(kSmallChunk == 4096, "the shortest chunk");
+    if (table > (uint32_t)kMaxGroups) table = (uint32_t)kMaxGroups;
+    if (table < s.nchunks) table = s.nchunks;
+    s.run_table = c.take<uint2>((size_t)P * table);
+    s.run_off = c.take<uint32_t>((size_t)P * table);
     s.ord_idx = c.take<uint32_t>((size_t)P * s.cap);
     s.ord_val = c.take<float>((size_t)P * s.cap);
     {
         uint32_t g = s.gcand > s.gdense ? s.gcand : s.gdense;
-        if (run_groups(m, k) && table > g) g = table;      // one group per run
-        // (only the dense top-k, one row, is ever finished by k_finish: see local_grid.  Without the
-        // offsets the groups of short chunks fit in where the fewer groups of long ones were.)
+        if (run_groups(m, k) && s.nchunks > g) g = s.nchunks;      // one group per run
+        // (only the dense top-k, one row, is ever finished by k_finish: see local_grid)
         s.sel = carve_select(c, P, s.cap, g, /*with_dense_hist=*/true, /*with_finish=*/P == 1);
+        // The sample histograms lie where the list of in-bin keys will: k_bucket writes that long after they
+        // have been read.  (Rows that need one are longer than 2^14, so their list has at least 8192 entries.)
+        static_assert(kMidSampleMin >= 8192.0 && 8192 * sizeof(uint2) == kSampleBins * sizeof(uint32_t), "fits");
+        s.samp_words = mid_problem(m, k, P) ? 0 : (size_t)P * kSampleBins;
+        s.samp_hist = s.samp_words ? reinterpret_cast<uint32_t*>(s.sel.list) : nullptr;
     }
     const size_t pairs = P > 1 ? P / 2 : 1;
     s.mrg = carve_merge(c, k, pairs);
@@ -388,8 +381,8 @@ void mark_stage(int i, void* const* events, hipStream_t st) {
 
 ZeroJob zero_job(uint32_t* p0 = nullptr, size_t n0 = 0, uint32_t* p1 = nullptr, size_t n1 = 0,
                  uint32_t* p2 = nullptr, size_t n2 = 0, uint32_t* p3 = nullptr, size_t n3 = 0,
-                 uint32_t* p4 = nullptr, size_t n4 = 0) {
-    return ZeroJob{{p0, p1, p2, p3, p4, nullptr}, {n0, n1, n2, n3, n4, 0}};
+                 uint32_t* p4 = nullptr, size_t n4 = 0, uint32_t* p5 = nullptr, size_t n5 = 0) {
+    return ZeroJob{{p0, p1, p2, p3, p4, p5}, {n0, n1, n2, n3, n4, n5}};
 }
 
 // blocks that clear the longest array of the job, `words` words each, at most 1024
@@ -840,7 +833,7 @@ int gtopk_local_select(const float* grad, float* residual, int64_t m, int64_t st
     const StepWs w = carve_step(ws, m, (uint32_t)k, (uint32_t)P);
     if (ws_bytes < w.bytes) return GTOPK_EWORKSPACE;
     return do_local_select(grad, residual, m, stride, (uint32_t)P, (uint32_t)k, out_idx, out_val, w, true,
-                           zero_job(w.samp_hist, (size_t)(w.tspec - w.samp_hist), w.sel.hist,
+                           zero_job(w.samp_hist, w.samp_words, w.cand_count, (size_t)P, w.sel.hist,
                                     select_clear_words(w.sel)),
                            (hipStream_t)stream);
 }
@@ -930,7 +923,7 @@ static int step_impl(const float* grad, float* residual, int64_t m, int64_t stri
     mark_stage(0, events, st);
     // one clear for everything this step needs zeroed: the sampler's histograms and the
     // candidate counters; both selects' histograms and tickets; the global-set bitmap
-    const ZeroJob job = zero_job(w.samp_hist, (size_t)(w.tspec - w.samp_hist), w.sel.hist,
+    const ZeroJob job = zero_job(w.samp_hist, w.samp_words, w.cand_count, (size_t)P, w.sel.hist,
                                  select_clear_words(w.sel), w.mrg.sel.hist, select_clear_words(w.mrg.sel),
                                  w.mrg.sel_alt.hist, w.mrg.alt_clear_words, w.gbits, w.gbits_words);
     int rc = do_local_select(grad, residual, m, stride, (uint32_t)P, (uint32_t)k, li, lv, w, false,
@@ -1097,8 +1090,7 @@ int gtopk_dense_topk(const float* dense, int64_t m, int32_t k, uint32_t* g_idx, 
     const StepWs w = carve_step(ws, m, (uint32_t)k, 1);
     if (ws_bytes < w.bytes) return GTOPK_EWORKSPACE;
     hipStream_t st = (hipStream_t)stream;
-    const ZeroJob job = zero_job(w.samp_hist, (size_t)(w.tspec - w.samp_hist), w.sel.hist,
-                                 select_clear_words(w.sel));
+    const ZeroJob job = zero_job(w.samp_hist, w.samp_words, w.cand_count, 1, w.sel.hist, select_clear_words(w.sel));
     const bool filter = dense_topk_filters(m);
     bool producer_hist = false;
     if (filter)

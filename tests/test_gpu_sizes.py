@@ -4,8 +4,8 @@ import pytest
 
 from oracle import gtopk_oracle as orc
 from paper_1901_04359_amd import workloads as W
-from tests.gpu_harness import bits_equal, first_diff, say
-from tests.test_gpu_parity import _check_two_iterations, run_merge
+from tests.gpu_harness import Device, bits_equal, first_diff, say
+from tests.test_gpu_parity import _check_two_iterations, check_select, run_merge
 
 pytestmark = pytest.mark.gpu
 
@@ -125,3 +125,31 @@ def test_dense_average_of_crowded_blocks(m, P):
     exp /= np.float32(P)
     got = dense.cpu().numpy()
     assert bits_equal(got, exp), first_diff(got, exp)
+
+
+@pytest.mark.parametrize("kind", ["gauss", "ties"])
+@pytest.mark.parametrize("P,m,k", [
+    (4, 16_384, 3), (4, 16_385, 3),      # sizes of the few-launch path, in the general kernels
+    (2, 16_384, 16_384),
+    (1, 1, 1), (8, 63, 2),
+    (128, 16_384, 5), (128, 16_387, 5),
+])
+def test_rows_no_longer_than_the_sample(P, m, k, kind):
+    """Either side of the row length up to which the whole row is the one-block sampler's sample."""
+    from paper_1901_04359_amd import binding as B
+    assert B.gtopk_debug_plan(m, k, P)["tile_len"] == (16 if m <= 16_384 else 64)
+    rng = np.random.default_rng(P + m + k)
+    dev = Device(P, m, k)
+    res = rng.standard_normal((P, m)).astype(np.float32)
+    g = rng.standard_normal((P, m)).astype(np.float32)
+    if kind == "ties":
+        res, g = np.round(res), np.round(g)
+    check_select(dev, res, g, f"short rows P={P} m={m} k={k} kind={kind}")
+    dev.set_res(res)
+    dev.set_grad(g)
+    for _ in range(3):                   # the thresholds are carried over from the second call on
+        gi, gv = dev.step_carry()
+        exp = orc.step(res, g, k)
+        assert np.array_equal(gi, exp["g_idx"]) and bits_equal(gv, exp["g_val"])
+        assert bits_equal(dev.residual(), exp["residual"])
+        res = exp["residual"]
