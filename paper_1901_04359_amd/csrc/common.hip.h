@@ -70,7 +70,7 @@ __device__ inline uint32_t block_incl_scan(uint32_t v, uint32_t* s_wave, uint32_
 
 // Thread t owns the PER histogram bins [t*PER, (t+1)*PER), counts in loc[].  Finds the
 // largest bin d with sum_{b >= d} >= target.  s_out[0] = d, s_out[1] = sum_{b > d},
-// s_out[2] = 1 if such a bin exists (0 if the histogram holds fewer than target entries).
+// s_out[2] = count of bin d (0 if there is no such bin: the histogram holds fewer than target entries).
 template <int PER>
 __device__ inline void suffix_pick(const uint32_t (&loc)[PER], uint32_t target, uint32_t* s_wave,
                                    uint32_t* s_out) {
@@ -89,7 +89,7 @@ __device__ inline void suffix_pick(const uint32_t (&loc)[PER], uint32_t target, 
             if (run < target && run + c >= target) {
                 s_out[0] = (uint32_t)(threadIdx.x * PER + j);
                 s_out[1] = run;
-                s_out[2] = 1;
+                s_out[2] = c;
             }
             run += c;
         }

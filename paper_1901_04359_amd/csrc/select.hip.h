@@ -65,7 +65,8 @@ struct SelState {
 // holds nothing.  group_range() hands a block the slots of a group of a set that is not
 // read as a dense row; sources whose groups are not equal cuts of the logical order
 // (kRunGroups: the runs of the streaming pass, the tiles of a filtered union) answer it
-// from their own tables.  skip() takes a set out of a launch altogether.
+// from their own tables.  skip() takes a set out of a launch altogether.  kTies: the walk
+// records what a long list of equal keys needs (see record_extremes).
 
 // Local select: the candidate list of worker s, or - when the speculative threshold
 // left fewer than k candidates or more than the list holds - the worker's dense row.
@@ -85,6 +86,7 @@ struct CandSrc {
     __device__ bool is_tomb(int, uint32_t) const { return false; }
     static constexpr bool kIdentity = false;
     static constexpr bool kRunScan = true;
+    static constexpr bool kTies = true;
     const float* res;
     int64_t stride;
     uint32_t m, k, cap, nchunks;
@@ -302,6 +304,7 @@ struct MergedSrc {
     static constexpr bool kSegList = true;          // no set of this source is ever read as a dense row
     __device__ const uint32_t* value_row(int s) const { return reinterpret_cast<const uint32_t*>(val) + (size_t)s * stride; }
     static constexpr bool kIdentity = true;
+    static constexpr bool kTies = false;
     static constexpr bool kRunScan = false;
     // A tombstone's value is +0.0: its key falls into the lowest bin of either digit layout, so
     // a walk that only counts keys ABOVE a bin, and looks closer only at keys INSIDE it, can
@@ -378,6 +381,7 @@ struct FiltSrc {
     static constexpr bool kSegList = true;          // no set of this source is ever read as a dense row
     __device__ const uint32_t* value_row(int s) const { return reinterpret_cast<const uint32_t*>(val) + (size_t)s * stride; }
     static constexpr bool kIdentity = false;
+    static constexpr bool kTies = false;
     static constexpr bool kRunScan = false;
     static constexpr bool kValueOnlyWalk = true;
     const uint32_t* idx;
@@ -509,10 +513,39 @@ __global__ __launch_bounds__(kHistBlock) void k_hist(Src src, SelState st, uint3
 
 // Block b of set s walks the physical slots [b*L, (b+1)*L), L = group_slots(); a set with
 // more such segments than the grid has blocks (a dense row) is walked in several turns.
-// For a dense row, whose list can overflow, every group's count of in-bin keys and the
-// row's smallest and largest in-bin key are recorded besides the list: if the list
-// overflows although all in-bin keys are equal (rows of equal magnitudes), the finish needs
-// nothing more than those.
+
+// Masses of equal keys (rows of few distinct magnitudes: signs, zeros, rounded values) make a
+// list of in-bin keys as long as the set, which every block of k_emit, or the one block of
+// k_finish, would read two to four times.  For the sets of the local selection and the dense top-k
+// (kTies) every group's count of in-bin keys and the set's smallest and largest in-bin key are
+// recorded besides the list: if all in-bin keys are equal, the finish of a list that is long
+// (or incomplete) needs nothing more than those.  gtopk_local_select of normal values rounded to integers
+// in us, lists read / counts alone (rows of ordinary values take the same time either way, 85 us at the first size):
+//   m = 1 M  P = 8  k = 125,000   2804 / 107        m = 25.6 M  P = 32  k = 1.85 M  355,600 / 5360
+//   m = 3 M  P = 8  k = 15,001     664 / 452        m = 4 M  P = 64  k = 400,000     86,500 / 1970
+constexpr uint32_t kLongList = 4096;               // (lists of ordinary rows: up to some thousands)
+// hi, lo_inv: a thread's largest in-bin key and largest (kAbs - in-bin key), 0 for none; s_ext: LDS, two words, zero.
+// Every thread of the block calls it.
+__device__ __forceinline__ void record_extremes(const SelState& st, int s, uint32_t hi, uint32_t lo_inv, uint32_t* s_ext) {
+#pragma unroll
+    for (int d = 32; d >= 1; d >>= 1) {
+        const uint32_t h = __shfl_xor(hi, d), l = __shfl_xor(lo_inv, d);
+        hi = h > hi ? h : hi;
+        lo_inv = l > lo_inv ? l : lo_inv;
+    }
+    if (lane_id() == 0) {
+        atomicMax(&s_ext[0], hi);
+        atomicMax(&s_ext[1], lo_inv);
+    }
+    __syncthreads();
+    if (threadIdx.x < 2) {
+        // (equal keys: all blocks but the first few find nothing to do; atomics on one address queue up)
+        uint32_t* to = threadIdx.x == 0 ? &st.bin_hi[s] : &st.bin_lo_inv[s];
+        const uint32_t mine = s_ext[threadIdx.x];
+        if (mine > __hip_atomic_load(to, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) atomicMax(to, mine);
+    }
+}
+
 // ---- the plain walk ----
 // The walk of a set that is NOT read as a dense row: one segment per block, nothing that
 // only a dense row needs.
@@ -526,9 +559,10 @@ __device__ __forceinline__ void bucket_fast(const Src& src, const SelState& st, 
     constexpr int kStash = 1024;
     __shared__ uint2 s_stash[kStash];
     __shared__ uint32_t s_nstash;
+    __shared__ uint32_t s_ext[2];
     const int s = blockIdx.y;
     const uint32_t g = blockIdx.x;
-    if (threadIdx.x == 0) s_nstash = 0u;       // visible after the barrier inside the pick
+    if (threadIdx.x == 0) s_nstash = s_ext[0] = s_ext[1] = 0u;       // visible after the barrier inside the pick
     constexpr bool dn = false;
     constexpr bool kOwnGroup = Src::kIdentity || Src::kRunGroups;     // every slot of the walk is of group g
     const uint32_t L = src.group_slots(dn);
@@ -572,6 +606,7 @@ __device__ __forceinline__ void bucket_fast(const Src& src, const SelState& st, 
         suffix_pick<kPer>(loc, k, s_wave, s_out);
     }
     const uint32_t d1 = s_out[0];
+    const bool ties = Src::kTies && s_out[2] > kLongList;     // block-uniform
     if (g == 0 && threadIdx.x == 0) {
         st.d1[s] = d1;
         st.krem[s] = k - s_out[1];
@@ -603,6 +638,8 @@ __device__ __forceinline__ void bucket_fast(const Src& src, const SelState& st, 
                 const uint32_t pos = base + rank_in(inm);
                 if (inside && pos < (uint32_t)kStash) s_stash[pos] = make_uint2(key, lg);
                 in += cnt;
+                static_assert(!(Src::kTies && kOwnGroup), "the group's count would be the block's");
+                if (ties) add_grouped(inside, lg, st.grp_in + (size_t)s * st.maxgroups);
             }
         }
     }
@@ -623,14 +660,23 @@ __device__ __forceinline__ void bucket_fast(const Src& src, const SelState& st, 
     const uint32_t total = s_nstash;
     if (total == 0) return;
     uint2* list = st.list + (size_t)s * st.list_cap;
+    uint32_t hi = 0, lo_inv = 0;               // this lane's in-bin extremes
+    auto see = [&](uint32_t key) {
+        hi = key > hi ? key : hi;
+        lo_inv = kAbs - key > lo_inv ? kAbs - key : lo_inv;
+    };
     if (total <= (uint32_t)kStash) {
-        for (uint32_t i = threadIdx.x; i < total; i += kBlock)
-            if (s_base + i < st.list_cap) list[s_base + i] = s_stash[i];
+        for (uint32_t i = threadIdx.x; i < total; i += kBlock) {
+            const uint2 e = s_stash[i];
+            if (s_base + i < st.list_cap) list[s_base + i] = e;
+            if (ties) see(e.x);
+        }
+        if (ties) record_extremes(st, s, hi, lo_inv, s_ext);
         return;
     }
     // more in-bin entries than the stash holds: walk the group again; this wave's entries
     // go to its slice of the block's reservation
-    if (in == 0) return;
+    if (in == 0 && !ties) return;
     uint32_t off = s_base;
     for (uint32_t v = 0; v < wave; ++v) off += s_in[v];
     for (uint32_t i0 = (uint32_t)first; i0 < end; i0 += kBlock * kBatch) {
@@ -644,10 +690,12 @@ __device__ __forceinline__ void bucket_fast(const Src& src, const SelState& st, 
             if (inside) {
                 const uint32_t pos = off + rank_in(inm);
                 if (pos < st.list_cap) list[pos] = make_uint2(key, kOwnGroup ? g : lp[j] / L);
+                if (ties) see(key);
             }
             off += (uint32_t)__popcll(inm);
         }
     }
+    if (ties) record_extremes(st, s, hi, lo_inv, s_ext);
 }
 
 // ---- the plain walk, four slots per load ----
@@ -794,6 +842,7 @@ __device__ __forceinline__ void bucket_vec(const Src& src, const SelState& st, u
 constexpr int kRunBatch = 8;                // loads a lane keeps in flight while it walks a run
 template <class Src>
 __device__ __forceinline__ void bucket_runs(const Src& src, const SelState& st, uint32_t k) {
+    static_assert(Src::kTies, "runs of rows");
     constexpr int kWaves = kBlock / kWave;
     __shared__ uint32_t s_wave[kWaves];
     __shared__ uint32_t s_out[3];
@@ -802,13 +851,14 @@ __device__ __forceinline__ void bucket_runs(const Src& src, const SelState& st, 
     constexpr int kStash = 1024;
     __shared__ uint2 s_stash[kStash];
     __shared__ uint32_t s_nstash;
+    __shared__ uint32_t s_ext[2];
     const int s = blockIdx.y;
     const uint32_t wave = threadIdx.x / kWave, lane = lane_id();
     const uint32_t g = blockIdx.x * kWaves + wave;
     constexpr bool dn = false;
     // (block 0 stays even when its groups hold nothing: it records the bin)
     if (blockIdx.x != 0 && blockIdx.x * kWaves >= src.ngroups(s, dn)) return;
-    if (threadIdx.x == 0) s_nstash = 0u;       // visible after the barrier inside the pick
+    if (threadIdx.x == 0) s_nstash = s_ext[0] = s_ext[1] = 0u;       // visible after the barrier inside the pick
     uint32_t first = 0, end = 0;               // wave-uniform
     if (!src.group_range(s, g, first, end)) first = end = 0;
     const Digit dg = src.digit(s, dn, st);
@@ -833,6 +883,7 @@ __device__ __forceinline__ void bucket_runs(const Src& src, const SelState& st, 
         suffix_pick<kPer>(loc, k, s_wave, s_out);
     }
     const uint32_t d1 = s_out[0];
+    const bool ties = Src::kTies && s_out[2] > kLongList;     // block-uniform
     if (blockIdx.x == 0 && threadIdx.x == 0) {
         st.d1[s] = d1;
         st.krem[s] = k - s_out[1];
@@ -873,14 +924,24 @@ __device__ __forceinline__ void bucket_runs(const Src& src, const SelState& st, 
     const uint32_t total = s_nstash;
     if (total == 0) return;
     uint2* list = st.list + (size_t)s * st.list_cap;
+    if (ties && lane == 0 && in != 0) st.grp_in[(size_t)s * st.maxgroups + g] = in;
+    uint32_t hi = 0, lo_inv = 0;               // this lane's in-bin extremes
+    auto see = [&](uint32_t key) {
+        hi = key > hi ? key : hi;
+        lo_inv = kAbs - key > lo_inv ? kAbs - key : lo_inv;
+    };
     if (total <= (uint32_t)kStash) {
-        for (uint32_t i = threadIdx.x; i < total; i += kBlock)
-            if (s_base + i < st.list_cap) list[s_base + i] = s_stash[i];
+        for (uint32_t i = threadIdx.x; i < total; i += kBlock) {
+            const uint2 e = s_stash[i];
+            if (s_base + i < st.list_cap) list[s_base + i] = e;
+            if (ties) see(e.x);
+        }
+        if (ties) record_extremes(st, s, hi, lo_inv, s_ext);
         return;
     }
     // more in-bin entries than the stash holds: every wave walks its run again; its entries
     // go to its slice of the block's reservation
-    if (in == 0) return;
+    if (in == 0 && !ties) return;
     uint32_t off = s_base;
     for (uint32_t v = 0; v < wave; ++v) off += s_in[v];
     for (uint32_t i0 = first; i0 < end; i0 += kWave * kRunBatch) {
@@ -893,10 +954,12 @@ __device__ __forceinline__ void bucket_runs(const Src& src, const SelState& st, 
             if (inside) {
                 const uint32_t pos = off + rank_in(inm);
                 if (pos < st.list_cap) list[pos] = make_uint2(key, g);
+                if (ties) see(key);
             }
             off += (uint32_t)__popcll(inm);
         }
     }
+    if (ties) record_extremes(st, s, hi, lo_inv, s_ext);
 }
 
 // ---- the general walk ----
@@ -910,9 +973,9 @@ __device__ __forceinline__ void bucket_general(const Src& src, const SelState& s
     constexpr int kStash = 1024;
     __shared__ uint2 s_stash[kStash];
     __shared__ uint32_t s_nstash;
-    __shared__ uint32_t s_hi, s_lo_inv;
+    __shared__ uint32_t s_ext[2];
     const int s = blockIdx.y;
-    if (threadIdx.x == 0) { s_nstash = 0u; s_hi = 0u; s_lo_inv = 0u; }   // visible after the barrier inside the pick
+    if (threadIdx.x == 0) s_nstash = s_ext[0] = s_ext[1] = 0u;       // visible after the barrier inside the pick
     const bool dn = src.dense(s);
     const uint32_t n = src.nphys(s, dn);
     const uint32_t L = src.group_slots(dn);
@@ -1040,17 +1103,7 @@ __device__ __forceinline__ void bucket_general(const Src& src, const SelState& s
         if (threadIdx.x == 0) s_nstash = 0u;
         __syncthreads();
     }
-    // only a dense row's list can overflow (any other list holds the whole set)
-    if (!dn) return;
-    if (hi | lo_inv) {
-        atomicMax(&s_hi, hi);
-        atomicMax(&s_lo_inv, lo_inv);
-    }
-    __syncthreads();
-    if (threadIdx.x == 0 && (s_hi | s_lo_inv)) {
-        atomicMax(&st.bin_hi[s], s_hi);
-        atomicMax(&st.bin_lo_inv[s], s_lo_inv);
-    }
+    record_extremes(st, s, hi, lo_inv, s_ext);
 }
 
 // Block b of set s walks the physical slots [b*L, (b+1)*L), L = group_slots().  A set
@@ -1153,7 +1206,7 @@ __global__ __launch_bounds__(1024) void k_finish(Src src, SelState st) {
     // an overflowed list whose in-bin keys are all one key (rows of equal magnitudes): that
     // key is T, and k_bucket's per-group in-bin counts are the tie counts
     const uint32_t bin_hi = st.bin_hi[s], bin_lo = kAbs - st.bin_lo_inv[s];
-    const bool one_key = overflow && bin_hi == bin_lo;
+    const bool one_key = (overflow || (Src::kTies && nlist > kLongList)) && bin_hi == bin_lo;
     const uint32_t gin0 = (one_key && 2 * t < ng) ? st.grp_in[(size_t)s * st.maxgroups + 2 * t] : 0u;
     const uint32_t gin1 = (one_key && 2 * t + 1 < ng) ? st.grp_in[(size_t)s * st.maxgroups + 2 * t + 1] : 0u;
     const bool seg = Src::kSegList && st.seg_list != 0;      // uniform
@@ -1379,18 +1432,24 @@ __device__ __forceinline__ void emit_fast(
             const uint32_t i = t + (uint32_t)j * kT;
             ent[j] = (cached && i < nlist) ? list[i] : make_uint2(kNone, 0u);
         }
+        // a long list of one key: nothing of it is read (the passes below then find nothing and change nothing)
+        uint32_t lim = nlist, one_key = kNone;
+        if (Src::kTies && nlist > kLongList && st.bin_hi[s] == kAbs - st.bin_lo_inv[s]) {
+            one_key = st.bin_hi[s];
+            lim = 0;
+        }
         // f(key, group): key == kNone = nothing
         auto for_each_entry = [&](auto&& f) {
             if (cached) {
 #pragma unroll
                 for (int j = 0; j < kCache; ++j) f(ent[j].x, ent[j].y);
             } else if (!overflow) {
-                for (uint32_t i0 = 0; i0 < nlist; i0 += kT * kBatch) {
+                for (uint32_t i0 = 0; i0 < lim; i0 += kT * kBatch) {
                     uint2 e[kBatch];
 #pragma unroll
                     for (int j = 0; j < kBatch; ++j) {
                         const uint32_t i = i0 + j * kT + t;
-                        e[j] = i < nlist ? list[i] : make_uint2(kNone, 0u);
+                        e[j] = i < lim ? list[i] : make_uint2(kNone, 0u);
                     }
 #pragma unroll
                     for (int j = 0; j < kBatch; ++j) f(e[j].x, e[j].y);
@@ -1439,11 +1498,13 @@ __device__ __forceinline__ void emit_fast(
             prefix = (prefix << bits) | s_out[0];
             krem -= s_out[1];
         }
-        T = lo + prefix;
+        T = one_key != kNone ? one_key : lo + prefix;
         need = krem;
 
         // list keys of the groups before this one: above T, equal to T
         uint32_t c_gt = before_gt, c_eq = 0;
+        if (one_key != kNone)
+            for (uint32_t gp = t; gp < g; gp += kT) c_eq += st.grp_in[(size_t)s * st.maxgroups + gp];
         for_each_entry([&](uint32_t key, uint32_t grp) {
             if (key != kNone && grp < g) {
                 c_gt += key > T ? 1u : 0u;
@@ -1632,7 +1693,7 @@ __device__ __forceinline__ void emit_general(
                 overflow = nlist > st.list_cap;       // the list is incomplete
                 // all in-bin keys are one key (rows of equal magnitudes): no pass over the set
                 const uint32_t bin_hi = st.bin_hi[s], bin_lo = kAbs - st.bin_lo_inv[s];
-                one_key = overflow && bin_hi == bin_lo;
+                one_key = (overflow || (Src::kTies && nlist > kLongList)) && bin_hi == bin_lo;
                 const uint32_t lo = dg.lo(d1), width = dg.width(d1);    // bin d1 = [lo, lo + width)
                 cached = !overflow && nlist <= (uint32_t)(kCache * kT);
 #pragma unroll

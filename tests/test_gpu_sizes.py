@@ -153,3 +153,64 @@ def test_rows_no_longer_than_the_sample(P, m, k, kind):
         assert np.array_equal(gi, exp["g_idx"]) and bits_equal(gv, exp["g_val"])
         assert bits_equal(dev.residual(), exp["residual"])
         res = exp["residual"]
+
+
+def _us(call, reps=5):
+    import torch
+    call(), call()
+    best = float("inf")
+    for _ in range(reps):
+        a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+        a.record()
+        call()
+        b.record()
+        b.synchronize()
+        best = min(best, a.elapsed_time(b) * 1e3)
+    return best
+
+
+@pytest.mark.parametrize("P,m,k", [(8, 1_000_003, 125_000), (2, 4_000_003, 240_000)])
+def test_rows_of_few_magnitudes_are_not_read_per_block(P, m, k):
+    """Values rounded to integers: the bin of the k-th key holds more than 100,000 equal keys.  Reading
+    that list in every block of the emit takes over thirty times as long as a row of distinct values; the
+    bound leaves the few times as long that writing the list and reading it once would take."""
+    dev = Device(P, m, k)
+    rng = np.random.default_rng(m)
+    res = rng.standard_normal((P, m)).astype(np.float32)
+    zero = np.zeros((P, m), dtype=np.float32)
+    us = {}
+    for kind, rows in (("distinct", res), ("rounded", np.round(2 * res))):
+        check_select(dev, rows, zero, f"few magnitudes P={P} m={m} k={k} kind={kind}")
+        # the selected entries are cleared by every call: the rows are put back in between
+        rows_d = dev.torch.from_numpy(rows).cuda()
+
+        def call():
+            dev.res.copy_(rows_d)
+            dev.B.gtopk_local_select(dev.grad, dev.res, k, dev.loc_idx, dev.loc_val, dev.ws)
+
+        us[kind] = _us(call)
+    say(f"us per call: {us}")
+    assert us["rounded"] < 5 * us["distinct"], us
+
+
+@pytest.mark.parametrize("kind", ["one key", "two keys", "none above"])
+@pytest.mark.parametrize("P,m,k", [
+    (2, 3_000_001, 10_000),              # candidates put into index order
+    (2, 3_000_001, 100_000),             # runs selected in place
+    (1, 700_001, 20_000),
+])
+def test_long_lists_of_equal_keys(P, m, k, kind):
+    """Either side of the list length (4096) from which equal in-bin keys are counted and not listed; a
+    second key in the bin (the next float) sends the finish back to the list."""
+    for n_eq in (4095, 4096, 4097, 9000):
+        rng = np.random.default_rng(m + n_eq)
+        rows = (1e-3 * rng.standard_normal((P, m))).astype(np.float32)
+        for w in range(P):
+            at = rng.permutation(m)
+            n_top = 0 if kind == "none above" else k - n_eq // 2
+            rows[w, at[:n_top]] = (2.0 + rng.random(n_top)).astype(np.float32)
+            plateau = at[n_top:n_top + (n_eq if n_top else k + n_eq)]
+            rows[w, plateau] = np.where(rng.random(plateau.size) < 0.5, np.float32(1.0), np.float32(-1.0))
+            if kind == "two keys":
+                rows[w, plateau[::3]] = np.nextafter(np.float32(1.0), np.float32(2.0))
+        check_select(Device(P, m, k), rows, np.zeros_like(rows), f"equal keys P={P} m={m} k={k} {kind} n_eq={n_eq}")
