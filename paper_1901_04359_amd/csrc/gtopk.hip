@@ -440,22 +440,26 @@ void run_select(const Src& src, const SelState& ss0, const SelGrid& gr, uint32_t
     SelState ss = ss0;
     ss.seg_list = (Src::kSegList && gr.own_finish) ? 1u : 0u;
     // few blocks per set (a popular bin takes one same-address atomic per block): 4 slots per
-    // thread up to 32 blocks, then 32 blocks with more slots per thread, then, while the chip is not
-    // full (1024 blocks in all), 32 slots per thread up to 256 blocks.  Every block flushes up to 4096
-    // bins by global atomics.  A step in us with 32 / 64 / 170 blocks per set: m = 25.6 M, P = 32, k = 1.85 M
-    // 3636 / 3635 / 3665;  m = 14 M, P = 16, k = 1 M  1043 / 1045 / 1057;  m = 30 M, P = 2, k = 1.8 M  344 / 333 / 329
-    uint32_t hb = ceil_div(gr.nphys_max, 4 * kHistBlock);
+    // thread up to 32 blocks, then 32 blocks with more slots per thread, then 32 slots per thread up to
+    // 256 blocks, of which a list gets at most its share of the 1024 that fill the chip.  Every block flushes up
+    // to 4096 bins by global atomics.  A step in us with 32 / 64 / 170 blocks per list: m = 25.6 M, P = 32, k = 1.85 M
+    // 3636 / 3635 / 3665;  m = 14 M, P = 16, k = 1 M  1043 / 1045 / 1057;  m = 30 M, P = 2, k = 1.8 M  344 / 333 / 329.
+    // A dense row among lists keeps them all: gtopk_local_select with one row of zeros at the first of these sizes
+    // 3.93 / 3.54 ms with the list's 32 blocks / 170 (3.27 ms without such a row).
+    uint32_t hb = ceil_div(gr.nphys_max, 4 * kHistBlock), dense_hb;
     if (hb > 32) {
         hb = ceil_div(gr.nphys_max, 32 * kHistBlock);
+        hb = hb < 32 ? 32 : (hb > 256 ? 256 : hb);
+        dense_hb = hb;
         const uint32_t most = 1024u / gr.sets;
-        hb = hb > 256 ? 256 : hb;
         hb = hb > most ? most : hb;
         hb = hb < 32 ? 32 : hb;
+    } else {
+        dense_hb = hb = hb < 1 ? 1 : hb;
     }
-    if (hb < 1) hb = 1;
     if (with_hist)
-        hipLaunchKernelGGL((k_hist<Src>), dim3(hb + (Src::kRunScan ? 1 : 0), gr.sets), dim3(kHistBlock), 0,
-                           st, src, ss, hb);
+        hipLaunchKernelGGL((k_hist<Src>), dim3(dense_hb + (Src::kRunScan ? 1 : 0), gr.sets), dim3(kHistBlock), 0,
+                           st, src, ss, hb, dense_hb);
     hipLaunchKernelGGL((k_bucket<Src>), dim3(gr.walk_blocks, gr.sets), dim3(kBlock), 0, st, src, ss, k);
     // small sets: every block of the emit finishes the select itself (the list of keys it
     // needs for that is short); large sets: once per set, in a kernel of its own

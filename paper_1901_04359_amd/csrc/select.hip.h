@@ -449,7 +449,7 @@ struct FiltSrc {
 
 // Few, large blocks per set: a popular bin receives one global atomic per block.  The grid
 // is sized for the sets' lists; a set that is read as a dense row (far longer) is walked
-// by the same blocks with more loads in flight.
+// with more loads in flight.
 template <class Src, int BATCH>
 __device__ __forceinline__ void hist_walk(const Src& src, int s, bool dn, const Digit& dg, uint32_t n,
                                           uint32_t fl, uint32_t hist_blocks, uint32_t* h) {
@@ -479,18 +479,21 @@ __device__ __forceinline__ void hist_walk(const Src& src, int s, bool dn, const 
     }
 }
 
-// For a source whose runs need ordering, one extra block per set (the last one of the
-// grid's x dimension) scans the run counts.
+// A set that is read as a dense row is histogrammed by dense_blocks blocks, any other by the first
+// list_blocks (<= dense_blocks) of them.  For a source whose runs need ordering, one extra block per set (the
+// last one of the grid's x dimension) scans the run counts.
 template <class Src>
-__global__ __launch_bounds__(kHistBlock) void k_hist(Src src, SelState st, uint32_t hist_blocks) {
+__global__ __launch_bounds__(kHistBlock) void k_hist(Src src, SelState st, uint32_t list_blocks, uint32_t dense_blocks) {
     __shared__ uint32_t h[kHistBins];
     __shared__ uint32_t s_wave[kHistBlock / kWave];
     const int s = blockIdx.y;
-    if (Src::kRunScan && blockIdx.x == hist_blocks) {
+    if (Src::kRunScan && blockIdx.x == dense_blocks) {
         src.scan_runs(s, s_wave);
         return;
     }
     const bool dn = src.dense(s);
+    const uint32_t hist_blocks = dn ? dense_blocks : list_blocks;
+    if (blockIdx.x >= hist_blocks) return;
     if (!src.wants_hist(s, dn)) return;          // block-uniform: this set's histogram exists already
     for (int b = threadIdx.x; b < kHistBins; b += kHistBlock) h[b] = 0u;
     __syncthreads();
