@@ -246,7 +246,7 @@ static bool small_problem(int64_t m, int64_t k, int64_t P) {
            m + 3 <= (int64_t)kSmallMaxChunks * kSmallChunk;
 }
 
-struct SamplePlan { uint32_t tile_stride, n_tiles, target; };
+struct SamplePlan { uint32_t tile_stride, n_tiles, target; uint64_t sampled; };
 
 // Long candidate lists are selected where the streaming pass left them, one group per run
 // (RunSrc): from about 256 expected candidates per chunk of the row on, and while the runs
@@ -495,6 +495,7 @@ SamplePlan plan_sample(int64_t m, uint32_t k, uint32_t tile, double sample_mean,
     p.n_tiles = ceil_div((uint64_t)m, p.tile_stride);
     const uint64_t last = (uint64_t)m - (uint64_t)(p.n_tiles - 1) * p.tile_stride;
     const uint64_t sampled = (uint64_t)(p.n_tiles - 1) * tile + (last < tile ? last : tile);
+    p.sampled = sampled < (uint64_t)m ? sampled : (uint64_t)m;
     if (sampled >= (uint64_t)m) {
         p.target = k;                        // the "sample" is the whole row: exact count
     } else {
@@ -523,10 +524,10 @@ bool pass_histograms(int64_t m, uint32_t k) {
 
 // the candidate lists (or dense rows) of the P workers as the select kernels' source
 CandSrc cand_source(const float* rows, int64_t stride, int64_t m, uint32_t k, const StepWs& w,
-                    bool producer_hist, bool no_bounds, uint32_t* thr_state = nullptr) {
+                    bool producer_hist, bool no_bounds, uint32_t* thr_state = nullptr, bool row_hist = false) {
     return CandSrc{rows, stride, (uint32_t)m, k, w.cap, w.nchunks, w.chunk_log2, w.Lc, w.Ld,
                    w.cand_idx, w.cand_val, w.cand_count, w.tspec, w.run_table, w.run_off,
-                   w.ord_idx, w.ord_val, producer_hist, no_bounds, reinterpret_cast<uint4*>(thr_state)};
+                   w.ord_idx, w.ord_val, producer_hist, no_bounds, row_hist, reinterpret_cast<uint4*>(thr_state)};
 }
 
 // The grids are sized for the candidate lists.  A worker that is selected from its dense
@@ -545,7 +546,7 @@ void launch_pass(const float* grad, float* residual, int64_t m, int64_t stride, 
 #define GTOPK_PASS(ITERS)                                                                                   \
     hipLaunchKernelGGL((k_accum_filter<HIST, ITERS, SUM>), grid, block, 0, st, grad, residual, (uint32_t)m,     \
                        stride, w.tspec, w.cand_idx, w.cand_val, w.cap, w.cand_count, w.run_table, w.nchunks, \
-                       w.sel.hist)
+                       w.sel.hist, HIST ? w.sel.hist_dense : w.sel.hist)
     static_assert(kIters == 16, "a chunk of 2^15 elements per block of 16 float4 per lane");
     switch (w.chunk_log2) {
         case 12: GTOPK_PASS(2); break;
@@ -568,10 +569,13 @@ bool filter_rows(const float* grad, float* residual, int64_t m, int64_t stride, 
     // kernels are launched all the same: who samples is decided on the device)
     const uint4* carry = reinterpret_cast<const uint4*>(thr_state);
     const SamplePlan sp = plan_row_sample(m, k, P);
+    // A row that is summed goes through the pass anyway, and one that overfills its list still gains from the
+    // threshold; a row that is not has nothing of a pass whose list will not hold.
+    const uint32_t most = SUM ? 0xFFFFFFFFu : (uint32_t)((double)w.cap * (double)sp.sampled / (double)m);
     if (mid_problem(m, k, P)) {
         const uint32_t zblocks = zero_blocks(job, 4 * kSmallBlock);
         hipLaunchKernelGGL((k_small_sample<kMidSampleTile, true, SUM>), dim3(P + zblocks), dim3(kSmallBlock), 0,
-                           st, grad, residual, (uint32_t)m, stride, P, sp.tile_stride, sp.n_tiles, sp.target,
+                           st, grad, residual, (uint32_t)m, stride, P, sp.tile_stride, sp.n_tiles, sp.target, most,
                            w.tspec, w.cand_count, carry, job);
     } else {
         zero_async(st, job);
@@ -582,7 +586,7 @@ bool filter_rows(const float* grad, float* residual, int64_t m, int64_t stride, 
         if (sblocks < 1) sblocks = 1;
         hipLaunchKernelGGL((k_sample<SUM>), dim3(sblocks, P), dim3(kSampleBlock), 0, st, grad, residual,
                            (uint32_t)m, stride, sp.tile_stride, sp.n_tiles, w.samp_hist, carry);
-        hipLaunchKernelGGL(k_sample_pick, dim3(P), dim3(kSampleBlock), 0, st, w.samp_hist, sp.target,
+        hipLaunchKernelGGL(k_sample_pick, dim3(P), dim3(kSampleBlock), 0, st, w.samp_hist, sp.target, most,
                            w.tspec, carry);
     }
     mark_stage(1, events, st);
@@ -718,7 +722,7 @@ void do_merge_batch(const uint32_t* a_idx, const float* a_val, const uint32_t* b
         hipLaunchKernelGGL(k_merge_sample, dim3(mp.blocks, batch), dim3(kSampleBlock), 0, st, a_idx, a_val,
                            b_idx, b_val, k, in_stride, mp.tile_stride, mp.n_tiles, w.f_samp_hist);
         hipLaunchKernelGGL(k_sample_pick, dim3(batch), dim3(kSampleBlock), 0, st,
-                           (const uint32_t*)w.f_samp_hist, mp.target, w.f_tspec, (const uint4*)nullptr);
+                           (const uint32_t*)w.f_samp_hist, mp.target, 0xFFFFFFFFu, w.f_tspec, (const uint4*)nullptr);
         launch_union_cuts(a_idx, b_idx, k, in_stride, tile, ntiles, batch, w.cuts, st);
         hipLaunchKernelGGL((k_union_path<kUnionPathEpt, true, kUnionHistBlock, true, true>), dim3(ntiles, batch),
                            dim3(kUnionHistBlock), 0, st, a_idx, a_val, b_idx, b_val, k, in_stride, w.m_idx,
@@ -910,13 +914,13 @@ static int step_impl(const float* grad, float* residual, int64_t m, int64_t stri
         // one block per worker samples, picks the threshold and clears the candidate counter
         const SamplePlan sp = plan_sample(m, (uint32_t)k, kSampleTile, kSmallSampleMean, kSmallSampleMin);
         hipLaunchKernelGGL((k_small_sample<kSampleTile, false, true>), dim3(P), dim3(kSmallBlock), 0, st, grad, residual,
-                           (uint32_t)m, stride, (uint32_t)P, sp.tile_stride, sp.n_tiles, sp.target, w.tspec,
-                           w.cand_count, (const uint4*)nullptr, ZeroJob{});
+                           (uint32_t)m, stride, (uint32_t)P, sp.tile_stride, sp.n_tiles, sp.target, 0xFFFFFFFFu,
+                           w.tspec, w.cand_count, (const uint4*)nullptr, ZeroJob{});
         // small blocks: one run per 4096 elements (the run table was carved for that many)
         const uint32_t nruns = ceil_div((uint64_t)m + 3, kSmallChunk);
         hipLaunchKernelGGL((k_accum_filter<false, kSmallIters>), dim3(nruns, P), dim3(kSBlock), 0, st,
                            grad, residual, (uint32_t)m, stride, w.tspec, w.cand_idx, w.cand_val, w.cap,
-                           w.cand_count, w.run_table, nruns, w.sel.hist);
+                           w.cand_count, w.run_table, nruns, w.sel.hist, (uint32_t*)nullptr);
         CandSrc src = cand_source(residual, stride, m, (uint32_t)k, w, false, false);
         src.nchunks = nruns;
         hipLaunchKernelGGL(k_small_select, dim3(P), dim3(kSmallBlock), 0, st, src, (uint32_t)k, li, lv);
@@ -1082,7 +1086,8 @@ int gtopk_topk_allreduce(const uint32_t* loc_idx, const float* loc_val, int32_t 
 //   m = 4,000,001   k = 4000    59.1 / 40.6     k = 240,000     68.8 / 45.0
 //   m = 25,557,032  k = 25,557  180.7 / 63.6    k = 1,533,421  244.4 / 96.6
 //   m = 25,557,032  k = 6.4 M   881.9 / 174.9   k = 23 M       392.4 / 361.3
-// A row with fewer than k non-zeros is read three times as before (212 -> 228 us at the fourth size).
+// A row that its sample shows to be unfit for that (fewer than k non-zeros, masses of few magnitudes) is read three
+// times, the first of them by the pass (see k_accum_filter); one whose sample misleads, on top of the pass.
 static bool dense_topk_filters(int64_t m) { return m >= ((int64_t)1 << 19); }
 
 int gtopk_dense_topk(const float* dense, int64_t m, int32_t k, uint32_t* g_idx, float* g_val,
@@ -1101,7 +1106,8 @@ int gtopk_dense_topk(const float* dense, int64_t m, int32_t k, uint32_t* g_idx, 
         producer_hist = filter_rows<false>(nullptr, const_cast<float*>(dense), m, m, 1, (uint32_t)k, w, job, st);
     else
         zero_async(st, job);       // a candidate count of zero makes the select read the dense row itself
-    const CandSrc src = cand_source(dense, m, m, (uint32_t)k, w, producer_hist, /*no_bounds=*/!filter);
+    const CandSrc src = cand_source(dense, m, m, (uint32_t)k, w, producer_hist, /*no_bounds=*/!filter, nullptr,
+                                    /*row_hist=*/filter);
     // one set: the grids follow the dense row's groups (a row whose sample misled is read as one);
     // without a lower bound of the k-th key the list can be long, so large rows are finished once
     const uint32_t gx = filter && w.gcand > w.gdense ? w.gcand : w.gdense;

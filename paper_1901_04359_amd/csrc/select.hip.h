@@ -102,6 +102,7 @@ struct CandSrc {
     float* ord_val;
     bool producer_hist;                   // the streaming pass has histogrammed the candidates
     bool no_bounds;                       // dense rows without any threshold (the dense top-k)
+    bool row_hist;                        // the pass has histogrammed the rows whose threshold is 0
     uint4* carry_state;                   // [P] or NULL: thresholds carried from call to call
 
     // Called once per set, by the thread that records the set's exact k-th key T: works out
@@ -154,6 +155,7 @@ struct CandSrc {
     // histogram (which counts every candidate, stored or not) is the row's.
     __device__ bool overfull(int s) const { return !no_bounds && cand_count[s] > cap; }
     __device__ bool wants_hist(int s, bool dn) const {
+        if (row_hist && dn && tspec[s] == 0u) return false;
         return !producer_hist || (dn && !overfull(s));
     }
     // Entries of such a row below the speculative threshold cannot be selected (more than k

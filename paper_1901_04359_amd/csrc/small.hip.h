@@ -165,14 +165,14 @@ __device__ __forceinline__ void wave_select_any(const uint32_t* keys, uint32_t n
 // Worker w = blockIdx.x.  Sample tile t covers [t*tile_stride, t*tile_stride + TILE) of the
 // accumulated row (clipped to m), TILE lanes per tile; the block histograms the keys of all
 // tiles in LDS and stores the lower edge of the bucket at which the count from the top
-// reaches `target`.  It also clears the worker's candidate counter for the streaming pass
+// reaches `target` (0 as in k_sample_pick).  It also clears the worker's candidate counter for the streaming pass
 // that follows in stream order.  GENERAL, in front of the general kernels: blocks from P on clear
 // what the rest of the step needs cleared (`job`), and a worker whose threshold is carried over
 // (`carry`, see k_sample) takes that.  !SUM: the row is res alone, grad is not read.
 template <int TILE, bool GENERAL, bool SUM>
 __global__ __launch_bounds__(kSmallBlock) void k_small_sample(
         const float* __restrict__ grad, const float* __restrict__ res, uint32_t m, int64_t stride,
-        uint32_t P, uint32_t tile_stride, uint32_t n_tiles, uint32_t target, uint32_t* __restrict__ tspec,
+        uint32_t P, uint32_t tile_stride, uint32_t n_tiles, uint32_t target, uint32_t most, uint32_t* __restrict__ tspec,
         uint32_t* __restrict__ cand_count, const uint4* __restrict__ carry, ZeroJob job) {
     constexpr int kT = kSmallBlock;
     __shared__ uint32_t h[kSampleBins];
@@ -212,11 +212,13 @@ __global__ __launch_bounds__(kSmallBlock) void k_small_sample(
             gv[u] = SUM && ok[u] ? g[q] : 0.0f;
             rv[u] = ok[u] ? r[q] : 0.0f;
         }
-#pragma unroll
-        for (int u = 0; u < kSmallSampleUnroll; ++u) {
-            const uint32_t bin = (__float_as_uint(SUM ? rv[u] + gv[u] : rv[u]) & kAbs) >> kSampleShift;
-            if (ok[u] && (SUM || bin != 0u)) atomicAdd(&h[bin], 1u);      // (see k_sample)
+        if (!SUM) {
+            count_sampled(h, rv, ok);
+            continue;
         }
+#pragma unroll
+        for (int u = 0; u < kSmallSampleUnroll; ++u)
+            if (ok[u]) atomicAdd(&h[(__float_as_uint(rv[u] + gv[u]) & kAbs) >> kSampleShift], 1u);
     }
     __syncthreads();
     constexpr int kPer = kSampleBins / kT;
@@ -224,7 +226,7 @@ __global__ __launch_bounds__(kSmallBlock) void k_small_sample(
 #pragma unroll
     for (int j = 0; j < kPer; ++j) loc[j] = h[t * kPer + j];
     suffix_pick<kPer>(loc, target, s_wave, s_out);
-    if (t == 0) tspec[w] = s_out[2] ? (s_out[0] << kSampleShift) : 0u;
+    if (t == 0) tspec[w] = s_out[2] && s_out[1] + s_out[2] <= most ? (s_out[0] << kSampleShift) : 0u;
 }
 
 // ---------------------------------------------------------------------------------

@@ -6,6 +6,33 @@
 
 namespace gtopk {
 
+// Counts N sampled values of a row that is not summed into h: mostly zeros, or of few magnitudes, all lanes on
+// one counter.  The lowest bin's count makes no difference (whether the pick ends in it or finds too few
+// entries above it, the threshold is 0); where the wave's first values have one bin, lanes that agree add once.
+template <int N>
+__device__ __forceinline__ void count_sampled(uint32_t* h, const float (&v)[N], const bool (&ok)[N]) {
+    auto bin_of = [&](int u) { return (__float_as_uint(v[u]) & kAbs) >> kSampleShift; };
+    const uint32_t b = bin_of(0);
+    if (__ballot(ok[0] && b != (uint32_t)__builtin_amdgcn_readfirstlane(b))) {
+#pragma unroll
+        for (int u = 0; u < N; ++u)
+            if (ok[u] && bin_of(u) != 0u) atomicAdd(&h[bin_of(u)], 1u);
+        return;
+    }
+    for (int u = 0; u < N; ++u) {
+        const uint32_t bu = bin_of(u);
+        const bool counts = ok[u] && bu != 0u;
+        const uint64_t act = __ballot(counts);
+        if (act == 0) continue;
+        const uint32_t first = (uint32_t)__builtin_ctzll(act), b0 = __shfl(bu, first);
+        if (__ballot(counts && bu == b0) != act) {
+            if (counts) atomicAdd(&h[bu], 1u);
+        } else if (lane_id() == first) {
+            atomicAdd(&h[b0], (uint32_t)__popcll(act));
+        }
+    }
+}
+
 // Sample tile t of a row covers [t*tile_stride, t*tile_stride + 64) (clipped to m): one
 // wave per tile.  A block of 1024 threads takes sixteen tiles per round and keeps four
 // rounds of loads in flight.  (SUM: the row is res + grad; else it is res alone, grad is not read.)
@@ -36,14 +63,15 @@ __global__ __launch_bounds__(kSampleBlock) void k_sample(
             gv[u] = SUM && ok[u] ? g[q] : 0.0f;
             rv[u] = ok[u] ? r[q] : 0.0f;
         }
+        if (!SUM) {
+            count_sampled(h, rv, ok);
+            continue;
+        }
 #pragma unroll
         for (int u = 0; u < kUnroll; ++u) {
             if (ok[u]) {
-                const uint32_t key = __float_as_uint(SUM ? rv[u] + gv[u] : rv[u]) & kAbs;
-                // (a row that is not summed is mostly zeros, all lanes on one counter; the lowest
-                // bin's count makes no difference: whether the pick ends in it or finds too few
-                // entries above it, the threshold is 0)
-                if (SUM || (key >> kSampleShift) != 0u) atomicAdd(&h[key >> kSampleShift], 1u);
+                const uint32_t key = __float_as_uint(rv[u] + gv[u]) & kAbs;
+                atomicAdd(&h[key >> kSampleShift], 1u);
             }
         }
     }
@@ -57,9 +85,9 @@ __global__ __launch_bounds__(kSampleBlock) void k_sample(
 
 // One block per worker turns the worker's sample histogram into the speculative
 // threshold: the lower edge of the bucket at which the count from the top reaches
-// `target`.
+// `target`; 0 if the sample holds fewer entries than that, or more than `most` from that edge on.
 __global__ __launch_bounds__(kSampleBlock) void k_sample_pick(
-        const uint32_t* __restrict__ samp_hist, uint32_t target, uint32_t* __restrict__ tspec,
+        const uint32_t* __restrict__ samp_hist, uint32_t target, uint32_t most, uint32_t* __restrict__ tspec,
         const uint4* __restrict__ carry) {
     __shared__ uint32_t s_wave[kSampleBlock / kWave];
     __shared__ uint32_t s_out[3];
@@ -77,7 +105,7 @@ __global__ __launch_bounds__(kSampleBlock) void k_sample_pick(
 #pragma unroll
     for (int j = 0; j < kPer; ++j) loc[j] = hist[threadIdx.x * kPer + j];
     suffix_pick<kPer>(loc, target, s_wave, s_out);
-    if (threadIdx.x == 0) tspec[w] = s_out[2] ? (s_out[0] << kSampleShift) : 0u;
+    if (threadIdx.x == 0) tspec[w] = s_out[2] && s_out[1] + s_out[2] <= most ? (s_out[0] << kSampleShift) : 0u;
 }
 
 // Rows need not start on a 16-byte boundary (stride and m are arbitrary).  With
@@ -101,17 +129,25 @@ __global__ __launch_bounds__(kSampleBlock) void k_sample_pick(
 // candidates are spread evenly, and far worse where they crowd into a few blocks.)
 // !SUM (the dense top-k): the row is `res` as it stands: grad is not read and nothing is stored to the
 // row.  Half the bytes per block of the sum's pass and no writes: 22 us at m = 25,557,032 = 4.6 TB/s.
+// A threshold of 0 there says that the sample found nothing to filter by (fewer than k non-zeros, masses of one
+// magnitude): the counter stays 0, the select reads the row itself, and the pass counts the coarse first digits
+// of the whole row into row_hist in the histogram kernel's place (34 against 53 us at m = 25,557,032).  That pays
+// for the sample: gtopk_dense_topk in us, reading the row three times with no sample / threshold as it comes and
+// the histogram kernel / this, m = 25,557,032, k = 25,557 and m = 530,000, k = 530:
+//   half as many non-zeros as k  210 / 226 / 207   39 / 46 / 38       one magnitude     207 / 297 / 206   39 / 58 / 41
+//   just k non-zeros             161 / 176 / 170   32 / 39 / 35       powers of two     218 / 215 / 240   38 / 48 / 48
 template <bool HIST, int ITERS = kIters, bool SUM = true>
 __global__ __launch_bounds__(kSBlock) void k_accum_filter(
         const float* __restrict__ grad, float* __restrict__ res, uint32_t m, int64_t stride,
         const uint32_t* __restrict__ tspec, uint32_t* __restrict__ cand_idx,
         float* __restrict__ cand_val, uint32_t cap, uint32_t* __restrict__ cand_count,
-        uint2* __restrict__ run_table, uint32_t nchunks, uint32_t* __restrict__ hist) {
+        uint2* __restrict__ run_table, uint32_t nchunks, uint32_t* __restrict__ hist,
+        uint32_t* __restrict__ row_hist) {
     constexpr int kWaves = kSBlock / kWave;
     __shared__ uint32_t s_cnt[kWaves];
     __shared__ uint32_t s_base;
     __shared__ uint32_t s_total;
-    __shared__ uint32_t s_h[HIST ? kHistBins : 1];
+    __shared__ uint32_t s_h[HIST || !SUM ? kHistBins : 1];
     if (HIST)
         for (int b = threadIdx.x; b < kHistBins; b += kSBlock) s_h[b] = 0u;     // a barrier follows
     const int w = blockIdx.y;
@@ -124,9 +160,6 @@ __global__ __launch_bounds__(kSBlock) void k_accum_filter(
     float* r = res + (int64_t)w * stride - head;
     const uint32_t vend = head + m;          // <= 2^31 + 3
     const uint32_t ts = tspec[w];
-    // a sample without enough entries above the lowest bin (fewer than k non-zeros): nothing to filter by.
-    // The counter stays 0 and the select reads the row itself (block-uniform).
-    if (!SUM && ts == 0u) return;
     // chunk < ceil((m + 3) / 32768), so none of the offsets below wraps
     constexpr uint32_t kSpan = ITERS * 4 * kWave;            // elements per wave
     const uint32_t wbase = chunk * (kSpan * (uint32_t)kWaves) + wave * kSpan;
@@ -179,6 +212,39 @@ __global__ __launch_bounds__(kSBlock) void k_accum_filter(
         }
     }
 
+    if (!SUM && ts == 0u) {                                      // block-uniform
+        const Digit coarse{0u, (uint32_t)kCoarseShift};
+        uint32_t low = 0;                                        // entries of the lowest bin, wave-uniform
+        if (!HIST)
+            for (int b = threadIdx.x; b < kHistBins; b += kSBlock) s_h[b] = 0u;
+        __syncthreads();                                         // s_h is clear
+#pragma unroll
+        for (int i = 0; i < ITERS; ++i) {
+            const uint32_t v = wbase + i * 256 + lane * 4;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const bool in = v + e >= head && v + e < vend;
+                const uint32_t b = coarse.bin(__float_as_uint(a[i][e]) & kAbs);
+                low += (uint32_t)__popcll(__ballot(in && b == 0u));
+                const uint64_t act = __ballot(in && b != 0u);
+                if (act == 0) continue;
+                // (one value throughout: one add, as in the histogram kernel)
+                const uint32_t b0 = __shfl(b, __builtin_ctzll(act));
+                if (__ballot(in && b == b0) == act) {
+                    if (lane == (uint32_t)__builtin_ctzll(act)) atomicAdd(&s_h[b0], (uint32_t)__popcll(act));
+                } else if (in && b != 0u) {
+                    atomicAdd(&s_h[b], 1u);
+                }
+            }
+        }
+        if (lane == 0 && low) atomicAdd(&s_h[0], low);
+        __syncthreads();
+        for (int b = threadIdx.x; b < kHistBins; b += kSBlock) {
+            const uint32_t n = s_h[b];
+            if (n) atomicAdd(&row_hist[(size_t)w * kHistBins + b], n);
+        }
+        return;
+    }
     uint32_t cnt = 0;   // wave-uniform
 #pragma unroll
     for (int i = 0; i < ITERS; ++i) {

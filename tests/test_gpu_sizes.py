@@ -247,3 +247,50 @@ def test_one_dense_row_among_many_lists():
     assert torch.equal(dev.loc_idx[6], top)              # (with this seed the border is no tie)
     say(f"us per call: {us}")
     assert us["one of zeros"] < 1.12 * us["ordinary"], us          # 1.06; with the lists' blocks 1.18
+
+
+@pytest.mark.parametrize("kind", ["zeros", "few", "just k", "one magnitude", "powers of two", "most of one"])
+@pytest.mark.parametrize("m,k", [
+    (1 << 19, 700),                      # one-block sampler, the pass histograms
+    (700_001, 5000),                     # one-block sampler, it does not
+    (3_000_001, 1000),                   # the large sample
+    (3_000_001, 30_000),
+])
+def test_dense_topk_of_rows_that_cannot_be_filtered(m, k, kind):
+    """Rows whose sample shows fewer than k non-zeros, or more entries at one magnitude than the candidate list
+    holds: the pass filters nothing (no candidate is counted) and histograms the row instead."""
+    import torch
+    from paper_1901_04359_amd import binding as B
+    rng = np.random.default_rng(m + k)
+    d = np.zeros(m, dtype=np.float32)
+    if kind == "few":
+        at = rng.choice(m, k // 2, replace=False)
+        d[at] = rng.standard_normal(at.size)
+    elif kind == "just k":
+        at = rng.choice(m, k, replace=False)
+        d[at] = rng.standard_normal(at.size)
+    elif kind == "one magnitude":
+        d = np.where(rng.random(m) < 0.5, np.float32(0.25), np.float32(-0.25)).astype(np.float32)
+    elif kind == "powers of two":
+        x = rng.standard_normal(m)
+        d = (np.sign(x) * np.exp2(np.minimum(np.floor(np.log2(np.abs(x) + 1e-9)), 0.0))).astype(np.float32)
+    elif kind == "most of one":
+        d = (1e-3 * rng.standard_normal(m)).astype(np.float32)
+        d[rng.random(m) < 0.6] = np.float32(3.0)
+        d[rng.choice(m, k // 3, replace=False)] = np.float32(5.0)
+    d[::7] *= np.float32(-1.0)           # -0.0 among the zeros
+    say(f"dense top-k that cannot be filtered: m={m} k={k} kind={kind}")
+    row = torch.from_numpy(d).cuda()
+    gi = torch.zeros(k, dtype=torch.int32, device="cuda")
+    gv = torch.zeros(k, device="cuda")
+    ws = B.alloc_workspace(m, k, 1)
+    ws.fill_(0xA5)
+    B.gtopk_dense_topk(row, k, gi, gv, ws)
+    torch.cuda.synchronize()
+    counts, _ = B.gtopk_debug_candidate_counts(ws, m, k, 1)
+    assert counts == [0], (counts, kind)
+    oi, ov = orc.dense_topk(d, k)
+    gi, gv = gi.cpu().numpy().view(np.uint32), gv.cpu().numpy()
+    assert np.array_equal(gi, oi), first_diff(gi, oi)
+    assert bits_equal(gv, ov), first_diff(gv, ov)
+    assert bits_equal(row.cpu().numpy(), d), "the row was written to"
