@@ -273,9 +273,9 @@ constexpr double kMidSampleMin = 16384.0, kMidSampleMax = 32768.0;
 // a spread of a sixth; a list of 3 k + 8192 entries has room for that only while k is in the
 // thousands.  At rank 64 it keeps 1.7 k +- an eighth.
 static double mid_sample_mean(uint32_t k) { return k <= 4096u ? 16.0 : 64.0; }
-// Rows no longer than the smallest sample are one, whatever k and P are.
+// Rows no longer than the few-launch path's smallest sample, which is all of them there too, always are.
 static bool mid_problem(int64_t m, uint32_t k, uint64_t P) {
-    if ((double)m <= kMidSampleMin) return true;
+    if ((double)m <= kSmallSampleMin) return true;
     return (uint64_t)m * P <= kMidElements && mid_sample_mean(k) * (double)m <= kMidSampleMax * (double)k &&
            !merge_filtered(k) && !small_problem(m, k, (int64_t)P);
 }
@@ -345,8 +345,8 @@ StepWs carve_step(void* ws, int64_t m, uint32_t k, uint32_t P) {
         // (only the dense top-k, one row, is ever finished by k_finish: see local_grid)
         s.sel = carve_select(c, P, s.cap, g, /*with_dense_hist=*/true, /*with_finish=*/P == 1);
         // The sample histograms lie where the list of in-bin keys will: k_bucket writes that long after they
-        // have been read.  (Rows that need one are longer than 2^14, so their list has at least 8192 entries.)
-        static_assert(kMidSampleMin >= 8192.0 && 8192 * sizeof(uint2) == kSampleBins * sizeof(uint32_t), "fits");
+        // have been read.  (Rows that need one are longer than 8192, and so is their list.)
+        static_assert(kSmallSampleMin >= 8192.0 && 8192 * sizeof(uint2) == kSampleBins * sizeof(uint32_t), "fits");
         s.samp_words = mid_problem(m, k, P) ? 0 : (size_t)P * kSampleBins;
         s.samp_hist = s.samp_words ? reinterpret_cast<uint32_t*>(s.sel.list) : nullptr;
     }

@@ -129,15 +129,15 @@ def test_dense_average_of_crowded_blocks(m, P):
 
 @pytest.mark.parametrize("kind", ["gauss", "ties"])
 @pytest.mark.parametrize("P,m,k", [
-    (4, 16_384, 3), (4, 16_385, 3),      # sizes of the few-launch path, in the general kernels
-    (2, 16_384, 16_384),
+    (4, 8_192, 3), (4, 8_193, 3),        # sizes of the few-launch path, in the general kernels
+    (2, 8_192, 8_192),
     (1, 1, 1), (8, 63, 2),
-    (128, 16_384, 5), (128, 16_387, 5),
+    (128, 8_192, 3), (128, 8_195, 3),
 ])
 def test_rows_no_longer_than_the_sample(P, m, k, kind):
     """Either side of the row length up to which the whole row is the one-block sampler's sample."""
     from paper_1901_04359_amd import binding as B
-    assert B.gtopk_debug_plan(m, k, P)["tile_len"] == (16 if m <= 16_384 else 64)
+    assert B.gtopk_debug_plan(m, k, P)["tile_len"] == (16 if m <= 8_192 else 64)
     rng = np.random.default_rng(P + m + k)
     dev = Device(P, m, k)
     res = rng.standard_normal((P, m)).astype(np.float32)

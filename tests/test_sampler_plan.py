@@ -50,3 +50,16 @@ def test_sample_plan_keeps_between_k_and_capacity(m, k, nseg):
         assert kept_lo <= plan["capacity"], f"trial {trial}: {kept_lo} > capacity {plan['capacity']}"
         ratios.append(kept_lo / k)
     assert max(ratios) < 2.5, ratios      # the margin is a fraction of k, not a multiple
+
+
+@pytest.mark.parametrize("m,k,P", [(8_193, 20, 4), (9_000, 64, 64), (16_384, 50, 4), (269_722, 270, 8)])
+def test_the_plan_of_the_few_launch_path_has_one_tile_length(m, k, P):
+    """plan[8] .. plan[10] describe a sampler whose tiles are tile_len long, as the general kernels' are there."""
+    try:
+        plan = B.gtopk_debug_plan(m, k, P)
+    except OSError as e:          # library not built
+        pytest.skip(str(e))
+    assert plan["small_path"] == 1 and plan["tile_len"] == 64
+    covered = (plan["small_n_tiles"] - 1) * plan["small_tile_stride"] + plan["tile_len"]
+    assert m - plan["small_tile_stride"] < covered                    # tiles up to the row's end
+    assert plan["small_n_tiles"] * plan["tile_len"] >= 8_192
