@@ -323,7 +323,8 @@ int gtopk_debug_merge_kept(const void* ws, int32_t k, int32_t batch, uint32_t* h
  *   plan[12] merge_tile_stride, plan[13] merge_n_tiles, plan[14] merge_target: that sample -
  *                        tile t covers positions [t*merge_tile_stride, +plan[2]) of both
  *                        operands (all 0 where plan[11] is 0)
- *   plan[15] reserved (0)
+ *   plan[15] chunk_log2: a block of the general kernels' streaming pass covers 2^plan[15] elements of a
+ *                        row - one run of candidates (a block of the few-launch path: 4096)
  */
 #define GTOPK_PLAN_WORDS 16
 int gtopk_debug_plan(int64_t m, int32_t k, int32_t P, uint32_t* plan);

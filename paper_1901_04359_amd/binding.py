@@ -352,7 +352,7 @@ def gtopk_probe_stream(a, b, n: int, mode: int, sink=None) -> None:
 
 PLAN_FIELDS = ("tile_stride", "n_tiles", "tile_len", "target", "capacity", "pass_histogram",
                "small_path", "run_groups", "small_tile_stride", "small_n_tiles", "small_target",
-               "merge_filtered", "merge_tile_stride", "merge_n_tiles", "merge_target", "reserved")
+               "merge_filtered", "merge_tile_stride", "merge_n_tiles", "merge_target", "chunk_log2")
 
 
 def gtopk_debug_plan(m: int, k: int, P: int) -> dict:

@@ -1186,6 +1186,7 @@ int gtopk_debug_plan(int64_t m, int32_t k, int32_t P, uint32_t* plan) {
         plan[9] = ss.n_tiles;
         plan[10] = ss.target;
     }
+    plan[15] = pass_chunk_log2(m, (uint32_t)k, (uint64_t)P);
     return GTOPK_OK;
 }
 

@@ -25,20 +25,26 @@ def test_merge_batches_at_the_unions_border(kind, k, batch):
 
 
 @pytest.mark.parametrize("kind", ["gauss", "ties"])
-@pytest.mark.parametrize("P,m,k,pad,tile", [
-    (2, 33_001, 900, 1, 16),             # 4096-element chunks, runs selected in place
-    (4, 900_001, 4000, 0, 16),           # 4096, runs put into index order
-    (4, 1_500_003, 300_000, 3, 16),      # 4096, a dense selection
-    (8, 1_100_003, 5000, 2, 16),         # 8192
-    (16, 1_048_581, 5000, 0, 16),        # 16384
-    (2, 3_000_001, 4500, 5, 64),         # the large sample, whose histogram's place the run tables take
+@pytest.mark.parametrize("P,m,k,pad,tile,chunk_log2,in_place", [
+    # few blocks: chunks down to 4096 elements
+    (2, 33_001, 900, 1, 16, 12, 1),
+    (4, 900_001, 4000, 0, 16, 12, 0),    # runs put into index order
+    (4, 1_500_003, 300_000, 3, 16, 12, 1),
+    (8, 1_100_003, 5000, 2, 16, 13, 0),
+    (16, 1_048_581, 5000, 0, 16, 14, 0),
+    (2, 3_000_001, 4500, 5, 64, 12, 0),  # the large sample
+    # blocks enough: chunks by the density
+    (32, 2_200_003, 120_000, 1, 64, 13, 1),
+    (32, 2_200_003, 12_000, 0, 64, 15, 0),
+    (32, 3_000_017, 20_000, 3, 64, 14, 1),
 ])
-def test_step_at_every_chunk_size(P, m, k, pad, tile, kind):
-    """Medium rows: the one-block sampler (tiles of 16) and each size of the pass's chunks, on
-    rows of ragged length and alignment."""
+def test_step_at_every_chunk_size(P, m, k, pad, tile, chunk_log2, in_place, kind):
+    """Each size of the pass's chunks by either rule, with runs selected in place and put into index order, after
+    the one-block sampler (tiles of 16) and the large one, on rows of ragged length and alignment."""
     from paper_1901_04359_amd import binding as B
     plan = B.gtopk_debug_plan(m, k, P)
     assert plan["tile_len"] == tile and plan["small_path"] == 0
+    assert plan["chunk_log2"] == chunk_log2 and plan["run_groups"] == in_place
     _check_two_iterations(P, m, k, kind, pad, "chunk sizes")
 
 
