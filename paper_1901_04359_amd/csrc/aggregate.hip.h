@@ -7,7 +7,7 @@
 
 namespace gtopk {
 
-constexpr int kAggRange = 8192;        // dense elements per block (held in LDS)
+constexpr int kAggRange = 8192;        // dense elements per range of the bounds = per block of k_scatter_mean (in LDS)
 constexpr int kAggMaxP = 1024;         // workers, at most
 
 constexpr int kAggRangeLog2 = 13;
@@ -19,8 +19,9 @@ constexpr int kFewBlock = 256;
 static_assert(kAggRange % kFewRange == 0, "a block's elements lie in one range");
 
 // bounds[g][b] = number of entries of worker g's (index-ascending) k-set with index below
-// b * kAggRange, for b = 0 .. nranges: the slices that k_scatter_mean's blocks take.  One
-// binary search per bound; the searches of neighbouring bounds share their first probes.
+// b * kAggRange, for b = 0 .. nranges: the slices that k_scatter_mean's blocks take, and between which
+// k_scatter_mean_few's search on.  One binary search per bound; the searches of neighbouring bounds
+// share their first probes.
 __global__ __launch_bounds__(kBlock) void k_slice_bounds(
         const uint32_t* __restrict__ loc_idx, uint32_t k, uint32_t nranges,
         uint32_t* __restrict__ bounds) {
@@ -251,7 +252,7 @@ __global__ __launch_bounds__(kFewBlock) void k_scatter_mean_few(
         }
 #pragma unroll
         for (int u = 0; u < kEpt; ++u) {
-            mine[u] = mine[u] && ei[u] < (uint32_t)kFewRange;      // not the other half's
+            mine[u] = mine[u] && ei[u] < (uint32_t)kFewRange;      // always for a sorted set; stays in LDS for any other
             if (mine[u]) atomicOr(&who[ei[u]], 1u << eg[u]);
         }
         __syncthreads();

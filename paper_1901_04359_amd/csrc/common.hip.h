@@ -7,11 +7,11 @@ namespace gtopk {
 
 constexpr int kWave = 64;
 constexpr int kSBlock = 512;                // threads per block of the streaming pass
-constexpr int kIters = 16;                  // float4 loads per lane and array in the streaming pass
+constexpr int kIters = 16;                  // float4 loads per lane and array in the streaming pass, at most
 constexpr int kWaveSpan = kIters * 4 * kWave;            // 4096 elements per wave
 constexpr int kChunkLog2 = 15;
-constexpr int kChunk = 1 << kChunkLog2;                  // 32768 elements per block = one run
-static_assert(kChunk == kWaveSpan * (kSBlock / kWave), "a block covers exactly one chunk");
+constexpr int kChunk = 1 << kChunkLog2;                  // elements per block = one run, at most (2^12 .. 2^15)
+static_assert(kChunk == kWaveSpan * (kSBlock / kWave), "a block of kIters covers exactly the largest chunk");
 constexpr int kBlock = 256;                 // threads per block of the select kernels
 constexpr int kBatch = 2;                   // items a thread loads before it processes any (swept: 1, 2, 4, 8)
 constexpr int kHistBatch = 2;               // the same in the histogram kernel

@@ -249,10 +249,15 @@ static bool small_problem(int64_t m, int64_t k, int64_t P) {
 struct SamplePlan { uint32_t tile_stride, n_tiles, target; uint64_t sampled; };
 
 // Long candidate lists are selected where the streaming pass left them, one group per run
-// (RunSrc): from about 256 expected candidates per chunk of the row on, and while the runs
-// of a row are no more than the select's group tables hold.
+// (RunSrc): from about 256 expected candidates per 2^15 elements of the row on (k = 0.56 % of m),
+// whatever the pass's chunks, and while the runs of a row are no more than the select's group tables hold.
+// The line is that of chunks of 2^15.  gtopk_local_select in us, put into index order first / in place:
+//   chunks of 2^15, m = 3 M  P = 32  k = 9000   260 / 262   k = 15,000   272 / 276   (2^14) k = 60,000  313 / 323
+//   2^13 .. 2^14    m = 3 M  P = 8   k = 9000  97.5 / 94.5  k = 24,000  98.1 / 95.8  k = 750,000       177 / 171
+//   2^12            m = 1 M  P = 8   k = 1000  54.8 / 49.0  k = 8000    63.6 / 58.0  k = 125,000      81.3 / 85.0
+// so with short chunks it could lie lower, and rows of an eighth dense go either way.
 static bool run_groups(int64_t m, uint32_t k) {
-    const double per_chunk = 1.4 * (double)k * (double)kChunk / (double)m;
+    const double per_chunk = 1.4 * (double)k * (double)kChunk / (double)m;     // of the largest chunk
     return per_chunk >= 256.0 && ceil_div((uint64_t)m + 3, kChunk) <= (uint64_t)kMaxGroups;
 }
 // (the few-launch path takes a smaller sample: one block per worker reads it)
@@ -269,9 +274,14 @@ SamplePlan plan_sample(int64_t m, uint32_t k, uint32_t tile, double sample_mean,
 // block loses: 65,536 elements at m = 8 M, P = 4, k = 8000 take the step from 148 to 161 us.
 constexpr uint64_t kMidElements = 1ull << 26;            // of all rows together
 constexpr double kMidSampleMin = 16384.0, kMidSampleMax = 32768.0;
-// Expected sample rank of the k-th key.  At rank 16 the threshold keeps 2.5 k candidates on average with
-// a spread of a sixth; a list of 3 k + 8192 entries has room for that only while k is in the
-// thousands.  At rank 64 it keeps 1.7 k +- an eighth.
+// Expected sample rank of the k-th key, at least.  At rank 16 the threshold keeps 2.5 k candidates on average
+// with a spread of a sixth; a list of 3 k + 8192 entries has room for that only while k is in the
+// thousands (k = 4096, the shortest list for it: 5 k, missed with a probability of some 1e-5 per worker, and
+// then that worker is selected from its dense row).  At rank 64 it keeps 1.7 k +- an eighth.
+// The step from one to the other leaves a gap: rows of 512 k .. 2048 k elements (2.1 to 8.4 M at the border)
+// take the three launches from k = 4097 until rank 64 fits too.  With rank 16 up to k = 8192 in its place
+// gtopk_local_select takes, m = 3 M, k = 6000, P = 4: 67.0 -> 61.5 us, P = 8: 107.5 -> 106.0, but lists are
+// missed where they are shortest, m = 8 M, P = 2, k = 5600: 72.6 -> 138.
 static double mid_sample_mean(uint32_t k) { return k <= 4096u ? 16.0 : 64.0; }
 // Rows no longer than the few-launch path's smallest sample, which is all of them there too, always are.
 static bool mid_problem(int64_t m, uint32_t k, uint64_t P) {
@@ -329,8 +339,8 @@ StepWs carve_step(void* ws, int64_t m, uint32_t k, uint32_t P) {
     s.cand_idx = c.take<uint32_t>((size_t)P * s.cap);
     s.cand_val = c.take<float>((size_t)P * s.cap);
     // The run tables are sized for the shortest chunks (the few-launch path's among them): how long the chunks
-    // are changes in steps with m and k, and a workspace should serve shorter rows and smaller k too
-    // (a density that comes down; a tree, whose rows are m = k).
+    // are changes in steps with m and k, and a workspace should serve smaller k too (a density that comes
+    // down), and the tree, whose rows are m = k.  (The groups' tables still go up and down by some KB.)
     uint32_t table = ceil_div((uint64_t)m + 3, 4096);
     static_assert(kSmallChunk == 4096, "the shortest chunk");
     if (table > (uint32_t)kMaxGroups) table = (uint32_t)kMaxGroups;
@@ -473,14 +483,15 @@ void run_select(const Src& src, const SelState& ss0, const SelGrid& gr, uint32_t
     }
 }
 
-// Sample plan for the speculative threshold: tiles of 64 contiguous elements, evenly
-// spaced, about kSampleMean / rho elements per worker but at least 4096 tiles (all
-// elements if the row is short).  `target` is the rank in the sample whose bucket edge is taken: the
-// expected sample rank of the k-th key plus 5.5 standard deviations, so that the
-// candidate list holds at least k entries except with probability ~1e-8 per worker
-// (and then that worker is merely selected from its dense row).
-// sample_mean: expected sample rank of the k-th key, at least.  min_tiles: spread (with
-// 4096, a layer of 1 % of the row still gets ~40 tiles).
+// Sample plan for the speculative threshold: tiles of `tile` contiguous elements, evenly spaced, about
+// sample_mean / rho elements per worker but at least min_elements (all elements if the row is short).
+// `target` is the rank in the sample whose bucket edge is taken: the expected sample rank of the
+// k-th key plus 5.5 standard deviations, so that the candidate list holds at least k entries except
+// with probability ~1e-8 per worker (and then that worker is merely selected from its dense row;
+// lists that come out too long are as rare, but for the small samples of medium rows, see
+// mid_sample_mean).
+// sample_mean: expected sample rank of the k-th key, at least.  min_elements: spread (a layer of 1 % of
+// the row still gets ~40 of the 4096 tiles of 64 of long rows, ~10 of the 1024 tiles of 16 of medium ones).
 SamplePlan plan_sample(int64_t m, uint32_t k, uint32_t tile, double sample_mean, double min_elements) {
     SamplePlan p;
     double want = sample_mean * (double)m / (double)k;
@@ -517,6 +528,11 @@ SamplePlan plan_sample(int64_t m, uint32_t k, uint32_t tile, double sample_mean,
 // loses 55 us and the select gains 13 us; at rho = 0.0725 (3,300 per block) the pass loses
 // 120 us and the select gains 85 us; at rho = 0.25 (11,500 per block) the pass loses
 // 80 us and the select gains 230 us.  So at both ends, not in between.
+// (The blocks of that sweep, and of the rule, are those of 2^15 elements.  Shorter ones, 2^12 .. 2^14, flush more
+// often for fewer candidates; there the two are within 4 % of each other, gtopk_local_select in us, histogram
+// kernel / pass, by candidates per real block:  m = 1 M  P = 8  6: 54.8 / 54.7  46: 58.1 / 60.5  115: 68.2 / 67.5
+// 717: 86.0 / 85.3   m = 3 M  P = 8  115: 96.2 / 97.1  573: 125.1 / 129.6  2867: 179.2 / 170.7   m = 1 M  P = 32
+// 229: 131.9 / 127.2  573: 155.2 / 148.9.  Where a row overfills its list the pass's histogram serves the dense row too.)
 bool pass_histograms(int64_t m, uint32_t k) {
     const double per_block = 1.4 * (double)k * (double)kChunk / (double)m;
     return per_block <= 128.0 || per_block >= 4096.0;

@@ -114,10 +114,10 @@ __global__ __launch_bounds__(kSampleBlock) void k_sample_pick(
 // float4 accesses are laid out on v, so every vector access is aligned and only the
 // few lanes that straddle a row end fall back to scalar accesses.
 //
-// Block (chunk, w) handles virtual positions [chunk*32768, +32768) of worker w; each of
-// its 8 waves a contiguous 4096 of them, 16 float4 per lane, all held in registers.
-// (ITERS float4 per lane in general: 2048 * ITERS positions per block.  Short rows of few
-// workers take small blocks, so that they spread over more than a handful of CUs.)
+// Block (chunk, w) handles virtual positions [chunk * C, +C) of worker w, C = 2048 * ITERS; each of
+// its 8 waves a contiguous eighth of them, ITERS float4 per lane, all held in registers.
+// (ITERS = 16 for long sparse rows.  Short rows of few workers take smaller blocks, so that they
+// spread over more than a handful of CUs, dense selections too: pass_chunk_log2.)
 // Phase 1 loads, adds, stores and counts the entries whose key reaches the speculative
 // threshold; one atomicAdd per block reserves a contiguous range ("run") of the worker's
 // candidate list; phase 2 writes the block's candidates there in index order.
@@ -160,7 +160,7 @@ __global__ __launch_bounds__(kSBlock) void k_accum_filter(
     float* r = res + (int64_t)w * stride - head;
     const uint32_t vend = head + m;          // <= 2^31 + 3
     const uint32_t ts = tspec[w];
-    // chunk < ceil((m + 3) / 32768), so none of the offsets below wraps
+    // chunk < ceil((m + 3) / C), so none of the offsets below wraps
     constexpr uint32_t kSpan = ITERS * 4 * kWave;            // elements per wave
     const uint32_t wbase = chunk * (kSpan * (uint32_t)kWaves) + wave * kSpan;
 
