@@ -279,7 +279,8 @@ int gtopk_probe_stream(const float* a, float* b, int64_t n, int32_t mode, float*
 
 /*
  * Instrumentation for tests (not part of the method): after a gtopk_local_select or
- * gtopk_step on workspace `ws` with these sizes has COMPLETED, copy to the host how
+ * gtopk_step (or, P = 1, a gtopk_dense_topk of a row that it samples first: 0 if the sample found
+ * nothing to filter by) on workspace `ws` with these sizes has COMPLETED, copy to the host how
  * many candidates the streaming pass kept for each worker (host_counts[P]) and the
  * capacity of a worker's candidate list (*host_capacity).  A worker whose count is
  * below k or above the capacity was selected from its dense row instead.

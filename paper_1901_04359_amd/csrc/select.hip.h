@@ -516,9 +516,6 @@ __global__ __launch_bounds__(kHistBlock) void k_hist(Src src, SelState st, uint3
 // kernel 2: pick the bin; count keys above it per group, list keys inside it
 // ---------------------------------------------------------------------------------
 
-// Block b of set s walks the physical slots [b*L, (b+1)*L), L = group_slots(); a set with
-// more such segments than the grid has blocks (a dense row) is walked in several turns.
-
 // Masses of equal keys (rows of few distinct magnitudes: signs, zeros, rounded values) make a
 // list of in-bin keys as long as the set, which every block of k_emit, or the one block of
 // k_finish, would read two to four times.  For the sets of the local selection and the dense top-k
@@ -548,6 +545,8 @@ __device__ __forceinline__ void record_extremes(const SelState& st, int s, uint3
         atomicMax(threadIdx.x == 0 ? &st.bin_hi[s] : &st.bin_lo_inv[s], s_ext[threadIdx.x]);
 }
 
+// Block b of set s walks the physical slots [b*L, (b+1)*L), L = group_slots(); a set with
+// more such segments than the grid has blocks (a dense row) is walked in several turns.
 // ---- the plain walk ----
 // The walk of a set that is NOT read as a dense row: one segment per block, nothing that
 // only a dense row needs.
