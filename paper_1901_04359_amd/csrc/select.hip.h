@@ -1114,10 +1114,10 @@ __device__ __forceinline__ void bucket_general(const Src& src, const SelState& s
 // Block b of set s walks the physical slots [b*L, (b+1)*L), L = group_slots().  A set
 // that is read as a dense row takes the general walk (several segments per block, the
 // bookkeeping for an overflowing list); every other set the plain one.
-// (Occupancy spelled out: the compiler otherwise schedules the general walk's loads apart when the plain one
-// grows, 134 instead of 89 us for a dense row of 25.6 M elements.)
+// (Occupancy spelled out where a set can be a dense row: the compiler otherwise schedules the general walk's loads
+// apart when the plain one grows, 134 instead of 89 us for a row of 25.6 M elements.)
 template <class Src>
-__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(8, 8))) void k_bucket(Src src, SelState st, uint32_t k) {
+__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(Src::kTies ? 8 : 1, 8))) void k_bucket(Src src, SelState st, uint32_t k) {
     if (src.skip(blockIdx.y)) return;
     if (src.dense(blockIdx.y)) bucket_general(src, st, k);
     else if constexpr (Src::kWaveGroups) bucket_runs(src, st, k);
