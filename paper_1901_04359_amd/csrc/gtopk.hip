@@ -17,6 +17,8 @@
 //                  merged through a speculative threshold of their own (a sample of
 //                  the union; only the slots that reach it are kept), with the
 //                  complete union standing by for a pair whose threshold misses.
+//   large densities  (an eighth and more, large rows) go another way behind the
+//                  sample: see grouped.hip.h.
 //   restore        membership test of each local entry in the global index set.
 //
 // Nothing here is a dense contraction, so there is no MFMA; the streaming pass is
@@ -34,6 +36,7 @@
 #include "apply.hip.h"
 #include "aggregate.hip.h"
 #include "small.hip.h"
+#include "grouped.hip.h"
 
 using namespace gtopk;
 
@@ -375,6 +378,72 @@ StepWs carve_step(void* ws, int64_t m, uint32_t k, uint32_t P) {
     return s;
 }
 
+// The step at large densities (grouped.hip.h) lives in memory that the other path uses for the candidates in index
+// order and for the merged pairs.
+struct GroupWs {
+    GroupSets gs;
+    size_t clear_words;         // from gs.hist on
+    uint64_t* bits;             // [P][ngroups * kGroup / 64] the workers' sets
+    uint64_t* gbits;            // [ngroups * kGroup / 64] the global set
+    uint32_t* samples;          // [P / 2][ngroups * per_group] of a round's unions; before them [P][row_samples] of the rows
+    uint32_t per_group, row_samples;
+    bool fits;
+};
+GroupWs carve_grouped(const StepWs& s, int64_t m, uint32_t k, uint32_t P) {
+    GroupWs w;
+    const size_t ng = ceil_div((uint64_t)m, kGroup), sets = 2 * (size_t)P;
+    Carver c{reinterpret_cast<char*>(s.ord_idx)};
+    GroupSets& gs = w.gs;
+    gs.m = (uint32_t)m;
+    gs.ngroups = (uint32_t)ng;
+    gs.hist = c.take<uint32_t>(sets * kBrkBins);
+    gs.hist_all = c.take<uint32_t>(sets * 2048);
+    gs.list_cnt = c.take<uint32_t>(sets);
+    gs.brk_cnt = c.take<uint32_t>(P);
+    const size_t clear_end = c.off;
+    w.clear_words = clear_end / sizeof(uint32_t);
+    gs.lo = c.take<uint32_t>(sets);
+    gs.hi = c.take<uint32_t>(sets);
+    gs.d1 = c.take<uint32_t>(sets);
+    gs.krem = c.take<uint32_t>(sets);
+    gs.T = c.take<uint32_t>(sets);
+    gs.need = c.take<uint32_t>(sets);
+    gs.run = c.take<uint4>(sets * ng);
+    gs.grp_gt = c.take<uint32_t>(sets * ng);
+    gs.off = c.take<uint2>(sets * (ng + 1));
+    gs.tail = c.take<uint32_t>((size_t)P * ng * 3);
+    gs.mask = c.take<uint64_t>((size_t)P * (ng + 1));
+    w.bits = c.take<uint64_t>((size_t)P * ng * (kGroup / 64));
+    w.gbits = c.take<uint64_t>(ng * (kGroup / 64));
+    // about 2^16 sampled elements of a pair's union
+    w.per_group = 2 * kGrpWaves;
+    while (w.per_group < kGroup / kGrpPer && 2 * w.per_group * ng <= 65536) w.per_group *= 2;
+    w.row_samples = plan_row_sample(m, k, P).n_tiles * kSampleKept;
+    const size_t of_rows = (size_t)P * w.row_samples, of_pairs = (size_t)(P / 2) * ng * w.per_group;
+    w.samples = c.take<uint32_t>(of_rows > of_pairs ? of_rows : of_pairs);
+    w.fits = ng <= kMaxIndexGroups && c.off <= 2 * align_up((size_t)P * s.cap * sizeof(uint32_t));
+    return w;
+}
+
+// Which steps take the grouped path: it reads the hot parts of the rows where the other one writes, walks and reads
+// lists of their candidates, and pays per element there instead of per entry, so it wins from a density of an eighth
+// on.  Its tree has no fewer launches, so short rows stay with the other one but for the highest densities (up to a
+// third: above that a bracket has little room).  A step in us, lists / groups, rows of 20 layers | of one:
+//   m = 25.6 M  P = 32  k = m/4   6434 / 4488 | 7199 / 5576     m/8  4813 / 3955 | 5129 / 4545     m/10  4293 / 3785 | 4482 / 4308
+//   m = 25.6 M  P = 8   k = m/4   1856 / 1386 | 1933 / 1479     m/8  1280 / 1097 | 1306 / 1269     m/10  1129 / 1065 | 1175 / 1221
+//   m = 17 M    P = 2   k = m/4    383 / 254  |  367 / 282      m/8   281 / 219  |  271 / 242      m/10   246 / 216  |  245 / 239
+//   m = 5 M     P = 16  k = m/4    870 / 649  |  888 / 716      m/8   624 / 570  |  646 / 621      m/10   537 / 555  |  561 / 609
+//   m = 2.1 M   P = 8   k = m/4    287 / 247  |  287 / 262      m/6   230 / 244  |  233 / 250
+//   m = 1.05 M  P = 32  k = m/4    481 / 442  |  485 / 439      m/6   394 / 417  |  381 / 416
+//   m = 0.5 M   P = 32  k = m/4    332 / 358  |  311 / 322
+// (Masses of equal values besides: a row of zeros among ordinary ones at the first of these sizes 41.7 / 6.5 ms, all rows
+// of one magnitude 188 / 4.7 ms, values rounded to integers 52.8 / 5.7 ms.)
+static bool grouped_step(int64_t m, uint32_t k, uint32_t P, const StepWs& s) {
+    const uint64_t n = (uint64_t)m;
+    const bool size = (n >= (1u << 22) && 8ull * k >= n) || (n >= (1u << 20) && n * P >= (1u << 24) && 5ull * k >= n);
+    return P >= 2 && size && 3ull * k <= n && carve_grouped(s, m, k, P).fits;
+}
+
 constexpr int64_t kMaxMergeK = (int64_t)1 << 30;     // a merged pair has 2k slots, a uint32
 
 bool sizes_ok(int64_t m, int64_t k, int64_t P) {
@@ -520,6 +589,14 @@ SamplePlan plan_sample(int64_t m, uint32_t k, uint32_t tile, double sample_mean,
     return p;
 }
 
+// Rank in a sample, `mean` the expected sample rank of the k-th key, that at most `target_hi` keys of the sample
+// reach at a key above the k-th: the counterpart of plan_sample's target (`placed`: 1 less its share for the
+// tiles' placement).
+uint32_t bracket_target_hi(double mean, double placed) {
+    const double t = placed * mean - 5.5 * __builtin_sqrt(mean) - 2.0;
+    return t > 0.0 ? (uint32_t)t : 0u;
+}
+
 // The pass can also histogram the candidates it keeps; the select's own histogram kernel
 // then only serves workers that fall back to their dense row.  That costs LDS atomics and,
 // per block and non-empty bin, a global atomic in the pass.  Measured against the
@@ -573,26 +650,24 @@ void launch_pass(const float* grad, float* residual, int64_t m, int64_t stride, 
 #undef GTOPK_PASS
 }
 
-// The speculative thresholds of P rows and the pass that filters them; before that, clears what
-// `job` says (the candidate counters among it).  SUM: the rows are residual + grad, the sums replace the
-// residual; else the rows are `residual` as it stands, nothing is written to it.  Returns whether the
-// pass has histogrammed its candidates.
+// The speculative thresholds of P rows; before that, clears what `job` says (the candidate counters among it).
+// SUM: the rows are residual + grad; else they are `residual` as it stands.  thi != NULL: brackets instead; samples: see k_sample.
 template <bool SUM>
-bool filter_rows(const float* grad, float* residual, int64_t m, int64_t stride, uint32_t P, uint32_t k,
-                 const StepWs& w, const ZeroJob& job, hipStream_t st, void* const* events = nullptr,
-                 uint32_t* thr_state = nullptr) {
+void sample_rows(const float* grad, const float* residual, int64_t m, int64_t stride, uint32_t P, uint32_t k,
+                 const StepWs& w, const SamplePlan& sp, const ZeroJob& job, uint32_t* tspec, uint32_t* thi,
+                 uint32_t* samples, hipStream_t st, uint32_t* thr_state = nullptr) {
     // workers whose threshold is carried over from the previous call skip the sampling (the
     // kernels are launched all the same: who samples is decided on the device)
     const uint4* carry = reinterpret_cast<const uint4*>(thr_state);
-    const SamplePlan sp = plan_row_sample(m, k, P);
     // A row that is summed goes through the pass anyway, and one that overfills its list still gains from the
     // threshold; a row that is not has nothing of a pass whose list will not hold.
     const uint32_t most = SUM ? 0xFFFFFFFFu : (uint32_t)((double)w.cap * (double)sp.sampled / (double)m);
+    const uint32_t target_hi = thi ? bracket_target_hi((double)k * (double)sp.sampled / (double)m, 0.97) : 0u;
     if (mid_problem(m, k, P)) {
         const uint32_t zblocks = zero_blocks(job, 4 * kSmallBlock);
         hipLaunchKernelGGL((k_small_sample<kMidSampleTile, true, SUM>), dim3(P + zblocks), dim3(kSmallBlock), 0,
                            st, grad, residual, (uint32_t)m, stride, P, sp.tile_stride, sp.n_tiles, sp.target, most,
-                           w.tspec, w.cand_count, carry, job);
+                           tspec, w.cand_count, carry, job, target_hi, thi, samples);
     } else {
         zero_async(st, job);
         uint32_t sblocks = ceil_div(sp.n_tiles, (kSampleBlock / kSampleTile) * 8);
@@ -601,10 +676,20 @@ bool filter_rows(const float* grad, float* residual, int64_t m, int64_t stride, 
         if (sblocks > sb_max) sblocks = sb_max;
         if (sblocks < 1) sblocks = 1;
         hipLaunchKernelGGL((k_sample<SUM>), dim3(sblocks, P), dim3(kSampleBlock), 0, st, grad, residual,
-                           (uint32_t)m, stride, sp.tile_stride, sp.n_tiles, w.samp_hist, carry);
+                           (uint32_t)m, stride, sp.tile_stride, sp.n_tiles, w.samp_hist, carry, samples);
         hipLaunchKernelGGL(k_sample_pick, dim3(P), dim3(kSampleBlock), 0, st, w.samp_hist, sp.target, most,
-                           w.tspec, carry);
+                           tspec, carry, target_hi, thi);
     }
+}
+
+// The thresholds and the pass that filters the rows by them (the sums replace the residual; a row that is not
+// summed is not written).  Returns whether the pass has histogrammed its candidates.
+template <bool SUM>
+bool filter_rows(const float* grad, float* residual, int64_t m, int64_t stride, uint32_t P, uint32_t k,
+                 const StepWs& w, const ZeroJob& job, hipStream_t st, void* const* events = nullptr,
+                 uint32_t* thr_state = nullptr) {
+    sample_rows<SUM>(grad, residual, m, stride, P, k, w, plan_row_sample(m, k, P), job, w.tspec, nullptr, nullptr, st,
+                     thr_state);
     mark_stage(1, events, st);
 
     const bool producer_hist = pass_histograms(m, k);
@@ -738,7 +823,8 @@ void do_merge_batch(const uint32_t* a_idx, const float* a_val, const uint32_t* b
         hipLaunchKernelGGL(k_merge_sample, dim3(mp.blocks, batch), dim3(kSampleBlock), 0, st, a_idx, a_val,
                            b_idx, b_val, k, in_stride, mp.tile_stride, mp.n_tiles, w.f_samp_hist);
         hipLaunchKernelGGL(k_sample_pick, dim3(batch), dim3(kSampleBlock), 0, st,
-                           (const uint32_t*)w.f_samp_hist, mp.target, 0xFFFFFFFFu, w.f_tspec, (const uint4*)nullptr);
+                           (const uint32_t*)w.f_samp_hist, mp.target, 0xFFFFFFFFu, w.f_tspec, (const uint4*)nullptr,
+                           0u, (uint32_t*)nullptr);
         launch_union_cuts(a_idx, b_idx, k, in_stride, tile, ntiles, batch, w.cuts, st);
         hipLaunchKernelGGL((k_union_path<kUnionPathEpt, true, kUnionHistBlock, true, true>), dim3(ntiles, batch),
                            dim3(kUnionHistBlock), 0, st, a_idx, a_val, b_idx, b_val, k, in_stride, w.m_idx,
@@ -818,6 +904,67 @@ int do_tree(const uint32_t* loc_idx, const float* loc_val, const uint32_t* loc_m
         }
     }
     return launch_status();
+}
+
+// gtopk_step at large densities.
+int do_grouped_step(const float* grad, float* residual, int64_t m, int64_t stride, uint32_t P, uint32_t k, uint32_t* g_idx,
+                    float* g_val, uint32_t* loc_idx, float* loc_val, const StepWs& w, hipStream_t st, void* const* events) {
+    const GroupWs gw = carve_grouped(w, m, k, P);
+    const GroupSets& gs = gw.gs;
+    const uint32_t ng = gs.ngroups;
+    const SamplePlan sp = plan_row_sample(m, k, P);
+    sample_rows<true>(grad, residual, m, stride, P, k, w, sp,
+                      zero_job(w.samp_hist, w.samp_words, w.cand_count, (size_t)P, gs.hist, gw.clear_words), gs.lo, gs.hi, gw.samples, st);
+    mark_stage(1, events, st);
+    hipLaunchKernelGGL(k_group_pass, dim3(ceil_div((uint64_t)m + 3, kGrpPassChunk), P), dim3(kSBlock), 0, st, grad, residual, stride,
+                       gs, w.cand_val, w.cap, w.cand_count);
+    mark_stage(2, events, st);
+
+    const uint32_t walk_blocks = 1 + ceil_div(ng, kGrpWalkBlock / kWave * kGrpWalkRuns);
+    auto finish = [&](const GroupBatch& gb, uint32_t sets, uint32_t samples, double fraction) {
+        const double mean = (double)k * fraction;            // expected sample rank of the k-th key of a union
+        const GroupSample sm{gb.first + sets, sets / 2, gw.samples, samples,
+                             (uint32_t)(1.02 * mean + 5.5 * __builtin_sqrt(mean) + 2.0), bracket_target_hi(mean, 0.98)};
+        hipLaunchKernelGGL(k_group_walk, dim3(walk_blocks, sets), dim3(kGrpWalkBlock), 0, st, gs, gb, sm);
+        hipLaunchKernelGGL(k_group_finish, dim3(sets), dim3(kGrpFinishBlock), 0, st, gs, gb);
+    };
+    GroupBatch gb{0u, k, reinterpret_cast<const uint32_t*>(w.cand_val), w.cap, w.sel.list, w.cap, w.cap, residual, stride,
+                  nullptr, nullptr, 0u};
+    // (of the rows' sample every fourth element of a tile of 64, every one of a tile of 16)
+    finish(gb, P, gw.row_samples, (double)sp.sampled / (double)m / (mid_problem(m, k, P) ? 1.0 : (double)(kSampleTile / kSampleKept)));
+    GroupNext nx{P, w.mrg.m_val, w.mrg.m_stride, P > 2 ? gw.samples : nullptr, gw.per_group};
+    hipLaunchKernelGGL(k_group_select, dim3(ng, P / 2), dim3(kGrpBlock), 0, st, gs, nx, residual, stride, k, loc_idx, loc_val,
+                       gw.bits);
+    mark_stage(3, events, st);
+
+    const uint32_t* in_idx = loc_idx;
+    const float* in_val = loc_val;
+    uint32_t first_in = 0;
+    uint32_t* ping_i = w.x_idx; float* ping_v = w.x_val;
+    uint32_t* pong_i = w.y_idx; float* pong_v = w.y_val;
+    for (uint32_t pairs = P / 2; pairs >= 1; pairs /= 2) {
+        const uint32_t first = first_in + 2 * pairs;
+        gb = GroupBatch{first, k, reinterpret_cast<const uint32_t*>(w.mrg.m_val), w.mrg.m_stride, w.mrg.sel.list, 2 * k, 0u,
+                        nullptr, 0, in_idx, in_val, first_in};
+        finish(gb, pairs, ng * gw.per_group, (double)gw.per_group / (double)kGroup);
+        if (pairs == 1) {
+            hipLaunchKernelGGL(k_group_merge<1>, dim3(ng, 1), dim3(kGrpBlock), 0, st, gs, nx, first, first_in, in_idx, in_val, k,
+                               g_idx, g_val, (float)P, gw.gbits);
+        } else {
+            nx = GroupNext{first + pairs, w.mrg.m_val, w.mrg.m_stride, pairs > 2 ? gw.samples : nullptr, gw.per_group};
+            hipLaunchKernelGGL(k_group_merge<2>, dim3(ng, pairs / 2), dim3(kGrpBlock), 0, st, gs, nx, first, first_in, in_idx,
+                               in_val, k, ping_i, ping_v, 1.0f, (uint64_t*)nullptr);
+        }
+        first_in = first;
+        in_idx = ping_i; in_val = ping_v;
+        uint32_t* ti = ping_i; ping_i = pong_i; pong_i = ti;
+        float* tv = ping_v; ping_v = pong_v; pong_v = tv;
+    }
+    mark_stage(4, events, st);
+    hipLaunchKernelGGL(k_group_restore, dim3(ceil_div(ng * kGroupWords, kRestoreWords * (kBlock / kWave)), P), dim3(kBlock), 0, st, residual, stride, gs, gw.bits, gw.gbits);
+    const int rc = launch_status();
+    mark_stage(5, events, st);
+    return rc;
 }
 
 }  // namespace
@@ -945,6 +1092,8 @@ static int step_impl(const float* grad, float* residual, int64_t m, int64_t stri
         return launch_status();
     }
     mark_stage(0, events, st);
+    if (!thr_state && grouped_step(m, (uint32_t)k, (uint32_t)P, w))
+        return do_grouped_step(grad, residual, m, stride, (uint32_t)P, (uint32_t)k, g_idx, g_val, li, lv, w, st, events);
     // one clear for everything this step needs zeroed: the sampler's histograms and the
     // candidate counters; both selects' histograms and tickets; the global-set bitmap
     const ZeroJob job = zero_job(w.samp_hist, w.samp_words, w.cand_count, (size_t)P, w.sel.hist,

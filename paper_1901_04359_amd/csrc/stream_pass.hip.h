@@ -36,11 +36,13 @@ __device__ __forceinline__ void count_sampled(uint32_t* h, const float (&v)[N], 
 // Sample tile t of a row covers [t*tile_stride, t*tile_stride + 64) (clipped to m): one
 // wave per tile.  A block of 1024 threads takes sixteen tiles per round and keeps four
 // rounds of loads in flight.  (SUM: the row is res + grad; else it is res alone, grad is not read.)
+// samples != NULL (with SUM): every fourth sampled value is kept as it is, kSampleKept per tile (0xFFFFFFFF: behind the row).
+constexpr uint32_t kSampleKept = 16;
 template <bool SUM>
 __global__ __launch_bounds__(kSampleBlock) void k_sample(
         const float* __restrict__ grad, const float* __restrict__ res, uint32_t m, int64_t stride,
         uint32_t tile_stride, uint32_t n_tiles, uint32_t* __restrict__ samp_hist,
-        const uint4* __restrict__ carry) {
+        const uint4* __restrict__ carry, uint32_t* __restrict__ samples) {
     __shared__ uint32_t h[kSampleBins];
     const int w = blockIdx.y;
     if (carry && carry[w].x == 2u) return;        // this worker filters with a carried threshold
@@ -69,10 +71,11 @@ __global__ __launch_bounds__(kSampleBlock) void k_sample(
         }
 #pragma unroll
         for (int u = 0; u < kUnroll; ++u) {
-            if (ok[u]) {
-                const uint32_t key = __float_as_uint(rv[u] + gv[u]) & kAbs;
-                atomicAdd(&h[key >> kSampleShift], 1u);
-            }
+            const uint64_t t = t0 + (uint64_t)u * tiles_per_round;
+            const uint32_t bits = __float_as_uint(rv[u] + gv[u]);
+            if (ok[u]) atomicAdd(&h[(bits & kAbs) >> kSampleShift], 1u);
+            if (samples && (el & 3u) == 0u && t < n_tiles)
+                samples[((size_t)w * n_tiles + t) * kSampleKept + el / 4u] = ok[u] ? bits : 0xFFFFFFFFu;
         }
     }
     __syncthreads();
@@ -83,12 +86,25 @@ __global__ __launch_bounds__(kSampleBlock) void k_sample(
     }
 }
 
+// (the ends of a bracket are numbers: infinity at most)
+__device__ __forceinline__ uint32_t upper_bound_key(uint32_t key) { return key < 0x7F800000u ? key : 0x7F800000u; }
+// Upper end of a bracket of the k-th key: the lowest bucket edge that at most target_hi keys reach.  Thread t owns
+// the buckets [t*PER, (t+1)*PER), counts in loc[]; every thread of the block calls it.
+template <int PER>
+__device__ __forceinline__ void upper_end(const uint32_t (&loc)[PER], uint32_t target_hi, uint32_t* s_wave, uint32_t* s_out,
+                                          uint32_t* hi) {
+    __syncthreads();                              // s_out may still be read
+    suffix_pick<PER>(loc, target_hi + 1u, s_wave, s_out);
+    if (threadIdx.x == 0) *hi = s_out[2] ? upper_bound_key((s_out[0] + 1u) << kSampleShift) : 1u << kSampleShift;
+}
+
 // One block per worker turns the worker's sample histogram into the speculative
 // threshold: the lower edge of the bucket at which the count from the top reaches
 // `target`; 0 if the sample holds fewer entries than that, or more than `most` from that edge on.
+// thi != NULL: also the upper end of a bracket, the lowest edge that at most `target_hi` sampled keys reach.
 __global__ __launch_bounds__(kSampleBlock) void k_sample_pick(
         const uint32_t* __restrict__ samp_hist, uint32_t target, uint32_t most, uint32_t* __restrict__ tspec,
-        const uint4* __restrict__ carry) {
+        const uint4* __restrict__ carry, uint32_t target_hi, uint32_t* __restrict__ thi) {
     __shared__ uint32_t s_wave[kSampleBlock / kWave];
     __shared__ uint32_t s_out[3];
     const int w = blockIdx.x;
@@ -106,6 +122,10 @@ __global__ __launch_bounds__(kSampleBlock) void k_sample_pick(
     for (int j = 0; j < kPer; ++j) loc[j] = hist[threadIdx.x * kPer + j];
     suffix_pick<kPer>(loc, target, s_wave, s_out);
     if (threadIdx.x == 0) tspec[w] = s_out[2] && s_out[1] + s_out[2] <= most ? (s_out[0] << kSampleShift) : 0u;
+    if (thi) {
+        if (threadIdx.x == 0) tspec[w] = upper_bound_key(tspec[w]);
+        upper_end<kPer>(loc, target_hi, s_wave, s_out, thi + w);
+    }
 }
 
 // Rows need not start on a 16-byte boundary (stride and m are arbitrary).  With
