@@ -33,6 +33,7 @@
 #include "stream_pass.hip.h"
 #include "select.hip.h"
 #include "merge.hip.h"
+#include "merge_block.hip.h"
 #include "apply.hip.h"
 #include "aggregate.hip.h"
 #include "small.hip.h"
@@ -482,9 +483,9 @@ inline uint32_t min_key_blocks(uint32_t k) {
 }
 
 // Smallest keys of `sets` sets (rows of v0, or of v0 and v1 in turn) into out; clears what `job` says.
-// Sets up to kMinKeyWholeK: in one launch, a block per set.  A merge call in us, clear and several
-// blocks per set / one launch:  1 pair  k = 200: 19.9 / 17.7   k = 16,000: 23.6 / 21.7   k = 32,000: 26.6 / 26.8
-// 16 pairs  k = 200: 21.2 / 19.3   k = 16,000: 31.6 / 29.7   k = 65,000: 52.8 / 65.9
+// Sets up to kMinKeyWholeK (and longer than one block merges): in one launch, a block per set.  A merge call in us, clear and
+// several blocks per set / one launch:  1 pair  k = 16,000: 23.6 / 21.7   k = 32,000: 26.6 / 26.8
+// 16 pairs  k = 16,000: 31.6 / 29.7   k = 65,000: 52.8 / 65.9
 constexpr uint32_t kMinKeyWholeK = 16384;
 void find_min_keys(const float* v0, const float* v1, int64_t stride, uint32_t k, uint32_t sets, uint32_t* out,
                    ZeroJob job, hipStream_t st) {
@@ -651,8 +652,9 @@ void launch_pass(const float* grad, float* residual, int64_t m, int64_t stride, 
 }
 
 // The speculative thresholds of P rows; before that, clears what `job` says (the candidate counters among it).
-// SUM: the rows are residual + grad; else they are `residual` as it stands.  thi != NULL: brackets instead; samples: see k_sample.
-template <bool SUM>
+// SUM: the rows are residual + grad; else they are `residual` as it stands.  BRACKET: brackets [tspec, thi) instead, and
+// samples are kept (see k_sample).
+template <bool SUM, bool BRACKET>
 void sample_rows(const float* grad, const float* residual, int64_t m, int64_t stride, uint32_t P, uint32_t k,
                  const StepWs& w, const SamplePlan& sp, const ZeroJob& job, uint32_t* tspec, uint32_t* thi,
                  uint32_t* samples, hipStream_t st, uint32_t* thr_state = nullptr) {
@@ -662,10 +664,10 @@ void sample_rows(const float* grad, const float* residual, int64_t m, int64_t st
     // A row that is summed goes through the pass anyway, and one that overfills its list still gains from the
     // threshold; a row that is not has nothing of a pass whose list will not hold.
     const uint32_t most = SUM ? 0xFFFFFFFFu : (uint32_t)((double)w.cap * (double)sp.sampled / (double)m);
-    const uint32_t target_hi = thi ? bracket_target_hi((double)k * (double)sp.sampled / (double)m, 0.97) : 0u;
+    const uint32_t target_hi = BRACKET ? bracket_target_hi((double)k * (double)sp.sampled / (double)m, 0.97) : 0u;
     if (mid_problem(m, k, P)) {
         const uint32_t zblocks = zero_blocks(job, 4 * kSmallBlock);
-        hipLaunchKernelGGL((k_small_sample<kMidSampleTile, true, SUM>), dim3(P + zblocks), dim3(kSmallBlock), 0,
+        hipLaunchKernelGGL((k_small_sample<kMidSampleTile, true, SUM, BRACKET>), dim3(P + zblocks), dim3(kSmallBlock), 0,
                            st, grad, residual, (uint32_t)m, stride, P, sp.tile_stride, sp.n_tiles, sp.target, most,
                            tspec, w.cand_count, carry, job, target_hi, thi, samples);
     } else {
@@ -675,9 +677,9 @@ void sample_rows(const float* grad, const float* residual, int64_t m, int64_t st
         const uint32_t sb_max = P >= 64 ? 4u : (P <= 16 ? 16u : 256u / P);
         if (sblocks > sb_max) sblocks = sb_max;
         if (sblocks < 1) sblocks = 1;
-        hipLaunchKernelGGL((k_sample<SUM>), dim3(sblocks, P), dim3(kSampleBlock), 0, st, grad, residual,
+        hipLaunchKernelGGL((k_sample<SUM, BRACKET>), dim3(sblocks, P), dim3(kSampleBlock), 0, st, grad, residual,
                            (uint32_t)m, stride, sp.tile_stride, sp.n_tiles, w.samp_hist, carry, samples);
-        hipLaunchKernelGGL(k_sample_pick, dim3(P), dim3(kSampleBlock), 0, st, w.samp_hist, sp.target, most,
+        hipLaunchKernelGGL(k_sample_pick<BRACKET>, dim3(P), dim3(kSampleBlock), 0, st, w.samp_hist, sp.target, most,
                            tspec, carry, target_hi, thi);
     }
 }
@@ -688,7 +690,7 @@ template <bool SUM>
 bool filter_rows(const float* grad, float* residual, int64_t m, int64_t stride, uint32_t P, uint32_t k,
                  const StepWs& w, const ZeroJob& job, hipStream_t st, void* const* events = nullptr,
                  uint32_t* thr_state = nullptr) {
-    sample_rows<SUM>(grad, residual, m, stride, P, k, w, plan_row_sample(m, k, P), job, w.tspec, nullptr, nullptr, st,
+    sample_rows<SUM, false>(grad, residual, m, stride, P, k, w, plan_row_sample(m, k, P), job, w.tspec, nullptr, nullptr, st,
                      thr_state);
     mark_stage(1, events, st);
 
@@ -771,6 +773,27 @@ inline void launch_union_cuts(const uint32_t* a_idx, const uint32_t* b_idx, uint
         hipLaunchKernelGGL(k_union_cuts<16>, grid, dim3(kBlock), 0, st, a_idx, b_idx, k, in_stride, tile, ntiles, cuts);
 }
 
+// Sets that one block merges (k_merge_block).  A call in us, three kernels a round / this, tree of 8 sets and merge of 4 | 16 pairs:
+//   k = 300   53.4 / 26.3   20.3 / 9.3 | 20.8 / 9.4     k = 4096  60.8 / 41.0   22.2 / 14.2 | 25.0 / 14.3
+//   k = 1000  58.7 / 27.9   21.8 / 9.7 | 21.9 / 9.9     k = 6000  61.2 / 57.3   22.6 / 19.4 | 27.5 / 19.7
+//   k = 2000  59.1 / 32.0   22.1 / 11.1 | 22.9 / 11.3   k = 8192  62.2 / 61.0   23.3 / 20.8 | 29.5 / 20.9
+// Longer ones, with 32 slots per thread, lose: k = 12,000 63.0 / 102, 24.6 / 34.3 | 33.5 / 34.5.
+inline bool merge_in_block(uint32_t k) { return k <= kMergeBlockMaxK; }
+template <bool DIVIDE>
+void launch_merge_block(const uint32_t* a_idx, const float* a_val, const uint32_t* b_idx, const float* b_val, uint32_t k,
+                        uint32_t batch, int64_t in_stride, uint32_t* out_idx, float* out_val, int64_t out_stride,
+                        const uint32_t* in_min, bool in_min_inverted, uint32_t* out_min, float divisor, uint32_t* gbits,
+                        hipStream_t st) {
+#define GTOPK_MERGE_BLOCK(EPT)                                                                                          \
+    hipLaunchKernelGGL((k_merge_block<EPT, DIVIDE>), dim3(batch), dim3(kMbBlock), 0, st, a_idx, a_val, b_idx, \
+                       b_val, k, in_stride, out_idx, out_val, out_stride, in_min, in_min_inverted, out_min, divisor, gbits)
+    if (k <= 1024) GTOPK_MERGE_BLOCK(2);
+    else if (k <= 2048) GTOPK_MERGE_BLOCK(4);
+    else if (k <= 4096) GTOPK_MERGE_BLOCK(8);
+    else GTOPK_MERGE_BLOCK(16);
+#undef GTOPK_MERGE_BLOCK
+}
+
 // one batch of merges: union + exact select + ordered emit.  `round` picks which of the
 // two select states is used (it must be clear on entry); the other one is cleared on the
 // side for the next round.
@@ -780,6 +803,11 @@ void do_merge_batch(const uint32_t* a_idx, const float* a_val, const uint32_t* b
                     uint32_t* out_idx, float* out_val, int64_t out_stride, const MergeWs& w,
                     int round, const uint32_t* in_min, bool in_min_inverted, uint32_t* out_min,
                     float divisor, uint32_t* gbits, hipStream_t st) {
+    if (merge_in_block(k)) {
+        launch_merge_block<DIVIDE>(a_idx, a_val, b_idx, b_val, k, batch, in_stride, out_idx, out_val, out_stride, in_min,
+                                   in_min_inverted, out_min, divisor, gbits, st);
+        return;
+    }
     const bool odd = (round & 1) != 0;
     uint32_t* zp = odd ? w.sel.hist : w.sel_alt.hist;
     const uint32_t zw = (uint32_t)(odd ? select_clear_words(w.sel) : w.alt_clear_words);
@@ -822,7 +850,7 @@ void do_merge_batch(const uint32_t* a_idx, const float* a_val, const uint32_t* b
         const MergeSamplePlan mp = plan_merge_sample(k);
         hipLaunchKernelGGL(k_merge_sample, dim3(mp.blocks, batch), dim3(kSampleBlock), 0, st, a_idx, a_val,
                            b_idx, b_val, k, in_stride, mp.tile_stride, mp.n_tiles, w.f_samp_hist);
-        hipLaunchKernelGGL(k_sample_pick, dim3(batch), dim3(kSampleBlock), 0, st,
+        hipLaunchKernelGGL(k_sample_pick<false>, dim3(batch), dim3(kSampleBlock), 0, st,
                            (const uint32_t*)w.f_samp_hist, mp.target, 0xFFFFFFFFu, w.f_tspec, (const uint4*)nullptr,
                            0u, (uint32_t*)nullptr);
         launch_union_cuts(a_idx, b_idx, k, in_stride, tile, ntiles, batch, w.cuts, st);
@@ -865,12 +893,12 @@ int do_tree(const uint32_t* loc_idx, const float* loc_val, const uint32_t* loc_m
         return launch_status();
     }
     ZeroJob job = zero_job();
-    if (!pre_cleared)
+    if (!pre_cleared && !merge_in_block(k))
         job = zero_job(w.mrg.sel.hist, select_clear_words(w.mrg.sel), w.mrg.sel_alt.hist, w.mrg.alt_clear_words);
     bool inverted = false;
     if (loc_min) {
         zero_async(st, job);
-    } else {
+    } else if (!merge_in_block(k)) {
         // sets from the caller: find their smallest keys, the first round's lower bounds
         find_min_keys(loc_val, nullptr, (int64_t)k, k, P, w.mrg.inv_min, job, st);
         loc_min = w.mrg.inv_min;
@@ -913,7 +941,7 @@ int do_grouped_step(const float* grad, float* residual, int64_t m, int64_t strid
     const GroupSets& gs = gw.gs;
     const uint32_t ng = gs.ngroups;
     const SamplePlan sp = plan_row_sample(m, k, P);
-    sample_rows<true>(grad, residual, m, stride, P, k, w, sp,
+    sample_rows<true, true>(grad, residual, m, stride, P, k, w, sp,
                       zero_job(w.samp_hist, w.samp_words, w.cand_count, (size_t)P, gs.hist, gw.clear_words), gs.lo, gs.hi, gw.samples, st);
     mark_stage(1, events, st);
     hipLaunchKernelGGL(k_group_pass, dim3(ceil_div((uint64_t)m + 3, kGrpPassChunk), P), dim3(kSBlock), 0, st, grad, residual, stride,
@@ -1022,10 +1050,12 @@ int gtopk_merge(const uint32_t* a_idx, const float* a_val, const uint32_t* b_idx
     const MergeWs w = carve_merge(c, (uint32_t)k, (size_t)batch);
     if (ws_bytes < w.bytes) return GTOPK_EWORKSPACE;
     hipStream_t st = (hipStream_t)stream;
-    find_min_keys(a_val, b_val, in_stride, (uint32_t)k, 2 * (uint32_t)batch, w.inv_min,
-                  zero_job(w.sel.hist, select_clear_words(w.sel)), st);
+    const uint32_t* in_min = merge_in_block((uint32_t)k) ? nullptr : w.inv_min;
+    if (in_min)
+        find_min_keys(a_val, b_val, in_stride, (uint32_t)k, 2 * (uint32_t)batch, w.inv_min,
+                      zero_job(w.sel.hist, select_clear_words(w.sel)), st);
     do_merge_batch<false>(a_idx, a_val, b_idx, b_val, (uint32_t)k, (uint32_t)batch, in_stride,
-                          out_idx, out_val, out_stride, w, 0, w.inv_min, true, nullptr, 1.0f, nullptr,
+                          out_idx, out_val, out_stride, w, 0, in_min, true, nullptr, 1.0f, nullptr,
                           st);
     return launch_status();
 }
@@ -1096,9 +1126,10 @@ static int step_impl(const float* grad, float* residual, int64_t m, int64_t stri
         return do_grouped_step(grad, residual, m, stride, (uint32_t)P, (uint32_t)k, g_idx, g_val, li, lv, w, st, events);
     // one clear for everything this step needs zeroed: the sampler's histograms and the
     // candidate counters; both selects' histograms and tickets; the global-set bitmap
+    const bool in_block = merge_in_block((uint32_t)k);       // its rounds need no select state
     const ZeroJob job = zero_job(w.samp_hist, w.samp_words, w.cand_count, (size_t)P, w.sel.hist,
-                                 select_clear_words(w.sel), w.mrg.sel.hist, select_clear_words(w.mrg.sel),
-                                 w.mrg.sel_alt.hist, w.mrg.alt_clear_words, w.gbits, w.gbits_words);
+                                 select_clear_words(w.sel), w.mrg.sel.hist, in_block ? 0 : select_clear_words(w.mrg.sel),
+                                 w.mrg.sel_alt.hist, in_block ? 0 : w.mrg.alt_clear_words, w.gbits, w.gbits_words);
     int rc = do_local_select(grad, residual, m, stride, (uint32_t)P, (uint32_t)k, li, lv, w, false,
                              job, st, events, thr_state);
     if (rc != GTOPK_OK) return rc;

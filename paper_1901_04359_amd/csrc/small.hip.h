@@ -168,8 +168,8 @@ __device__ __forceinline__ void wave_select_any(const uint32_t* keys, uint32_t n
 // reaches `target` (0 as in k_sample_pick).  It also clears the worker's candidate counter for the streaming pass
 // that follows in stream order.  GENERAL, in front of the general kernels: blocks from P on clear
 // what the rest of the step needs cleared (`job`), and a worker whose threshold is carried over
-// (`carry`, see k_sample) takes that; thi as in k_sample_pick, samples as in k_sample (all values).  !SUM: the row is res alone, grad is not read.
-template <int TILE, bool GENERAL, bool SUM>
+// (`carry`, see k_sample) takes that; BRACKET as in k_sample_pick, with samples as in k_sample (all values).  !SUM: the row is res alone, grad is not read.
+template <int TILE, bool GENERAL, bool SUM, bool BRACKET = false>
 __global__ __launch_bounds__(kSmallBlock) void k_small_sample(
         const float* __restrict__ grad, const float* __restrict__ res, uint32_t m, int64_t stride,
         uint32_t P, uint32_t tile_stride, uint32_t n_tiles, uint32_t target, uint32_t most, uint32_t* __restrict__ tspec,
@@ -221,8 +221,8 @@ __global__ __launch_bounds__(kSmallBlock) void k_small_sample(
         for (int u = 0; u < kSmallSampleUnroll; ++u) {
             const uint32_t bits = __float_as_uint(rv[u] + gv[u]);
             if (ok[u]) atomicAdd(&h[(bits & kAbs) >> kSampleShift], 1u);
-            if (GENERAL && samples && t0 + u * kTiles < n_tiles) {
-                static_assert(!GENERAL || TILE == kSampleKept, "every sampled value is kept");
+            if (BRACKET && t0 + u * kTiles < n_tiles) {
+                static_assert(!BRACKET || TILE == kSampleKept, "every sampled value is kept");
                 samples[((size_t)w * n_tiles + t0 + u * kTiles) * kSampleKept + el] = ok[u] ? bits : 0xFFFFFFFFu;
             }
         }
@@ -234,7 +234,7 @@ __global__ __launch_bounds__(kSmallBlock) void k_small_sample(
     for (int j = 0; j < kPer; ++j) loc[j] = h[t * kPer + j];
     suffix_pick<kPer>(loc, target, s_wave, s_out);
     if (t == 0) tspec[w] = s_out[2] && s_out[1] + s_out[2] <= most ? (s_out[0] << kSampleShift) : 0u;
-    if (GENERAL && thi) {
+    if (BRACKET) {
         if (t == 0) tspec[w] = upper_bound_key(tspec[w]);
         upper_end<kPer>(loc, target_hi, s_wave, s_out, thi + w);
     }

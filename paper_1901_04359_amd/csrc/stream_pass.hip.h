@@ -36,9 +36,9 @@ __device__ __forceinline__ void count_sampled(uint32_t* h, const float (&v)[N], 
 // Sample tile t of a row covers [t*tile_stride, t*tile_stride + 64) (clipped to m): one
 // wave per tile.  A block of 1024 threads takes sixteen tiles per round and keeps four
 // rounds of loads in flight.  (SUM: the row is res + grad; else it is res alone, grad is not read.)
-// samples != NULL (with SUM): every fourth sampled value is kept as it is, kSampleKept per tile (0xFFFFFFFF: behind the row).
+// KEEP (with SUM): every fourth sampled value is kept as it is, kSampleKept per tile (0xFFFFFFFF: behind the row).
 constexpr uint32_t kSampleKept = 16;
-template <bool SUM>
+template <bool SUM, bool KEEP>
 __global__ __launch_bounds__(kSampleBlock) void k_sample(
         const float* __restrict__ grad, const float* __restrict__ res, uint32_t m, int64_t stride,
         uint32_t tile_stride, uint32_t n_tiles, uint32_t* __restrict__ samp_hist,
@@ -74,7 +74,7 @@ __global__ __launch_bounds__(kSampleBlock) void k_sample(
             const uint64_t t = t0 + (uint64_t)u * tiles_per_round;
             const uint32_t bits = __float_as_uint(rv[u] + gv[u]);
             if (ok[u]) atomicAdd(&h[(bits & kAbs) >> kSampleShift], 1u);
-            if (samples && (el & 3u) == 0u && t < n_tiles)
+            if (KEEP && (el & 3u) == 0u && t < n_tiles)
                 samples[((size_t)w * n_tiles + t) * kSampleKept + el / 4u] = ok[u] ? bits : 0xFFFFFFFFu;
         }
     }
@@ -101,7 +101,8 @@ __device__ __forceinline__ void upper_end(const uint32_t (&loc)[PER], uint32_t t
 // One block per worker turns the worker's sample histogram into the speculative
 // threshold: the lower edge of the bucket at which the count from the top reaches
 // `target`; 0 if the sample holds fewer entries than that, or more than `most` from that edge on.
-// thi != NULL: also the upper end of a bracket, the lowest edge that at most `target_hi` sampled keys reach.
+// BRACKET: also the upper end of a bracket, the lowest edge that at most `target_hi` sampled keys reach.
+template <bool BRACKET>
 __global__ __launch_bounds__(kSampleBlock) void k_sample_pick(
         const uint32_t* __restrict__ samp_hist, uint32_t target, uint32_t most, uint32_t* __restrict__ tspec,
         const uint4* __restrict__ carry, uint32_t target_hi, uint32_t* __restrict__ thi) {
@@ -122,7 +123,7 @@ __global__ __launch_bounds__(kSampleBlock) void k_sample_pick(
     for (int j = 0; j < kPer; ++j) loc[j] = hist[threadIdx.x * kPer + j];
     suffix_pick<kPer>(loc, target, s_wave, s_out);
     if (threadIdx.x == 0) tspec[w] = s_out[2] && s_out[1] + s_out[2] <= most ? (s_out[0] << kSampleShift) : 0u;
-    if (thi) {
+    if (BRACKET) {
         if (threadIdx.x == 0) tspec[w] = upper_bound_key(tspec[w]);
         upper_end<kPer>(loc, target_hi, s_wave, s_out, thi + w);
     }
