@@ -40,17 +40,32 @@ __device__ __forceinline__ uint32_t rank_in(uint64_t mask) {
 
 // ---- block-wide primitives: every thread of the block must call them ----------------
 
-__device__ __forceinline__ uint32_t wave_incl_scan(uint32_t v) {
-    const uint32_t lane = lane_id();
-#pragma unroll
-    for (int d = 1; d < kWave; d <<= 1) {
-        const uint32_t t = __shfl_up(v, d);
-        if (lane >= (uint32_t)d) v += t;
-    }
+// x moved along the lanes by a DPP pattern (row_shr:n = 0x110 + n, row_bcast:15 = 0x142, row_bcast:31 = 0x143), 0 for
+// lanes that receive nothing: a few cycles, where a shuffle goes through LDS hardware and takes some hundred.
+template <int CTRL, int ROWS>
+__device__ __forceinline__ uint32_t dpp_moved(uint32_t x) {
+    return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, CTRL, ROWS, 0xf, false);
+}
+// inclusive prefix sum inside each row of 16 lanes
+__device__ __forceinline__ uint32_t row_incl_scan(uint32_t v) {
+    v += dpp_moved<0x111, 0xf>(v);
+    v += dpp_moved<0x112, 0xf>(v);
+    v += dpp_moved<0x114, 0xf>(v);
+    v += dpp_moved<0x118, 0xf>(v);
     return v;
 }
+__device__ __forceinline__ uint32_t wave_incl_scan(uint32_t v) {
+    v = row_incl_scan(v);
+    v += dpp_moved<0x142, 0xa>(v);         // rows 1 and 3: the sum of the row before
+    v += dpp_moved<0x143, 0xc>(v);         // rows 2 and 3: the sum of the first two
+    return v;
+}
+// sum over the wave; uniform
+__device__ __forceinline__ uint32_t wave_total(uint32_t v) {
+    return (uint32_t)__builtin_amdgcn_readlane((int)wave_incl_scan(v), kWave - 1);
+}
 
-// inclusive prefix sum over the block in thread order; s_wave: LDS, >= blockDim.x/64 words
+// inclusive prefix sum over the block (<= 16 waves) in thread order; s_wave: LDS, >= blockDim.x/64 words
 __device__ inline uint32_t block_incl_scan(uint32_t v, uint32_t* s_wave, uint32_t& total) {
     const uint32_t wave = threadIdx.x / kWave;
     const uint32_t nw = blockDim.x / kWave;
@@ -58,14 +73,11 @@ __device__ inline uint32_t block_incl_scan(uint32_t v, uint32_t* s_wave, uint32_
     __syncthreads();                       // s_wave may still be read from an earlier call
     if (lane_id() == kWave - 1) s_wave[wave] = incl;
     __syncthreads();
-    uint32_t base = 0, tot = 0;
-    for (uint32_t i = 0; i < nw; ++i) {
-        const uint32_t x = s_wave[i];
-        if (i < wave) base += x;
-        tot += x;
-    }
-    total = tot;
-    return incl + base;
+    // (the waves' sums in the lanes of one row, not one after the other)
+    const uint32_t sums = row_incl_scan(lane_id() < nw ? s_wave[lane_id()] : 0u);
+    total = (uint32_t)__builtin_amdgcn_readlane((int)sums, 15);
+    const uint32_t before = (uint32_t)__builtin_amdgcn_readlane((int)sums, __builtin_amdgcn_readfirstlane((int)(wave ? wave - 1u : 0u)));
+    return incl + (wave ? before : 0u);
 }
 
 // Thread t owns the PER histogram bins [t*PER, (t+1)*PER), counts in loc[].  Finds the
