@@ -60,9 +60,24 @@ __device__ __forceinline__ uint32_t wave_incl_scan(uint32_t v) {
     v += dpp_moved<0x143, 0xc>(v);         // rows 2 and 3: the sum of the first two
     return v;
 }
-// sum over the wave; uniform
+// value of a lane whose number is uniform; uniform
+__device__ __forceinline__ uint32_t lane_value(uint32_t x, uint32_t lane) {
+    return (uint32_t)__builtin_amdgcn_readlane((int)x, __builtin_amdgcn_readfirstlane((int)lane));
+}
+// sum / maximum over the wave; uniform
 __device__ __forceinline__ uint32_t wave_total(uint32_t v) {
     return (uint32_t)__builtin_amdgcn_readlane((int)wave_incl_scan(v), kWave - 1);
+}
+
+__device__ __forceinline__ uint32_t wave_largest(uint32_t v) {
+    auto with = [&](uint32_t x) { v = x > v ? x : v; };
+    with(dpp_moved<0x111, 0xf>(v));
+    with(dpp_moved<0x112, 0xf>(v));
+    with(dpp_moved<0x114, 0xf>(v));
+    with(dpp_moved<0x118, 0xf>(v));
+    with(dpp_moved<0x142, 0xa>(v));
+    with(dpp_moved<0x143, 0xc>(v));
+    return (uint32_t)__builtin_amdgcn_readlane((int)v, kWave - 1);
 }
 
 // inclusive prefix sum over the block (<= 16 waves) in thread order; s_wave: LDS, >= blockDim.x/64 words
@@ -115,7 +130,7 @@ __device__ __forceinline__ void add_grouped(bool pred, uint32_t g, uint32_t* arr
     uint64_t todo = __ballot(pred);
     while (todo) {
         const uint32_t leader = (uint32_t)__builtin_ctzll(todo);
-        const uint32_t gl = __shfl(g, leader);
+        const uint32_t gl = lane_value(g, leader);
         const uint64_t same = __ballot(pred && g == gl);
         if (lane_id() == leader) atomicAdd(&arr[gl], (uint32_t)__popcll(same));
         todo &= ~same;
@@ -129,7 +144,7 @@ __device__ __forceinline__ void add_grouped_lds(bool pred, uint32_t g, uint32_t*
     const uint64_t todo = __ballot(pred);
     if (!todo) return;
     const uint32_t leader = (uint32_t)__builtin_ctzll(todo);
-    const uint32_t gl = __shfl(g, leader);
+    const uint32_t gl = lane_value(g, leader);
     if (__ballot(pred && g == gl) == todo) {
         if (lane_id() == leader) atomicAdd(&arr[gl], (uint32_t)__popcll(todo));
     } else if (pred) {

@@ -266,12 +266,8 @@ __global__ __launch_bounds__(kSBlock) void k_group_pass(
                         mn = key < mn ? key : mn;
                     }
                 }
-#pragma unroll
-        for (int d = 32; d >= 1; d >>= 1) {
-            const uint32_t x = __shfl_xor(mx, d), y = __shfl_xor(mn, d);
-            mx = x > mx ? x : mx;
-            mn = y < mn ? y : mn;
-        }
+        mx = wave_largest(mx);
+        mn = kAbs - wave_largest(kAbs - mn);
         if (lane == 0) { s_max[wave] = mx; s_min[wave] = mn; }
         __syncthreads();
 #pragma unroll
@@ -586,7 +582,7 @@ __device__ inline void count_all(const GroupSets& gs, const GroupBatch& gb, uint
             const uint64_t act = __ballot(key[j] != kAbsent);
             if (!act) continue;
             const uint32_t b = key[j] >> 20, first = (uint32_t)__builtin_ctzll(act);
-            if (__ballot(key[j] != kAbsent && b == (uint32_t)__shfl(b, first)) == act) {
+            if (__ballot(key[j] != kAbsent && b == lane_value(b, first)) == act) {
                 if (lane_id() == first) atomicAdd(&h[b], (uint32_t)__popcll(act));
             } else if (key[j] != kAbsent) {
                 atomicAdd(&h[b], 1u);
@@ -710,14 +706,10 @@ __global__ __launch_bounds__(kGrpWalkBlock) void k_group_walk(GroupSets gs, Grou
                 mn = run.w < mn ? run.w : mn;
             }
         }
-#pragma unroll
-        for (int d = 32; d >= 1; d >>= 1) {
-            own_gt += __shfl_xor(own_gt, d);
-            in += __shfl_xor(in, d);
-            const uint32_t x = __shfl_xor(mx, d), y = __shfl_xor(mn, d);
-            mx = x > mx ? x : mx;
-            mn = y < mn ? y : mn;
-        }
+        own_gt = wave_total(own_gt);
+        in = wave_total(in);
+        mx = wave_largest(mx);
+        mn = kAbs - wave_largest(kAbs - mn);
         gt += own_gt;
         if (lane == 0) gs.grp_gt[(size_t)id * gs.ngroups + g] = gt;
         if (in == 0u) continue;
@@ -733,7 +725,7 @@ __global__ __launch_bounds__(kGrpWalkBlock) void k_group_walk(GroupSets gs, Grou
         else {
             uint32_t b = 0;
             if (lane == 0) b = atomicAdd(&gs.list_cnt[id], entries);
-            pos = __shfl(b, 0);
+            pos = lane_value(b, 0u);
             dst = list;
             room = gb.list_cap;
         }
@@ -876,7 +868,7 @@ __global__ __launch_bounds__(kGrpFinishBlock) void k_group_finish(GroupSets gs, 
             const uint64_t act = __ballot(mine);
             if (!act) return;
             // (masses of one key: added once)
-            const uint32_t first = (uint32_t)__builtin_ctzll(act), b0 = __shfl(b, first);
+            const uint32_t first = (uint32_t)__builtin_ctzll(act), b0 = lane_value(b, first);
             if (missed && __ballot(mine && b == b0) == act) {
                 if (lane_id() == first) atomicAdd(&h[b0], (uint32_t)__popcll(act));
             } else if (mine) {

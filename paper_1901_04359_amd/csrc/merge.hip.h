@@ -580,11 +580,7 @@ __global__ __launch_bounds__(kMinKeyBlock) void k_set_min_key(
             best = inv > best ? inv : best;
         }
     }
-#pragma unroll
-    for (int d = 32; d >= 1; d >>= 1) {
-        const uint32_t o = __shfl_xor(best, d);
-        best = o > best ? o : best;
-    }
+    best = wave_largest(best);
     if (lane_id() == 0) s_wave[threadIdx.x / kWave] = best;
     __syncthreads();
     if (threadIdx.x == 0) {

@@ -75,12 +75,8 @@ __global__ __launch_bounds__(kMbBlock) void k_merge_block(
             ma = x > ma ? x : ma;
             mb = y > mb ? y : mb;
         }
-#pragma unroll
-        for (int d = 32; d >= 1; d >>= 1) {
-            const uint32_t x = __shfl_xor(ma, d), y = __shfl_xor(mb, d);
-            ma = x > ma ? x : ma;
-            mb = y > mb ? y : mb;
-        }
+        ma = wave_largest(ma);
+        mb = wave_largest(mb);
         if (lane_id() == 0) {
             atomicMax(&s_min[0], ma);
             atomicMax(&s_min[1], mb);

@@ -471,7 +471,7 @@ __device__ __forceinline__ void hist_walk(const Src& src, int s, bool dn, const 
             const uint32_t b = dg.bin(key[j]);
             const uint64_t act = __ballot(ok[j]);
             if (act == 0) continue;
-            const uint32_t b0 = __shfl(b, __builtin_ctzll(act));
+            const uint32_t b0 = lane_value(b, (uint32_t)__builtin_ctzll(act));
             if (__ballot(ok[j] && b == b0) == act) {
                 if (lane_id() == (uint32_t)__builtin_ctzll(act)) atomicAdd(&h[b0], (uint32_t)__popcll(act));
             } else if (ok[j]) {
@@ -529,12 +529,8 @@ constexpr uint32_t kLongList = 4096;               // (lists of ordinary rows: u
 // hi, lo_inv: a thread's largest in-bin key and largest (kAbs - in-bin key), 0 for none; s_ext: LDS, two words, zero.
 // Every thread of the block calls it.
 __device__ __forceinline__ void record_extremes(const SelState& st, int s, uint32_t hi, uint32_t lo_inv, uint32_t* s_ext) {
-#pragma unroll
-    for (int d = 32; d >= 1; d >>= 1) {
-        const uint32_t h = __shfl_xor(hi, d), l = __shfl_xor(lo_inv, d);
-        hi = h > hi ? h : hi;
-        lo_inv = l > lo_inv ? l : lo_inv;
-    }
+    hi = wave_largest(hi);
+    lo_inv = wave_largest(lo_inv);
     if (lane_id() == 0) {
         atomicMax(&s_ext[0], hi);
         atomicMax(&s_ext[1], lo_inv);
@@ -635,7 +631,7 @@ __device__ __forceinline__ void bucket_fast(const Src& src, const SelState& st, 
                 const uint32_t cnt = (uint32_t)__popcll(inm);
                 uint32_t base = 0;
                 if (lane_id() == 0) base = atomicAdd(&s_nstash, cnt);
-                base = __shfl(base, 0);
+                base = lane_value(base, 0u);
                 const uint32_t pos = base + rank_in(inm);
                 if (inside && pos < (uint32_t)kStash) s_stash[pos] = make_uint2(key, lg);
                 in += cnt;
@@ -780,7 +776,7 @@ __device__ __forceinline__ void bucket_vec(const Src& src, const SelState& st, u
                     const uint32_t cnt = (uint32_t)__popcll(inm);
                     uint32_t base = 0;
                     if (lane_id() == 0) base = atomicAdd(&s_nstash, cnt);
-                    base = __shfl(base, 0);
+                    base = lane_value(base, 0u);
                     const uint32_t pos = base + rank_in(inm);
                     if (inside && pos < (uint32_t)kStash) s_stash[pos] = make_uint2(key, g);
                     in += cnt;
@@ -788,8 +784,7 @@ __device__ __forceinline__ void bucket_vec(const Src& src, const SelState& st, u
             }
         }
     }
-#pragma unroll
-    for (int d = 32; d >= 1; d >>= 1) gt += __shfl_xor(gt, d);
+    gt = wave_total(gt);
     if (lane_id() == 0) { s_gt[wave] = gt; s_in[wave] = in; }
     __syncthreads();
     if (threadIdx.x == 0) {
@@ -908,7 +903,7 @@ __device__ __forceinline__ void bucket_runs(const Src& src, const SelState& st, 
                 const uint32_t cnt = (uint32_t)__popcll(inm);
                 uint32_t base = 0;
                 if (lane == 0) base = atomicAdd(&s_nstash, cnt);
-                base = __shfl(base, 0);
+                base = lane_value(base, 0u);
                 const uint32_t pos = base + rank_in(inm);
                 if (inside && pos < (uint32_t)kStash) s_stash[pos] = make_uint2(key, g);
                 in += cnt;
@@ -1055,7 +1050,7 @@ __device__ __forceinline__ void bucket_general(const Src& src, const SelState& s
                     const uint32_t cnt = (uint32_t)__popcll(inm);
                     uint32_t base = 0;
                     if (lane_id() == 0) base = atomicAdd(&s_nstash, cnt);
-                    base = __shfl(base, 0);
+                    base = lane_value(base, 0u);
                     const uint32_t pos = base + rank_in(inm);
                     if (inside) {
                         if (pos < (uint32_t)kStash) s_stash[pos] = make_uint2(key, grp[j]);
@@ -1297,7 +1292,7 @@ __global__ __launch_bounds__(1024) void k_finish(Src src, SelState st) {
                 // a wave whose keys all fall into one bin (masses of equal keys) adds once
                 const uint64_t act = __ballot(mine);
                 if (act) {
-                    const uint32_t b0 = __shfl(b, __builtin_ctzll(act));
+                    const uint32_t b0 = lane_value(b, (uint32_t)__builtin_ctzll(act));
                     if (__ballot(mine && b == b0) == act) {
                         if (lane_id() == (uint32_t)__builtin_ctzll(act)) atomicAdd(&h[b0], (uint32_t)__popcll(act));
                     } else if (mine) {
@@ -1518,11 +1513,8 @@ __device__ __forceinline__ void emit_fast(
                 c_eq += key == T ? 1u : 0u;
             }
         });
-#pragma unroll
-        for (int d = 32; d >= 1; d >>= 1) {
-            c_gt += __shfl_xor(c_gt, d);
-            c_eq += __shfl_xor(c_eq, d);
-        }
+        c_gt = wave_total(c_gt);
+        c_eq = wave_total(c_eq);
         if (lane_id() == 0) { s_red[0][wave] = c_gt; s_red[1][wave] = c_eq; }
         __syncthreads();
         off_gt = 0;
@@ -1761,11 +1753,8 @@ __device__ __forceinline__ void emit_general(
                     }
                 });
             }
-#pragma unroll
-            for (int d = 32; d >= 1; d >>= 1) {
-                c_gt += __shfl_xor(c_gt, d);
-                c_eq += __shfl_xor(c_eq, d);
-            }
+            c_gt = wave_total(c_gt);
+            c_eq = wave_total(c_eq);
             if (lane_id() == 0) { s_red[0][wave] = c_gt; s_red[1][wave] = c_eq; }
             __syncthreads();
             off_gt = 0;

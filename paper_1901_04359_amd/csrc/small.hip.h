@@ -341,7 +341,7 @@ __global__ __launch_bounds__(kSmallBlock) void k_small_select(
             const uint32_t b = dg.bin(key[j]);
             const uint64_t act = __ballot(ok[j]);
             if (act == 0) continue;
-            const uint32_t b0 = __shfl(b, __builtin_ctzll(act));
+            const uint32_t b0 = lane_value(b, (uint32_t)__builtin_ctzll(act));
             if (__ballot(ok[j] && b == b0) == act) {
                 if (lane_id() == (uint32_t)__builtin_ctzll(act)) atomicAdd(&h[b0], (uint32_t)__popcll(act));
             } else if (ok[j]) {
@@ -386,7 +386,7 @@ __global__ __launch_bounds__(kSmallBlock) void k_small_select(
                 const uint32_t b = (rel >> shift) & ((1u << bits) - 1u);
                 const uint64_t act = __ballot(mine);
                 if (act == 0) continue;
-                const uint32_t b0 = __shfl(b, __builtin_ctzll(act));
+                const uint32_t b0 = lane_value(b, (uint32_t)__builtin_ctzll(act));
                 if (__ballot(mine && b == b0) == act) {
                     if (lane_id() == (uint32_t)__builtin_ctzll(act)) atomicAdd(&h[b0], (uint32_t)__popcll(act));
                 } else if (mine) {
@@ -546,7 +546,7 @@ __global__ __launch_bounds__(kSmallBlock) void k_small_tree(
                 const uint32_t c = v < words ? (uint32_t)__popc(selw[q * words + v]) : 0u;
                 const uint32_t incl = wave_incl_scan(c);
                 if (v < words) wpre[q * words + v] = before + incl - c;
-                before += __shfl(incl, kWave - 1);
+                before += lane_value(incl, kWave - 1);
             }
         }
         __syncthreads();

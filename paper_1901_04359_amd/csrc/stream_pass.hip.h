@@ -24,7 +24,7 @@ __device__ __forceinline__ void count_sampled(uint32_t* h, const float (&v)[N], 
         const bool counts = ok[u] && bu != 0u;
         const uint64_t act = __ballot(counts);
         if (act == 0) continue;
-        const uint32_t first = (uint32_t)__builtin_ctzll(act), b0 = __shfl(bu, first);
+        const uint32_t first = (uint32_t)__builtin_ctzll(act), b0 = lane_value(bu, first);
         if (__ballot(counts && bu == b0) != act) {
             if (counts) atomicAdd(&h[bu], 1u);
         } else if (lane_id() == first) {
@@ -250,7 +250,7 @@ __global__ __launch_bounds__(kSBlock) void k_accum_filter(
                 const uint64_t act = __ballot(in && b != 0u);
                 if (act == 0) continue;
                 // (one value throughout: one add, as in the histogram kernel)
-                const uint32_t b0 = __shfl(b, __builtin_ctzll(act));
+                const uint32_t b0 = lane_value(b, (uint32_t)__builtin_ctzll(act));
                 if (__ballot(in && b == b0) == act) {
                     if (lane == (uint32_t)__builtin_ctzll(act)) atomicAdd(&s_h[b0], (uint32_t)__popcll(act));
                 } else if (in && b != 0u) {
