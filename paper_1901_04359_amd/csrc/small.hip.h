@@ -456,37 +456,219 @@ __global__ __launch_bounds__(kSmallBlock) void k_small_select(
 // the whole tree, the average and the extra residual in one block
 // ---------------------------------------------------------------------------------
 
-// All P k-sets sit in LDS (P * k <= 4096 entries).  Round j merges set 2p with set 2p+1 of
-// the surviving sets for every pair p, the pairs side by side:
-//   union      `team` = 1024 / pairs threads per pair: entry x of A goes to slot
-//              x + #{B < A[x]}, entry y of B to y + #{A <= B[y]} (binary searches in LDS);
-//              A's copy carries the sum at a shared index, B's slot there becomes a
-//              tombstone: the union in index order in 2k slots;
-//   select     one wave per pair (a wave takes two pairs in turn where there are 32) finds
-//              the k largest keys of the pair's union in registers, ties to the lower slot
-//              = lower index (Definition 1); see wave_select;
-//   compact    selected slots, in slot (= index) order, become set p of the next round.
-// After the last round set 0 is the global set: its values are divided by P and written
-// out, and every worker's locally selected entries whose index is in it (or whose value is
-// -0.0, which the literal zero-then-add-back would turn into +0.0) are stored as +0.0 in
-// the worker's row - the rows still hold the accumulated values at the selected entries.
+// All P k-sets sit in LDS (P * k <= 4096 entries).  Round j merges set 2p with set 2p+1 of the surviving sets for
+// every pair p, the pairs side by side: a team of 1024 / pairs threads each (at least a wave; 32 pairs in two turns), a
+// thread owns at most kTreeEpt consecutive slots of its pair's union in index order:
+//   union      a binary search along the diagonal, then a sequential merge; A's copy carries the sum at a shared
+//              index, B's slot there is a tombstone;
+//   select     the keys above the larger of the operands' smallest keys are counted in 1024 bins that widen with the
+//              distance (a 32nd of an octave each), the team picks the bin of the k-th, and while that holds more than
+//              kTreeList keys it is cut into 1024 again; what is left goes to a list, where every key's owner ranks it;
+//   emit       one prefix sum over the team's threads, selected slots to set p of the next round.
+// (Every barrier is the block's, about nine per round, and a round is its chain of dependent LDS reads and barriers:
+// some 6 us.  One wave per pair that held all keys in registers and searched the k-th in a bracket, with the slots in
+// LDS for a bitmap and a compaction, took 8 us per round of sets of 270; the tree of 8 such sets 26.9 -> 20.3 us.  With the
+// teams' sizes known only at run time 23.4.)
+// After the last round the global set's values are divided by P and written out, and every worker's locally selected
+// entries whose index is in it (or whose value is -0.0, which the literal zero-then-add-back would turn into +0.0) are
+// stored as +0.0 in the worker's row - the rows still hold the accumulated values at the selected entries.
+constexpr int kTreeEpt = kSmallMaxEntries / kSmallBlock;
+constexpr int kTreeTeams = 16;
+constexpr uint32_t kTreeBins = 1024;
+constexpr uint32_t kTreeList = 32;
+// bin of a key at distance rel from the bound: the distance itself below 32, then 32 bins per octave
+__device__ __forceinline__ uint32_t tree_bin(uint32_t rel) {
+    if (rel < 32u) return rel;
+    const uint32_t e = 31u - (uint32_t)__builtin_clz(rel);
+    return ((e - 4u) << 5) + ((rel >> (e - 5u)) & 31u);
+}
+// smallest distance of bin b, and how many distances it holds (as a power of two)
+__device__ __forceinline__ uint32_t tree_bin_first(uint32_t b) { return b < 32u ? b : (32u + (b & 31u)) << ((b >> 5) - 1u); }
+__device__ __forceinline__ uint32_t tree_bin_bits(uint32_t b) { return b < 32u ? 0u : (b >> 5) - 1u; }
+
+struct TreeShared {
+    // two buffers of surviving sets, k entries each, that the rounds take in turn
+    uint32_t idx[kSmallMaxEntries + kSmallMaxEntries / 2];
+    uint32_t val[kSmallMaxEntries + kSmallMaxEntries / 2];
+    __align__(16) uint32_t hist[kTreeTeams * kTreeBins];       // zero between the rounds
+    uint32_t list[kTreeTeams][kTreeList];
+    uint32_t min[2][kSmallMaxP];                               // the sets' smallest keys
+    uint32_t wave[kSmallBlock / kWave];
+    uint32_t pick[kTreeTeams][3], n[kTreeTeams], T[kTreeTeams], need[kTreeTeams];
+};
+
+// One round, SIZE threads per team: the sets at `from` are merged into those at `to`.
+template <uint32_t SIZE>
+__device__ __forceinline__ void tree_round(TreeShared& sh, uint32_t pairs, uint32_t k, uint32_t from, uint32_t to, int turn_min) {
+    constexpr uint32_t teams = kSmallBlock / SIZE, team_waves = SIZE / kWave, per = kTreeBins / SIZE;    // bins per thread
+    const uint32_t t = threadIdx.x, lane = lane_id(), wave = t / kWave;
+    const uint32_t team = t / SIZE, l = t % SIZE, first_wave = team * team_waves;
+    constexpr int kE = SIZE == 1024 ? 1 : (SIZE == 512 ? 2 : kTreeEpt);       // slots per thread, at most
+    static_assert(2 * kSmallMaxK <= 1024 && kSmallMaxEntries <= 1024 * kTreeEpt, "2k slots fit a team's threads");
+    uint32_t* hist = sh.hist + team * kTreeBins;
+    const uint32_t n = 2 * k, ept = (n + SIZE - 1) / SIZE;                   // <= kE
+    for (uint32_t q = team; q < pairs; q += teams) {                        // (pairs is a multiple of teams)
+        // ---- union ------------------------------------------------------------------
+        const uint32_t* ai = sh.idx + from + 2 * q * k;
+        const uint32_t* bi = ai + k;
+        const uint32_t* av = sh.val + from + 2 * q * k;
+        const uint32_t* bv = av + k;
+        const uint32_t bound = op_max(sh.min[turn_min][2 * q], sh.min[turn_min][2 * q + 1]);
+        uint32_t oi[kE], ov[kE];
+#pragma unroll
+        for (int j = 0; j < kE; ++j) { oi[j] = kTomb; ov[j] = 0u; }
+        const uint32_t d0 = l * ept;
+        if (d0 < n) {
+            uint32_t x = d0 > k ? d0 - k : 0u, hi = d0 < k ? d0 : k;
+            while (x < hi) {
+                const uint32_t mid = (x + hi) >> 1;
+                if (ai[mid] <= bi[d0 - 1 - mid]) x = mid + 1; else hi = mid;
+            }
+            uint32_t y = d0 - x;
+            uint32_t a = x < k ? ai[x] : kTomb, b = y < k ? bi[y] : kTomb, aprev = x > 0 ? ai[x - 1] : kTomb;
+#pragma unroll
+            for (int j = 0; j < kE; ++j) {
+                if ((uint32_t)j >= ept || d0 + j >= n) continue;
+                if (a <= b && x < k) {
+                    oi[j] = a;
+                    ov[j] = av[x];
+                    if (b == a) ov[j] = __float_as_uint(__uint_as_float(ov[j]) + __uint_as_float(bv[y]));   // one fp32 add
+                    aprev = a;
+                    ++x;
+                    a = x < k ? ai[x] : kTomb;
+                } else if (y < k) {
+                    oi[j] = b == aprev ? kTomb : b;
+                    ov[j] = bv[y];
+                    ++y;
+                    b = y < k ? bi[y] : kTomb;
+                }
+            }
+        }
+        // ---- select -----------------------------------------------------------------
+        // the k-th key lies in base + [lo, lo + 2^bits), `rank` of the `count` keys there reach it.  base: the bound,
+        // which k keys of the union reach unless sums cancel, else 0.
+        uint32_t base = bound, lo = 0, bits = 31, rank = k, count = 0;
+        bool by_octave = true, more = true;
+        auto candidate = [&](int j) {
+            const uint32_t key = ov[j] & kAbs;
+            return oi[j] != kTomb && key >= base && key - base - lo < (1u << bits);
+        };
+        do {                                       // (every thread of the block takes the same turns)
+            const uint32_t shift = bits > 10u ? bits - 10u : 0u;
+            if (more)
+#pragma unroll
+                for (int j = 0; j < kE; ++j)
+                    if (candidate(j)) {
+                        const uint32_t rel = (ov[j] & kAbs) - base;
+                        atomicAdd(&hist[by_octave ? tree_bin(rel) : (rel - lo) >> shift], 1u);
+                    }
+            __syncthreads();
+            uint32_t mine = 0, loc[per];
+#pragma unroll
+            for (uint32_t i = 0; i < per; ++i) {
+                loc[i] = hist[l * per + i];
+                hist[l * per + i] = 0u;            // (for the next turn, and the next round)
+                mine += loc[i];
+            }
+            const uint32_t incl = wave_incl_scan(mine);
+            if (lane == kWave - 1) sh.wave[wave] = incl;
+            if (l == 0) { sh.pick[team][2] = 0u; sh.n[team] = 0u; }
+            __syncthreads();
+            const uint32_t sums = row_incl_scan(lane < team_waves ? sh.wave[first_wave + lane] : 0u);
+            const uint32_t w_in = wave - first_wave;
+            uint32_t above = lane_value(sums, 15u) - incl - (w_in ? lane_value(sums, w_in - 1u) : 0u);
+            if (above < rank && above + mine >= rank) {                     // one thread owns the crossing
+#pragma unroll
+                for (int i = (int)per - 1; i >= 0; --i) {
+                    if (above < rank && above + loc[i] >= rank) {
+                        sh.pick[team][0] = l * per + (uint32_t)i;
+                        sh.pick[team][1] = above;
+                        sh.pick[team][2] = loc[i];
+                    }
+                    above += loc[i];
+                }
+            }
+            __syncthreads();
+            if (more) {
+                const uint32_t b = sh.pick[team][0], c = sh.pick[team][2];
+                if (c == 0u) {                     // fewer than k keys reach the bound
+                    more = base != 0u;             // (always so: the union has k entries)
+                    if (!more) bits = 0;
+                    base = 0;
+                } else {
+                    rank -= sh.pick[team][1];
+                    count = c;
+                    lo = by_octave ? tree_bin_first(b) : lo + (b << shift);
+                    bits = by_octave ? tree_bin_bits(b) : shift;
+                    by_octave = false;
+                    more = count > kTreeList && bits > 0u;
+                }
+            }
+        } while (__syncthreads_or(more ? 1 : 0));
+        if (bits > 0u) {
+#pragma unroll
+            for (int j = 0; j < kE; ++j)
+                if (candidate(j)) sh.list[team][atomicAdd(&sh.n[team], 1u) & (kTreeList - 1u)] = ov[j] & kAbs;    // count of them
+        } else if (l == 0) {
+            sh.T[team] = base + lo;
+            sh.need[team] = rank;
+        }
+        __syncthreads();
+        if (bits > 0u)
+#pragma unroll
+            for (int j = 0; j < kE; ++j) {
+                if (!candidate(j)) continue;
+                const uint32_t key = ov[j] & kAbs;
+                uint32_t gt = 0, eq = 0;
+                for (uint32_t i = 0; i < count; ++i) {
+                    const uint32_t x = sh.list[team][i];
+                    gt += x > key ? 1u : 0u;
+                    eq += x == key ? 1u : 0u;
+                }
+                if (gt < rank && gt + eq >= rank) { sh.T[team] = key; sh.need[team] = rank - gt; }     // (all who do agree)
+            }
+        __syncthreads();
+        const uint32_t T = sh.T[team], need = sh.need[team];
+        // ---- emit -------------------------------------------------------------------
+        uint32_t mine = 0;                         // entries above T, and equal to it << 16
+#pragma unroll
+        for (int j = 0; j < kE; ++j) {
+            const uint32_t key = ov[j] & kAbs;
+            if (oi[j] != kTomb) mine += key > T ? 1u : (key == T ? 0x10000u : 0u);
+        }
+        const uint32_t incl = wave_incl_scan(mine);
+        if (lane == kWave - 1) sh.wave[wave] = incl;
+        if (l == 0) sh.min[turn_min ^ 1][q] = T;
+        __syncthreads();
+        const uint32_t sums = row_incl_scan(lane < team_waves ? sh.wave[first_wave + lane] : 0u);
+        const uint32_t w_in = wave - first_wave;
+        const uint32_t before = incl - mine + (w_in ? lane_value(sums, w_in - 1u) : 0u);
+        uint32_t eq = before >> 16, pos = (before & 0xFFFFu) + (eq < need ? eq : need);
+#pragma unroll
+        for (int j = 0; j < kE; ++j) {
+            if (oi[j] == kTomb) continue;
+            const uint32_t key = ov[j] & kAbs;
+            bool sel = key > T;
+            if (key == T) sel = eq++ < need;
+            if (sel && pos < k) {                  // (always inside)
+                sh.idx[to + q * k + pos] = oi[j];
+                sh.val[to + q * k + pos] = ov[j];
+                ++pos;
+            }
+        }
+        __syncthreads();
+    }
+}
+
 __global__ __launch_bounds__(kSmallBlock) void k_small_tree(
         const uint32_t* __restrict__ loc_idx, const float* __restrict__ loc_val, uint32_t P,
         uint32_t k, uint32_t* __restrict__ g_idx, float* __restrict__ g_val, float divisor,
         float* __restrict__ res, int64_t stride) {
     constexpr int kT = kSmallBlock;
     constexpr int kWaves = kT / kWave;
-    constexpr int kMaxPairs = kSmallMaxP / 2;
     constexpr int kPer = kSmallMaxEntries / kT;       // entries of the input sets per thread
-    __shared__ uint32_t a_idx[kSmallMaxEntries];      // the surviving sets, k entries each
-    __shared__ uint32_t a_val[kSmallMaxEntries];
-    __shared__ uint32_t m_idx[kSmallMaxEntries];      // per pair: the 2k slots of its union
-    __shared__ uint32_t m_val[kSmallMaxEntries];
-    __shared__ uint32_t m_key[kSmallMaxEntries];      // key + 1 of every slot (0: tombstone)
-    __shared__ uint32_t selw[kSmallMaxEntries / 32 + kMaxPairs];   // per pair: one bit per slot
-    __shared__ uint32_t wpre[kSmallMaxEntries / 32 + kMaxPairs];   // selected slots before each word
-    __shared__ uint32_t s_gather[kT];                 // 64 words per wave
-    const uint32_t t = threadIdx.x;
+    __shared__ TreeShared sh;
+    const uint32_t t = threadIdx.x, lane = lane_id(), wave = t / kWave;
     const uint32_t total = P * k;
     uint32_t in_idx[kPer], in_val[kPer];              // kept for the extra residual
 #pragma unroll
@@ -496,73 +678,37 @@ __global__ __launch_bounds__(kSmallBlock) void k_small_tree(
         if (e < total) {
             in_idx[c] = loc_idx[e];
             in_val[c] = __float_as_uint(loc_val[e]);
-            a_idx[e] = in_idx[c];
-            a_val[e] = in_val[c];
+            sh.idx[e] = in_idx[c];
+            sh.val[e] = in_val[c];
         }
+    }
+#pragma unroll
+    for (uint32_t b = 0; b < kTreeTeams * kTreeBins; b += 4 * kT)
+        *reinterpret_cast<uint4*>(&sh.hist[b + 4 * t]) = make_uint4(0u, 0u, 0u, 0u);
+    __syncthreads();
+    for (uint32_t w = wave; w < P; w += kWaves) {      // smallest keys, a wave per set
+        uint32_t inv = 0;
+        for (uint32_t x = lane; x < k; x += kWave) inv = op_max(inv, kAbs - (sh.val[w * k + x] & kAbs));
+        inv = wave_largest(inv);
+        if (lane == 0) sh.min[0][w] = kAbs - inv;
     }
     __syncthreads();
-    const uint32_t n2 = 2 * k;
-    const uint32_t words = (n2 + 31) / 32;            // bitmap words per pair
+    uint32_t from = 0, to = kSmallMaxEntries;         // the buffers
+    int turn_min = 0;
     for (uint32_t nsets = P; nsets > 1; nsets >>= 1) {
         const uint32_t pairs = nsets >> 1;
-        const uint32_t team = kT / pairs;             // threads per pair (pairs <= 32: >= 32)
-        const uint32_t p = t / team, l = t % team;
-        const uint32_t* ai = a_idx + (2 * p) * k;
-        const uint32_t* av = a_val + (2 * p) * k;
-        const uint32_t* bi = ai + k;
-        const uint32_t* bv = av + k;
-        uint32_t* mi = m_idx + p * n2;
-        uint32_t* mv = m_val + p * n2;
-        uint32_t* mk = m_key + p * n2;
-        // ---- union ------------------------------------------------------------------
-        // (one entry of A or of B per thread and turn: e < k is entry e of A, else entry e - k of B)
-        for (uint32_t e = l; e < n2; e += team) {
-            const bool of_b = e >= k;
-            const uint32_t x = of_b ? e - k : e;
-            const uint32_t* oi = of_b ? ai : bi;      // the other set
-            const uint32_t mine = of_b ? bi[x] : ai[x];
-            const uint32_t bound = mine + (of_b ? 1u : 0u);      // #{other < bound}; indices are < 2^31
-            uint32_t lo = 0, hi = k;
-            while (lo < hi) { const uint32_t mid = (lo + hi) >> 1; if (oi[mid] < bound) lo = mid + 1; else hi = mid; }
-            uint32_t idx = mine, val = of_b ? bv[x] : av[x];
-            if (of_b) {
-                if (lo > 0 && ai[lo - 1] == mine) idx = kTomb;                  // A's copy carries the sum
-            } else if (lo < k && bi[lo] == mine) {
-                val = __float_as_uint(__uint_as_float(val) + __uint_as_float(bv[lo]));     // one fp32 add
-            }
-            mi[x + lo] = idx;
-            mv[x + lo] = val;
-            mk[x + lo] = idx == kTomb ? 0u : (val & kAbs) + 1u;
-        }
-        __syncthreads();
-        // ---- select: one wave per pair (pairs in turns where there are more than waves),
-        // which then counts the selected slots before each bitmap word of the pair
-        for (uint32_t q = t / kWave; q < pairs; q += kWaves) {
-            wave_select_any<2 * kSmallMaxK / kWave>(m_key + q * n2, n2, k, selw + q * words,
-                                                    s_gather + (t / kWave) * kWave);
-            uint32_t before = 0;
-            for (uint32_t v0 = 0; v0 < words; v0 += kWave) {
-                const uint32_t v = v0 + lane_id();
-                const uint32_t c = v < words ? (uint32_t)__popc(selw[q * words + v]) : 0u;
-                const uint32_t incl = wave_incl_scan(c);
-                if (v < words) wpre[q * words + v] = before + incl - c;
-                before += lane_value(incl, kWave - 1);
-            }
-        }
-        __syncthreads();
-        // ---- compact into set p of the next round --------------------------------------
-        // (every read of the current sets is over: they are overwritten in place)
-        for (uint32_t i = l; i < n2; i += team) {
-            const uint32_t wd = selw[p * words + (i >> 5)];
-            if ((wd >> (i & 31)) & 1u) {
-                // < k: exactly k slots are selected
-                const uint32_t pos = wpre[p * words + (i >> 5)] + (uint32_t)__popc(wd & ((1u << (i & 31)) - 1u));
-                a_idx[p * k + pos] = mi[i];
-                a_val[p * k + pos] = mv[i];
-            }
-        }
-        __syncthreads();
+        if (pairs == 1) tree_round<1024>(sh, pairs, k, from, to, turn_min);
+        else if (pairs == 2) tree_round<512>(sh, pairs, k, from, to, turn_min);
+        else if (pairs == 4) tree_round<256>(sh, pairs, k, from, to, turn_min);
+        else if (pairs == 8) tree_round<128>(sh, pairs, k, from, to, turn_min);
+        else tree_round<64>(sh, pairs, k, from, to, turn_min);
+        const uint32_t x = from;
+        from = to;
+        to = x;
+        turn_min ^= 1;
     }
+    const uint32_t* a_idx = sh.idx + from;              // the global set
+    const uint32_t* a_val = sh.val + from;
     // ---- the global set: average, write out ------------------------------------------------
     for (uint32_t i = t; i < k; i += kT) {
         g_idx[i] = a_idx[i];
