@@ -3,9 +3,8 @@
 //   k_small_sample  the speculative threshold of one worker in ONE block (sample histogram
 //                   in LDS and the pick), which also clears the worker's candidate counter;
 //   k_small_select  the exact local selection (Algorithm 4 lines 5-7) of one worker in ONE
-//                   block, with block-level synchronisation only: a short candidate list by
-//                   one wave that holds all keys in registers, anything else by histogram,
-//                   radix refinement and ordered emit;
+//                   block, with block-level synchronisation only: a short candidate list
+//                   in registers, anything else by histogram, radix refinement and ordered emit;
 //   k_small_tree    the whole gTopKAllReduce tree (Algorithm 3 lines 4-18: every round's
 //                   Top-k operations of Definition 1), the division by P (Eq. 3) and the
 //                   extra residual (Algorithm 4 line 10) in ONE block, all sets in LDS.
@@ -24,138 +23,151 @@ constexpr int kSmallMaxChunks = 256;         // rows of at most 2^20 elements
 constexpr int kSmallMaxEntries = 4096;       // P * k, at most
 constexpr int kSmallMaxK = 512;
 constexpr int kSmallMaxP = 64;
-constexpr int kSmallRankList = 2048;         // candidate lists up to here: selection by one wave
+constexpr int kSmallRankList = 2048;         // candidate lists up to here: held in registers
 constexpr int kMidSampleTile = 16;           // elements per tile where it serves rows of millions of elements
 constexpr int kSmallSampleUnroll = 16;       // tiles that each of its groups of lanes keeps in flight
 
-// Sum / maximum / minimum of v over the 64 lanes of the wave (every lane takes part; the
-// result is uniform): butterfly steps inside each row of 16 lanes, then the four row
-// results on the scalar side.
-#define GTOPK_ROW_BUTTERFLY(v, OP)                                                                  \
-    do {                                                                                           \
-        v = OP(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(v), 0xB1, 0xf, 0xf, true));  /* quad_perm [1,0,3,2] */ \
-        v = OP(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(v), 0x4E, 0xf, 0xf, true));  /* quad_perm [2,3,0,1] */ \
-        v = OP(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(v), 0x141, 0xf, 0xf, true)); /* row_half_mirror */     \
-        v = OP(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(v), 0x140, 0xf, 0xf, true)); /* row_mirror */          \
-    } while (0)
-#define GTOPK_ROWS(v, OP)                                                                           \
-    OP(OP((uint32_t)__builtin_amdgcn_readlane((int)(v), 0), (uint32_t)__builtin_amdgcn_readlane((int)(v), 16)), \
-       OP((uint32_t)__builtin_amdgcn_readlane((int)(v), 32), (uint32_t)__builtin_amdgcn_readlane((int)(v), 48)))
-__device__ __forceinline__ uint32_t op_add(uint32_t a, uint32_t b) { return a + b; }
 __device__ __forceinline__ uint32_t op_max(uint32_t a, uint32_t b) { return a > b ? a : b; }
-__device__ __forceinline__ uint32_t op_min(uint32_t a, uint32_t b) { return a < b ? a : b; }
-__device__ __forceinline__ uint32_t wave_sum(uint32_t v) { GTOPK_ROW_BUTTERFLY(v, op_add); return GTOPK_ROWS(v, op_add); }
-__device__ __forceinline__ uint32_t wave_max(uint32_t v) { GTOPK_ROW_BUTTERFLY(v, op_max); return GTOPK_ROWS(v, op_max); }
-__device__ __forceinline__ uint32_t wave_min(uint32_t v) { GTOPK_ROW_BUTTERFLY(v, op_min); return GTOPK_ROWS(v, op_min); }
-#undef GTOPK_ROW_BUTTERFLY
-#undef GTOPK_ROWS
 
-// ONE wave selects the k largest of n <= 64 * NCH keys in LDS; keys[j] = key + 1 of position
-// j, or 0 for a position that holds nothing and is never selected (at least k positions
-// hold something).  Among equal keys the lower positions win.  The wave holds the keys in
-// registers, 64 per register; no barrier and next to no LDS traffic inside the search.
-//   1. T, the k-th largest key, is bracketed: count_ge(lo) >= k > count_ge(hi).  The bracket
-//      starts at [smallest key, largest key + 1) and shrinks around a trial value placed
-//      where a straight line through the two counts crosses k; after two moves of the same
-//      end the next trial halves the bracket, so the loop ends on any input.
-//   2. Once the bracket holds at most 64 keys they are gathered, one per lane, and T is
-//      found bit by bit below the common prefix of the bracket's ends.
-//   3. Positions above T are selected, and the lowest positions among those equal to T.
-// Bit j of `selbits` (ceil(n / 32) words, all of them stored by this wave) tells whether
-// position j is selected.  `gather`: 64 words of LDS of this wave's own.
-template <int NCH>
-__device__ __forceinline__ void wave_select(const uint32_t* keys, uint32_t n, uint32_t k,
-                                            uint32_t* selbits, uint32_t* gather) {
-    const uint32_t lane = lane_id();
-    const uint64_t below = (1ull << lane) - 1ull;
-    uint32_t K[NCH];
-#pragma unroll
-    for (int c = 0; c < NCH; ++c) K[c] = (uint32_t)c * kWave + lane < n ? keys[c * kWave + lane] : 0u;
-    auto count_ge = [&](uint32_t v) {
-        uint32_t mine = 0;
-#pragma unroll
-        for (int c = 0; c < NCH; ++c) mine += K[c] >= v ? 1u : 0u;
-        return wave_sum(mine);
-    };
-    uint32_t mx = 0, mn = 0xFFFFFFFFu;
-#pragma unroll
-    for (int c = 0; c < NCH; ++c) {
-        mx = op_max(mx, K[c]);
-        mn = op_min(mn, K[c] - 1u);                  // an empty position counts as the largest value
-    }
-    // ---- 1. bracket ---------------------------------------------------------------------
-    uint32_t lo = wave_min(mn) + 1u, hi = wave_max(mx) + 1u;       // 1 <= lo < hi <= 2^31 + 1
-    uint32_t c_lo = count_ge(lo), c_hi = 0u;                       // c_lo = positions that hold something
-    int last = 0, run = 0;                                         // which end moved last, how often in a row
-    while (hi - lo > 1u && c_lo - c_hi > (uint32_t)kWave) {
-        const uint32_t w = hi - lo;
-        uint32_t d = w >> 1;
-        if (run < 2) {
-            const float f = (float)w * (((float)(c_lo - k) + 0.5f) / (float)(c_lo - c_hi));
-            d = (uint32_t)f;
-            d = d < 1u ? 1u : (d > w - 1u ? w - 1u : d);
-        } else {
-            run = 0;
-        }
-        const uint32_t v = lo + d;                                 // lo < v < hi
-        const uint32_t c = count_ge(v);
-        const int side = c >= k ? 1 : 2;
-        if (side == 1) { lo = v; c_lo = c; } else { hi = v; c_hi = c; }
-        run = side == last ? run + 1 : 1;
-        last = side;
-    }
-    // ---- 2. inside the bracket ------------------------------------------------------------
-    uint32_t T = lo;
-    if (hi - lo > 1u) {                              // wave-uniform; at most 64 keys in [lo, hi)
-        uint32_t base = 0;
-#pragma unroll
-        for (int c = 0; c < NCH; ++c) {
-            const bool in = K[c] >= lo && K[c] < hi;
-            const uint64_t m = __ballot(in);
-            if (in) gather[base + (uint32_t)__popcll(m & below)] = K[c];
-            base += (uint32_t)__popcll(m);
-        }
-        const uint32_t X = lane < base ? gather[lane] : 0u;        // the wave reads its own stores
-        const uint32_t r = k - c_hi;                               // T is the r-th largest of them
-        const int top = 31 - __builtin_clz(lo ^ (hi - 1u));        // the ends differ: lo < hi - 1
-        T = top == 31 ? 0u : lo & ~((2u << top) - 1u);             // their common prefix
-        for (int b = top; b >= 0; --b) {
-            const uint32_t cand = T | (1u << b);
-            if ((uint32_t)__popcll(__ballot(X >= cand)) >= r) T = cand;
-        }
-    }
-    // ---- 3. mark --------------------------------------------------------------------------
-    const uint32_t need = k - count_ge(T + 1u);      // positions with key == T to take (T <= 2^31)
-    const uint32_t words = (n + 31) / 32;
-    uint32_t eq_before = 0;
-#pragma unroll
-    for (int c = 0; c < NCH; ++c) {
-        if ((uint32_t)c * kWave >= n) continue;      // wave-uniform
-        const uint64_t eq = __ballot(K[c] == T);
-        const bool sel = K[c] != 0u &&
-                         (K[c] > T || (K[c] == T && eq_before + (uint32_t)__popcll(eq & below) < need));
-        const uint64_t m = __ballot(sel);
-        if (lane == 0) {
-            selbits[2 * c] = (uint32_t)m;
-            if ((uint32_t)(2 * c + 1) < words) selbits[2 * c + 1] = (uint32_t)(m >> 32);
-        }
-        eq_before += (uint32_t)__popcll(eq);
-    }
+// ---------------------------------------------------------------------------------
+// selection by a team of waves
+// ---------------------------------------------------------------------------------
+
+constexpr int kTreeEpt = kSmallMaxEntries / kSmallBlock;
+constexpr int kTreeTeams = 16;
+constexpr uint32_t kTreeBins = 1024;
+constexpr uint32_t kTreeList = 32;
+// bin of a key at distance rel from the bound: the distance itself below 32, then 32 bins per octave
+__device__ __forceinline__ uint32_t tree_bin(uint32_t rel) {
+    if (rel < 32u) return rel;
+    const uint32_t e = 31u - (uint32_t)__builtin_clz(rel);
+    return ((e - 4u) << 5) + ((rel >> (e - 5u)) & 31u);
+}
+// smallest distance of bin b, and how many distances it holds (as a power of two)
+__device__ __forceinline__ uint32_t tree_bin_first(uint32_t b) { return b < 32u ? b : (32u + (b & 31u)) << ((b >> 5) - 1u); }
+__device__ __forceinline__ uint32_t tree_bin_bits(uint32_t b) { return b < 32u ? 0u : (b >> 5) - 1u; }
+
+
+template <int TEAMS>
+struct TeamShared {
+    __align__(16) uint32_t hist[TEAMS * kTreeBins];            // zero between selections
+    uint32_t list[TEAMS][kTreeList];
+    uint32_t wave[kSmallBlock / kWave];
+    uint32_t pick[TEAMS][3], n[TEAMS], T[TEAMS], need[TEAMS];
+};
+template <int TEAMS>
+__device__ __forceinline__ void clear_teams(TeamShared<TEAMS>& sh) {
+    for (uint32_t b = 4 * threadIdx.x; b < TEAMS * kTreeBins; b += 4 * kSmallBlock)
+        *reinterpret_cast<uint4*>(&sh.hist[b]) = make_uint4(0u, 0u, 0u, 0u);
 }
 
-// the same for a list length known at run time (n <= 64 * MAXCH, MAXCH = 16 or 32)
-template <int MAXCH>
-__device__ __forceinline__ void wave_select_any(const uint32_t* keys, uint32_t n, uint32_t k,
-                                                uint32_t* selbits, uint32_t* gather) {
-    if (n <= 128u) wave_select<2>(keys, n, k, selbits, gather);
-    else if (n <= 192u) wave_select<3>(keys, n, k, selbits, gather);
-    else if (n <= 256u) wave_select<4>(keys, n, k, selbits, gather);
-    else if (n <= 384u) wave_select<6>(keys, n, k, selbits, gather);
-    else if (n <= 512u) wave_select<8>(keys, n, k, selbits, gather);
-    else if (n <= 640u) wave_select<10>(keys, n, k, selbits, gather);
-    else if (n <= 768u) wave_select<12>(keys, n, k, selbits, gather);
-    else if (MAXCH == 16 || n <= 1024u) wave_select<16>(keys, n, k, selbits, gather);
-    else wave_select<32>(keys, n, k, selbits, gather);
+// Each of the block's teams of SIZE threads (>= a wave) selects the k largest of its threads' keys (E each, kNoKey:
+// none), among equal ones the first in thread order.  The keys from `bound` on, which k of them are expected to reach,
+// are counted in 1024 bins that widen with the distance (a 32nd of an octave each), the team picks the bin of the k-th, and
+// while that holds more than kTreeList keys it is cut into 1024 again; what is left goes to a list, where every key's
+// owner ranks it.  Every thread of the block calls it; about eight barriers.
+struct TeamCut { uint32_t T, need, pos, eq; };     // the k-th key, keys equal to it to take; selected before this thread, equal ones before it
+template <uint32_t SIZE, int TEAMS, int E>
+__device__ __forceinline__ TeamCut team_select(TeamShared<TEAMS>& sh, const uint32_t (&key)[E], uint32_t bound, uint32_t k) {
+    constexpr uint32_t team_waves = SIZE / kWave, per = kTreeBins / SIZE;      // bins per thread
+    const uint32_t t = threadIdx.x, lane = lane_id(), wave = t / kWave;
+    const uint32_t team = t / SIZE, l = t % SIZE, first_wave = team * team_waves;
+    uint32_t* hist = sh.hist + team * kTreeBins;
+    // the k-th key lies in base + [lo, lo + 2^bits), `rank` of the `count` keys there reach it.  base: the bound,
+    // which k keys of the union reach unless sums cancel, else 0.
+    uint32_t base = bound, lo = 0, bits = 31, rank = k, count = 0;
+    bool by_octave = true, more = true;
+    auto candidate = [&](int j) {
+        return key[j] >= base && key[j] - base - lo < (1u << bits);            // (never kNoKey)
+    };
+    do {                                       // (every thread of the block takes the same turns)
+        const uint32_t shift = bits > 10u ? bits - 10u : 0u;
+        if (more)
+#pragma unroll
+            for (int j = 0; j < E; ++j)
+                if (candidate(j)) {
+                    const uint32_t rel = key[j] - base;
+                    atomicAdd(&hist[by_octave ? tree_bin(rel) : (rel - lo) >> shift], 1u);
+                }
+        __syncthreads();
+        uint32_t mine = 0, loc[per];
+#pragma unroll
+        for (uint32_t i = 0; i < per; ++i) {
+            loc[i] = hist[l * per + i];
+            hist[l * per + i] = 0u;            // (for the next turn, and the next round)
+            mine += loc[i];
+        }
+        const uint32_t incl = wave_incl_scan(mine);
+        if (lane == kWave - 1) sh.wave[wave] = incl;
+        if (l == 0) { sh.pick[team][2] = 0u; sh.n[team] = 0u; }
+        __syncthreads();
+        const uint32_t sums = row_incl_scan(lane < team_waves ? sh.wave[first_wave + lane] : 0u);
+        const uint32_t w_in = wave - first_wave;
+        uint32_t above = lane_value(sums, 15u) - incl - (w_in ? lane_value(sums, w_in - 1u) : 0u);
+        if (above < rank && above + mine >= rank) {                     // one thread owns the crossing
+#pragma unroll
+            for (int i = (int)per - 1; i >= 0; --i) {
+                if (above < rank && above + loc[i] >= rank) {
+                    sh.pick[team][0] = l * per + (uint32_t)i;
+                    sh.pick[team][1] = above;
+                    sh.pick[team][2] = loc[i];
+                }
+                above += loc[i];
+            }
+        }
+        __syncthreads();
+        if (more) {
+            const uint32_t b = sh.pick[team][0], c = sh.pick[team][2];
+            if (c == 0u) {                     // fewer than k keys reach the bound
+                more = base != 0u;             // (always so: the union has k entries)
+                if (!more) bits = 0;
+                base = 0;
+            } else {
+                rank -= sh.pick[team][1];
+                count = c;
+                lo = by_octave ? tree_bin_first(b) : lo + (b << shift);
+                bits = by_octave ? tree_bin_bits(b) : shift;
+                by_octave = false;
+                more = count > kTreeList && bits > 0u;
+            }
+        }
+    } while (__syncthreads_or(more ? 1 : 0));
+    if (bits > 0u) {
+#pragma unroll
+        for (int j = 0; j < E; ++j)
+            if (candidate(j)) sh.list[team][atomicAdd(&sh.n[team], 1u) & (kTreeList - 1u)] = key[j];    // count of them
+    } else if (l == 0) {
+        sh.T[team] = base + lo;
+        sh.need[team] = rank;
+    }
+    __syncthreads();
+    if (bits > 0u)
+#pragma unroll
+        for (int j = 0; j < E; ++j) {
+            if (!candidate(j)) continue;
+            uint32_t gt = 0, eq = 0;
+            for (uint32_t i = 0; i < count; ++i) {
+                const uint32_t x = sh.list[team][i];
+                gt += x > key[j] ? 1u : 0u;
+                eq += x == key[j] ? 1u : 0u;
+            }
+            if (gt < rank && gt + eq >= rank) { sh.T[team] = key[j]; sh.need[team] = rank - gt; }     // (all who do agree)
+        }
+    __syncthreads();
+    const uint32_t T = sh.T[team], need = sh.need[team];
+    uint32_t mine = 0;                         // entries above T, and equal to it << 16
+#pragma unroll
+    for (int j = 0; j < E; ++j) {
+        if (key[j] != kNoKey) mine += key[j] > T ? 1u : (key[j] == T ? 0x10000u : 0u);
+    }
+    const uint32_t incl = wave_incl_scan(mine);
+    if (lane == kWave - 1) sh.wave[wave] = incl;
+    __syncthreads();
+    const uint32_t sums = row_incl_scan(lane < team_waves ? sh.wave[first_wave + lane] : 0u);
+    const uint32_t w_in = wave - first_wave;
+    const uint32_t before = incl - mine + (w_in ? lane_value(sums, w_in - 1u) : 0u);
+    const uint32_t eq = before >> 16;
+    return TeamCut{T, need, (before & 0xFFFFu) + (eq < need ? eq : need), eq};
 }
 
 // ---------------------------------------------------------------------------------
@@ -247,7 +259,7 @@ __global__ __launch_bounds__(kSmallBlock) void k_small_sample(
 // Worker s = blockIdx.x.  The items are the worker's candidate list (or, if the
 // speculative threshold left fewer than k candidates or more than the list holds, its
 // dense row; slow for a long row, but rows are short here).  A candidate list of at most
-// 2048 entries goes to LDS and one wave selects from it (wave_select).  Anything else takes
+// 2048 entries is held in registers and selected from by the block as one team.  Anything else takes
 // three stages, each a walk over the items:
 //   1. LDS histogram of the first digit -> the bin d1 of the k-th key;
 //   2. up to three LDS radix passes over the keys inside bin d1 -> the exact key T and the
@@ -261,61 +273,54 @@ __global__ __launch_bounds__(kSmallBlock) void k_small_select(
     __shared__ uint32_t s_out[3];
     __shared__ uint32_t s_rx[kSmallMaxChunks];
     __shared__ uint32_t s_roff[kSmallMaxChunks + 1];
-    __shared__ uint32_t s_gather[kWave];
+    __shared__ TeamShared<1> s_team;
     const int s = blockIdx.x;
     const uint32_t t = threadIdx.x;
     const bool dn = src.dense(s);
     const uint32_t n = src.nphys(s, dn);
     if (!dn && n <= (uint32_t)kSmallRankList) {
-        // ---- a short candidate list: the keys go to LDS in index order (run after run in
-        // chunk order), one wave selects the k largest, ties to the lower index (Algorithm 4
-        // line 5), and every thread writes out its selected entries
-        uint32_t* keys = h;                                    // kSmallRankList <= kHistBins
-        static_assert(kSmallRankList <= kHistBins && kSmallRankList / 32 <= kWave && kSmallRankList / 32 <= kSmallMaxChunks, "");
+        // ---- a short candidate list: every thread takes two consecutive entries in index order (run after run in
+        // chunk order); the block selects the k largest, ties to the lower index (Algorithm 4 line 5)
         const uint32_t nruns = src.nchunks;                    // <= kSmallMaxChunks <= kT
         uint2 run = make_uint2(0u, 0u);
         if (t < nruns) run = src.run_table[(size_t)s * src.nchunks + t];
+        clear_teams(s_team);
         uint32_t tot;
         const uint32_t incl = block_incl_scan(run.y, s_wave, tot);
         if (t < nruns) { s_rx[t] = run.x; s_roff[t + 1] = incl; }
         if (t == 0) s_roff[0] = 0u;
         __syncthreads();
         constexpr int kPer = kSmallRankList / kT;
-        uint32_t idx[kPer], bits[kPer];
-#pragma unroll
-        for (int c = 0; c < kPer; ++c) {
-            const uint32_t lp = (uint32_t)c * kT + t;
-            idx[c] = 0u; bits[c] = 0u;
-            if (lp < n) {
-                uint32_t r = 0, hi = nruns;             // the run r with roff[r] <= lp < roff[r+1]
-                while (hi - r > 1) {
-                    const uint32_t mid = (r + hi) >> 1;
-                    if (s_roff[mid] <= lp) r = mid; else hi = mid;
-                }
-                src.fetch_phys(s, false, s_rx[r] + (lp - s_roff[r]), idx[c], bits[c]);
+        uint32_t idx[kPer], bits[kPer], key[kPer];
+        uint32_t r = 0;
+        {
+            uint32_t hi = nruns;                               // the run r with roff[r] <= first entry < roff[r+1]
+            while (hi - r > 1) {
+                const uint32_t mid = (r + hi) >> 1;
+                if (s_roff[mid] <= t * kPer) r = mid; else hi = mid;
             }
-            keys[lp] = lp < n ? (bits[c] & kAbs) + 1u : 0u;    // padding: beats nobody
         }
-        __syncthreads();
-        uint32_t* selbits = s_rx;                              // the run table has been used
-        uint32_t* wpre = s_roff;
-        if (t < (uint32_t)kWave) {                             // one wave selects
-            wave_select_any<kSmallRankList / kWave>(keys, n, k, selbits, s_gather);
-            // selected entries before each bitmap word (the wave reads its own stores)
-            const uint32_t c = t < (n + 31) / 32 ? (uint32_t)__popc(selbits[t]) : 0u;
-            wpre[t] = wave_incl_scan(c) - c;
-        }
-        __syncthreads();
 #pragma unroll
         for (int c = 0; c < kPer; ++c) {
-            const uint32_t lp = (uint32_t)c * kT + t;
-            if (lp >= n) break;
-            const uint32_t wd = selbits[lp >> 5];
-            if ((wd >> (lp & 31)) & 1u) {
-                // < k: exactly k entries are selected
-                const uint32_t pos = wpre[lp >> 5] + (uint32_t)__popc(wd & ((1u << (lp & 31)) - 1u));
+            const uint32_t lp = t * kPer + c;
+            idx[c] = 0u; bits[c] = 0u; key[c] = kNoKey;
+            if (lp < n) {
+                while (s_roff[r + 1] <= lp) ++r;               // (r + 1 <= nruns: the last run ends at n)
+                src.fetch_phys(s, false, s_rx[r] + (lp - s_roff[r]), idx[c], bits[c]);
+                key[c] = bits[c] & kAbs;
+            }
+        }
+        const TeamCut cut = team_select<kT>(s_team, key, src.tspec[s], k);
+        uint32_t eq = cut.eq, pos = cut.pos;
+#pragma unroll
+        for (int c = 0; c < kPer; ++c) {
+            if (key[c] == kNoKey) continue;
+            bool sel = key[c] > cut.T;
+            if (key[c] == cut.T) sel = eq++ < cut.need;
+            if (sel && pos < k) {                              // (always inside)
                 out_idx[(size_t)s * k + pos] = idx[c];
                 out_val[(size_t)s * k + pos] = __uint_as_float(bits[c]);
+                ++pos;
             }
         }
         return;
@@ -461,51 +466,30 @@ __global__ __launch_bounds__(kSmallBlock) void k_small_select(
 // thread owns at most kTreeEpt consecutive slots of its pair's union in index order:
 //   union      a binary search along the diagonal, then a sequential merge; A's copy carries the sum at a shared
 //              index, B's slot there is a tombstone;
-//   select     the keys above the larger of the operands' smallest keys are counted in 1024 bins that widen with the
-//              distance (a 32nd of an octave each), the team picks the bin of the k-th, and while that holds more than
-//              kTreeList keys it is cut into 1024 again; what is left goes to a list, where every key's owner ranks it;
+//   select     see team_select; the larger of the operands' smallest keys is the bound, which k keys reach unless sums cancel;
 //   emit       one prefix sum over the team's threads, selected slots to set p of the next round.
 // (Every barrier is the block's, about nine per round, and a round is its chain of dependent LDS reads and barriers:
 // some 6 us.  One wave per pair that held all keys in registers and searched the k-th in a bracket, with the slots in
-// LDS for a bitmap and a compaction, took 8 us per round of sets of 270; the tree of 8 such sets 26.9 -> 20.3 us.  With the
-// teams' sizes known only at run time 23.4.)
+// LDS for a bitmap and a compaction, took 8 us per round of sets of 270; the tree of 8 such sets 26.9 -> 20.0 us, the selection
+// of 270 among 680 candidates 10.6 -> 7.5.  With the teams' sizes known only at run time the tree takes 23.4.)
 // After the last round the global set's values are divided by P and written out, and every worker's locally selected
 // entries whose index is in it (or whose value is -0.0, which the literal zero-then-add-back would turn into +0.0) are
 // stored as +0.0 in the worker's row - the rows still hold the accumulated values at the selected entries.
-constexpr int kTreeEpt = kSmallMaxEntries / kSmallBlock;
-constexpr int kTreeTeams = 16;
-constexpr uint32_t kTreeBins = 1024;
-constexpr uint32_t kTreeList = 32;
-// bin of a key at distance rel from the bound: the distance itself below 32, then 32 bins per octave
-__device__ __forceinline__ uint32_t tree_bin(uint32_t rel) {
-    if (rel < 32u) return rel;
-    const uint32_t e = 31u - (uint32_t)__builtin_clz(rel);
-    return ((e - 4u) << 5) + ((rel >> (e - 5u)) & 31u);
-}
-// smallest distance of bin b, and how many distances it holds (as a power of two)
-__device__ __forceinline__ uint32_t tree_bin_first(uint32_t b) { return b < 32u ? b : (32u + (b & 31u)) << ((b >> 5) - 1u); }
-__device__ __forceinline__ uint32_t tree_bin_bits(uint32_t b) { return b < 32u ? 0u : (b >> 5) - 1u; }
-
 struct TreeShared {
     // two buffers of surviving sets, k entries each, that the rounds take in turn
     uint32_t idx[kSmallMaxEntries + kSmallMaxEntries / 2];
     uint32_t val[kSmallMaxEntries + kSmallMaxEntries / 2];
-    __align__(16) uint32_t hist[kTreeTeams * kTreeBins];       // zero between the rounds
-    uint32_t list[kTreeTeams][kTreeList];
+    TeamShared<kTreeTeams> team;
     uint32_t min[2][kSmallMaxP];                               // the sets' smallest keys
-    uint32_t wave[kSmallBlock / kWave];
-    uint32_t pick[kTreeTeams][3], n[kTreeTeams], T[kTreeTeams], need[kTreeTeams];
 };
 
 // One round, SIZE threads per team: the sets at `from` are merged into those at `to`.
 template <uint32_t SIZE>
 __device__ __forceinline__ void tree_round(TreeShared& sh, uint32_t pairs, uint32_t k, uint32_t from, uint32_t to, int turn_min) {
-    constexpr uint32_t teams = kSmallBlock / SIZE, team_waves = SIZE / kWave, per = kTreeBins / SIZE;    // bins per thread
-    const uint32_t t = threadIdx.x, lane = lane_id(), wave = t / kWave;
-    const uint32_t team = t / SIZE, l = t % SIZE, first_wave = team * team_waves;
+    constexpr uint32_t teams = kSmallBlock / SIZE;
+    const uint32_t team = threadIdx.x / SIZE, l = threadIdx.x % SIZE;
     constexpr int kE = SIZE == 1024 ? 1 : (SIZE == 512 ? 2 : kTreeEpt);       // slots per thread, at most
     static_assert(2 * kSmallMaxK <= 1024 && kSmallMaxEntries <= 1024 * kTreeEpt, "2k slots fit a team's threads");
-    uint32_t* hist = sh.hist + team * kTreeBins;
     const uint32_t n = 2 * k, ept = (n + SIZE - 1) / SIZE;                   // <= kE
     for (uint32_t q = team; q < pairs; q += teams) {                        // (pairs is a multiple of teams)
         // ---- union ------------------------------------------------------------------
@@ -544,112 +528,18 @@ __device__ __forceinline__ void tree_round(TreeShared& sh, uint32_t pairs, uint3
                 }
             }
         }
-        // ---- select -----------------------------------------------------------------
-        // the k-th key lies in base + [lo, lo + 2^bits), `rank` of the `count` keys there reach it.  base: the bound,
-        // which k keys of the union reach unless sums cancel, else 0.
-        uint32_t base = bound, lo = 0, bits = 31, rank = k, count = 0;
-        bool by_octave = true, more = true;
-        auto candidate = [&](int j) {
-            const uint32_t key = ov[j] & kAbs;
-            return oi[j] != kTomb && key >= base && key - base - lo < (1u << bits);
-        };
-        do {                                       // (every thread of the block takes the same turns)
-            const uint32_t shift = bits > 10u ? bits - 10u : 0u;
-            if (more)
+        // ---- select and emit ------------------------------------------------------------
+        uint32_t key[kE];
 #pragma unroll
-                for (int j = 0; j < kE; ++j)
-                    if (candidate(j)) {
-                        const uint32_t rel = (ov[j] & kAbs) - base;
-                        atomicAdd(&hist[by_octave ? tree_bin(rel) : (rel - lo) >> shift], 1u);
-                    }
-            __syncthreads();
-            uint32_t mine = 0, loc[per];
-#pragma unroll
-            for (uint32_t i = 0; i < per; ++i) {
-                loc[i] = hist[l * per + i];
-                hist[l * per + i] = 0u;            // (for the next turn, and the next round)
-                mine += loc[i];
-            }
-            const uint32_t incl = wave_incl_scan(mine);
-            if (lane == kWave - 1) sh.wave[wave] = incl;
-            if (l == 0) { sh.pick[team][2] = 0u; sh.n[team] = 0u; }
-            __syncthreads();
-            const uint32_t sums = row_incl_scan(lane < team_waves ? sh.wave[first_wave + lane] : 0u);
-            const uint32_t w_in = wave - first_wave;
-            uint32_t above = lane_value(sums, 15u) - incl - (w_in ? lane_value(sums, w_in - 1u) : 0u);
-            if (above < rank && above + mine >= rank) {                     // one thread owns the crossing
-#pragma unroll
-                for (int i = (int)per - 1; i >= 0; --i) {
-                    if (above < rank && above + loc[i] >= rank) {
-                        sh.pick[team][0] = l * per + (uint32_t)i;
-                        sh.pick[team][1] = above;
-                        sh.pick[team][2] = loc[i];
-                    }
-                    above += loc[i];
-                }
-            }
-            __syncthreads();
-            if (more) {
-                const uint32_t b = sh.pick[team][0], c = sh.pick[team][2];
-                if (c == 0u) {                     // fewer than k keys reach the bound
-                    more = base != 0u;             // (always so: the union has k entries)
-                    if (!more) bits = 0;
-                    base = 0;
-                } else {
-                    rank -= sh.pick[team][1];
-                    count = c;
-                    lo = by_octave ? tree_bin_first(b) : lo + (b << shift);
-                    bits = by_octave ? tree_bin_bits(b) : shift;
-                    by_octave = false;
-                    more = count > kTreeList && bits > 0u;
-                }
-            }
-        } while (__syncthreads_or(more ? 1 : 0));
-        if (bits > 0u) {
-#pragma unroll
-            for (int j = 0; j < kE; ++j)
-                if (candidate(j)) sh.list[team][atomicAdd(&sh.n[team], 1u) & (kTreeList - 1u)] = ov[j] & kAbs;    // count of them
-        } else if (l == 0) {
-            sh.T[team] = base + lo;
-            sh.need[team] = rank;
-        }
-        __syncthreads();
-        if (bits > 0u)
-#pragma unroll
-            for (int j = 0; j < kE; ++j) {
-                if (!candidate(j)) continue;
-                const uint32_t key = ov[j] & kAbs;
-                uint32_t gt = 0, eq = 0;
-                for (uint32_t i = 0; i < count; ++i) {
-                    const uint32_t x = sh.list[team][i];
-                    gt += x > key ? 1u : 0u;
-                    eq += x == key ? 1u : 0u;
-                }
-                if (gt < rank && gt + eq >= rank) { sh.T[team] = key; sh.need[team] = rank - gt; }     // (all who do agree)
-            }
-        __syncthreads();
-        const uint32_t T = sh.T[team], need = sh.need[team];
-        // ---- emit -------------------------------------------------------------------
-        uint32_t mine = 0;                         // entries above T, and equal to it << 16
+        for (int j = 0; j < kE; ++j) key[j] = oi[j] != kTomb ? ov[j] & kAbs : kNoKey;
+        const TeamCut c = team_select<SIZE>(sh.team, key, bound, k);
+        if (l == 0) sh.min[turn_min ^ 1][q] = c.T;
+        uint32_t eq = c.eq, pos = c.pos;
 #pragma unroll
         for (int j = 0; j < kE; ++j) {
-            const uint32_t key = ov[j] & kAbs;
-            if (oi[j] != kTomb) mine += key > T ? 1u : (key == T ? 0x10000u : 0u);
-        }
-        const uint32_t incl = wave_incl_scan(mine);
-        if (lane == kWave - 1) sh.wave[wave] = incl;
-        if (l == 0) sh.min[turn_min ^ 1][q] = T;
-        __syncthreads();
-        const uint32_t sums = row_incl_scan(lane < team_waves ? sh.wave[first_wave + lane] : 0u);
-        const uint32_t w_in = wave - first_wave;
-        const uint32_t before = incl - mine + (w_in ? lane_value(sums, w_in - 1u) : 0u);
-        uint32_t eq = before >> 16, pos = (before & 0xFFFFu) + (eq < need ? eq : need);
-#pragma unroll
-        for (int j = 0; j < kE; ++j) {
-            if (oi[j] == kTomb) continue;
-            const uint32_t key = ov[j] & kAbs;
-            bool sel = key > T;
-            if (key == T) sel = eq++ < need;
+            if (key[j] == kNoKey) continue;
+            bool sel = key[j] > c.T;
+            if (key[j] == c.T) sel = eq++ < c.need;
             if (sel && pos < k) {                  // (always inside)
                 sh.idx[to + q * k + pos] = oi[j];
                 sh.val[to + q * k + pos] = ov[j];
@@ -682,9 +572,7 @@ __global__ __launch_bounds__(kSmallBlock) void k_small_tree(
             sh.val[e] = in_val[c];
         }
     }
-#pragma unroll
-    for (uint32_t b = 0; b < kTreeTeams * kTreeBins; b += 4 * kT)
-        *reinterpret_cast<uint4*>(&sh.hist[b + 4 * t]) = make_uint4(0u, 0u, 0u, 0u);
+    clear_teams(sh.team);
     __syncthreads();
     for (uint32_t w = wave; w < P; w += kWaves) {      // smallest keys, a wave per set
         uint32_t inv = 0;
