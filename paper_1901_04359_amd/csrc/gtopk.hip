@@ -598,6 +598,22 @@ uint32_t bracket_target_hi(double mean, double placed) {
     return t > 0.0 ? (uint32_t)t : 0u;
 }
 
+// Entries per thread with which one block selects from a worker's candidate list (k_small_select), 0: the general
+// kernels do, three of them.  A list is expected to hold 2.5 k entries (mid_sample_mean), a longer one than the threads hold
+// takes the block some walks.  A row that cannot be filtered is read by the one block; the line in m keeps that within
+// what the general kernels take.  gtopk_step in us, three kernels and three per round of the tree / one and one:
+//   m = 30,000  P = 8  k = 1000   86.5 / 45.1     m = 400,000  P = 4   k = 1000  74.2 / 43.8    k = 4000  73.0 / 60.1
+//   m = 100,000 P = 8  k = 4000   92.7 / 73.4     m = 400,000  P = 16  k = 900  123.7 / 62.2
+//   m = 100,000 P = 32 k = 2000  136.3 / 81.6     m = 524,288  P = 32  k = 4000  169 / 119
+// rows of zeros, P = 8, k = 2000:  m = 200,000  189 / 111   m = 524,288  283 / 158 (P = 32, k = 4000: 518 / 233); rows of
+// ones, whose equal values the steps spread over many ranges: m = 200,000  147 / 93   m = 524,288  256 / 356 (the one
+// slower kind found, P = 32, k = 4000: 443 / 422).
+uint32_t select_in_block(int64_t m, uint32_t k) {
+    if (m > (1 << 19)) return 0;
+    const uint32_t n = 4 * k + 256;
+    return n <= 4096 ? 4 : (n <= 8192 ? 8 : (n <= 16384 ? 16 : 0));
+}
+
 // The pass can also histogram the candidates it keeps; the select's own histogram kernel
 // then only serves workers that fall back to their dense row.  That costs LDS atomics and,
 // per block and non-empty bin, a global atomic in the pass.  Measured against the
@@ -689,12 +705,12 @@ void sample_rows(const float* grad, const float* residual, int64_t m, int64_t st
 template <bool SUM>
 bool filter_rows(const float* grad, float* residual, int64_t m, int64_t stride, uint32_t P, uint32_t k,
                  const StepWs& w, const ZeroJob& job, hipStream_t st, void* const* events = nullptr,
-                 uint32_t* thr_state = nullptr) {
+                 uint32_t* thr_state = nullptr, bool histogram = true) {
     sample_rows<SUM, false>(grad, residual, m, stride, P, k, w, plan_row_sample(m, k, P), job, w.tspec, nullptr, nullptr, st,
                      thr_state);
     mark_stage(1, events, st);
 
-    const bool producer_hist = pass_histograms(m, k);
+    const bool producer_hist = histogram && pass_histograms(m, k);
     if (producer_hist) launch_pass<true, SUM>(grad, residual, m, stride, P, w, st);
     else launch_pass<false, SUM>(grad, residual, m, stride, P, w, st);
     mark_stage(2, events, st);
@@ -708,11 +724,18 @@ int do_local_select(const float* grad, float* residual, int64_t m, int64_t strid
                     uint32_t k, uint32_t* out_idx, float* out_val, const StepWs& w, bool zero_rows,
                     const ZeroJob& job, hipStream_t st, void* const* events = nullptr,
                     uint32_t* thr_state = nullptr) {
-    const bool producer_hist = filter_rows<true>(grad, residual, m, stride, P, k, w, job, st, events, thr_state);
+    const uint32_t entries = select_in_block(m, k);
+    const bool producer_hist = filter_rows<true>(grad, residual, m, stride, P, k, w, job, st, events, thr_state, entries == 0);
     const CandSrc src = cand_source(residual, stride, m, k, w, producer_hist, false, thr_state);
     // the histogram kernel always runs: where the pass has counted its candidates it serves
     // only the workers that came back with fewer than k of them
-    if (run_groups(m, k)) {
+    if (entries != 0) {
+#define GTOPK_SELECT(E) hipLaunchKernelGGL(k_small_select<E>, dim3(P), dim3(kSmallBlock), 0, st, src, k, out_idx, out_val, w.sel.T)
+        if (entries == 4) GTOPK_SELECT(4);
+        else if (entries == 8) GTOPK_SELECT(8);
+        else GTOPK_SELECT(16);
+#undef GTOPK_SELECT
+    } else if (run_groups(m, k)) {
         RunSrc rs;
         static_cast<CandSrc&>(rs) = src;
         // k_bucket: every wave of a block takes a run; k_emit: a block per run; a worker on its
@@ -1033,7 +1056,7 @@ int gtopk_local_select(const float* grad, float* residual, int64_t m, int64_t st
     if (ws_bytes < w.bytes) return GTOPK_EWORKSPACE;
     return do_local_select(grad, residual, m, stride, (uint32_t)P, (uint32_t)k, out_idx, out_val, w, true,
                            zero_job(w.samp_hist, w.samp_words, w.cand_count, (size_t)P, w.sel.hist,
-                                    select_clear_words(w.sel)),
+                                    select_in_block(m, (uint32_t)k) ? 0 : select_clear_words(w.sel)),
                            (hipStream_t)stream);
 }
 
@@ -1116,7 +1139,8 @@ static int step_impl(const float* grad, float* residual, int64_t m, int64_t stri
                            w.cand_count, w.run_table, nruns, w.sel.hist, (uint32_t*)nullptr);
         CandSrc src = cand_source(residual, stride, m, (uint32_t)k, w, false, false);
         src.nchunks = nruns;
-        hipLaunchKernelGGL(k_small_select, dim3(P), dim3(kSmallBlock), 0, st, src, (uint32_t)k, li, lv);
+        hipLaunchKernelGGL(k_small_select<kSmallEntries>, dim3(P), dim3(kSmallBlock), 0, st, src, (uint32_t)k, li, lv,
+                           (uint32_t*)nullptr);
         hipLaunchKernelGGL(k_small_tree, dim3(1), dim3(kSmallBlock), 0, st, li, lv, (uint32_t)P,
                            (uint32_t)k, g_idx, g_val, (float)P, residual, stride);
         return launch_status();
@@ -1128,7 +1152,7 @@ static int step_impl(const float* grad, float* residual, int64_t m, int64_t stri
     // candidate counters; both selects' histograms and tickets; the global-set bitmap
     const bool in_block = merge_in_block((uint32_t)k);       // its rounds need no select state
     const ZeroJob job = zero_job(w.samp_hist, w.samp_words, w.cand_count, (size_t)P, w.sel.hist,
-                                 select_clear_words(w.sel), w.mrg.sel.hist, in_block ? 0 : select_clear_words(w.mrg.sel),
+                                 select_in_block(m, (uint32_t)k) ? 0 : select_clear_words(w.sel), w.mrg.sel.hist, in_block ? 0 : select_clear_words(w.mrg.sel),
                                  w.mrg.sel_alt.hist, in_block ? 0 : w.mrg.alt_clear_words, w.gbits, w.gbits_words);
     int rc = do_local_select(grad, residual, m, stride, (uint32_t)P, (uint32_t)k, li, lv, w, false,
                              job, st, events, thr_state);

@@ -23,7 +23,7 @@ constexpr int kSmallMaxChunks = 256;         // rows of at most 2^20 elements
 constexpr int kSmallMaxEntries = 4096;       // P * k, at most
 constexpr int kSmallMaxK = 512;
 constexpr int kSmallMaxP = 64;
-constexpr int kSmallRankList = 2048;         // candidate lists up to here: held in registers
+constexpr int kSmallEntries = 2;             // entries per thread of a candidate list held in registers
 constexpr int kMidSampleTile = 16;           // elements per tile where it serves rows of millions of elements
 constexpr int kSmallSampleUnroll = 16;       // tiles that each of its groups of lanes keeps in flight
 
@@ -256,17 +256,32 @@ __global__ __launch_bounds__(kSmallBlock) void k_small_sample(
 // local selection of one worker in one block
 // ---------------------------------------------------------------------------------
 
+// Whether all keys of a wave are `one`.  Rows of zeros or of equal values are what a threshold cannot filter, and a block
+// that walks one of 524,288 entries is bound by the instructions per key: step 380 / 158 us with zeros, 594 / 356 with ones
+// (P = 8), each key binned / sixteen per thread compared first.
+template <int N>
+__device__ inline bool same_keys(const uint32_t (&key)[N], uint32_t& one) {
+    one = lane_value(key[0], 0u);
+    uint32_t diff = 0;
+#pragma unroll
+    for (int j = 0; j < N; ++j) diff |= key[j] ^ one;
+    return __ballot(diff != 0u) == 0;
+}
+
 // Worker s = blockIdx.x.  The items are the worker's candidate list (or, if the
 // speculative threshold left fewer than k candidates or more than the list holds, its
 // dense row; slow for a long row, but rows are short here).  A candidate list of at most
-// 2048 entries is held in registers and selected from by the block as one team.  Anything else takes
+// 1024 E entries is held in registers and selected from by the block as one team.  Anything else takes
 // three stages, each a walk over the items:
 //   1. LDS histogram of the first digit -> the bin d1 of the k-th key;
 //   2. up to three LDS radix passes over the keys inside bin d1 -> the exact key T and the
 //      number of ties to take;
 //   3. the emit in index order (for a candidate list: run after run in chunk order).
+// E: entries of a candidate list that a thread holds.  T_out != NULL: the smallest key of each set, for what follows in
+// the general path (where thresholds are carried on as well).
+template <int E>
 __global__ __launch_bounds__(kSmallBlock) void k_small_select(
-        CandSrc src, uint32_t k, uint32_t* __restrict__ out_idx, float* __restrict__ out_val) {
+        CandSrc src, uint32_t k, uint32_t* __restrict__ out_idx, float* __restrict__ out_val, uint32_t* __restrict__ T_out) {
     constexpr int kT = kSmallBlock;
     __shared__ uint32_t h[kHistBins];
     __shared__ uint32_t s_wave[kT / kWave];
@@ -278,8 +293,8 @@ __global__ __launch_bounds__(kSmallBlock) void k_small_select(
     const uint32_t t = threadIdx.x;
     const bool dn = src.dense(s);
     const uint32_t n = src.nphys(s, dn);
-    if (!dn && n <= (uint32_t)kSmallRankList) {
-        // ---- a short candidate list: every thread takes two consecutive entries in index order (run after run in
+    if (!dn && n <= (uint32_t)(E * kT)) {
+        // ---- a short candidate list: every thread takes E consecutive entries in index order (run after run in
         // chunk order); the block selects the k largest, ties to the lower index (Algorithm 4 line 5)
         const uint32_t nruns = src.nchunks;                    // <= kSmallMaxChunks <= kT
         uint2 run = make_uint2(0u, 0u);
@@ -290,7 +305,7 @@ __global__ __launch_bounds__(kSmallBlock) void k_small_select(
         if (t < nruns) { s_rx[t] = run.x; s_roff[t + 1] = incl; }
         if (t == 0) s_roff[0] = 0u;
         __syncthreads();
-        constexpr int kPer = kSmallRankList / kT;
+        constexpr int kPer = E;
         uint32_t idx[kPer], bits[kPer], key[kPer];
         uint32_t r = 0;
         {
@@ -311,6 +326,10 @@ __global__ __launch_bounds__(kSmallBlock) void k_small_select(
             }
         }
         const TeamCut cut = team_select<kT>(s_team, key, src.tspec[s], k);
+        if (T_out && t == 0) {
+            T_out[s] = cut.T;
+            src.carry(s, cut.T);
+        }
         uint32_t eq = cut.eq, pos = cut.pos;
 #pragma unroll
         for (int c = 0; c < kPer; ++c) {
@@ -325,23 +344,32 @@ __global__ __launch_bounds__(kSmallBlock) void k_small_select(
         }
         return;
     }
+    constexpr int kAhead = 16;                                 // loads in flight per thread (a row is walked by one block)
+    const uint32_t first = t / kWave * (kWave * kAhead) + lane_id();          // a wave's keys of a turn lie next to each other
     const Digit dg = src.digit(s, dn, SelState{});
     const uint32_t fl = src.floor_key(s, dn);
 
     // ---- 1. first digit --------------------------------------------------------------
     for (int b = t; b < kHistBins; b += kT) h[b] = 0u;
     __syncthreads();
-    for (uint32_t p0 = 0; p0 < n; p0 += kT * 4) {
-        uint32_t key[4];
-        bool ok[4];
+    for (uint32_t p0 = 0; p0 < n; p0 += kT * kAhead) {
+        if (p0 + (first - lane_id()) >= n) break;
+        uint32_t key[kAhead];
+        bool ok[kAhead];
 #pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            const uint32_t p = p0 + j * kT + t;
-            key[j] = 0;
-            ok[j] = p < n && src.fetch_key_phys(s, dn, p, key[j]) && key[j] >= fl;
+        for (int j = 0; j < kAhead; ++j) {
+            const uint32_t p = p0 + first + j * kWave;
+            src.fetch_key_phys(s, dn, p < n ? p : n - 1, key[j]);
+        }
+        uint32_t one;
+        if (p0 + kT * kAhead <= n && same_keys(key, one)) {
+            if (lane_id() == 0 && one >= fl) atomicAdd(&h[dg.bin(one)], (uint32_t)(kWave * kAhead));
+            continue;
         }
 #pragma unroll
-        for (int j = 0; j < 4; ++j) {
+        for (int j = 0; j < kAhead; ++j) ok[j] = p0 + first + j * kWave < n && key[j] >= fl;
+#pragma unroll
+        for (int j = 0; j < kAhead; ++j) {
             // a wave whose keys all fall into one bin (rows of zeros, equal values) adds once
             const uint32_t b = dg.bin(key[j]);
             const uint64_t act = __ballot(ok[j]);
@@ -375,17 +403,26 @@ __global__ __launch_bounds__(kSmallBlock) void k_small_select(
         __syncthreads();                                         // the last pick has read h
         for (int b = t; b < 2048; b += kT) h[b] = 0u;
         __syncthreads();
-        for (uint32_t p0 = 0; p0 < n; p0 += kT * 4) {
-            uint32_t key[4];
-            bool ok[4];
+        for (uint32_t p0 = 0; p0 < n; p0 += kT * kAhead) {
+            if (p0 + (first - lane_id()) >= n) break;
+            uint32_t key[kAhead];
+            bool ok[kAhead];
 #pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                const uint32_t p = p0 + j * kT + t;
-                key[j] = 0;
-                ok[j] = p < n && src.fetch_key_phys(s, dn, p, key[j]) && key[j] >= fl;
+            for (int j = 0; j < kAhead; ++j) {
+                const uint32_t p = p0 + first + j * kWave;
+                src.fetch_key_phys(s, dn, p < n ? p : n - 1, key[j]);
+            }
+            uint32_t one;
+            if (p0 + kT * kAhead <= n && same_keys(key, one)) {
+                const uint32_t rel = one - lo;
+                if (lane_id() == 0 && one >= fl && dg.bin(one) == d1 && (rel >> (shift + bits)) == prefix)
+                    atomicAdd(&h[(rel >> shift) & ((1u << bits) - 1u)], (uint32_t)(kWave * kAhead));
+                continue;
             }
 #pragma unroll
-            for (int j = 0; j < 4; ++j) {
+            for (int j = 0; j < kAhead; ++j) ok[j] = p0 + first + j * kWave < n && key[j] >= fl;
+#pragma unroll
+            for (int j = 0; j < kAhead; ++j) {
                 const uint32_t rel = key[j] - lo;
                 const bool mine = ok[j] && dg.bin(key[j]) == d1 && (rel >> (shift + bits)) == prefix;
                 const uint32_t b = (rel >> shift) & ((1u << bits) - 1u);
@@ -407,6 +444,10 @@ __global__ __launch_bounds__(kSmallBlock) void k_small_select(
     }
     const uint32_t T = lo + prefix;
     const uint32_t need = krem;
+    if (T_out && t == 0) {
+        T_out[s] = T;
+        src.carry(s, T);
+    }
 
     // ---- 3. ordered emit ---------------------------------------------------------------
     // a candidate list is read run after run in chunk order: first slots and running counts
@@ -421,39 +462,53 @@ __global__ __launch_bounds__(kSmallBlock) void k_small_select(
         if (t == 0) s_roff[0] = 0u;
     }
     __syncthreads();
-    uint32_t outp = 0, eq_before = 0;
-    for (uint32_t base = 0; base < n; base += kT) {
-        const uint32_t lp = base + t;
-        uint32_t idx = 0, bits = 0;
-        bool ok = lp < n;
-        if (ok) {
-            uint32_t p = lp;
+    // eight consecutive entries per thread and turn, one prefix sum; the rest of a row behind the k-th entry is not read
+    constexpr uint32_t kTurn = 8;
+    uint32_t gt_before = 0, eq_before = 0;
+    for (uint32_t base = 0; base < n; base += kT * kTurn) {
+        const uint32_t lp0 = base + t * kTurn;
+        uint32_t r = 0;
+        if (!dn && lp0 < n) {
+            uint32_t hi = nruns;                        // the run r with roff[r] <= lp0 < roff[r+1]
+            while (hi - r > 1) {
+                const uint32_t mid = (r + hi) >> 1;
+                if (s_roff[mid] <= lp0) r = mid; else hi = mid;
+            }
+        }
+        uint32_t idx[kTurn], bits[kTurn], key[kTurn], mine = 0;         // entries above T, and equal to it << 16
+#pragma unroll
+        for (uint32_t j = 0; j < kTurn; ++j) {
+            const uint32_t lp = lp0 + j < n ? lp0 + j : n - 1;
+            uint32_t at = lp;
             if (!dn) {
-                uint32_t r = 0, hi = nruns;             // the run r with roff[r] <= lp < roff[r+1]
-                while (hi - r > 1) {
-                    const uint32_t mid = (r + hi) >> 1;
-                    if (s_roff[mid] <= lp) r = mid; else hi = mid;
-                }
-                p = s_rx[r] + (lp - s_roff[r]);
+                while (s_roff[r + 1] <= lp) ++r;
+                at = s_rx[r] + (lp - s_roff[r]);
             }
-            ok = src.fetch_phys(s, dn, p, idx, bits) && (bits & kAbs) >= fl;
+            src.fetch_phys(s, dn, at, idx[j], bits[j]);
         }
-        const uint32_t key = bits & kAbs;
-        const bool is_gt = ok && key > T;
-        const bool is_eq = ok && key == T;
-        uint32_t eq_tot, sel_tot;
-        const uint32_t eq_incl = block_incl_scan(is_eq ? 1u : 0u, s_wave, eq_tot);
-        const bool sel = is_gt || (is_eq && eq_before + eq_incl - 1u < need);
-        const uint32_t sel_incl = block_incl_scan(sel ? 1u : 0u, s_wave, sel_tot);
-        if (sel) {
-            const uint32_t pos = outp + sel_incl - 1u;
-            if (pos < k) {          // always true when the counts are consistent
-                out_idx[(size_t)s * k + pos] = idx;
-                out_val[(size_t)s * k + pos] = __uint_as_float(bits);
+#pragma unroll
+        for (uint32_t j = 0; j < kTurn; ++j) {
+            key[j] = bits[j] & kAbs;
+            if (lp0 + j >= n || key[j] < fl) key[j] = kNoKey;
+            if (key[j] != kNoKey) mine += key[j] > T ? 1u : (key[j] == T ? 0x10000u : 0u);
+        }
+        uint32_t all;
+        const uint32_t before = block_incl_scan(mine, s_wave, all) - mine;
+        uint32_t eq = eq_before + (before >> 16), pos = gt_before + (before & 0xFFFFu) + (eq < need ? eq : need);
+#pragma unroll
+        for (uint32_t j = 0; j < kTurn; ++j) {
+            if (key[j] == kNoKey) continue;
+            bool sel = key[j] > T;
+            if (key[j] == T) sel = eq++ < need;
+            if (sel && pos < k) {       // always inside when the counts are consistent
+                out_idx[(size_t)s * k + pos] = idx[j];
+                out_val[(size_t)s * k + pos] = __uint_as_float(bits[j]);
+                ++pos;
             }
         }
-        outp += sel_tot;
-        eq_before += eq_tot;
+        gt_before += all & 0xFFFFu;
+        eq_before += all >> 16;
+        if (gt_before + (eq_before < need ? eq_before : need) >= k) break;                    // block-uniform
     }
 }
 
