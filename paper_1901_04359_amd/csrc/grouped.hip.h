@@ -912,8 +912,9 @@ __global__ __launch_bounds__(kGrpFinishBlock) void k_group_finish(GroupSets gs, 
         ia += a[j];
         iq += q[j];
     }
+    // (every entry holds running totals, the last one too: group_cut takes differences for the groups' ties)
+    if (t == kT - 1 && gs.ngroups == kMaxIndexGroups) off[gs.ngroups] = make_uint2(ia, iq);
     if (t == 0) {
-        if (gs.ngroups == kMaxIndexGroups) off[gs.ngroups] = make_uint2(gb.k - need, need);
         gs.T[id] = T;
         gs.need[id] = need;
     }

@@ -112,3 +112,35 @@ def test_step_by_index_groups(P, m, k, kind, pad):
         for w in range(P):
             assert bits_equal(out[w], exp["residual"][w]), (w, first_diff(out[w], exp["residual"][w]))
         res = np.stack(list(exp["residual"]))
+
+
+# The longest rows that go by groups: the last group's ties are found at the end of the groups' table.
+# ties: of either worker, equal to the k-th key, in front of the last group / in it (six of them are selected)
+@pytest.mark.parametrize("m,ties", [(8192 * GROUP, ((3, 9), (6, 5))), (8191 * GROUP + 40, ((0, 9), (2, 7)))])
+def test_ties_in_the_last_of_the_most_groups(m, ties):
+    P, k, need = 2, m // 8 + 1, 6
+    last = 8191 * GROUP
+    rng = np.random.default_rng(m)
+    large = rng.choice(last, k - need + 100, replace=False)      # (the first k - need, the others are free for ties)
+    base = rng.random(m, dtype=np.float32) * np.float32(0.3) + np.float32(0.1)
+    base[large[:k - need]] = rng.random(k - need, dtype=np.float32) * np.float32(2.0) + np.float32(2.0)
+    # the workers share their large entries, so that the k-th key of the pair is that of their ties too
+    g = np.stack([base, base])
+    behind = rng.permutation(np.arange(last, m))
+    for w, (before, inside) in enumerate(ties):
+        g[w, large[k - need + 50 * w:][:before]] = 1.0
+        g[w, behind[20 * w:][:inside]] = -1.0
+    dev = Device(P, m, k)
+    dev.set_grad(g)
+    say(f"index groups, ties in the last group P={P} m={m} k={k}")
+    gi, gv = dev.step()
+    exp = dict(zip(("loc_idx", "loc_val", "g_idx", "g_val", "residual"), oracle_step_parallel(np.zeros_like(g), g, k)))
+    li, lv = idx_np(dev.loc_idx), val_np(dev.loc_val)
+    for w in range(P):
+        assert np.array_equal(li[w], exp["loc_idx"][w]), (w, first_diff(li[w], exp["loc_idx"][w]))
+        assert bits_equal(lv[w], exp["loc_val"][w]), (w, first_diff(lv[w], exp["loc_val"][w]))
+    assert np.array_equal(gi, exp["g_idx"]), first_diff(gi, exp["g_idx"])
+    assert bits_equal(gv, exp["g_val"]), first_diff(gv, exp["g_val"])
+    out = dev.residual()
+    for w in range(P):
+        assert bits_equal(out[w], exp["residual"][w]), (w, first_diff(out[w], exp["residual"][w]))
