@@ -22,8 +22,12 @@
 // (pass 2122 / 1700, local select and first union 1630 / 800, rounds behind it 1970 / 1350, restore 852 / 790).
 // Every list is written once and read once per round, no merged set is ever stored, and no cut point is
 // searched for: the sub-lists of a group are known from the groups' output positions.
-// A set whose k-th key lies outside its bracket (the sample misled) is counted whole by k_group_walk and selected by
-// k_group_finish from all of its keys: correct and slow (one block reads them three times).
+// A set whose k-th key lies outside its bracket (the sample misled) is counted whole by k_group_walk and gets another
+// bracket from that, whose keys several blocks of k_group_finish collect.  A step whose rows are made to mislead the sampler, in
+// us (lists / one block of k_group_finish reads all keys / now; without such rows 690 and 4750):
+//   m = 25.6 M  P = 4   k = m/4   one row of the four 1990 .. 2970 / 43,300 / 2520   all 3920 .. 6570 / 55,500 / 2770
+//   m = 25.6 M  P = 32  k = m/4   one row             8140 .. 9010 / 49,400 / 9530   all 26,900 .. 43,300 / 67,800 / 13,100
+//   m = 4.2 M   P = 4   k = m/8   one row               320 .. 440 / 6200 / 690      all     580 .. 850 / 6200 / 680
 #pragma once
 #include "common.hip.h"
 
@@ -42,6 +46,8 @@ constexpr uint32_t kInfKey = 0x7F800000u;               // a bracket ends here a
 constexpr int kBrkBins = 2048;                          // a bracket's histogram: 1024 bins at most ..
 constexpr uint32_t kAboveBin = (uint32_t)kBrkBins - 1;  // .. and the count of the keys above
 constexpr uint32_t kMissed = 0xFFFFFFFFu;               // GroupSets::d1 of a set whose bracket does not hold the k-th key
+constexpr uint32_t kTopBins = 2048;                     // a key's bits 30 .. 20
+constexpr uint32_t kAllBins = kTopBins + 1024;          // .. and bits 19 .. 10 of the keys in the k-th key's one of those
 constexpr uint32_t kPlainRun = 0xFFFFFFFFu;             // run.w: the keys are stored (else: all of them are this key)
 
 // A value as it is kept in registers and LDS, where kAbsent stands for "none" (one NaN pattern of either sign gives way
@@ -70,8 +76,9 @@ __device__ __forceinline__ uint32_t load_at(const uint32_t* base, uint32_t offse
 // Per-set state; sets are numbered through: the workers' 0 .. P-1, then the pairs of each round.
 struct GroupSets {
     uint32_t* hist;      // [sets][kBrkBins] bracket keys, the last one the keys above                      } cleared
-    uint32_t* hist_all;  // [sets][2048] top 11 bits of all keys of a set that missed its bracket           } before
+    uint32_t* hist_all;  // [sets][kAllBins] all keys of a set that missed its bracket                      } before
     uint32_t* list_cnt;  // [sets]                                                                          } a step
+    uint32_t* arrived;   // [sets] blocks that have collected their groups of such a set                    }
     uint32_t* brk_cnt;   // [P] bracket keys that the pass has stored (or tried to)                         }
     uint32_t* lo;        // [sets] the bracket
     uint32_t* hi;
@@ -548,66 +555,74 @@ __device__ inline void pick_bracket(const GroupSets& gs, const GroupBatch& gb, c
     }
 }
 
-// A set that missed its bracket: the blocks of its row share its groups, count the top digit of every key (which spares
-// k_group_finish the widest of its passes) and, of a pair, store the keys where those of the bracket would be.
-// h: 2048 + kGroup words of LDS.
+// A set that missed its bracket: the blocks of its row share its groups, count the top digit of every key (the bracket
+// that k_group_finish takes instead) and, of a pair, store the keys where those of the bracket would be.
+// h: kTopBins + kGroup words of LDS.
 __device__ inline void count_all(const GroupSets& gs, const GroupBatch& gb, uint32_t id, uint32_t* h) {
     const uint32_t t = threadIdx.x, p = blockIdx.y;
-    uint32_t* s_cell = h + 2048;
-    for (int b = t; b < 2048; b += kGrpWalkBlock) h[b] = 0u;
+    uint32_t* s_cell = h + kTopBins;
+    for (uint32_t b = t; b < kTopBins; b += kGrpWalkBlock) h[b] = 0u;
     __syncthreads();
-    for (uint32_t g = blockIdx.x - 1u; g < gs.ngroups; g += gridDim.x - 1u) {
-        Operands o;
-        if (!gb.rows) {
-            o = group_operands(gs, gb.in_idx, gb.in_val, gb.first_in, gb.k, p, g);
-            OperandBatch b;
-            load_operand<kGrpWalkBlock>(o, 0, o.first[0], b.idx[0], b.val[0]);
-            load_operand<kGrpWalkBlock>(o, 1, o.first[1], b.idx[1], b.val[1]);
-            clear_cells<false, kGrpWalkBlock>(s_cell);
-            unite<false, kGrpWalkBlock>(o, b, g, s_cell);
+    auto count = [&](uint32_t key) {                         // (masses of one key: added once)
+        const uint64_t act = __ballot(key != kAbsent);
+        if (!act) return;
+        const uint32_t b = key >> 20, first = (uint32_t)__builtin_ctzll(act);
+        if (__ballot(key != kAbsent && b == lane_value(b, first)) == act) {
+            if (lane_id() == first) atomicAdd(&h[b], (uint32_t)__popcll(act));
+        } else if (key != kAbsent) {
+            atomicAdd(&h[b], 1u);
         }
+    };
+    if (gb.rows) {                                           // a wave per stretch of 1024 elements
+        constexpr int kU = 16;
+        const float* row = gb.rows + (int64_t)p * gb.stride;
+        constexpr uint32_t kStretch = kWave * kU;
+        for (uint32_t i0 = ((blockIdx.x - 1u) * (kGrpWalkBlock / kWave) + t / kWave) * kStretch; i0 < gs.m;
+             i0 += (gridDim.x - 1u) * (kGrpWalkBlock / kWave) * kStretch) {
+            uint32_t key[kU];
+#pragma unroll
+            for (int j = 0; j < kU; ++j) {
+                const uint32_t i = i0 + j * kWave + lane_id();
+                key[j] = i < gs.m ? present_key(__float_as_uint(row[i])) : kAbsent;
+            }
+#pragma unroll
+            for (int j = 0; j < kU; ++j) count(key[j]);
+        }
+    }
+    for (uint32_t g = blockIdx.x - 1u; !gb.rows && g < gs.ngroups; g += gridDim.x - 1u) {
+        const Operands o = group_operands(gs, gb.in_idx, gb.in_val, gb.first_in, gb.k, p, g);
+        OperandBatch b;
+        load_operand<kGrpWalkBlock>(o, 0, o.first[0], b.idx[0], b.val[0]);
+        load_operand<kGrpWalkBlock>(o, 1, o.first[1], b.idx[1], b.val[1]);
+        clear_cells<false, kGrpWalkBlock>(s_cell);
+        unite<false, kGrpWalkBlock>(o, b, g, s_cell);
         constexpr int kPer = (int)kGroup / kGrpWalkBlock;
         uint32_t key[kPer];
 #pragma unroll
         for (int j = 0; j < kPer; ++j) {
-            const uint32_t c = j * kGrpWalkBlock + t, i = g * kGroup + c;
-            if (gb.rows) {
-                key[j] = i < gs.m ? present_key(__float_as_uint(gb.rows[(int64_t)p * gb.stride + i])) : kAbsent;
-            } else {
-                key[j] = s_cell[c] == kAbsent ? kAbsent : s_cell[c] & kAbs;
-            }
+            const uint32_t v = s_cell[j * kGrpWalkBlock + t];
+            key[j] = v == kAbsent ? kAbsent : v & kAbs;
         }
 #pragma unroll
-        for (int j = 0; j < kPer; ++j) {
-            const uint64_t act = __ballot(key[j] != kAbsent);
-            if (!act) continue;
-            const uint32_t b = key[j] >> 20, first = (uint32_t)__builtin_ctzll(act);
-            if (__ballot(key[j] != kAbsent && b == lane_value(b, first)) == act) {
-                if (lane_id() == first) atomicAdd(&h[b], (uint32_t)__popcll(act));
-            } else if (key[j] != kAbsent) {
-                atomicAdd(&h[b], 1u);
-            }
-        }
-        if (!gb.rows) {
-            __syncthreads();                                 // the cells have been read
-            if (t == 0) s_cell[0] = 0u;
-            __syncthreads();
-            const uint32_t region = o.first[0] + o.first[1];
-            uint32_t* keys = const_cast<uint32_t*>(gb.keys) + (size_t)p * gb.key_stride;
+        for (int j = 0; j < kPer; ++j) count(key[j]);
+        __syncthreads();                                     // the cells have been read
+        if (t == 0) s_cell[0] = 0u;
+        __syncthreads();
+        const uint32_t region = o.first[0] + o.first[1];
+        uint32_t* keys = const_cast<uint32_t*>(gb.keys) + (size_t)p * gb.key_stride;
 #pragma unroll
-            for (int j = 0; j < kPer; ++j)
-                if (key[j] != kAbsent) {
-                    const uint32_t at = region + atomicAdd(&s_cell[0], 1u);
-                    if (at < gb.key_stride) keys[at] = key[j];
-                }
-            __syncthreads();
-            if (t == 0) gs.run[(size_t)id * gs.ngroups + g] = make_uint4(region, s_cell[0], 0u, kPlainRun);
-            __syncthreads();
-        }
+        for (int j = 0; j < kPer; ++j)
+            if (key[j] != kAbsent) {
+                const uint32_t at = region + atomicAdd(&s_cell[0], 1u);
+                if (at < gb.key_stride) keys[at] = key[j];
+            }
+        __syncthreads();
+        if (t == 0) gs.run[(size_t)id * gs.ngroups + g] = make_uint4(region, s_cell[0], 0u, kPlainRun);
+        __syncthreads();
     }
     __syncthreads();
-    for (int b = t; b < 2048; b += kGrpWalkBlock)
-        if (h[b]) atomicAdd(&gs.hist_all[(size_t)id * 2048 + b], h[b]);
+    for (uint32_t b = t; b < kTopBins; b += kGrpWalkBlock)
+        if (h[b]) atomicAdd(&gs.hist_all[(size_t)id * kAllBins + b], h[b]);
 }
 
 // Block 0 of row p: the next round's pair p; blocks from 1 on: sixteen waves with kGrpWalkRuns groups each of set p.
@@ -768,67 +783,180 @@ __global__ __launch_bounds__(kGrpWalkBlock) void k_group_walk(GroupSets gs, Grou
 // exact key, ties to take, output positions of the groups
 // ---------------------------------------------------------------------------------
 
-// One block per set of the batch.
 constexpr int kGrpFinishBlock = 1024;
-__global__ __launch_bounds__(kGrpFinishBlock) void k_group_finish(GroupSets gs, GroupBatch gb) {
+
+// All keys of group g of a set that missed its bracket: where they lie and how many there are.
+__device__ __forceinline__ uint32_t group_keys(const GroupSets& gs, const GroupBatch& gb, uint32_t p, uint32_t g, const uint32_t*& from) {
+    if (gb.rows) {
+        from = reinterpret_cast<const uint32_t*>(gb.rows) + (int64_t)p * gb.stride + (size_t)g * kGroup;
+        return gs.m - g * kGroup < kGroup ? gs.m - g * kGroup : kGroup;
+    }
+    const uint4 run = gs.run[(size_t)(gb.first + p) * gs.ngroups + g];
+    from = gb.keys + (size_t)p * gb.key_stride + run.x;
+    return run.y;
+}
+
+// A set that missed its bracket gets another one, which holds the k-th key for certain: the top digit `top` that all its
+// keys' histogram gives.  Its blocks share its groups, a wave per group: keys above are counted, those inside listed as
+// k_group_walk would (1024 elements whose keys agree are one entry) and their next ten bits histogrammed.
+// A wave goes over its group twice, so that the block reserves room for sixteen groups at once.  h: 1024 words of LDS,
+// s_cnt: two rows of a word per wave and one more.
+__device__ inline void collect_missed(const GroupSets& gs, const GroupBatch& gb, uint32_t p, uint32_t top, uint32_t* h, uint32_t* s_cnt) {
+    constexpr int kU = 16;
+    constexpr uint32_t kWaves = kGrpFinishBlock / kWave, kTurns = kGroup / (kWave * kU);
+    const uint32_t id = gb.first + p, t = threadIdx.x, lane = lane_id(), wave = t / kWave;
+    uint2* list = gb.list + (size_t)p * gb.list_cap;
+    h[t] = 0u;
+    uint32_t* cnt = s_cnt;
+    for (uint32_t g0 = blockIdx.y * kWaves; g0 < gs.ngroups; g0 += gridDim.y * kWaves) {         // block-uniform
+        const uint32_t g = g0 + wave;
+        const uint32_t* from = nullptr;
+        const uint32_t count = g < gs.ngroups ? group_keys(gs, gb, p, g, from) : 0u;
+        uint32_t key[kU];
+        auto load = [&](uint32_t turn) {
+#pragma unroll
+            for (int j = 0; j < kU; ++j) {
+                const uint32_t i = turn * (kWave * kU) + j * kWave + lane;
+                key[j] = i < count ? present_key(from[i]) : kAbsent;
+            }
+        };
+        // (all wave-uniform) keys above, entries; turns with any, turns whose keys agree
+        uint32_t gt = 0, entries = 0, some = 0, agree = 0;
+        for (uint32_t turn = 0; turn < kTurns && turn * (kWave * kU) < count; ++turn) {
+            load(turn);
+            uint32_t in = 0, mx = 0, mn = kAbs;
+#pragma unroll
+            for (int j = 0; j < kU; ++j) {
+                const uint32_t d = key[j] >> 20;
+                gt += (uint32_t)__popcll(__ballot(key[j] != kAbsent && d > top));
+                in += (uint32_t)__popcll(__ballot(d == top));
+                if (d == top) {
+                    mx = key[j] > mx ? key[j] : mx;
+                    mn = key[j] < mn ? key[j] : mn;
+                }
+            }
+            if (in == 0u) continue;
+            some |= 1u << turn;
+            const bool one = wave_largest(mx) == kAbs - wave_largest(kAbs - mn);
+            agree |= one ? 1u << turn : 0u;
+            entries += one ? 1u : in;
+        }
+        if (lane == 0) {
+            cnt[wave] = entries;
+            if (g < gs.ngroups) gs.grp_gt[(size_t)id * gs.ngroups + g] = gt;
+        }
+        __syncthreads();
+        const uint32_t all = row_incl_scan(lane < kWaves ? cnt[lane] : 0u);
+        if (t == 0) s_cnt[2 * kWaves] = atomicAdd(&gs.list_cnt[id], lane_value(all, kWaves - 1u));
+        __syncthreads();
+        uint32_t pos = s_cnt[2 * kWaves] + lane_value(all, wave) - entries;
+        for (uint32_t turn = 0; turn < kTurns; ++turn) {
+            if (((some >> turn) & 1u) == 0u) continue;
+            load(turn);
+            if ((agree >> turn) & 1u) {
+                uint32_t in = 0, mx = 0;
+#pragma unroll
+                for (int j = 0; j < kU; ++j) {
+                    const bool c = key[j] >> 20 == top;
+                    in += (uint32_t)__popcll(__ballot(c));
+                    mx = c ? key[j] : mx;
+                }
+                mx = wave_largest(mx);
+                if (lane == 0) {
+                    if (pos < gb.list_cap) list[pos] = make_uint2(mx, g | in << kGrpWeightShift);
+                    atomicAdd(&h[(mx >> 10) & 1023u], in);
+                }
+                ++pos;
+                continue;
+            }
+#pragma unroll
+            for (int j = 0; j < kU; ++j) {
+                const bool c = key[j] >> 20 == top;
+                const uint64_t b = __ballot(c);
+                if (c) {
+                    const uint32_t at = pos + rank_in(b);
+                    if (at < gb.list_cap) list[at] = make_uint2(key[j], g | 1u << kGrpWeightShift);
+                    atomicAdd(&h[(key[j] >> 10) & 1023u], 1u);
+                }
+                pos += (uint32_t)__popcll(b);
+            }
+        }
+        cnt = cnt == s_cnt ? s_cnt + kWaves : s_cnt;         // (the other row may still be read)
+    }
+    __syncthreads();
+    const uint32_t n = h[t];
+    if (n) atomicAdd(&gs.hist_all[(size_t)id * kAllBins + kTopBins + t], n);
+}
+
+struct FinishShared {
+    uint32_t h[2048];
+    uint32_t g_gt[kMaxIndexGroups], g_eq[kMaxIndexGroups];
+    uint32_t wave[kGrpFinishBlock / kWave];
+    uint32_t out[3];
+    uint32_t turn, cnt[2 * (kGrpFinishBlock / kWave) + 1];
+};
+// The exact key, the ties and the groups' output positions of set p from its list of n entries: the keys in
+// [base, base + width), among which the k-th has rank krem.  MISSED: a long list, see collect_missed.
+template <bool MISSED>
+__device__ __forceinline__ void finish_set(FinishShared& sh, const GroupSets& gs, const GroupBatch& gb, uint32_t p, uint32_t base,
+                                           uint32_t width, uint32_t krem, uint32_t n) {
     constexpr int kT = kGrpFinishBlock;
     constexpr int kPer = (int)(kMaxIndexGroups / kT);
-    __shared__ uint32_t h[2048];
-    __shared__ uint32_t g_gt[kMaxIndexGroups], g_eq[kMaxIndexGroups];
-    __shared__ uint32_t s_wave[kT / kWave];
-    __shared__ uint32_t s_out[3];
-    const uint32_t p = blockIdx.x, id = gb.first + p, t = threadIdx.x;
-    const uint32_t d1 = gs.d1[id];
-    uint32_t krem = gs.krem[id];
-    const uint32_t n = gs.list_cnt[id];
-    const bool missed = d1 == kMissed;                       // block-uniform
+    uint32_t* h = sh.h;
+    uint32_t* g_gt = sh.g_gt;
+    uint32_t* g_eq = sh.g_eq;
+    uint32_t* s_wave = sh.wave;
+    uint32_t* s_out = sh.out;
+    const uint32_t id = gb.first + p, t = threadIdx.x;
     const uint2* list = gb.list + (size_t)p * gb.list_cap;
+    const uint32_t* all = gs.hist_all + (size_t)id * kAllBins;
+    // (masses of few keys: the list of a row may not hold them, then all of its keys are read)
+    const bool whole = MISSED && n > gb.list_cap;            // block-uniform
+    // (every load from an address that is there, so that none waits for the one before: eight in turn took 3 us)
+    const uint32_t* grp_gt = gs.grp_gt + (size_t)id * gs.ngroups;
+    uint32_t above[kPer];
 #pragma unroll
-    for (int j = 0; j < kPer; ++j) {
-        const uint32_t g = t * kPer + j;
-        g_gt[g] = g < gs.ngroups && !missed ? gs.grp_gt[(size_t)id * gs.ngroups + g] : 0u;
-        g_eq[g] = 0u;
-    }
-    // f(key, group, count) for every entry that may be the k-th: the list, or of a set that missed its bracket all
+    for (int j = 0; j < kPer; ++j) above[j] = grp_gt[t + j * kT < gs.ngroups ? t + j * kT : 0u];
+    // f(key, group, count) for every entry that may be the k-th: the list, or of a set that it does not hold all
     // there are.  The lanes of a wave call f in step; key == kAbsent: nothing.
-    constexpr int kCache = 4;
+    constexpr int kCache = 4, kAhead = MISSED ? 16 : kCache;
     uint2 e[kCache];
-    const bool cached = !missed && n <= (uint32_t)(kCache * kT);
+    const bool cached = n <= (uint32_t)(kCache * kT);
 #pragma unroll
     for (int j = 0; j < kCache; ++j) {
         const uint32_t i = j * kT + t;
-        e[j] = cached && i < n ? list[i] : make_uint2(kAbsent, 0u);
+        e[j] = list[i < n ? i : 0u];
+        if (!cached || i >= n) e[j] = make_uint2(kAbsent, 0u);
+    }
+#pragma unroll
+    for (int j = 0; j < kPer; ++j) {
+        const uint32_t g = t + j * kT;
+        g_gt[g] = g < gs.ngroups && !whole ? above[j] : 0u;
+        g_eq[g] = 0u;
     }
     auto entry = [&](const uint2& x, auto&& f) { f(x.x, x.y & (kMaxIndexGroups - 1u), x.y >> kGrpWeightShift); };
     auto each = [&](auto&& f) {
         if (cached) {
 #pragma unroll
             for (int j = 0; j < kCache; ++j) entry(e[j], f);
-        } else if (!missed) {
-            for (uint32_t i0 = 0; i0 < n; i0 += kT * kCache) {
-                uint2 x[kCache];
+        } else if (!whole) {
+            for (uint32_t i0 = 0; i0 < n; i0 += kT * kAhead) {
+                uint2 x[kAhead];
 #pragma unroll
-                for (int j = 0; j < kCache; ++j) {
+                for (int j = 0; j < kAhead; ++j) {
                     const uint32_t i = i0 + j * kT + t;
-                    x[j] = i < n ? list[i] : make_uint2(kAbsent, 0u);
+                    x[j] = list[i < n ? i : 0u];
+                    if (i >= n) x[j] = make_uint2(kAbsent, 0u);
                 }
 #pragma unroll
-                for (int j = 0; j < kCache; ++j) entry(x[j], f);
+                for (int j = 0; j < kAhead; ++j) entry(x[j], f);
             }
         } else {
             // a wave per group; f is called in step within a wave
             constexpr int kU = 16;
             for (uint32_t g = t / kWave; g < gs.ngroups; g += kT / kWave) {
-                const uint32_t* from = gb.keys + (size_t)p * gb.key_stride;
-                uint32_t count;
-                if (gb.rows) {
-                    from = reinterpret_cast<const uint32_t*>(gb.rows) + (int64_t)p * gb.stride + (size_t)g * kGroup;
-                    count = gs.m - g * kGroup < kGroup ? gs.m - g * kGroup : kGroup;
-                } else {
-                    const uint4 run = gs.run[(size_t)id * gs.ngroups + g];
-                    from += run.x;
-                    count = run.y;
-                }
+                const uint32_t* from;
+                const uint32_t count = group_keys(gs, gb, p, g, from);
                 for (uint32_t i0 = 0; i0 < count; i0 += kWave * kU) {
                     uint32_t x[kU];
 #pragma unroll
@@ -843,33 +971,42 @@ __global__ __launch_bounds__(kGrpFinishBlock) void k_group_finish(GroupSets gs, 
         }
     };
     // radix passes over key - base: bits 30..20, 19..10, 9..0; a pass whose bits are zero throughout is skipped
-    uint32_t base = 0, width = 0x80000000u;
-    if (!missed) {
-        const Bracket bk(gs, id);
-        base = bk.bin_lo(d1);
-        width = 1u << bk.shift;
-    } else {
+    if (whole) {
+        base = 0u;
+        width = 0x80000000u;
         krem = gb.k;
     }
+    // (of a set that missed its bracket the list is long, a group's entries behind one another: added once per wave)
+    auto count_above = [&](bool c, uint32_t g, uint32_t count) {
+        const uint64_t act = __ballot(c);
+        if (!act) return;
+        const uint32_t first = (uint32_t)__builtin_ctzll(act), g0 = lane_value(g, first);
+        if (__ballot(c && g == g0 && count == 1u) == act) {
+            if (lane_id() == first) atomicAdd(&g_gt[g0], (uint32_t)__popcll(act));
+        } else if (c) {
+            atomicAdd(&g_gt[g], count);
+        }
+    };
     uint32_t prefix = 0;
     for (int pass = 0; pass < 3; ++pass) {
         const int shift = pass == 0 ? 20 : (pass == 1 ? 10 : 0);
         const int bits = pass == 0 ? 11 : 10;
         if (shift > 0 && width <= (1u << shift)) continue;   // uniform
-        // (of a set that missed its bracket the walk has counted these)
-        const bool counted = missed && pass == 0;
-        h[t] = counted ? gs.hist_all[(size_t)id * 2048 + t] : 0u;
-        h[t + kT] = counted ? gs.hist_all[(size_t)id * 2048 + t + kT] : 0u;
+        // (of a set that missed its bracket the walk has counted these, or the collecting blocks have)
+        const bool counted = whole ? pass == 0 : MISSED && pass == 1;
+        h[t] = counted ? all[pass * kTopBins + t] : 0u;
+        h[t + kT] = counted && pass == 0 ? all[t + kT] : 0u;
         __syncthreads();
-        if (!counted) each([&](uint32_t key, uint32_t, uint32_t count) {
-            const uint32_t rel = key - base;
-            const bool mine = key != kAbsent && key >= base && (rel >> (shift + bits)) == prefix;
+        if (!counted) each([&](uint32_t key, uint32_t g, uint32_t count) {
+            const uint32_t rel = key - base, digits = rel >> (shift + bits);
+            const bool mine = key != kAbsent && key >= base && digits == prefix;
+            if (MISSED && !whole) count_above(key != kAbsent && digits > prefix, g, count);
             const uint32_t b = (rel >> shift) & ((1u << bits) - 1u);
             const uint64_t act = __ballot(mine);
             if (!act) return;
             // (masses of one key: added once)
             const uint32_t first = (uint32_t)__builtin_ctzll(act), b0 = lane_value(b, first);
-            if (missed && __ballot(mine && b == b0) == act) {
+            if (whole && __ballot(mine && b == b0) == act) {
                 if (lane_id() == first) atomicAdd(&h[b0], (uint32_t)__popcll(act));
             } else if (mine) {
                 atomicAdd(&h[b], count);
@@ -884,10 +1021,14 @@ __global__ __launch_bounds__(kGrpFinishBlock) void k_group_finish(GroupSets gs, 
     }
     const uint32_t T = base + prefix, need = krem;
     each([&](uint32_t key, uint32_t g, uint32_t count) {
-        if (missed) {                                        // one group per wave
+        if (whole) {                                         // one group per wave
             const uint64_t a = __ballot(key != kAbsent && key > T), q = __ballot(key == T);
             if (lane_id() == 0 && a) atomicAdd(&g_gt[g], (uint32_t)__popcll(a));
             if (lane_id() == 0 && q) atomicAdd(&g_eq[g], (uint32_t)__popcll(q));
+        } else if (MISSED) {                                 // (those above the k-th key's second digit have been counted)
+            if (key == kAbsent || (key - base) >> 10 != prefix >> 10) return;
+            if (key > T) atomicAdd(&g_gt[g], count);
+            else if (key == T) atomicAdd(&g_eq[g], count);
         } else if (key != kAbsent) {
             if (key > T) atomicAdd(&g_gt[g], count);
             else if (key == T) atomicAdd(&g_eq[g], count);
@@ -918,6 +1059,40 @@ __global__ __launch_bounds__(kGrpFinishBlock) void k_group_finish(GroupSets gs, 
         gs.T[id] = T;
         gs.need[id] = need;
     }
+}
+
+// Block (p, 0): set p of the batch, bound by its chain of loads and barriers (6 to 11 us).  The set's other blocks return at
+// once unless it missed its bracket: then they share its groups, and the last of them to be done with its part goes on as
+// block 0 does.  No block waits for another.
+__global__ __launch_bounds__(kGrpFinishBlock) void k_group_finish(GroupSets gs, GroupBatch gb) {
+    __shared__ FinishShared sh;
+    const uint32_t p = blockIdx.x, id = gb.first + p, t = threadIdx.x;
+    const uint32_t d1 = gs.d1[id];
+    uint32_t krem = gs.krem[id], n = gs.list_cnt[id];
+    const Bracket bk(gs, id);
+    if (d1 != kMissed) {                                     // block-uniform
+        if (blockIdx.y == 0) finish_set<false>(sh, gs, gb, p, bk.bin_lo(d1), 1u << bk.shift, krem, n);
+        return;
+    }
+    const uint32_t* all = gs.hist_all + (size_t)id * kAllBins;
+    const uint32_t loc[2] = {all[2 * t], all[2 * t + 1]};
+    suffix_pick<2>(loc, gb.k, sh.wave, sh.out);
+    const uint32_t top = sh.out[0];
+    krem = gb.k - sh.out[1];
+    collect_missed(gs, gb, p, top, sh.h, sh.cnt);
+    // (every wave's stores have reached the L2 before the block meets; then one fence writes them back for the last block,
+    // which may sit on another XCD)
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    __syncthreads();
+    if (t == 0) {
+        __threadfence();
+        sh.turn = atomicAdd(&gs.arrived[id], 1u);
+    }
+    __syncthreads();
+    if (sh.turn != gridDim.y - 1u) return;                   // block-uniform
+    __threadfence();
+    n = __hip_atomic_load(&gs.list_cnt[id], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    finish_set<true>(sh, gs, gb, p, top << 20, 1u << 20, krem, n);
 }
 
 // ---------------------------------------------------------------------------------

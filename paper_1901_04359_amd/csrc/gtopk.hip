@@ -398,8 +398,9 @@ GroupWs carve_grouped(const StepWs& s, int64_t m, uint32_t k, uint32_t P) {
     gs.m = (uint32_t)m;
     gs.ngroups = (uint32_t)ng;
     gs.hist = c.take<uint32_t>(sets * kBrkBins);
-    gs.hist_all = c.take<uint32_t>(sets * 2048);
+    gs.hist_all = c.take<uint32_t>(sets * kAllBins);
     gs.list_cnt = c.take<uint32_t>(sets);
+    gs.arrived = c.take<uint32_t>(sets);
     gs.brk_cnt = c.take<uint32_t>(P);
     const size_t clear_end = c.off;
     w.clear_words = clear_end / sizeof(uint32_t);
@@ -977,7 +978,11 @@ int do_grouped_step(const float* grad, float* residual, int64_t m, int64_t strid
         const GroupSample sm{gb.first + sets, sets / 2, gw.samples, samples,
                              (uint32_t)(1.02 * mean + 5.5 * __builtin_sqrt(mean) + 2.0), bracket_target_hi(mean, 0.98)};
         hipLaunchKernelGGL(k_group_walk, dim3(walk_blocks, sets), dim3(kGrpWalkBlock), 0, st, gs, gb, sm);
-        hipLaunchKernelGGL(k_group_finish, dim3(sets), dim3(kGrpFinishBlock), 0, st, gs, gb);
+        // blocks for the sets that miss their brackets: a wave per group, one block per CU (the others' return)
+        uint32_t shares = sets >= 32 ? 8u : (sets <= 4 ? 64u : 256u / sets);
+        const uint32_t most = ceil_div(ng, kGrpFinishBlock / kWave);
+        if (shares > most) shares = most;
+        hipLaunchKernelGGL(k_group_finish, dim3(sets, shares), dim3(kGrpFinishBlock), 0, st, gs, gb);
     };
     GroupBatch gb{0u, k, reinterpret_cast<const uint32_t*>(w.cand_val), w.cap, w.sel.list, w.cap, w.cap, residual, stride,
                   nullptr, nullptr, 0u};

@@ -69,6 +69,10 @@ def rows(kind, P, m, k, rng):
         g[:, at] = np.abs(g[:, at])
         g[1::2] = -g[0::2]
         g[1::2, at] *= -1
+    elif kind == "sample_two_values":       # .. and the other keys around the k-th are too many for a list
+        two = np.where(rng.random((P, m)) < 0.5, np.float32(1.0), np.float32(1.0625))
+        g = np.where(rng.random((P, m)) < 0.95, two, g)
+        g[:, at] *= 1e-4
     else:
         raise ValueError(kind)
     return g.astype(np.float32)
@@ -86,7 +90,8 @@ CASES = [
     (2, 512 * GROUP + 1, 524_289, "layers", 0),         # one round; the smallest density
     (4, 520 * GROUP - 3, 532_480, "flat", 1),
 ] + [(16, 1_050_003, 262_000, kind, pad) for pad, kind in enumerate(KINDS)] + [
-    (2, 4_200_001, 530_000, kind, 0) for kind in ("zeros", "sample_large", "sample_small", "sample_cancels")]
+    (2, 4_200_001, 530_000, kind, 0) for kind in ("zeros", "sample_large", "sample_small", "sample_cancels")] + [
+    (16, 1_050_003, 262_000, "sample_two_values", 1)]
 
 
 @pytest.mark.parametrize("P,m,k,kind,pad", CASES)
