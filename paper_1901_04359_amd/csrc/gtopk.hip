@@ -601,16 +601,24 @@ uint32_t bracket_target_hi(double mean, double placed) {
 
 // Entries per thread with which one block selects from a worker's candidate list (k_small_select), 0: the general
 // kernels do, three of them.  A list is expected to hold 2.5 k entries (mid_sample_mean), a longer one than the threads hold
-// takes the block some walks.  A row that cannot be filtered is read by the one block; the line in m keeps that within
-// what the general kernels take.  gtopk_step in us, three kernels and three per round of the tree / one and one:
+// takes the block some walks.  gtopk_step in us, three kernels and three per round of the tree / one and one:
 //   m = 30,000  P = 8  k = 1000   86.5 / 45.1     m = 400,000  P = 4   k = 1000  74.2 / 43.8    k = 4000  73.0 / 60.1
 //   m = 100,000 P = 8  k = 4000   92.7 / 73.4     m = 400,000  P = 16  k = 900  123.7 / 62.2
 //   m = 100,000 P = 32 k = 2000  136.3 / 81.6     m = 524,288  P = 32  k = 4000  169 / 119
-// rows of zeros, P = 8, k = 2000:  m = 200,000  189 / 111   m = 524,288  283 / 158 (P = 32, k = 4000: 518 / 233); rows of
-// ones, whose equal values the steps spread over many ranges: m = 200,000  147 / 93   m = 524,288  256 / 356 (the one
-// slower kind found, P = 32, k = 4000: 443 / 422).
-uint32_t select_in_block(int64_t m, uint32_t k) {
-    if (m > (1 << 19)) return 0;
+// A row that cannot be filtered (its sample misled, or masses of equal values) is read by the one block, and the line in m
+// keeps that within what the general kernels take.  Rows of zeros | of ones, whose residuals after 100 to 200 steps hold
+// many equal values | whose sample misled, in us as above:
+//   m = 200,000  P = 8   k = 2000   194 / 108 | 172 / 134 | 169 .. 175 / 111 .. 121
+//   m = 524,288  P = 8   k = 2000   291 / 146 | 261 / 191 | 242 .. 260 / 169 .. 190
+//   m = 524,288  P = 32  k = 4000   534 / 232 | 440 / 285 | 443 .. 489 / 238 .. 266
+//   m = 262,144  P = 2   k = 1000   138 /  78 | 129 / 103 | 123 / 93 .. 100
+//   m = 262,144  P = 1   k = 1000   111 /  71 | 106 /  95 |  97 .. 99 / 86 .. 93
+// Few workers leave the chip to the general kernels, which are faster with such rows then (m = 524,288, P = 4, k = 1000
+// 147 / 122 | 130 / 167 | 114 .. 214 / 151 .. 164, P = 1 70 / 102 | 64 / 148 | 54 .. 157 / 133 .. 142; ordinary rows lose some:
+// m = 300,000, P = 4, k = 1000 52.6 / 46.7, P = 1 36.6 / 31.8, m = 500,000, P = 4, k = 4000 62.0 / 63.4), and at densities at which
+// their pass histograms (see below) from 170,000 elements on (m = 200,000, P = 2, k = 520 81 / 74 | 79 / 92 | 63 .. 104 / 77 .. 81, ordinary rows 41 / 34).
+uint32_t select_in_block(int64_t m, uint32_t k, uint32_t P) {
+    if (m > (P < 8 ? 1 << 18 : 1 << 19) || (P < 4 && 360ull * k < (uint64_t)m)) return 0;
     const uint32_t n = 4 * k + 256;
     return n <= 4096 ? 4 : (n <= 8192 ? 8 : (n <= 16384 ? 16 : 0));
 }
@@ -725,11 +733,9 @@ int do_local_select(const float* grad, float* residual, int64_t m, int64_t strid
                     uint32_t k, uint32_t* out_idx, float* out_val, const StepWs& w, bool zero_rows,
                     const ZeroJob& job, hipStream_t st, void* const* events = nullptr,
                     uint32_t* thr_state = nullptr) {
-    const uint32_t entries = select_in_block(m, k);
+    const uint32_t entries = select_in_block(m, k, P);
     const bool producer_hist = filter_rows<true>(grad, residual, m, stride, P, k, w, job, st, events, thr_state, entries == 0);
     const CandSrc src = cand_source(residual, stride, m, k, w, producer_hist, false, thr_state);
-    // the histogram kernel always runs: where the pass has counted its candidates it serves
-    // only the workers that came back with fewer than k of them
     if (entries != 0) {
 #define GTOPK_SELECT(E) hipLaunchKernelGGL(k_small_select<E>, dim3(P), dim3(kSmallBlock), 0, st, src, k, out_idx, out_val, w.sel.T)
         if (entries == 4) GTOPK_SELECT(4);
@@ -737,6 +743,8 @@ int do_local_select(const float* grad, float* residual, int64_t m, int64_t strid
         else GTOPK_SELECT(16);
 #undef GTOPK_SELECT
     } else if (run_groups(m, k)) {
+        // (the histogram kernel always runs, here and below: where the pass has counted its candidates it serves
+        // only the workers that came back with fewer than k of them)
         RunSrc rs;
         static_cast<CandSrc&>(rs) = src;
         // k_bucket: every wave of a block takes a run; k_emit: a block per run; a worker on its
@@ -1061,7 +1069,7 @@ int gtopk_local_select(const float* grad, float* residual, int64_t m, int64_t st
     if (ws_bytes < w.bytes) return GTOPK_EWORKSPACE;
     return do_local_select(grad, residual, m, stride, (uint32_t)P, (uint32_t)k, out_idx, out_val, w, true,
                            zero_job(w.samp_hist, w.samp_words, w.cand_count, (size_t)P, w.sel.hist,
-                                    select_in_block(m, (uint32_t)k) ? 0 : select_clear_words(w.sel)),
+                                    select_in_block(m, (uint32_t)k, (uint32_t)P) ? 0 : select_clear_words(w.sel)),
                            (hipStream_t)stream);
 }
 
@@ -1157,7 +1165,7 @@ static int step_impl(const float* grad, float* residual, int64_t m, int64_t stri
     // candidate counters; both selects' histograms and tickets; the global-set bitmap
     const bool in_block = merge_in_block((uint32_t)k);       // its rounds need no select state
     const ZeroJob job = zero_job(w.samp_hist, w.samp_words, w.cand_count, (size_t)P, w.sel.hist,
-                                 select_in_block(m, (uint32_t)k) ? 0 : select_clear_words(w.sel), w.mrg.sel.hist, in_block ? 0 : select_clear_words(w.mrg.sel),
+                                 select_in_block(m, (uint32_t)k, (uint32_t)P) ? 0 : select_clear_words(w.sel), w.mrg.sel.hist, in_block ? 0 : select_clear_words(w.mrg.sel),
                                  w.mrg.sel_alt.hist, in_block ? 0 : w.mrg.alt_clear_words, w.gbits, w.gbits_words);
     int rc = do_local_select(grad, residual, m, stride, (uint32_t)P, (uint32_t)k, li, lv, w, false,
                              job, st, events, thr_state);

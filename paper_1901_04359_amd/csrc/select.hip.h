@@ -115,7 +115,7 @@ struct CandSrc {
     // next call may skip sampling once a prediction has come true to within half the
     // margin, and goes back to sampling when the list came close to either of its limits.
     // A wrong threshold costs time only: the select is exact whatever it filters with.
-    __device__ void carry(int s, uint32_t T) const {
+    __device__ __forceinline__ void carry(int s, uint32_t T) const {
         if (!carry_state) return;
         uint4 c = carry_state[s];
         const uint32_t n = cand_count[s], ts = tspec[s];
@@ -193,11 +193,11 @@ struct CandSrc {
     // Lower bound of the k-th key: the speculative threshold while at least k entries
     // reached it; for a worker with fewer the k-th key lies below it, and nothing bounds
     // it from below: plain coarse bins.
-    __device__ Digit digit(int s, bool dn, const SelState&) const {
+    __device__ __forceinline__ Digit digit(int s, bool dn, const SelState&) const {
         if (dn && !overfull(s)) return Digit{0u, (uint32_t)kCoarseShift};
         return Digit{tspec[s], (uint32_t)kFineShift};
     }
-    __device__ bool fetch_phys(int s, bool dn, uint32_t p, uint32_t& idx, uint32_t& bits) const {
+    __device__ __forceinline__ bool fetch_phys(int s, bool dn, uint32_t p, uint32_t& idx, uint32_t& bits) const {
         if (dn) {
             idx = p;
             bits = __float_as_uint(res[(int64_t)s * stride + p]);
@@ -207,7 +207,7 @@ struct CandSrc {
         }
         return true;
     }
-    __device__ bool fetch_key_phys(int s, bool dn, uint32_t p, uint32_t& key) const {
+    __device__ __forceinline__ bool fetch_key_phys(int s, bool dn, uint32_t p, uint32_t& key) const {
         key = __float_as_uint(dn ? res[(int64_t)s * stride + p] : cand_val[(size_t)s * cap + p]) & kAbs;
         return true;
     }

@@ -256,44 +256,286 @@ __global__ __launch_bounds__(kSmallBlock) void k_small_sample(
 // local selection of one worker in one block
 // ---------------------------------------------------------------------------------
 
-// Whether all keys of a wave are `one`.  Rows of zeros or of equal values are what a threshold cannot filter, and a block
-// that walks one of 524,288 entries is bound by the instructions per key: step 380 / 158 us with zeros, 594 / 356 with ones
-// (P = 8), each key binned / sixteen per thread compared first.
-template <int N>
-__device__ inline bool same_keys(const uint32_t (&key)[N], uint32_t& one) {
-    one = lane_value(key[0], 0u);
-    uint32_t diff = 0;
+// The k largest of a whole row, for a worker whose candidate list cannot be used, by one block.  Every wave owns a part of
+// the row, so that it counts and emits without a barrier; the row is read three times:
+//   1. the first digit of all keys (bits 30 .. 19) is counted, the bin of the k-th key picked;
+//   2. the keys in that bin go to a list in LDS, where a team selects; per wave the keys above it are counted.  A bin that
+//      the list does not hold (masses of few magnitudes) is cut again before, unless its keys are all the same;
+//   3. every wave emits its part.
+// Bound by the latency of the one block's loads and by the instructions per key; a step with such rows, m = 524,288, P = 8,
+// k = 2000, in us, by four to six walks of all waves in step / this: misled samples 706 / 180, zeros 166 / 146, ones 370 .. 472 / 193.
+struct DenseShared {
+    uint32_t h[kHistBins];                                     // the digits' counts, then the list
+    uint32_t wave[kSmallBlock / kWave], out[3];
+    uint32_t gt[kSmallBlock / kWave], eq[kSmallBlock / kWave]; // per wave: keys above the k-th, equal to it
+    uint32_t n, ext[2];
+};
+__device__ __forceinline__ uint32_t select_row(DenseShared& sh, TeamShared<1>& team, const float* __restrict__ row, uint32_t m, uint32_t k,
+                                      uint32_t* __restrict__ out_idx, float* __restrict__ out_val) {
+    constexpr int kT = kSmallBlock, kWaves = kT / kWave, kU = 32;
+    constexpr uint32_t kTurn = kWave * kU;
+    const uint32_t t = threadIdx.x, lane = lane_id(), wave = (uint32_t)__builtin_amdgcn_readfirstlane((int)(t / kWave));
+    const uint32_t turns = (m + kTurn - 1) / kTurn, per = (turns + kWaves - 1) / kWaves;
+    const uint32_t first = wave * per, end = first + per < turns ? first + per : turns;
+    // v[j]: element turn * kTurn + j * 64 + lane; behind the row kAbs, the largest key there is, which the counts leave out
+    const uint32_t behind = first < end && end == turns ? turns * kTurn - m : 0u;
+    uint32_t v[kU];
+    auto load = [&](uint32_t turn) {
+        const uint32_t at = turn * kTurn;
+        if (at + kTurn <= m) {
 #pragma unroll
-    for (int j = 0; j < N; ++j) diff |= key[j] ^ one;
-    return __ballot(diff != 0u) == 0;
+            for (int j = 0; j < kU; ++j) v[j] = __float_as_uint(row[at + j * kWave + lane]);
+        } else {
+#pragma unroll
+            for (int j = 0; j < kU; ++j) {
+                const uint32_t i = at + j * kWave + lane;
+                const uint32_t x = __float_as_uint(row[i < m ? i : m - 1u]);
+                v[j] = i < m ? x : kAbs;
+            }
+        }
+    };
+    // adds 1 to h[b] for every lane with c (cm: their mask); masses of one key add once
+    auto add = [&](bool c, uint64_t cm, uint32_t b) {
+        const uint32_t b0 = lane_value(b, (uint32_t)__builtin_ctzll(cm));
+        if (__ballot(c && b == b0) == cm) {
+            if (lane == 0) atomicAdd(&sh.h[b0], (uint32_t)__popcll(cm));
+        } else if (c) {
+            atomicAdd(&sh.h[b], 1u);
+        }
+    };
+    // whether the turn's keys are one: most of a row of zeros or of equal values
+    auto one_key = [&]() {
+        const uint32_t one = (uint32_t)__builtin_amdgcn_readfirstlane((int)(v[0] & kAbs));
+        if (__ballot((v[0] & kAbs) != one || (v[kU - 1] & kAbs) != one) != 0ull) return false;
+        uint32_t diff = 0;
+#pragma unroll
+        for (int j = 0; j < kU; ++j) diff |= v[j] ^ one;
+        return __ballot((diff & kAbs) != 0u) == 0ull;
+    };
+
+    // ---- 1. first digit ----------------------------------------------------------------
+    for (uint32_t b = t; b < (uint32_t)kHistBins; b += kT) sh.h[b] = 0u;
+    __syncthreads();
+    uint32_t run_bin = 0, run = 0;                             // wave-uniform: keys in steps that fell into one bin, not yet added
+    auto flush = [&]() {
+        if (lane == 0 && run) atomicAdd(&sh.h[run_bin], run);
+    };
+    for (uint32_t turn = first; turn < end; ++turn) {
+        load(turn);
+        if (one_key()) {
+            flush();
+            run_bin = (uint32_t)__builtin_amdgcn_readfirstlane((int)((v[0] & kAbs) >> kCoarseShift));
+            run = kTurn;
+            continue;
+        }
+#pragma unroll
+        for (int j = 0; j < kU; ++j) {
+            const uint32_t b = (v[j] & kAbs) >> kCoarseShift, b0 = (uint32_t)__builtin_amdgcn_readfirstlane((int)b);
+            if (__ballot(b != b0) != 0ull) {
+                atomicAdd(&sh.h[b], 1u);
+            } else {
+                if (b0 != run_bin) {
+                    flush();
+                    run_bin = b0;
+                    run = 0;
+                }
+                run += kWave;
+            }
+        }
+    }
+    flush();
+    __syncthreads();
+    uint32_t lo, bits = kCoarseShift, count, krem;             // the k-th key lies in [lo, lo + 2^bits), `count` keys do, its rank there
+    {
+        constexpr int kPer = kHistBins / kT;
+        uint32_t loc[kPer];
+#pragma unroll
+        for (int j = 0; j < kPer; ++j) loc[j] = sh.h[t * kPer + j];
+        if (t == kT - 1) loc[kPer - 1] -= turns * kTurn - m;   // (those behind the row)
+        suffix_pick<kPer>(loc, k, sh.wave, sh.out);
+        lo = sh.out[0] << kCoarseShift;
+        krem = k - sh.out[1];
+        count = sh.out[2];
+    }
+    // ---- 2. the exact key --------------------------------------------------------------
+    bool known = false;                                        // the per-wave counts are
+    uint32_t T = 0, need = 0;
+    while (count > (uint32_t)kHistBins && bits > 0u && !known) {         // block-uniform
+        const uint32_t shift = bits > 11u ? bits - 11u : 0u, width = 1u << bits;
+        __syncthreads();
+        sh.h[t] = sh.h[t + kT] = 0u;
+        if (t < 2) sh.ext[t] = 0u;
+        __syncthreads();
+        uint32_t gt = 0, in = 0, mx = 0, mn = kAbs;            // the first two wave-uniform
+        for (uint32_t turn = first; turn < end; ++turn) {
+            load(turn);
+            if (one_key()) {
+                const uint32_t key = (uint32_t)__builtin_amdgcn_readfirstlane((int)(v[0] & kAbs)), rel = key - lo;
+                if (key < lo) continue;
+                if (rel >= width) {
+                    gt += kTurn;
+                } else {
+                    in += kTurn;
+                    mx = key > mx ? key : mx;
+                    mn = key < mn ? key : mn;
+                    if (lane == 0) atomicAdd(&sh.h[rel >> shift], kTurn);
+                }
+                continue;
+            }
+#pragma unroll
+            for (int j = 0; j < kU; ++j) {
+                const uint32_t key = v[j] & kAbs, rel = key - lo;
+                const uint64_t reach = __ballot(key >= lo);
+                if (!reach) continue;
+                const bool c = rel < width;
+                const uint64_t cm = __ballot(c);
+                gt += (uint32_t)__popcll(reach) - (uint32_t)__popcll(cm);
+                if (!cm) continue;
+                in += (uint32_t)__popcll(cm);
+                if (c) {
+                    mx = key > mx ? key : mx;
+                    mn = key < mn ? key : mn;
+                }
+                add(c, cm, rel >> shift);
+            }
+        }
+        mx = wave_largest(mx);
+        mn = wave_largest(kAbs - mn);
+        if (lane == 0) {
+            atomicMax(&sh.ext[0], mx);
+            atomicMax(&sh.ext[1], mn);
+            sh.gt[wave] = gt - behind;
+            sh.eq[wave] = in;
+        }
+        __syncthreads();
+        if (sh.ext[0] == kAbs - sh.ext[1]) {
+            T = sh.ext[0];
+            need = krem;
+            known = true;
+        } else {
+            const uint32_t loc[2] = {sh.h[2 * t], sh.h[2 * t + 1]};
+            suffix_pick<2>(loc, krem, sh.wave, sh.out);
+            lo += sh.out[0] << shift;
+            krem -= sh.out[1];
+            count = sh.out[2];
+            bits = shift;
+        }
+    }
+    if (!known) {
+        const uint32_t width = 1u << bits;
+        __syncthreads();                                       // the picks have read h
+        if (t == 0) sh.n = 0u;
+        clear_teams(team);
+        __syncthreads();
+        uint32_t gt = 0, in = 0;                               // wave-uniform
+        for (uint32_t turn = first; turn < end; ++turn) {
+            load(turn);
+#pragma unroll
+            for (int j = 0; j < kU; ++j) {
+                const uint32_t key = v[j] & kAbs, rel = key - lo;
+                const uint64_t reach = __ballot(key >= lo);
+                if (!reach) continue;
+                const bool c = rel < width;
+                const uint64_t cm = __ballot(c);
+                gt += (uint32_t)__popcll(reach) - (uint32_t)__popcll(cm);
+                if (!cm) continue;
+                in += (uint32_t)__popcll(cm);
+                if (bits == 0u) continue;
+                uint32_t at = 0;
+                if (lane == 0) at = atomicAdd(&sh.n, (uint32_t)__popcll(cm));
+                at = lane_value(at, 0u) + rank_in(cm);
+                if (c && at < (uint32_t)kHistBins) sh.h[at] = rel << 4 | wave;
+            }
+        }
+        if (lane == 0) {
+            sh.gt[wave] = gt - behind;
+            sh.eq[wave] = bits == 0u ? in : 0u;
+        }
+        __syncthreads();
+        T = lo;
+        need = krem;
+        if (bits > 0u) {
+            static_assert(kWaves <= 16 && kCoarseShift + 4 < 32, "a list entry's fields");
+            constexpr int kPer = kHistBins / kT;
+            const uint32_t n = sh.n < (uint32_t)kHistBins ? sh.n : (uint32_t)kHistBins;
+            uint32_t key[kPer], owner[kPer];
+#pragma unroll
+            for (int j = 0; j < kPer; ++j) {
+                const uint32_t e = sh.h[j * kT + t];
+                key[j] = j * kT + t < n ? lo + (e >> 4) : kNoKey;
+                owner[j] = e & 15u;
+            }
+            const TeamCut cut = team_select<kT>(team, key, lo, krem);
+            T = cut.T;
+            need = cut.need;
+#pragma unroll
+            for (int j = 0; j < kPer; ++j)
+                if (key[j] != kNoKey && key[j] >= T) atomicAdd(key[j] > T ? &sh.gt[owner[j]] : &sh.eq[owner[j]], 1u);
+            __syncthreads();
+        }
+    }
+    // ---- 3. ordered emit ---------------------------------------------------------------
+    const uint32_t gts = row_incl_scan(lane < (uint32_t)kWaves ? sh.gt[lane] : 0u), eqs = row_incl_scan(lane < (uint32_t)kWaves ? sh.eq[lane] : 0u);
+    const uint32_t eq_end = lane_value(eqs, wave), gt_end = lane_value(gts, wave);
+    uint32_t eq = wave ? lane_value(eqs, wave - 1u) : 0u;
+    uint32_t out = (wave ? lane_value(gts, wave - 1u) : 0u) + (eq < need ? eq : need);
+    const uint32_t out_end = gt_end + (eq_end < need ? eq_end : need);
+    for (uint32_t turn = first; turn < end && out < out_end; ++turn) {
+        load(turn);
+#pragma unroll
+        for (int j = 0; j < kU; ++j) {
+            const uint32_t key = v[j] & kAbs;
+            if (__ballot(key >= T) == 0ull) continue;
+            const uint64_t eqm = __ballot(key == T);
+            const bool sel = key > T || (key == T && eq + rank_in(eqm) < need);
+            const uint64_t sm = __ballot(sel);
+            const uint32_t i = turn * kTurn + j * kWave + lane, pos = out + rank_in(sm);
+            if (sel && pos < k && i < m) {                     // (always so, but for keys behind the row)
+                out_idx[pos] = i;
+                out_val[pos] = __uint_as_float(v[j]);
+            }
+            out += (uint32_t)__popcll(sm);
+            eq += (uint32_t)__popcll(eqm);
+        }
+    }
+    return T;
 }
 
-// Worker s = blockIdx.x.  The items are the worker's candidate list (or, if the
+// Worker s = blockIdx.x.  The items are the worker's candidate list, or, if the
 // speculative threshold left fewer than k candidates or more than the list holds, its
-// dense row; slow for a long row, but rows are short here).  A candidate list of at most
-// 1024 E entries is held in registers and selected from by the block as one team.  Anything else takes
-// three stages, each a walk over the items:
+// dense row (select_row).  A candidate list of at most
+// 1024 E entries is held in registers and selected from by the block as one team.  A longer one takes
+// three stages, each a walk over it:
 //   1. LDS histogram of the first digit -> the bin d1 of the k-th key;
 //   2. up to three LDS radix passes over the keys inside bin d1 -> the exact key T and the
 //      number of ties to take;
-//   3. the emit in index order (for a candidate list: run after run in chunk order).
+//   3. the emit in index order, run after run in chunk order.
 // E: entries of a candidate list that a thread holds.  T_out != NULL: the smallest key of each set, for what follows in
 // the general path (where thresholds are carried on as well).
 template <int E>
 __global__ __launch_bounds__(kSmallBlock) void k_small_select(
         CandSrc src, uint32_t k, uint32_t* __restrict__ out_idx, float* __restrict__ out_val, uint32_t* __restrict__ T_out) {
     constexpr int kT = kSmallBlock;
-    __shared__ uint32_t h[kHistBins];
-    __shared__ uint32_t s_wave[kT / kWave];
-    __shared__ uint32_t s_out[3];
+    __shared__ DenseShared sh;
     __shared__ uint32_t s_rx[kSmallMaxChunks];
     __shared__ uint32_t s_roff[kSmallMaxChunks + 1];
     __shared__ TeamShared<1> s_team;
+    uint32_t* h = sh.h;
+    uint32_t* s_wave = sh.wave;
+    uint32_t* s_out = sh.out;
     const int s = blockIdx.x;
     const uint32_t t = threadIdx.x;
-    const bool dn = src.dense(s);
-    const uint32_t n = src.nphys(s, dn);
-    if (!dn && n <= (uint32_t)(E * kT)) {
+    if (src.dense(s)) {                                        // block-uniform
+        const uint32_t T = select_row(sh, s_team, src.res + (int64_t)s * src.stride, src.m, k, out_idx + (size_t)s * k,
+                                      out_val + (size_t)s * k);
+        if (T_out && t == 0) {
+            T_out[s] = T;
+            src.carry(s, T);
+        }
+        return;
+    }
+    const uint32_t n = src.nphys(s, false);
+    if (n <= (uint32_t)(E * kT)) {
         // ---- a short candidate list: every thread takes E consecutive entries in index order (run after run in
         // chunk order); the block selects the k largest, ties to the lower index (Algorithm 4 line 5)
         const uint32_t nruns = src.nchunks;                    // <= kSmallMaxChunks <= kT
@@ -344,10 +586,9 @@ __global__ __launch_bounds__(kSmallBlock) void k_small_select(
         }
         return;
     }
-    constexpr int kAhead = 16;                                 // loads in flight per thread (a row is walked by one block)
+    constexpr int kAhead = 16;                                 // loads in flight per thread
     const uint32_t first = t / kWave * (kWave * kAhead) + lane_id();          // a wave's keys of a turn lie next to each other
-    const Digit dg = src.digit(s, dn, SelState{});
-    const uint32_t fl = src.floor_key(s, dn);
+    const Digit dg = src.digit(s, false, SelState{});
 
     // ---- 1. first digit --------------------------------------------------------------
     for (int b = t; b < kHistBins; b += kT) h[b] = 0u;
@@ -359,18 +600,13 @@ __global__ __launch_bounds__(kSmallBlock) void k_small_select(
 #pragma unroll
         for (int j = 0; j < kAhead; ++j) {
             const uint32_t p = p0 + first + j * kWave;
-            src.fetch_key_phys(s, dn, p < n ? p : n - 1, key[j]);
-        }
-        uint32_t one;
-        if (p0 + kT * kAhead <= n && same_keys(key, one)) {
-            if (lane_id() == 0 && one >= fl) atomicAdd(&h[dg.bin(one)], (uint32_t)(kWave * kAhead));
-            continue;
+            src.fetch_key_phys(s, false, p < n ? p : n - 1, key[j]);
         }
 #pragma unroll
-        for (int j = 0; j < kAhead; ++j) ok[j] = p0 + first + j * kWave < n && key[j] >= fl;
+        for (int j = 0; j < kAhead; ++j) ok[j] = p0 + first + j * kWave < n;
 #pragma unroll
         for (int j = 0; j < kAhead; ++j) {
-            // a wave whose keys all fall into one bin (rows of zeros, equal values) adds once
+            // a wave whose keys all fall into one bin (equal values) adds once
             const uint32_t b = dg.bin(key[j]);
             const uint64_t act = __ballot(ok[j]);
             if (act == 0) continue;
@@ -410,17 +646,10 @@ __global__ __launch_bounds__(kSmallBlock) void k_small_select(
 #pragma unroll
             for (int j = 0; j < kAhead; ++j) {
                 const uint32_t p = p0 + first + j * kWave;
-                src.fetch_key_phys(s, dn, p < n ? p : n - 1, key[j]);
-            }
-            uint32_t one;
-            if (p0 + kT * kAhead <= n && same_keys(key, one)) {
-                const uint32_t rel = one - lo;
-                if (lane_id() == 0 && one >= fl && dg.bin(one) == d1 && (rel >> (shift + bits)) == prefix)
-                    atomicAdd(&h[(rel >> shift) & ((1u << bits) - 1u)], (uint32_t)(kWave * kAhead));
-                continue;
+                src.fetch_key_phys(s, false, p < n ? p : n - 1, key[j]);
             }
 #pragma unroll
-            for (int j = 0; j < kAhead; ++j) ok[j] = p0 + first + j * kWave < n && key[j] >= fl;
+            for (int j = 0; j < kAhead; ++j) ok[j] = p0 + first + j * kWave < n;
 #pragma unroll
             for (int j = 0; j < kAhead; ++j) {
                 const uint32_t rel = key[j] - lo;
@@ -450,25 +679,22 @@ __global__ __launch_bounds__(kSmallBlock) void k_small_select(
     }
 
     // ---- 3. ordered emit ---------------------------------------------------------------
-    // a candidate list is read run after run in chunk order: first slots and running counts
-    uint32_t nruns = 1;
-    if (!dn) {
-        nruns = src.nchunks;                                   // <= kSmallMaxChunks <= kT
-        uint2 run = make_uint2(0u, 0u);
-        if (t < nruns) run = src.run_table[(size_t)s * src.nchunks + t];
-        uint32_t tot;
-        const uint32_t incl = block_incl_scan(run.y, s_wave, tot);
-        if (t < nruns) { s_rx[t] = run.x; s_roff[t + 1] = incl; }
-        if (t == 0) s_roff[0] = 0u;
-    }
+    // the list is read run after run in chunk order: first slots and running counts
+    const uint32_t nruns = src.nchunks;                        // <= kSmallMaxChunks <= kT
+    uint2 run = make_uint2(0u, 0u);
+    if (t < nruns) run = src.run_table[(size_t)s * src.nchunks + t];
+    uint32_t tot;
+    const uint32_t incl = block_incl_scan(run.y, s_wave, tot);
+    if (t < nruns) { s_rx[t] = run.x; s_roff[t + 1] = incl; }
+    if (t == 0) s_roff[0] = 0u;
     __syncthreads();
-    // eight consecutive entries per thread and turn, one prefix sum; the rest of a row behind the k-th entry is not read
+    // eight consecutive entries per thread and turn, one prefix sum; the rest of the list behind the k-th entry is not read
     constexpr uint32_t kTurn = 8;
     uint32_t gt_before = 0, eq_before = 0;
     for (uint32_t base = 0; base < n; base += kT * kTurn) {
         const uint32_t lp0 = base + t * kTurn;
         uint32_t r = 0;
-        if (!dn && lp0 < n) {
+        if (lp0 < n) {
             uint32_t hi = nruns;                        // the run r with roff[r] <= lp0 < roff[r+1]
             while (hi - r > 1) {
                 const uint32_t mid = (r + hi) >> 1;
@@ -479,17 +705,13 @@ __global__ __launch_bounds__(kSmallBlock) void k_small_select(
 #pragma unroll
         for (uint32_t j = 0; j < kTurn; ++j) {
             const uint32_t lp = lp0 + j < n ? lp0 + j : n - 1;
-            uint32_t at = lp;
-            if (!dn) {
-                while (s_roff[r + 1] <= lp) ++r;
-                at = s_rx[r] + (lp - s_roff[r]);
-            }
-            src.fetch_phys(s, dn, at, idx[j], bits[j]);
+            while (s_roff[r + 1] <= lp) ++r;
+            src.fetch_phys(s, false, s_rx[r] + (lp - s_roff[r]), idx[j], bits[j]);
         }
 #pragma unroll
         for (uint32_t j = 0; j < kTurn; ++j) {
             key[j] = bits[j] & kAbs;
-            if (lp0 + j >= n || key[j] < fl) key[j] = kNoKey;
+            if (lp0 + j >= n) key[j] = kNoKey;
             if (key[j] != kNoKey) mine += key[j] > T ? 1u : (key[j] == T ? 0x10000u : 0u);
         }
         uint32_t all;

@@ -11,16 +11,26 @@ from tests.test_gpu_grouped import rows
 pytestmark = pytest.mark.gpu
 
 SIZES = [(8, 30_001, 960, 0), (8, 30_001, 961, 1), (4, 99_999, 1984, 0), (4, 100_000, 1985, 3), (2, 524_288, 4032, 0),
-         (2, 524_289, 4032, 0), (2, 524_288, 4033, 2), (16, 60_007, 600, 0), (2, 4_097, 4_000, 1)]
+         (2, 524_289, 4032, 0), (2, 524_288, 4033, 2), (16, 60_007, 600, 0), (2, 4_097, 4_000, 1),
+         # the lines of longer rows: 8 workers and fewer, densities from 0.28 % on for one or two
+         (8, 524_288, 4032, 0), (8, 524_289, 4032, 0), (8, 524_285, 4033, 2), (4, 262_144, 1000, 0), (4, 262_145, 1000, 3),
+         (2, 216_000, 600, 1), (2, 216_001, 600, 0), (1, 200_003, 1500, 0)]
 
 
-@pytest.mark.parametrize("kind", ["layers", "flat", "rounded", "zeros", "plateau", "sample_large", "sample_small"])
+@pytest.mark.parametrize("kind", ["layers", "flat", "rounded", "zeros", "plateau", "levels", "two_values", "sample_large",
+                                  "sample_small"])
 @pytest.mark.parametrize("P,m,k,pad", SIZES)
 def test_local_select_in_one_block(P, m, k, pad, kind):
     rng = np.random.default_rng(P * 31 + m + k)
     dev = Device(P, m, k, stride=m + pad if pad else None)
     res = (rng.standard_normal((P, m), dtype=np.float32) * np.float32(1e-5)).astype(np.float32)
-    g = rows(kind, P, m, k, rng)
+    if kind == "levels":                    # runs of equal values, the largest behind the others: cut twice for the k-th key
+        g = np.repeat(np.arange(1, m // 100 + 2), 100)[:m].clip(max=m // 400 + 1).astype(np.float32) * np.ones((P, 1), np.float32)
+        g[1::2] *= -1
+    elif kind == "two_values":              # mixed in every step, close together: more in the k-th key's bin than a list holds
+        g = np.where(rng.random((P, m)) < 0.5, np.float32(1.0), np.float32(1.0 + 2.0 ** -20))
+    else:
+        g = rows(kind, P, m, k, rng)
     if kind != "layers":
         res[:] = 0.0
     exp = orc.step(res, g, k)
