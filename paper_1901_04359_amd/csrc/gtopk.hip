@@ -1154,8 +1154,14 @@ static int step_impl(const float* grad, float* residual, int64_t m, int64_t stri
         src.nchunks = nruns;
         hipLaunchKernelGGL(k_small_select<kSmallEntries>, dim3(P), dim3(kSmallBlock), 0, st, src, (uint32_t)k, li, lv,
                            (uint32_t*)nullptr);
-        hipLaunchKernelGGL(k_small_tree, dim3(1), dim3(kSmallBlock), 0, st, li, lv, (uint32_t)P,
-                           (uint32_t)k, g_idx, g_val, (float)P, residual, stride);
+        // (see tree_round_by_waves; longer sets take the teams of threads)
+#define GTOPK_TREE(E) hipLaunchKernelGGL(k_small_tree<E>, dim3(1), dim3(kSmallBlock), 0, st, li, lv, (uint32_t)P, (uint32_t)k, \
+                                         g_idx, g_val, (float)P, residual, stride)
+        if (k <= 32) GTOPK_TREE(1);
+        else if (k <= 64) GTOPK_TREE(2);
+        else if (k <= 128) GTOPK_TREE(4);
+        else GTOPK_TREE(0);
+#undef GTOPK_TREE
         return launch_status();
     }
     mark_stage(0, events, st);

@@ -34,7 +34,7 @@ __device__ __forceinline__ uint32_t op_max(uint32_t a, uint32_t b) { return a > 
 // ---------------------------------------------------------------------------------
 
 constexpr int kTreeEpt = kSmallMaxEntries / kSmallBlock;
-constexpr int kTreeTeams = 16;
+constexpr int kTreeTeams = 8;
 constexpr uint32_t kTreeBins = 1024;
 constexpr uint32_t kTreeList = 32;
 // bin of a key at distance rel from the bound: the distance itself below 32, then 32 bins per octave
@@ -739,8 +739,9 @@ __global__ __launch_bounds__(kSmallBlock) void k_small_select(
 // ---------------------------------------------------------------------------------
 
 // All P k-sets sit in LDS (P * k <= 4096 entries).  Round j merges set 2p with set 2p+1 of the surviving sets for
-// every pair p, the pairs side by side: a team of 1024 / pairs threads each (at least a wave; 32 pairs in two turns), a
-// thread owns at most kTreeEpt consecutive slots of its pair's union in index order:
+// every pair p, the pairs side by side: a wave each where the sets are short (tree_round_by_waves), else a team of
+// 1024 / pairs threads (at most 8 pairs, as sets of more than 128 entries come 31 at most), of which a thread owns at most
+// kTreeEpt consecutive slots of its pair's union in index order:
 //   union      a binary search along the diagonal, then a sequential merge; A's copy carries the sum at a shared
 //              index, B's slot there is a tombstone;
 //   select     see team_select; the larger of the operands' smallest keys is the bound, which k keys reach unless sums cancel;
@@ -748,7 +749,7 @@ __global__ __launch_bounds__(kSmallBlock) void k_small_select(
 // (Every barrier is the block's, about nine per round, and a round is its chain of dependent LDS reads and barriers:
 // some 6 us.  One wave per pair that held all keys in registers and searched the k-th in a bracket, with the slots in
 // LDS for a bitmap and a compaction, took 8 us per round of sets of 270; the tree of 8 such sets 26.9 -> 20.0 us, the selection
-// of 270 among 680 candidates 10.6 -> 7.5.  With the teams' sizes known only at run time the tree takes 23.4.)
+// of 270 among 680 candidates 10.6 -> 7.5.)
 // After the last round the global set's values are divided by P and written out, and every worker's locally selected
 // entries whose index is in it (or whose value is -0.0, which the literal zero-then-add-back would turn into +0.0) are
 // stored as +0.0 in the worker's row - the rows still hold the accumulated values at the selected entries.
@@ -760,73 +761,155 @@ struct TreeShared {
     uint32_t min[2][kSmallMaxP];                               // the sets' smallest keys
 };
 
-// One round, SIZE threads per team: the sets at `from` are merged into those at `to`.
+// Slots [l * ept, (l + 1) * ept) of the union of pair q, in index order (ept <= E): kTomb where there is none.
+template <int E>
+__device__ __forceinline__ void tree_union(const TreeShared& sh, uint32_t q, uint32_t k, uint32_t from, uint32_t l, uint32_t ept,
+                                           uint32_t (&oi)[E], uint32_t (&ov)[E]) {
+    const uint32_t n = 2 * k;
+    const uint32_t* ai = sh.idx + from + 2 * q * k;
+    const uint32_t* bi = ai + k;
+    const uint32_t* av = sh.val + from + 2 * q * k;
+    const uint32_t* bv = av + k;
+#pragma unroll
+    for (int j = 0; j < E; ++j) { oi[j] = kTomb; ov[j] = 0u; }
+    const uint32_t d0 = l * ept;
+    if (d0 < n) {
+        uint32_t x = d0 > k ? d0 - k : 0u, hi = d0 < k ? d0 : k;
+        while (x < hi) {
+            const uint32_t mid = (x + hi) >> 1;
+            if (ai[mid] <= bi[d0 - 1 - mid]) x = mid + 1; else hi = mid;
+        }
+        uint32_t y = d0 - x;
+        uint32_t a = x < k ? ai[x] : kTomb, b = y < k ? bi[y] : kTomb, aprev = x > 0 ? ai[x - 1] : kTomb;
+#pragma unroll
+        for (int j = 0; j < E; ++j) {
+            if ((uint32_t)j >= ept || d0 + j >= n) continue;
+            if (a <= b && x < k) {
+                oi[j] = a;
+                ov[j] = av[x];
+                if (b == a) ov[j] = __float_as_uint(__uint_as_float(ov[j]) + __uint_as_float(bv[y]));   // one fp32 add
+                aprev = a;
+                ++x;
+                a = x < k ? ai[x] : kTomb;
+            } else if (y < k) {
+                oi[j] = b == aprev ? kTomb : b;
+                ov[j] = bv[y];
+                ++y;
+                b = y < k ? bi[y] : kTomb;
+            }
+        }
+    }
+}
+
+// One round, SIZE threads per team and a pair per team: the sets at `from` are merged into those at `to`.
 template <uint32_t SIZE>
-__device__ __forceinline__ void tree_round(TreeShared& sh, uint32_t pairs, uint32_t k, uint32_t from, uint32_t to, int turn_min) {
-    constexpr uint32_t teams = kSmallBlock / SIZE;
-    const uint32_t team = threadIdx.x / SIZE, l = threadIdx.x % SIZE;
+__device__ __forceinline__ void tree_round(TreeShared& sh, uint32_t k, uint32_t from, uint32_t to, int turn_min) {
+    const uint32_t q = threadIdx.x / SIZE, l = threadIdx.x % SIZE;            // the team's pair
     constexpr int kE = SIZE == 1024 ? 1 : (SIZE == 512 ? 2 : kTreeEpt);       // slots per thread, at most
     static_assert(2 * kSmallMaxK <= 1024 && kSmallMaxEntries <= 1024 * kTreeEpt, "2k slots fit a team's threads");
     const uint32_t n = 2 * k, ept = (n + SIZE - 1) / SIZE;                   // <= kE
-    for (uint32_t q = team; q < pairs; q += teams) {                        // (pairs is a multiple of teams)
-        // ---- union ------------------------------------------------------------------
-        const uint32_t* ai = sh.idx + from + 2 * q * k;
-        const uint32_t* bi = ai + k;
-        const uint32_t* av = sh.val + from + 2 * q * k;
-        const uint32_t* bv = av + k;
-        const uint32_t bound = op_max(sh.min[turn_min][2 * q], sh.min[turn_min][2 * q + 1]);
-        uint32_t oi[kE], ov[kE];
+    const uint32_t bound = op_max(sh.min[turn_min][2 * q], sh.min[turn_min][2 * q + 1]);
+    uint32_t oi[kE], ov[kE];
+    tree_union<kE>(sh, q, k, from, l, ept, oi, ov);
+    // ---- select and emit ------------------------------------------------------------
+    uint32_t key[kE];
 #pragma unroll
-        for (int j = 0; j < kE; ++j) { oi[j] = kTomb; ov[j] = 0u; }
-        const uint32_t d0 = l * ept;
-        if (d0 < n) {
-            uint32_t x = d0 > k ? d0 - k : 0u, hi = d0 < k ? d0 : k;
-            while (x < hi) {
-                const uint32_t mid = (x + hi) >> 1;
-                if (ai[mid] <= bi[d0 - 1 - mid]) x = mid + 1; else hi = mid;
-            }
-            uint32_t y = d0 - x;
-            uint32_t a = x < k ? ai[x] : kTomb, b = y < k ? bi[y] : kTomb, aprev = x > 0 ? ai[x - 1] : kTomb;
+    for (int j = 0; j < kE; ++j) key[j] = oi[j] != kTomb ? ov[j] & kAbs : kNoKey;
+    const TeamCut c = team_select<SIZE>(sh.team, key, bound, k);
+    if (l == 0) sh.min[turn_min ^ 1][q] = c.T;
+    uint32_t eq = c.eq, pos = c.pos;
 #pragma unroll
-            for (int j = 0; j < kE; ++j) {
-                if ((uint32_t)j >= ept || d0 + j >= n) continue;
-                if (a <= b && x < k) {
-                    oi[j] = a;
-                    ov[j] = av[x];
-                    if (b == a) ov[j] = __float_as_uint(__uint_as_float(ov[j]) + __uint_as_float(bv[y]));   // one fp32 add
-                    aprev = a;
-                    ++x;
-                    a = x < k ? ai[x] : kTomb;
-                } else if (y < k) {
-                    oi[j] = b == aprev ? kTomb : b;
-                    ov[j] = bv[y];
-                    ++y;
-                    b = y < k ? bi[y] : kTomb;
+    for (int j = 0; j < kE; ++j) {
+        if (key[j] == kNoKey) continue;
+        bool sel = key[j] > c.T;
+        if (key[j] == c.T) sel = eq++ < c.need;
+        if (sel && pos < k) {                  // (always inside)
+            sh.idx[to + q * k + pos] = oi[j];
+            sh.val[to + q * k + pos] = ov[j];
+            ++pos;
+        }
+    }
+    __syncthreads();
+}
+
+// One round of sets of at most 32 E entries, a wave per pair and 2 E slots per lane at most, no barrier but the one at
+// the end: for sets this short the teams' barriers are most of a round.  The k-th key is found bit by bit, the keys of all
+// lanes counted by ballots; most searches end early, with a bound that exactly k keys reach.  A step at m = 20,000 in us, by
+// a wave per pair that searched in a bracket / by teams / this:  P = 64  k = 1   43.3 / 50.3 / 28.8   k = 32   48.8 / 57.8 / 36.9
+// P = 16  k = 8   34.0 / 37.1 / 26.9   k = 128  46.8 / 41.3 / 36.3   P = 4  k = 32   27.1 / 27.1 / 23.4   k = 128  32.7 / 28.3 / 26.8
+template <int E>
+__device__ __forceinline__ void tree_round_by_waves(TreeShared& sh, uint32_t pairs, uint32_t k, uint32_t from, uint32_t to, int turn_min) {
+    const uint32_t lane = lane_id(), wave = threadIdx.x / kWave;
+    for (uint32_t q = wave; q < pairs; q += kSmallBlock / kWave) {           // wave-uniform
+        uint32_t oi[E], ov[E], key[E];
+        tree_union<E>(sh, q, k, from, lane, (2 * k + kWave - 1) / kWave, oi, ov);
+#pragma unroll
+        for (int j = 0; j < E; ++j) key[j] = oi[j] != kTomb ? ov[j] & kAbs : kNoKey;
+        // distances from a bound that k keys reach: the larger of the operands' smallest keys, unless sums cancel
+        auto reach = [&](uint32_t least) {                   // (never kNoKey)
+            uint32_t n = 0;
+#pragma unroll
+            for (int j = 0; j < E; ++j) n += (uint32_t)__popcll(__ballot(key[j] - least <= kAbs - least));
+            return n;
+        };
+        uint32_t base = op_max(sh.min[turn_min][2 * q], sh.min[turn_min][2 * q + 1]);
+        base = (uint32_t)__builtin_amdgcn_readfirstlane((int)base);
+        uint32_t n = reach(base);
+        if (n < k) {
+            base = 0u;
+            n = reach(0u);
+        }
+        uint32_t most = 0;
+#pragma unroll
+        for (int j = 0; j < E; ++j) most = key[j] != kNoKey && key[j] > most ? key[j] : most;
+        most = wave_largest(most);
+        uint32_t T = base;                                   // n keys reach T, at least k
+        if (n > k && most > base) {
+            for (int b = 31 - __builtin_clz(most - base); b >= 0 && n != k; --b) {
+                const uint32_t c = reach(T + (1u << b));
+                if (c >= k) {
+                    T += 1u << b;
+                    n = c;
                 }
             }
         }
-        // ---- select and emit ------------------------------------------------------------
-        uint32_t key[kE];
+        uint32_t ties = 0xFFFFFFFFu;                         // keys equal to T to take
+        if (n == k) {                                        // those that reach T, all of them: T becomes the smallest
+            uint32_t inv = 0;
 #pragma unroll
-        for (int j = 0; j < kE; ++j) key[j] = oi[j] != kTomb ? ov[j] & kAbs : kNoKey;
-        const TeamCut c = team_select<SIZE>(sh.team, key, bound, k);
-        if (l == 0) sh.min[turn_min ^ 1][q] = c.T;
-        uint32_t eq = c.eq, pos = c.pos;
+            for (int j = 0; j < E; ++j) inv = key[j] - T <= kAbs - T ? op_max(inv, kAbs - key[j]) : inv;
+            T = kAbs - wave_largest(inv);
+        } else if (n > k) {
+            ties = k - reach(T + 1u);
+        }
+        if (lane == 0) sh.min[turn_min ^ 1][q] = T;
+        // (slots lane by lane: those of the lanes below first)
+        uint32_t eq = 0, pos = 0, mine = 0;                  // mine: selected for certain, and equal to T << 16
 #pragma unroll
-        for (int j = 0; j < kE; ++j) {
+        for (int j = 0; j < E; ++j)
+            if (key[j] != kNoKey) mine += key[j] > T ? 1u : (key[j] == T ? 0x10000u : 0u);
+        const uint32_t before = wave_incl_scan(mine) - mine;
+        eq = before >> 16;
+        pos = (before & 0xFFFFu) + (eq < ties ? eq : ties);
+#pragma unroll
+        for (int j = 0; j < E; ++j) {
             if (key[j] == kNoKey) continue;
-            bool sel = key[j] > c.T;
-            if (key[j] == c.T) sel = eq++ < c.need;
-            if (sel && pos < k) {                  // (always inside)
+            bool sel = key[j] > T;
+            if (key[j] == T) sel = eq++ < ties;
+            if (sel && pos < k) {                            // (always inside)
                 sh.idx[to + q * k + pos] = oi[j];
                 sh.val[to + q * k + pos] = ov[j];
                 ++pos;
             }
         }
-        __syncthreads();
     }
+    __syncthreads();
 }
 
+// E: 0: teams of threads (sets of more than 128 entries); else waves (sets of at most 32 E entries).
+// (The teams' four sizes in one kernel take 128 registers and spill three; with the sizes known only at run time the tree of 8
+// sets of 270 takes 23.4 us instead of 20.)
+template <int E>
 __global__ __launch_bounds__(kSmallBlock) void k_small_tree(
         const uint32_t* __restrict__ loc_idx, const float* __restrict__ loc_val, uint32_t P,
         uint32_t k, uint32_t* __restrict__ g_idx, float* __restrict__ g_val, float divisor,
@@ -862,11 +945,11 @@ __global__ __launch_bounds__(kSmallBlock) void k_small_tree(
     int turn_min = 0;
     for (uint32_t nsets = P; nsets > 1; nsets >>= 1) {
         const uint32_t pairs = nsets >> 1;
-        if (pairs == 1) tree_round<1024>(sh, pairs, k, from, to, turn_min);
-        else if (pairs == 2) tree_round<512>(sh, pairs, k, from, to, turn_min);
-        else if (pairs == 4) tree_round<256>(sh, pairs, k, from, to, turn_min);
-        else if (pairs == 8) tree_round<128>(sh, pairs, k, from, to, turn_min);
-        else tree_round<64>(sh, pairs, k, from, to, turn_min);
+        if constexpr (E != 0) tree_round_by_waves<E>(sh, pairs, k, from, to, turn_min);
+        else if (pairs == 1) tree_round<1024>(sh, k, from, to, turn_min);
+        else if (pairs == 2) tree_round<512>(sh, k, from, to, turn_min);
+        else if (pairs == 4) tree_round<256>(sh, k, from, to, turn_min);
+        else tree_round<128>(sh, k, from, to, turn_min);
         const uint32_t x = from;
         from = to;
         to = x;

@@ -1,5 +1,5 @@
-"""The tree in one block (few-launch path), GPU against the oracle, bit for bit: every number of threads per pair, two
-turns of pairs, the largest sets, and value kinds whose sums cancel or whose keys crowd into one bin."""
+"""The tree in one block (few-launch path), GPU against the oracle, bit for bit: a wave per pair and every number
+of threads per pair, more pairs than waves, the largest sets, and value kinds whose sums cancel or whose keys crowd into one bin."""
 import numpy as np
 import pytest
 
@@ -11,7 +11,9 @@ pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("kind", ["layers", "cancel", "same", "rounded", "signs", "zeros", "plateau", "apart", "denormal"])
-@pytest.mark.parametrize("P,k", [(2, 1), (2, 512), (4, 33), (4, 512), (8, 270), (8, 512), (16, 256), (32, 128), (64, 64), (64, 3)])
+@pytest.mark.parametrize("P,k", [(2, 1), (2, 512), (4, 33), (4, 512), (8, 270), (8, 512), (16, 256), (32, 128), (64, 64), (64, 3),
+                                 # both sides of the lengths at which a wave of the short sets' rounds holds more, and of the longest
+                                 (16, 32), (64, 33), (2, 64), (8, 65), (2, 127), (16, 128), (16, 129), (2, 129)])
 def test_tree_of_small_sets(P, k, kind):
     from paper_1901_04359_amd import binding as B
     m = 20_011
