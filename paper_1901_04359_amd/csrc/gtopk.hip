@@ -616,9 +616,11 @@ uint32_t bracket_target_hi(double mean, double placed) {
 // Few workers leave the chip to the general kernels, which are faster with such rows then (m = 524,288, P = 4, k = 1000
 // 147 / 122 | 130 / 167 | 114 .. 214 / 151 .. 164, P = 1 70 / 102 | 64 / 148 | 54 .. 157 / 133 .. 142; ordinary rows lose some:
 // m = 300,000, P = 4, k = 1000 52.6 / 46.7, P = 1 36.6 / 31.8, m = 500,000, P = 4, k = 4000 62.0 / 63.4), and at densities at which
-// their pass histograms (see below) from 170,000 elements on (m = 200,000, P = 2, k = 520 81 / 74 | 79 / 92 | 63 .. 104 / 77 .. 81, ordinary rows 41 / 34).
+// their pass histograms (see below) above 2^17 elements (m = 200,000,
+// P = 2, k = 520 81 / 74 | 79 / 92 | 63 .. 104 / 77 .. 81, ordinary rows 41 / 34; up to there only rows of ones lose, gtopk_local_select
+// at m = 131,072, P = 1, k = 100 49 / 49 | 49 / 59, ordinary rows 33 / 27).
 uint32_t select_in_block(int64_t m, uint32_t k, uint32_t P) {
-    if (m > (P < 8 ? 1 << 18 : 1 << 19) || (P < 4 && 360ull * k < (uint64_t)m)) return 0;
+    if (m > (P < 8 ? 1 << 18 : 1 << 19) || (P < 4 && m > 1 << 17 && 360ull * k < (uint64_t)m)) return 0;
     const uint32_t n = 4 * k + 256;
     return n <= 4096 ? 4 : (n <= 8192 ? 8 : (n <= 16384 ? 16 : 0));
 }
