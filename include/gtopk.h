@@ -137,6 +137,10 @@ int gtopk_residual_restore(float* residual, int64_t m, int64_t stride, int32_t P
  * speculative threshold of a worker in one block, the streaming pass, the exact local
  * selection of a worker in one block, the whole tree with the average and the extra
  * residual in one block.
+ * Large densities (P >= 2; k from m/8 on for m >= 2^22, from m/5 on for m >= 2^20 and m*P >= 2^24; k up to m/3;
+ * m <= 2^26) go by index groups of the rows instead of candidate lists, which is some 1.1 to 1.6 times as fast.
+ * gtopk_step_carry and the three calls in sequence keep the lists there, with the same results: at these
+ * densities a step with carried thresholds is the slower one.
  *   m : 1 .. 2^31;  k : 1 .. m (and <= 2^30 if P > 1);  P : a power of two, 1 .. 32768;
  *   stride >= m;  ws : gtopk_workspace_bytes(m, k, P) bytes
  */
@@ -244,7 +248,8 @@ int gtopk_dense_topk(const float* dense, int64_t m, int32_t k, uint32_t* g_idx, 
  * records at its stage boundaries.  `events` holds the HOST handles of six hipEvent_t
  * (created by the caller, passed as void*), recorded on `stream`:
  *   [0] start  [1] after the speculative-threshold kernels  [2] after the streaming
- *   accumulate/filter kernel  [3] after the exact local selection
+ *   accumulate/filter kernel  [3] after the exact local selection (in a step by index
+ *   groups this includes the union of the first round's pairs)
  *   [4] after the tree  [5] after the residual restore.
  * The handles belong to this one call: the library keeps nothing between calls, so
  * concurrent callers (each with its own workspace, stream and events) do not interfere.
@@ -283,7 +288,9 @@ int gtopk_probe_stream(const float* a, float* b, int64_t n, int32_t mode, float*
  * nothing to filter by) on workspace `ws` with these sizes has COMPLETED, copy to the host how
  * many candidates the streaming pass kept for each worker (host_counts[P]) and the
  * capacity of a worker's candidate list (*host_capacity).  A worker whose count is
- * below k or above the capacity was selected from its dense row instead.
+ * below k or above the capacity was selected from its dense row instead.  (After a step by index groups there
+ * are no lists: the counts are the elements that reach the lower end of a worker's bracket, and
+ * gtopk_debug_missed_brackets tells how its set was selected.)
  * Synchronous (blocking device-to-host copy).
  */
 int gtopk_debug_candidate_counts(const void* ws, int64_t m, int32_t k, int32_t P,
@@ -310,13 +317,15 @@ int gtopk_debug_merge_kept(const void* ws, int32_t k, int32_t batch, uint32_t* h
  *   plan[4] capacity     entries a worker's candidate list holds
  *   plan[5] pass_histogram  1 if the streaming pass counts the first digits of its
  *                        candidates itself (the dense-row fallback then uses a histogram
- *                        of its own), 0 if the select's histogram kernel does
+ *                        of its own), 0 if the select's histogram kernel does, or one block
+ *                        per worker selects (gtopk_debug_routes, routes[2])
  *   plan[6] small_path   1 if gtopk_step takes the few-launch path for small problems at
  *                        these sizes (gtopk_step_carry, gtopk_step_timed and the stand-alone
  *                        calls always take the general kernels)
  *   plan[7] run_groups   1 if the local selection of the general kernels selects the candidates
  *                        where the streaming pass left them, one group per run (long runs),
- *                        0 if it first copies them into index order (short runs)
+ *                        0 if it first copies them into index order (short runs), or one
+ *                        block per worker selects
  *   plan[8] small_tile_stride, plan[9] small_n_tiles, plan[10] small_target: the sampler of
  *                        the few-launch path (same tile_len; all 0 where plan[6] is 0)
  *   plan[11] merge_filtered  1 if a merge of two k-sets of this k goes through a speculative
@@ -326,9 +335,38 @@ int gtopk_debug_merge_kept(const void* ws, int32_t k, int32_t batch, uint32_t* h
  *                        operands (all 0 where plan[11] is 0)
  *   plan[15] chunk_log2: a block of the general kernels' streaming pass covers 2^plan[15] elements of a
  *                        row - one run of candidates (a block of the few-launch path: 4096)
+ * A gtopk_step that goes by index groups (gtopk_debug_routes, routes[1]) has the sample of plan[0] .. plan[3]
+ * and nothing else of this: plan[4], [5], [7] and [11] .. [15] describe the calls that do not.
  */
 #define GTOPK_PLAN_WORDS 16
 int gtopk_debug_plan(int64_t m, int32_t k, int32_t P, uint32_t* plan);
+
+/*
+ * Instrumentation for tests (not part of the method; host only, touches no GPU): which kernels serve
+ * calls of these sizes, and the brackets of steps by index groups.
+ *   routes[0]  1 if gtopk_step takes the few-launch path (as plan[6])
+ *   routes[1]  groups of a row if gtopk_step (and gtopk_step_timed without carried thresholds) goes by index
+ *              groups: large densities; 0 if not.  gtopk_step_carry and the stand-alone calls never do
+ *   routes[2]  entries per thread of the one block per worker that selects from its candidate list in
+ *              gtopk_local_select and in steps outside the few-launch path; 0: several kernels do
+ *   routes[3]  1 if one block per pair merges sets of this k (gtopk_merge, gtopk_tree, the steps' rounds)
+ *   routes[4]  a worker's bracket ends at the lowest bucket edge that at most routes[4] of its sampled keys
+ *              reach (and starts where plan[3] of them do)
+ *   routes[5]  sampled elements per group of a pair's union; its bracket starts at the bucket edge that
+ *              routes[6] of them reach and ends at the lowest that at most routes[7] do (the first
+ *              round's pairs have a bracket from the workers' own samples)
+ *   routes[4] .. routes[7] are 0 where routes[1] is.
+ */
+#define GTOPK_ROUTE_WORDS 8
+int gtopk_debug_routes(int64_t m, int32_t k, int32_t P, uint32_t* routes);
+
+/*
+ * Instrumentation for tests (not part of the method): after a gtopk_step that went by index groups on
+ * workspace `ws` with these sizes has COMPLETED, copy to the host which sets were selected outside their
+ * sampled bracket (slower): host_missed[2 P - 1], the workers' sets, then the pairs of each round; 1: missed.
+ * GTOPK_EINVAL where gtopk_step does not go by index groups.  Synchronous (blocking device-to-host copy).
+ */
+int gtopk_debug_missed_brackets(const void* ws, int64_t m, int32_t k, int32_t P, uint32_t* host_missed);
 
 #ifdef __cplusplus
 }

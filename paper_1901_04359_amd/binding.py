@@ -23,7 +23,7 @@ EXPORTS = (
     "gtopk_apply_update", "gtopk_dense_mask",
     "gtopk_allreduce_workspace_bytes", "gtopk_topk_allreduce", "gtopk_dense_topk",
     "gtopk_step_timed", "gtopk_probe_stream", "gtopk_debug_candidate_counts", "gtopk_debug_plan",
-    "gtopk_debug_merge_kept",
+    "gtopk_debug_merge_kept", "gtopk_debug_routes", "gtopk_debug_missed_brackets",
 )
 
 GTOPK_OK, GTOPK_EINVAL, GTOPK_EWORKSPACE, GTOPK_EALIGN, GTOPK_EHIP = 0, -1, -2, -3, -4
@@ -88,6 +88,10 @@ def load() -> ctypes.CDLL:
     lib.gtopk_probe_stream.argtypes = [vp, vp, i64, i32, vp, vp]
     lib.gtopk_debug_plan.restype = c.c_int
     lib.gtopk_debug_plan.argtypes = [i64, i32, i32, c.POINTER(c.c_uint32)]
+    lib.gtopk_debug_routes.restype = c.c_int
+    lib.gtopk_debug_routes.argtypes = [i64, i32, i32, c.POINTER(c.c_uint32)]
+    lib.gtopk_debug_missed_brackets.restype = c.c_int
+    lib.gtopk_debug_missed_brackets.argtypes = [vp, i64, i32, i32, c.POINTER(c.c_uint32)]
     lib.gtopk_debug_merge_kept.restype = c.c_int
     lib.gtopk_debug_merge_kept.argtypes = [vp, i32, i32, c.POINTER(c.c_uint32)]
     lib.gtopk_debug_candidate_counts.restype = c.c_int
@@ -360,6 +364,27 @@ def gtopk_debug_plan(m: int, k: int, P: int) -> dict:
     plan = (ctypes.c_uint32 * len(PLAN_FIELDS))()
     _check(load().gtopk_debug_plan(m, k, P, plan), "gtopk_debug_plan")
     return dict(zip(PLAN_FIELDS, (int(x) for x in plan)))
+
+
+ROUTE_FIELDS = ("few_launches", "index_groups", "select_entries", "merge_block", "row_target_hi", "union_samples",
+                "union_target_lo", "union_target_hi")
+
+
+def gtopk_debug_routes(m: int, k: int, P: int) -> dict:
+    """Which kernels serve calls of these sizes (host only; see gtopk.h)."""
+    routes = (ctypes.c_uint32 * len(ROUTE_FIELDS))()
+    _check(load().gtopk_debug_routes(m, k, P, routes), "gtopk_debug_routes")
+    return dict(zip(ROUTE_FIELDS, (int(x) for x in routes)))
+
+
+def gtopk_debug_missed_brackets(ws, m: int, k: int, P: int):
+    """Per set of the last completed gtopk_step by index groups on `ws` (the workers', then the pairs' of each round):
+    whether it was selected outside its bracket (see gtopk.h)."""
+    torch = _torch()
+    torch.cuda.synchronize()
+    missed = (ctypes.c_uint32 * (2 * P - 1))()
+    _check(load().gtopk_debug_missed_brackets(_ptr(ws, torch.uint8, "ws"), m, k, P, missed), "gtopk_debug_missed_brackets")
+    return [bool(x) for x in missed]
 
 
 def gtopk_debug_merge_kept(ws, k: int, batch: int):

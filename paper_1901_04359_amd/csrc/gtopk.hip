@@ -598,6 +598,12 @@ uint32_t bracket_target_hi(double mean, double placed) {
     const double t = placed * mean - 5.5 * __builtin_sqrt(mean) - 2.0;
     return t > 0.0 ? (uint32_t)t : 0u;
 }
+// The ranks of the rows' brackets, and of the unions', whose samples are scattered.
+uint32_t row_bracket_target_hi(int64_t m, uint32_t k, const SamplePlan& sp) {
+    return bracket_target_hi((double)k * (double)sp.sampled / (double)m, 0.97);
+}
+uint32_t union_bracket_target_lo(double mean) { return (uint32_t)(1.02 * mean + 5.5 * __builtin_sqrt(mean) + 2.0); }
+uint32_t union_bracket_target_hi(double mean) { return bracket_target_hi(mean, 0.98); }
 
 // Entries per thread with which one block selects from a worker's candidate list (k_small_select), 0: the general
 // kernels do, three of them.  A list is expected to hold 2.5 k entries (mid_sample_mean), a longer one than the threads hold
@@ -691,7 +697,7 @@ void sample_rows(const float* grad, const float* residual, int64_t m, int64_t st
     // A row that is summed goes through the pass anyway, and one that overfills its list still gains from the
     // threshold; a row that is not has nothing of a pass whose list will not hold.
     const uint32_t most = SUM ? 0xFFFFFFFFu : (uint32_t)((double)w.cap * (double)sp.sampled / (double)m);
-    const uint32_t target_hi = BRACKET ? bracket_target_hi((double)k * (double)sp.sampled / (double)m, 0.97) : 0u;
+    const uint32_t target_hi = BRACKET ? row_bracket_target_hi(m, k, sp) : 0u;
     if (mid_problem(m, k, P)) {
         const uint32_t zblocks = zero_blocks(job, 4 * kSmallBlock);
         hipLaunchKernelGGL((k_small_sample<kMidSampleTile, true, SUM, BRACKET>), dim3(P + zblocks), dim3(kSmallBlock), 0,
@@ -812,6 +818,9 @@ inline void launch_union_cuts(const uint32_t* a_idx, const uint32_t* b_idx, uint
 //   k = 1000  58.7 / 27.9   21.8 / 9.7 | 21.9 / 9.9     k = 6000  61.2 / 57.3   22.6 / 19.4 | 27.5 / 19.7
 //   k = 2000  59.1 / 32.0   22.1 / 11.1 | 22.9 / 11.3   k = 8192  62.2 / 61.0   23.3 / 20.8 | 29.5 / 20.9
 // Longer ones, with 32 slots per thread, lose: k = 12,000 63.0 / 102, 24.6 / 34.3 | 33.5 / 34.5.
+// More pairs gain more: k = 1000 256 | 4096 pairs  34.7 / 9.9 | 227 / 64.1   k = 8192 64 | 1024 pairs  80.3 / 31.6 | 358 / 99.1.
+// Sets of one magnitude, whose keys all fall into one bin, take longer either way: k = 1000, 1 pair  30.6 / 13.9   k = 8192, 1 | 16
+// pairs 63.5 / 57.3 | 103 / 57.4.  The one slower kind found: a tree of 8 sets of 8192 that lie behind one another, 61.0 / 63.8.
 inline bool merge_in_block(uint32_t k) { return k <= kMergeBlockMaxK; }
 template <bool DIVIDE>
 void launch_merge_block(const uint32_t* a_idx, const float* a_val, const uint32_t* b_idx, const float* b_val, uint32_t k,
@@ -986,7 +995,7 @@ int do_grouped_step(const float* grad, float* residual, int64_t m, int64_t strid
     auto finish = [&](const GroupBatch& gb, uint32_t sets, uint32_t samples, double fraction) {
         const double mean = (double)k * fraction;            // expected sample rank of the k-th key of a union
         const GroupSample sm{gb.first + sets, sets / 2, gw.samples, samples,
-                             (uint32_t)(1.02 * mean + 5.5 * __builtin_sqrt(mean) + 2.0), bracket_target_hi(mean, 0.98)};
+                             union_bracket_target_lo(mean), union_bracket_target_hi(mean)};
         hipLaunchKernelGGL(k_group_walk, dim3(walk_blocks, sets), dim3(kGrpWalkBlock), 0, st, gs, gb, sm);
         // blocks for the sets that miss their brackets: a wave per group, one block per CU (the others' return)
         uint32_t shares = sets >= 32 ? 8u : (sets <= 4 ? 64u : 256u / sets);
@@ -1410,9 +1419,10 @@ int gtopk_debug_plan(int64_t m, int32_t k, int32_t P, uint32_t* plan) {
     plan[2] = (uint32_t)(mid_problem(m, (uint32_t)k, (uint64_t)P) ? kMidSampleTile : kSampleTile);
     plan[3] = sp.target;
     plan[4] = cand_capacity(m, (uint32_t)k);
-    plan[5] = pass_histograms(m, (uint32_t)k) ? 1u : 0u;
+    const bool in_block = select_in_block(m, (uint32_t)k, (uint32_t)P) != 0;      // neither of the two next
+    plan[5] = !in_block && pass_histograms(m, (uint32_t)k) ? 1u : 0u;
     plan[6] = small_problem(m, k, P) ? 1u : 0u;
-    plan[7] = run_groups(m, (uint32_t)k) ? 1u : 0u;
+    plan[7] = !in_block && run_groups(m, (uint32_t)k) ? 1u : 0u;
     for (int i = 8; i < GTOPK_PLAN_WORDS; ++i) plan[i] = 0u;
     if (P > 1 && merge_filtered((uint32_t)k)) {
         const MergeSamplePlan mp = plan_merge_sample((uint32_t)k);
@@ -1428,6 +1438,38 @@ int gtopk_debug_plan(int64_t m, int32_t k, int32_t P, uint32_t* plan) {
         plan[10] = ss.target;
     }
     plan[15] = pass_chunk_log2(m, (uint32_t)k, (uint64_t)P);
+    return GTOPK_OK;
+}
+
+int gtopk_debug_routes(int64_t m, int32_t k, int32_t P, uint32_t* routes) {
+    if (!routes || !sizes_ok(m, k, P)) return GTOPK_EINVAL;
+    for (int i = 0; i < GTOPK_ROUTE_WORDS; ++i) routes[i] = 0u;
+    routes[0] = small_problem(m, k, P) ? 1u : 0u;
+    routes[2] = select_in_block(m, (uint32_t)k, (uint32_t)P);
+    routes[3] = merge_in_block((uint32_t)k) ? 1u : 0u;
+    const StepWs w = carve_step(nullptr, m, (uint32_t)k, (uint32_t)P);
+    if (!routes[0] && grouped_step(m, (uint32_t)k, (uint32_t)P, w)) {
+        const GroupWs gw = carve_grouped(w, m, (uint32_t)k, (uint32_t)P);
+        const SamplePlan sp = plan_row_sample(m, (uint32_t)k, (uint64_t)P);
+        const double mean = (double)k * (double)gw.per_group / (double)kGroup;
+        routes[1] = gw.gs.ngroups;
+        routes[4] = row_bracket_target_hi(m, (uint32_t)k, sp);
+        routes[5] = gw.per_group;
+        routes[6] = union_bracket_target_lo(mean);
+        routes[7] = union_bracket_target_hi(mean);
+    }
+    return GTOPK_OK;
+}
+
+int gtopk_debug_missed_brackets(const void* ws, int64_t m, int32_t k, int32_t P, uint32_t* host_missed) {
+    if (!ws || !host_missed || !sizes_ok(m, k, P)) return GTOPK_EINVAL;
+    const StepWs w = carve_step(const_cast<void*>(ws), m, (uint32_t)k, (uint32_t)P);
+    if (small_problem(m, k, P) || !grouped_step(m, (uint32_t)k, (uint32_t)P, w)) return GTOPK_EINVAL;
+    const size_t sets = 2 * (size_t)P - 1;
+    if (hipMemcpy(host_missed, carve_grouped(w, m, (uint32_t)k, (uint32_t)P).gs.d1, sizeof(uint32_t) * sets, hipMemcpyDeviceToHost) !=
+        hipSuccess)
+        return GTOPK_EHIP;
+    for (size_t i = 0; i < sets; ++i) host_missed[i] = host_missed[i] == kMissed ? 1u : 0u;
     return GTOPK_OK;
 }
 

@@ -220,6 +220,36 @@ def test_debug_plan_describes_the_sampler():
     assert B.gtopk_debug_plan(1_048_574, 10, 2)["small_path"] == 0
 
 
+def test_debug_routes():
+    """Both sides of the lines between the kernels, and the plan's words where one block selects."""
+    r = lambda m, k, P: B.gtopk_debug_routes(m, k, P)
+    assert r(269_722, 270, 8)["few_launches"] == 1 and r(269_722, 600, 8)["few_launches"] == 0
+    # index groups: by row length, density, number of workers
+    assert r(25_557_032, 6_389_258, 32)["index_groups"] == 3120
+    assert r(4_194_304, 524_288, 2)["index_groups"] == 512 and r(4_194_304, 524_287, 2)["index_groups"] == 0
+    assert r(4_194_303, 524_288, 2)["index_groups"] == 0
+    assert r(1_048_576, 209_716, 16)["index_groups"] == 128 and r(1_048_576, 209_715, 16)["index_groups"] == 0
+    assert r(1_048_575, 209_716, 16)["index_groups"] == 0 and r(1_048_576, 209_716, 8)["index_groups"] == 0
+    assert r(3_000_000, 1_000_000, 8)["index_groups"] == 367 and r(3_000_000, 1_000_001, 8)["index_groups"] == 0
+    assert r(25_557_032, 6_389_258, 1)["index_groups"] == 0
+    assert r(8192 * 8192, 8_388_608, 2)["index_groups"] == 8192 and r(8192 * 8192 + 1, 8_388_609, 2)["index_groups"] == 0
+    # one block per worker, one block per pair
+    for m, k, P, entries in [(100_000, 960, 8, 4), (100_000, 961, 8, 8), (100_000, 4032, 8, 16), (100_000, 4033, 8, 0),
+                             (1 << 19, 4032, 8, 16), ((1 << 19) + 1, 4032, 8, 0), (1 << 18, 1000, 4, 8), ((1 << 18) + 1, 1000, 4, 0),
+                             (1 << 17, 100, 2, 4), ((1 << 17) + 1, 100, 2, 0), (200_000, 556, 2, 4), (200_000, 555, 2, 0)]:
+        assert r(m, k, P)["select_entries"] == entries, (m, k, P)
+        assert entries == 0 or B.gtopk_debug_plan(m, k, P)["run_groups"] == B.gtopk_debug_plan(m, k, P)["pass_histogram"] == 0
+    assert r(100_000, 8192, 2)["merge_block"] == 1 and r(100_000, 8193, 2)["merge_block"] == 0
+    with pytest.raises(B.GtopkError):
+        r(100, 0, 2)
+    lib = B.load()
+    out = (ctypes.c_uint32 * 64)()
+    assert lib.gtopk_debug_routes(100, 10, 2, None) == B.GTOPK_EINVAL
+    assert lib.gtopk_debug_missed_brackets(FAKE, 25_557_032, 255_570, 32, out) == B.GTOPK_EINVAL      # not by index groups
+    assert lib.gtopk_debug_missed_brackets(None, 25_557_032, 6_389_258, 32, out) == B.GTOPK_EINVAL
+    assert lib.gtopk_debug_missed_brackets(FAKE, 25_557_032, 6_389_258, 32, None) == B.GTOPK_EINVAL
+
+
 def test_argument_errors_step_static():
     lib = B.load()
     st = lambda **kw: lib.gtopk_step_static(

@@ -117,6 +117,8 @@ def test_fallback_step_mixed_workers(m, k, P, pass_hist):
     cfg, plan, g0, paths = build_case(m, k, P, seed=m + k)
     if not plan["small_path"]:
         assert plan["pass_histogram"] == pass_hist, plan
+        routes = B.gtopk_debug_routes(m, k, P)
+        assert routes["index_groups"] == 0 and routes["select_entries"] == 0, routes
         assert plan["run_groups"] == (1 if k * 1000 >= 6 * m else 0), plan
     assert plan["n_tiles"] * plan["tile_len"] < m, "the sampler must not see the whole row"
     dev = Device(P, m, k)

@@ -59,25 +59,31 @@ def test_full_size_step(name, iters):
         assert all(k <= c <= cap for c in counts), (name, it, min(counts), max(counts), cap)
 
 
-@pytest.mark.parametrize("rho,iters", [(0.25, 2), (0.0725, 2)])
-def test_full_size_warmup_densities(rho, iters):
+@pytest.mark.parametrize("rho,iters,call", [(0.25, 2, "step"), (0.25, 2, "step_carry"), (0.0725, 2, "step")])
+def test_full_size_warmup_densities(rho, iters, call):
     """The first two densities of the paper's warm-up schedule (Section IV-B) at the
     ResNet-50-sized configuration's full size (m = 25,557,032, P = 32): the sizes at which
-    the large-density timings are quoted.  Merged sets have up to 12.8 M slots here and a
+    the large-density timings are quoted.  The step at a density of a quarter goes by index groups, the one with
+    carried thresholds by candidate lists: merged sets have up to 12.8 M slots there and a
     worker's candidate list millions of entries, which no smaller case reaches."""
     base = W.CONFIGS["C4a"]
     k = int(round(rho * base.m))
     cfg = W.scaled(base, base.m, k=k, name=f"C4/rho={rho}")
     P, m = cfg.P, cfg.m
     dev = Device(P, m, k)
+    by_groups = call == "step" and dev.B.gtopk_debug_routes(m, k, P)["index_groups"] > 0
+    assert by_groups == (call == "step" and rho == 0.25)
     res = np.zeros((P, m), dtype=np.float32)
     for it in range(iters):
         say(f"full size rho={rho} it={it}: generating P={P} m={m}")
         g = W.gradients(cfg, it, threads=THREADS)
         dev.set_grad(g)
-        say(f"full size rho={rho} it={it}: gtopk_step k={k}")
-        gi, gv = dev.step()
-        counts, cap = dev.B.gtopk_debug_candidate_counts(dev.ws, m, k, P)
+        say(f"full size rho={rho} it={it}: gtopk_{call} k={k}")
+        gi, gv = getattr(dev, call)()
+        if by_groups:
+            missed = dev.B.gtopk_debug_missed_brackets(dev.ws, m, k, P)
+        else:
+            counts, cap = dev.B.gtopk_debug_candidate_counts(dev.ws, m, k, P)
         li, lv = idx_np(dev.loc_idx), val_np(dev.loc_val)
         out = dev.residual()
         say(f"full size rho={rho} it={it}: oracle")
@@ -92,8 +98,11 @@ def test_full_size_warmup_densities(rho, iters):
             assert bits_equal(out[w], o_res[w]), f"it={it} w={w} residual {first_diff(out[w], o_res[w])}"
         res = o_res
         del out, o_li, o_lv
-        # the timed path: every worker served from its candidate list
-        assert all(k <= c <= cap for c in counts), (rho, it, min(counts), max(counts), cap)
+        # the timed path: every set selected from its bracket, or every worker served from its candidate list
+        if by_groups:
+            assert not any(missed), (rho, it, missed)
+        else:
+            assert all(k <= c <= cap for c in counts), (rho, it, min(counts), max(counts), cap)
 
 
 @pytest.mark.parametrize("name", ["C4a", "C4b"])

@@ -60,15 +60,12 @@ def rows(kind, P, m, k, rng):
         g[:, at] *= 1e4
     elif kind == "sample_small":            # far more than k keys are above the bracket
         g[:, at] *= 1e-4
-    elif kind == "sample_cancels":          # pairs: the sampled sums are nothing, the others double
-        g[:] = g[:1]
-        g[1::2, at] *= -1
-    elif kind == "sample_doubles":
-        s = np.sign(rng.standard_normal((P, m), dtype=np.float32))
-        g = np.abs(g[:1]) * s
-        g[:, at] = np.abs(g[:, at])
-        g[1::2] = -g[0::2]
-        g[1::2, at] *= -1
+    elif kind == "sample_cancels":          # pairs: the sampled sums are nothing
+        g[1::2, at] = -g[0::2, at]
+    elif kind == "sample_doubles":          # pairs: more than half of the sums are nothing, but none of the sampled
+        off = rng.random(m) < 0.7
+        off[at] = False
+        g[1::2] = np.where(off, -g[0::2], g[1::2])
     elif kind == "sample_two_values":       # .. and the other keys around the k-th are too many for a list
         two = np.where(rng.random((P, m)) < 0.5, np.float32(1.0), np.float32(1.0625))
         g = np.where(rng.random((P, m)) < 0.95, two, g)
@@ -94,8 +91,23 @@ CASES = [
     (16, 1_050_003, 262_000, "sample_two_values", 1)]
 
 
+# Kinds that make every worker's set miss its bracket / every pair's of the first round; none of the others' sets do
+MISS_WORKERS = ("sample_large", "sample_small", "sample_two_values", "denormal")
+MISS_PAIRS = ("sample_large", "sample_small", "sample_two_values", "sample_cancels", "sample_doubles", "signs", "plateau")
+
+
+def check_missed(kind, P, missed):
+    first = missed[P:P + P // 2]
+    assert all(missed[:P]) if kind in MISS_WORKERS else not any(missed[:P]), missed
+    assert all(first) if kind in MISS_PAIRS else not any(missed[P:]), missed
+    if kind == "plateau":                   # (pairs of later rounds too)
+        assert any(missed[P + P // 2:]), missed
+
+
 @pytest.mark.parametrize("P,m,k,kind,pad", CASES)
 def test_step_by_index_groups(P, m, k, kind, pad):
+    from paper_1901_04359_amd import binding as B
+    assert B.gtopk_debug_routes(m, k, P)["index_groups"] == -(-m // GROUP)
     rng = np.random.default_rng(P * 7 + m + k)
     dev = Device(P, m, k, stride=m + pad if pad else None)
     res = (rng.standard_normal((P, m), dtype=np.float32) * np.float32(1e-6) if kind == "layers"
@@ -106,6 +118,9 @@ def test_step_by_index_groups(P, m, k, kind, pad):
         dev.set_grad(g)
         say(f"index groups P={P} m={m} k={k} kind={kind} pad={pad} it={it}")
         gi, gv = dev.step()
+        missed = dev.B.gtopk_debug_missed_brackets(dev.ws, m, k, P)
+        say(f"  missed brackets: workers {sum(missed[:P])} of {P}, pairs {sum(missed[P:])} of {P - 1}")
+        check_missed(kind, P, missed)
         exp = dict(zip(("loc_idx", "loc_val", "g_idx", "g_val", "residual"), oracle_step_parallel(res, g, k)))
         li, lv = idx_np(dev.loc_idx), val_np(dev.loc_val)
         for w in range(P):
@@ -138,7 +153,9 @@ def test_ties_in_the_last_of_the_most_groups(m, ties):
     dev = Device(P, m, k)
     dev.set_grad(g)
     say(f"index groups, ties in the last group P={P} m={m} k={k}")
+    assert dev.B.gtopk_debug_routes(m, k, P)["index_groups"] == 8192
     gi, gv = dev.step()
+    assert not any(dev.B.gtopk_debug_missed_brackets(dev.ws, m, k, P))
     exp = dict(zip(("loc_idx", "loc_val", "g_idx", "g_val", "residual"), oracle_step_parallel(np.zeros_like(g), g, k)))
     li, lv = idx_np(dev.loc_idx), val_np(dev.loc_val)
     for w in range(P):

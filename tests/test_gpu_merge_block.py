@@ -31,6 +31,7 @@ def _sets(n, k, kind, overlap, seed):
 def test_merge_in_one_block(k, kind, overlap):
     import torch
     from paper_1901_04359_amd import binding as B
+    assert B.gtopk_debug_routes(k, k, 2)["merge_block"] == (1 if k <= 8192 else 0)
     batch, pad = 3, 5
     idx, val = _sets(2 * batch, k, kind, overlap, 100 * k + len(kind))
     stride = k + pad                            # rows apart, so that none but the first is aligned

@@ -933,14 +933,16 @@ def _small_path_cases(n, seed):
 
 
 def _long_run_cases(n, seed):
-    """Densities at which the candidates are selected run by run where the pass left them."""
+    """Densities at which the candidates are selected run by run where the pass left them: n cases, and those among
+    them that are short enough in m and k for one block per worker."""
     rng = np.random.default_rng(seed)
     cases = []
-    for _ in range(n):
+    while sum(in_place for *_, in_place in cases) < n:
         P = int(rng.choice([1, 2, 4, 8]))
         m = int(rng.choice([rng.integers(40_000, 200_000), rng.integers(200_000, 1_500_000)]))
         rho = float(rng.choice([0.006, 0.01, 0.03, 0.1, 0.25, 0.5, 0.9]))
-        cases.append((P, m, min(m, max(513, int(m * rho))), str(rng.choice(_SWEEP_KINDS)), int(rng.choice([0, 0, 1, 3]))))
+        k = min(m, max(513, int(m * rho)))
+        cases.append((P, m, k, str(rng.choice(_SWEEP_KINDS)), int(rng.choice([0, 0, 1, 3])), m > 1 << 18 or k > 4032))
     return cases
 
 
@@ -972,12 +974,14 @@ def test_step_random_shapes_few_launch_path(P, m, k, kind, pad):
     _check_two_iterations(P, m, k, kind, pad, "few-launch sweep")
 
 
-@pytest.mark.parametrize("P,m,k,kind,pad", _long_run_cases(30, 20261128))
-def test_step_random_shapes_long_runs(P, m, k, kind, pad):
-    """Seeded shapes and value kinds at the densities where the candidates are selected in place."""
+@pytest.mark.parametrize("P,m,k,kind,pad,in_place", _long_run_cases(30, 20261128))
+def test_step_random_shapes_long_runs(P, m, k, kind, pad, in_place):
+    """Seeded shapes and value kinds at the densities where the candidates are selected in place, or by one block."""
     from paper_1901_04359_amd import binding as B
-    plan = B.gtopk_debug_plan(m, k, P)
-    assert plan["small_path"] == 0 and plan["run_groups"] == 1
+    plan, routes = B.gtopk_debug_plan(m, k, P), B.gtopk_debug_routes(m, k, P)
+    in_place = in_place and routes["select_entries"] == 0
+    assert plan["small_path"] == 0 and plan["run_groups"] == (1 if in_place else 0) and routes["index_groups"] == 0
+    assert in_place or routes["select_entries"] > 0
     _check_two_iterations(P, m, k, kind, pad, "long-run sweep")
 
 

@@ -10,17 +10,20 @@ from tests.test_gpu_grouped import rows
 
 pytestmark = pytest.mark.gpu
 
-SIZES = [(8, 30_001, 960, 0), (8, 30_001, 961, 1), (4, 99_999, 1984, 0), (4, 100_000, 1985, 3), (2, 524_288, 4032, 0),
-         (2, 524_289, 4032, 0), (2, 524_288, 4033, 2), (16, 60_007, 600, 0), (2, 4_097, 4_000, 1),
-         # the lines of longer rows: 8 workers and fewer, densities from 0.28 % on for one or two
-         (8, 524_288, 4032, 0), (8, 524_289, 4032, 0), (8, 524_285, 4033, 2), (4, 262_144, 1000, 0), (4, 262_145, 1000, 3),
-         (2, 216_000, 600, 1), (2, 216_001, 600, 0), (1, 200_003, 1500, 0)]
+# P, m, k, elements from the end of a row to the start of the next, entries that a thread holds (0: several kernels)
+SIZES = [(8, 30_001, 960, 0, 4), (8, 30_001, 961, 1, 8), (4, 99_999, 1984, 0, 8), (4, 100_000, 1985, 3, 16), (2, 524_288, 4032, 0, 0),
+         (2, 524_289, 4032, 0, 0), (2, 524_288, 4033, 2, 0), (16, 60_007, 600, 0, 4), (2, 4_097, 4_000, 1, 16),
+         # the lines of longer rows: 8 workers and fewer, and low densities for one or two
+         (8, 524_288, 4032, 0, 16), (8, 524_289, 4032, 0, 0), (8, 524_285, 4033, 2, 0), (4, 262_144, 1000, 0, 8), (4, 262_145, 1000, 3, 0),
+         (2, 216_000, 600, 1, 4), (2, 216_001, 600, 0, 0), (1, 200_003, 1500, 0, 8)]
 
 
 @pytest.mark.parametrize("kind", ["layers", "flat", "rounded", "zeros", "plateau", "levels", "two_values", "sample_large",
                                   "sample_small"])
-@pytest.mark.parametrize("P,m,k,pad", SIZES)
-def test_local_select_in_one_block(P, m, k, pad, kind):
+@pytest.mark.parametrize("P,m,k,pad,entries", SIZES)
+def test_local_select_in_one_block(P, m, k, pad, entries, kind):
+    from paper_1901_04359_amd import binding as B
+    assert B.gtopk_debug_routes(m, k, P)["select_entries"] == entries
     rng = np.random.default_rng(P * 31 + m + k)
     dev = Device(P, m, k, stride=m + pad if pad else None)
     res = (rng.standard_normal((P, m), dtype=np.float32) * np.float32(1e-5)).astype(np.float32)

@@ -27,7 +27,8 @@ def test_merge_batches_at_the_unions_border(kind, k, batch):
 @pytest.mark.parametrize("kind", ["gauss", "ties"])
 @pytest.mark.parametrize("P,m,k,pad,tile,chunk_log2,in_place", [
     # few blocks: chunks down to 4096 elements
-    (2, 33_001, 900, 1, 16, 12, 1),
+    (2, 33_001, 900, 1, 16, 12, 0),      # (one block selects)
+    (2, 33_001, 9000, 1, 16, 12, 1),
     (4, 900_001, 4000, 0, 16, 12, 0),    # runs put into index order
     (4, 1_500_003, 300_000, 3, 16, 12, 1),
     (8, 1_100_003, 5000, 2, 16, 13, 0),

@@ -8,7 +8,7 @@ gtopk_debug_plan; the estimate is modelled here with numpy: the threshold is the
 target-th largest magnitude among the sampled elements, rounded down to the edge of a
 histogram bucket (the sampler's buckets are at most 1/64 of the magnitude wide).  A miss
 would cost time only (the select is exact whatever it filters with), so this is a check of
-the margin, not of correctness."""
+the margin, not of correctness.  The same for both ends of the brackets that steps of large densities take instead."""
 import numpy as np
 import pytest
 
@@ -75,3 +75,53 @@ def test_the_plan_of_the_few_launch_path_has_one_tile_length(m, k, P):
     covered = (plan["small_n_tiles"] - 1) * plan["small_tile_stride"] + plan["tile_len"]
     assert m - plan["small_tile_stride"] < covered                    # tiles up to the row's end
     assert plan["small_n_tiles"] * plan["tile_len"] >= 8_192
+
+
+def _edges(sampled, lo_rank, hi_rank):
+    """A bracket's ends as the kernels take them: the lower edge of the histogram bucket (2^17 keys wide) that lo_rank of the
+    sampled keys reach (0 if the sample is smaller), the lowest edge that at most hi_rank do."""
+    desc = np.sort(sampled)[::-1]
+    lo = int(desc[lo_rank - 1]) >> 17 << 17 if lo_rank <= desc.size else 0
+    return lo, ((int(desc[hi_rank]) >> 17) + 1) << 17
+
+
+@pytest.mark.parametrize("nseg", [1, 8, 54, 400])
+@pytest.mark.parametrize("m,k,P", [
+    (1_048_579, 209_720, 16),                 # the shortest rows, the smallest density for them
+    (1_500_003, 500_000, 16),                 # the largest
+    (4_200_001, 525_001, 2),
+])
+def test_brackets_of_index_groups_hold_the_kth_key(m, k, P, nseg):
+    """Steps of large densities: the k-th key of a row, and of the union of two sets, lies between both ends of its bracket,
+    and the keys inside fit a row's storage.  Rows by the sampler's plan; the union by as many random elements of every
+    group of 8192 as the kernels take scattered ones."""
+    try:
+        plan, routes = B.gtopk_debug_plan(m, k, P), B.gtopk_debug_routes(m, k, P)
+    except OSError as e:          # library not built
+        pytest.skip(str(e))
+    groups = -(-m // 8192)
+    assert routes["index_groups"] == groups
+    t = np.arange(plan["n_tiles"], dtype=np.int64)[:, None] * plan["tile_stride"]
+    pos = (t + np.arange(plan["tile_len"], dtype=np.int64)[None, :]).ravel()
+    pos = pos[pos < m]
+    for trial in range(3):
+        rng = np.random.default_rng(1000 * nseg + trial)
+        first = _row(rng, m, nseg)
+        rows = first, first * rng.uniform(0.5, 1.5, m).astype(np.float32) * np.where(rng.random(m) < 0.5, -1, 1).astype(np.float32)
+        union = np.zeros(m, np.float32)
+        held = np.zeros(m, bool)
+        for row in rows:
+            key = np.abs(row).view(np.uint32)
+            kth = int(np.partition(key, m - k)[m - k])
+            lo, hi = _edges(key[pos], plan["target"], routes["row_target_hi"])
+            assert lo <= kth < hi, (trial, lo, kth, hi)
+            inside = int(((key >= lo) & (key < hi)).sum())
+            assert inside + 4 * groups <= plan["capacity"] and inside < 0.6 * k, (trial, inside)
+            union += np.where(key >= kth, row, np.float32(0.0))
+            held |= key >= kth
+        key = np.abs(union).view(np.uint32)
+        kth = int(np.sort(key[held])[held.sum() - k])
+        at = (np.arange(groups)[:, None] * 8192 + rng.integers(0, 8192, (groups, routes["union_samples"]))).ravel()
+        at = at[at < m]
+        lo, hi = _edges(key[at[held[at]]], routes["union_target_lo"], routes["union_target_hi"])
+        assert lo <= kth < hi, (trial, lo, kth, hi)
