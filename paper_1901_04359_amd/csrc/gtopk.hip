@@ -611,24 +611,35 @@ uint32_t union_bracket_target_hi(double mean) { return bracket_target_hi(mean, 0
 //   m = 30,000  P = 8  k = 1000   86.5 / 45.1     m = 400,000  P = 4   k = 1000  74.2 / 43.8    k = 4000  73.0 / 60.1
 //   m = 100,000 P = 8  k = 4000   92.7 / 73.4     m = 400,000  P = 16  k = 900  123.7 / 62.2
 //   m = 100,000 P = 32 k = 2000  136.3 / 81.6     m = 524,288  P = 32  k = 4000  169 / 119
-// A row that cannot be filtered (its sample misled, or masses of equal values) is read by the one block, and the line in m
-// keeps that within what the general kernels take.  Rows of zeros | of ones, whose residuals after 100 to 200 steps hold
-// many equal values | whose sample misled, in us as above:
+// One worker with more entries loses (k = 4000, m = 262,144 36.8 / 38.7; k = 1000 38.6 / 31.4).
+// A row that cannot be filtered (its sample misled, or masses of equal values) is read by the one block, or by a few where
+// few workers leave the chip idle (row_shares); the line in m keeps that within what the general kernels take.  Rows of zeros |
+// of ones, whose residuals after 100 to 300 steps hold many equal values | whose sample misled, in us as above:
 //   m = 200,000  P = 8   k = 2000   194 / 108 | 172 / 134 | 169 .. 175 / 111 .. 121
 //   m = 524,288  P = 8   k = 2000   291 / 146 | 261 / 191 | 242 .. 260 / 169 .. 190
 //   m = 524,288  P = 32  k = 4000   534 / 232 | 440 / 285 | 443 .. 489 / 238 .. 266
-//   m = 262,144  P = 2   k = 1000   138 /  78 | 129 / 103 | 123 / 93 .. 100
-//   m = 262,144  P = 1   k = 1000   111 /  71 | 106 /  95 |  97 .. 99 / 86 .. 93
-// Few workers leave the chip to the general kernels, which are faster with such rows then (m = 524,288, P = 4, k = 1000
-// 147 / 122 | 130 / 167 | 114 .. 214 / 151 .. 164, P = 1 70 / 102 | 64 / 148 | 54 .. 157 / 133 .. 142; ordinary rows lose some:
-// m = 300,000, P = 4, k = 1000 52.6 / 46.7, P = 1 36.6 / 31.8, m = 500,000, P = 4, k = 4000 62.0 / 63.4), and at densities at which
-// their pass histograms (see below) above 2^17 elements (m = 200,000,
-// P = 2, k = 520 81 / 74 | 79 / 92 | 63 .. 104 / 77 .. 81, ordinary rows 41 / 34; up to there only rows of ones lose, gtopk_local_select
-// at m = 131,072, P = 1, k = 100 49 / 49 | 49 / 59, ordinary rows 33 / 27).
+//   m = 524,288  P = 4   k = 1000   143 /  92 | 139 / 107 | 112 .. 212 / 82 .. 95
+//   m = 262,144  P = 2   k = 1000   138 /  73 | 130 /  87 | 123 / 64 .. 70
+//   m = 524,288  P = 2   k = 1000   101 /  79 |  91 /  95 |  78 .. 180 / 71 .. 81
+// With one worker the general kernels have the whole chip for such rows (m = 524,288, k = 1000 70 / 72 | 64 / 87 |
+// 54 .. 157 / 64 .. 72; m = 200,000, k = 520 60 / 63 | 56 / 72 | 44 .. 83 / 57 .. 62).
 uint32_t select_in_block(int64_t m, uint32_t k, uint32_t P) {
-    if (m > (P < 8 ? 1 << 18 : 1 << 19) || (P < 4 && m > 1 << 17 && 360ull * k < (uint64_t)m)) return 0;
+    if (m > 1 << 19 || (P == 1 && k > 1984)) return 0;
     const uint32_t n = 4 * k + 256;
     return n <= 4096 ? 4 : (n <= 8192 ? 8 : (n <= 16384 ? 16 : 0));
+}
+// Blocks that share a row that cannot be filtered, where few workers leave the chip idle.  A step in us, one block / up to
+// eight, rows of ones | misled samples:  m = 524,288, k = 1000  P = 4  167 / 107 | 151 .. 164 / 82 .. 95   P = 1  148 / 87 | 133 .. 142 /
+// 64 .. 72.  (Rows of 2^17 elements and less gain little: their one block takes some 20 us.)
+uint32_t row_shares(int64_t m, uint32_t k, uint32_t P) {
+    if (P >= 8 || m <= 1 << 17) return 1;
+    uint32_t most = cand_capacity(m, k) / k;                   // their entries lie where the ordered list would
+    if (most > 1024u * kRowPart / k) most = 1024u * kRowPart / k;
+    return most < 8 ? most : 8;
+}
+// What the select of a local selection needs cleared.
+ZeroJob local_clear(const StepWs& w, int64_t m, uint32_t k, uint32_t P) {
+    return select_in_block(m, k, P) ? zero_job(w.sel.list_cnt, (size_t)P) : zero_job(w.sel.hist, select_clear_words(w.sel));
 }
 
 // The pass can also histogram the candidates it keeps; the select's own histogram kernel
@@ -745,7 +756,8 @@ int do_local_select(const float* grad, float* residual, int64_t m, int64_t strid
     const bool producer_hist = filter_rows<true>(grad, residual, m, stride, P, k, w, job, st, events, thr_state, entries == 0);
     const CandSrc src = cand_source(residual, stride, m, k, w, producer_hist, false, thr_state);
     if (entries != 0) {
-#define GTOPK_SELECT(E) hipLaunchKernelGGL(k_small_select<E>, dim3(P), dim3(kSmallBlock), 0, st, src, k, out_idx, out_val, w.sel.T)
+#define GTOPK_SELECT(E) hipLaunchKernelGGL(k_small_select<E>, dim3(P, row_shares(m, k, P)), dim3(kSmallBlock), 0, st, src, k, \
+                                           out_idx, out_val, w.sel.T, w.sel.list_cnt)
         if (entries == 4) GTOPK_SELECT(4);
         else if (entries == 8) GTOPK_SELECT(8);
         else GTOPK_SELECT(16);
@@ -1078,10 +1090,9 @@ int gtopk_local_select(const float* grad, float* residual, int64_t m, int64_t st
         return GTOPK_EALIGN;
     const StepWs w = carve_step(ws, m, (uint32_t)k, (uint32_t)P);
     if (ws_bytes < w.bytes) return GTOPK_EWORKSPACE;
+    const ZeroJob sel = local_clear(w, m, (uint32_t)k, (uint32_t)P);
     return do_local_select(grad, residual, m, stride, (uint32_t)P, (uint32_t)k, out_idx, out_val, w, true,
-                           zero_job(w.samp_hist, w.samp_words, w.cand_count, (size_t)P, w.sel.hist,
-                                    select_in_block(m, (uint32_t)k, (uint32_t)P) ? 0 : select_clear_words(w.sel)),
-                           (hipStream_t)stream);
+                           zero_job(w.samp_hist, w.samp_words, w.cand_count, (size_t)P, sel.p[0], sel.n[0]), (hipStream_t)stream);
 }
 
 int gtopk_merge(const uint32_t* a_idx, const float* a_val, const uint32_t* b_idx, const float* b_val,
@@ -1164,7 +1175,7 @@ static int step_impl(const float* grad, float* residual, int64_t m, int64_t stri
         CandSrc src = cand_source(residual, stride, m, (uint32_t)k, w, false, false);
         src.nchunks = nruns;
         hipLaunchKernelGGL(k_small_select<kSmallEntries>, dim3(P), dim3(kSmallBlock), 0, st, src, (uint32_t)k, li, lv,
-                           (uint32_t*)nullptr);
+                           (uint32_t*)nullptr, (uint32_t*)nullptr);
         // (see tree_round_by_waves; longer sets take the teams of threads)
 #define GTOPK_TREE(E) hipLaunchKernelGGL(k_small_tree<E>, dim3(1), dim3(kSmallBlock), 0, st, li, lv, (uint32_t)P, (uint32_t)k, \
                                          g_idx, g_val, (float)P, residual, stride)
@@ -1181,8 +1192,9 @@ static int step_impl(const float* grad, float* residual, int64_t m, int64_t stri
     // one clear for everything this step needs zeroed: the sampler's histograms and the
     // candidate counters; both selects' histograms and tickets; the global-set bitmap
     const bool in_block = merge_in_block((uint32_t)k);       // its rounds need no select state
-    const ZeroJob job = zero_job(w.samp_hist, w.samp_words, w.cand_count, (size_t)P, w.sel.hist,
-                                 select_in_block(m, (uint32_t)k, (uint32_t)P) ? 0 : select_clear_words(w.sel), w.mrg.sel.hist, in_block ? 0 : select_clear_words(w.mrg.sel),
+    const ZeroJob sel = local_clear(w, m, (uint32_t)k, (uint32_t)P);
+    const ZeroJob job = zero_job(w.samp_hist, w.samp_words, w.cand_count, (size_t)P, sel.p[0], sel.n[0],
+                                 w.mrg.sel.hist, in_block ? 0 : select_clear_words(w.mrg.sel),
                                  w.mrg.sel_alt.hist, in_block ? 0 : w.mrg.alt_clear_words, w.gbits, w.gbits_words);
     int rc = do_local_select(grad, residual, m, stride, (uint32_t)P, (uint32_t)k, li, lv, w, false,
                              job, st, events, thr_state);

@@ -25,6 +25,7 @@ constexpr int kSmallMaxK = 512;
 constexpr int kSmallMaxP = 64;
 constexpr int kSmallEntries = 2;             // entries per thread of a candidate list held in registers
 constexpr int kMidSampleTile = 16;           // elements per tile where it serves rows of millions of elements
+constexpr int kRowPart = 16;                 // entries per thread where the parts of a row come together
 constexpr int kSmallSampleUnroll = 16;       // tiles that each of its groups of lanes keeps in flight
 
 __device__ __forceinline__ uint32_t op_max(uint32_t a, uint32_t b) { return a > b ? a : b; }
@@ -268,17 +269,16 @@ struct DenseShared {
     uint32_t h[kHistBins];                                     // the digits' counts, then the list
     uint32_t wave[kSmallBlock / kWave], out[3];
     uint32_t gt[kSmallBlock / kWave], eq[kSmallBlock / kWave]; // per wave: keys above the k-th, equal to it
-    uint32_t n, ext[2];
+    uint32_t n, ext[2], turn;
 };
 __device__ __forceinline__ uint32_t select_row(DenseShared& sh, TeamShared<1>& team, const float* __restrict__ row, uint32_t m, uint32_t k,
-                                      uint32_t* __restrict__ out_idx, float* __restrict__ out_val) {
+                                               uint32_t first_index, uint32_t* __restrict__ out_idx, float* __restrict__ out_val) {
     constexpr int kT = kSmallBlock, kWaves = kT / kWave, kU = 32;
     constexpr uint32_t kTurn = kWave * kU;
     const uint32_t t = threadIdx.x, lane = lane_id(), wave = (uint32_t)__builtin_amdgcn_readfirstlane((int)(t / kWave));
     const uint32_t turns = (m + kTurn - 1) / kTurn, per = (turns + kWaves - 1) / kWaves;
     const uint32_t first = wave * per, end = first + per < turns ? first + per : turns;
-    // v[j]: element turn * kTurn + j * 64 + lane; behind the row kAbs, the largest key there is, which the counts leave out
-    const uint32_t behind = first < end && end == turns ? turns * kTurn - m : 0u;
+    // v[j]: element turn * kTurn + j * 64 + lane; behind the row zeros, which come after all of its own entries (k <= m)
     uint32_t v[kU];
     auto load = [&](uint32_t turn) {
         const uint32_t at = turn * kTurn;
@@ -290,7 +290,7 @@ __device__ __forceinline__ uint32_t select_row(DenseShared& sh, TeamShared<1>& t
             for (int j = 0; j < kU; ++j) {
                 const uint32_t i = at + j * kWave + lane;
                 const uint32_t x = __float_as_uint(row[i < m ? i : m - 1u]);
-                v[j] = i < m ? x : kAbs;
+                v[j] = i < m ? x : 0u;
             }
         }
     };
@@ -351,7 +351,6 @@ __device__ __forceinline__ uint32_t select_row(DenseShared& sh, TeamShared<1>& t
         uint32_t loc[kPer];
 #pragma unroll
         for (int j = 0; j < kPer; ++j) loc[j] = sh.h[t * kPer + j];
-        if (t == kT - 1) loc[kPer - 1] -= turns * kTurn - m;   // (those behind the row)
         suffix_pick<kPer>(loc, k, sh.wave, sh.out);
         lo = sh.out[0] << kCoarseShift;
         krem = k - sh.out[1];
@@ -404,7 +403,7 @@ __device__ __forceinline__ uint32_t select_row(DenseShared& sh, TeamShared<1>& t
         if (lane == 0) {
             atomicMax(&sh.ext[0], mx);
             atomicMax(&sh.ext[1], mn);
-            sh.gt[wave] = gt - behind;
+            sh.gt[wave] = gt;
             sh.eq[wave] = in;
         }
         __syncthreads();
@@ -448,7 +447,7 @@ __device__ __forceinline__ uint32_t select_row(DenseShared& sh, TeamShared<1>& t
             }
         }
         if (lane == 0) {
-            sh.gt[wave] = gt - behind;
+            sh.gt[wave] = gt;
             sh.eq[wave] = bits == 0u ? in : 0u;
         }
         __syncthreads();
@@ -490,8 +489,8 @@ __device__ __forceinline__ uint32_t select_row(DenseShared& sh, TeamShared<1>& t
             const bool sel = key > T || (key == T && eq + rank_in(eqm) < need);
             const uint64_t sm = __ballot(sel);
             const uint32_t i = turn * kTurn + j * kWave + lane, pos = out + rank_in(sm);
-            if (sel && pos < k && i < m) {                     // (always so, but for keys behind the row)
-                out_idx[pos] = i;
+            if (sel && pos < k && i < m) {                     // (always so)
+                out_idx[pos] = first_index + i;
                 out_val[pos] = __uint_as_float(v[j]);
             }
             out += (uint32_t)__popcll(sm);
@@ -499,6 +498,28 @@ __device__ __forceinline__ uint32_t select_row(DenseShared& sh, TeamShared<1>& t
         }
     }
     return T;
+}
+
+// The k largest of the entries that a block's threads hold in index order, E each (key kNoKey: none); k of them reach `bound`.
+// Returns the k-th key.
+template <int E>
+__device__ __forceinline__ uint32_t select_held(TeamShared<1>& team, const uint32_t (&idx)[E], const uint32_t (&bits)[E],
+                                                const uint32_t (&key)[E], uint32_t bound, uint32_t k, uint32_t* __restrict__ out_idx,
+                                                float* __restrict__ out_val) {
+    const TeamCut cut = team_select<(uint32_t)kSmallBlock>(team, key, bound, k);
+    uint32_t eq = cut.eq, pos = cut.pos;
+#pragma unroll
+    for (int c = 0; c < E; ++c) {
+        if (key[c] == kNoKey) continue;
+        bool sel = key[c] > cut.T;
+        if (key[c] == cut.T) sel = eq++ < cut.need;
+        if (sel && pos < k) {                                  // (always inside)
+            out_idx[pos] = idx[c];
+            out_val[pos] = __uint_as_float(bits[c]);
+            ++pos;
+        }
+    }
+    return cut.T;
 }
 
 // Worker s = blockIdx.x.  The items are the worker's candidate list, or, if the
@@ -510,11 +531,14 @@ __device__ __forceinline__ uint32_t select_row(DenseShared& sh, TeamShared<1>& t
 //   2. up to three LDS radix passes over the keys inside bin d1 -> the exact key T and the
 //      number of ties to take;
 //   3. the emit in index order, run after run in chunk order.
+// Blocks (s, 1) .. share the row of a worker that has to be read whole, gridDim.y * k <= 1024 kRowPart, and return at once
+// from any other (arrived: a word per worker, zero; no block waits for another).
 // E: entries of a candidate list that a thread holds.  T_out != NULL: the smallest key of each set, for what follows in
 // the general path (where thresholds are carried on as well).
 template <int E>
 __global__ __launch_bounds__(kSmallBlock) void k_small_select(
-        CandSrc src, uint32_t k, uint32_t* __restrict__ out_idx, float* __restrict__ out_val, uint32_t* __restrict__ T_out) {
+        CandSrc src, uint32_t k, uint32_t* __restrict__ out_idx, float* __restrict__ out_val, uint32_t* __restrict__ T_out,
+        uint32_t* __restrict__ arrived) {
     constexpr int kT = kSmallBlock;
     __shared__ DenseShared sh;
     __shared__ uint32_t s_rx[kSmallMaxChunks];
@@ -526,14 +550,50 @@ __global__ __launch_bounds__(kSmallBlock) void k_small_select(
     const int s = blockIdx.x;
     const uint32_t t = threadIdx.x;
     if (src.dense(s)) {                                        // block-uniform
-        const uint32_t T = select_row(sh, s_team, src.res + (int64_t)s * src.stride, src.m, k, out_idx + (size_t)s * k,
-                                      out_val + (size_t)s * k);
+        const float* row = src.res + (int64_t)s * src.stride;
+        uint32_t T;
+        if (gridDim.y == 1u) {
+            T = select_row(sh, s_team, row, src.m, k, 0u, out_idx + (size_t)s * k, out_val + (size_t)s * k);
+        } else {
+            // every block selects k entries of its part of the row; the last to be done selects among those
+            const uint32_t len = ((src.m + gridDim.y - 1u) / gridDim.y + 1023u) & ~1023u, first = blockIdx.y * len;
+            const size_t part = (size_t)s * src.cap + (size_t)blockIdx.y * k;
+            uint32_t* bounds = src.run_off + (size_t)s * src.nchunks;        // (not in use here, as the ordered list is not)
+            T = select_row(sh, s_team, row + first, src.m - first < len ? src.m - first : len, k, first, src.ord_idx + part,
+                           src.ord_val + part);
+            if (t == 0) bounds[blockIdx.y] = T;
+            // (every wave's stores have reached the L2 before the block meets; then one fence writes them back for the last
+            // block, which may sit on another XCD)
+            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+            __syncthreads();
+            if (t == 0) {
+                __threadfence();
+                sh.turn = atomicAdd(&arrived[s], 1u);
+            }
+            clear_teams(s_team);
+            __syncthreads();
+            if (sh.turn != gridDim.y - 1u) return;             // block-uniform
+            __threadfence();
+            const uint32_t n = gridDim.y * k;                  // <= 1024 kRowPart
+            uint32_t idx[kRowPart], bits[kRowPart], key[kRowPart], bound = 0;
+            for (uint32_t y = 0; y < gridDim.y; ++y) bound = op_max(bound, bounds[y]);
+#pragma unroll
+            for (int c = 0; c < kRowPart; ++c) {
+                const uint32_t e = t * kRowPart + c;
+                const size_t at = (size_t)s * src.cap + (e < n ? e : 0u);
+                idx[c] = src.ord_idx[at];
+                bits[c] = __float_as_uint(src.ord_val[at]);
+                key[c] = e < n ? bits[c] & kAbs : kNoKey;
+            }
+            T = select_held(s_team, idx, bits, key, bound, k, out_idx + (size_t)s * k, out_val + (size_t)s * k);
+        }
         if (T_out && t == 0) {
             T_out[s] = T;
             src.carry(s, T);
         }
         return;
     }
+    if (blockIdx.y != 0u) return;
     const uint32_t n = src.nphys(s, false);
     if (n <= (uint32_t)(E * kT)) {
         // ---- a short candidate list: every thread takes E consecutive entries in index order (run after run in
@@ -567,22 +627,10 @@ __global__ __launch_bounds__(kSmallBlock) void k_small_select(
                 key[c] = bits[c] & kAbs;
             }
         }
-        const TeamCut cut = team_select<kT>(s_team, key, src.tspec[s], k);
+        const uint32_t T = select_held(s_team, idx, bits, key, src.tspec[s], k, out_idx + (size_t)s * k, out_val + (size_t)s * k);
         if (T_out && t == 0) {
-            T_out[s] = cut.T;
-            src.carry(s, cut.T);
-        }
-        uint32_t eq = cut.eq, pos = cut.pos;
-#pragma unroll
-        for (int c = 0; c < kPer; ++c) {
-            if (key[c] == kNoKey) continue;
-            bool sel = key[c] > cut.T;
-            if (key[c] == cut.T) sel = eq++ < cut.need;
-            if (sel && pos < k) {                              // (always inside)
-                out_idx[(size_t)s * k + pos] = idx[c];
-                out_val[(size_t)s * k + pos] = __uint_as_float(bits[c]);
-                ++pos;
-            }
+            T_out[s] = T;
+            src.carry(s, T);
         }
         return;
     }

@@ -942,7 +942,7 @@ def _long_run_cases(n, seed):
         m = int(rng.choice([rng.integers(40_000, 200_000), rng.integers(200_000, 1_500_000)]))
         rho = float(rng.choice([0.006, 0.01, 0.03, 0.1, 0.25, 0.5, 0.9]))
         k = min(m, max(513, int(m * rho)))
-        cases.append((P, m, k, str(rng.choice(_SWEEP_KINDS)), int(rng.choice([0, 0, 1, 3])), m > 1 << 18 or k > 4032))
+        cases.append((P, m, k, str(rng.choice(_SWEEP_KINDS)), int(rng.choice([0, 0, 1, 3])), m > 1 << 19 or k > (4032 if P > 1 else 1984)))
     return cases
 
 
@@ -979,9 +979,8 @@ def test_step_random_shapes_long_runs(P, m, k, kind, pad, in_place):
     """Seeded shapes and value kinds at the densities where the candidates are selected in place, or by one block."""
     from paper_1901_04359_amd import binding as B
     plan, routes = B.gtopk_debug_plan(m, k, P), B.gtopk_debug_routes(m, k, P)
-    in_place = in_place and routes["select_entries"] == 0
     assert plan["small_path"] == 0 and plan["run_groups"] == (1 if in_place else 0) and routes["index_groups"] == 0
-    assert in_place or routes["select_entries"] > 0
+    assert (routes["select_entries"] == 0) == in_place
     _check_two_iterations(P, m, k, kind, pad, "long-run sweep")
 
 

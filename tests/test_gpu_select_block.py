@@ -1,6 +1,6 @@
-"""The local selection of medium rows by one block per worker, GPU against the oracle, bit for bit, through
-gtopk_local_select, gtopk_step and gtopk_step_carry: both sides of every size at which a thread holds more entries and of
-the largest, and rows whose list cannot be used or does not fit a block's registers."""
+"""The local selection of medium rows by one block per worker (rows that cannot be filtered: by up to eight), GPU
+against the oracle, bit for bit, through gtopk_local_select, gtopk_step and gtopk_step_carry: both sides of every size at
+which a thread holds more entries and of the largest, and rows whose list cannot be used or does not fit a block's registers."""
 import numpy as np
 import pytest
 
@@ -11,11 +11,11 @@ from tests.test_gpu_grouped import rows
 pytestmark = pytest.mark.gpu
 
 # P, m, k, elements from the end of a row to the start of the next, entries that a thread holds (0: several kernels)
-SIZES = [(8, 30_001, 960, 0, 4), (8, 30_001, 961, 1, 8), (4, 99_999, 1984, 0, 8), (4, 100_000, 1985, 3, 16), (2, 524_288, 4032, 0, 0),
-         (2, 524_289, 4032, 0, 0), (2, 524_288, 4033, 2, 0), (16, 60_007, 600, 0, 4), (2, 4_097, 4_000, 1, 16),
-         # the lines of longer rows: 8 workers and fewer, and low densities for one or two
-         (8, 524_288, 4032, 0, 16), (8, 524_289, 4032, 0, 0), (8, 524_285, 4033, 2, 0), (4, 262_144, 1000, 0, 8), (4, 262_145, 1000, 3, 0),
-         (2, 216_000, 600, 1, 4), (2, 216_001, 600, 0, 0), (1, 200_003, 1500, 0, 8)]
+SIZES = [(8, 30_001, 960, 0, 4), (8, 30_001, 961, 1, 8), (4, 99_999, 1984, 0, 8), (4, 100_000, 1985, 3, 16), (2, 524_288, 4032, 0, 16),
+         (2, 524_289, 4032, 0, 0), (2, 524_288, 4033, 2, 0), (16, 60_007, 600, 0, 4), (2, 4_097, 4_000, 1, 16), (8, 524_285, 4032, 2, 16),
+         # a row is shared by several blocks: from 2^17 elements on, fewer than 8 workers, eight blocks to four
+         (4, 131_072, 1000, 0, 8), (4, 131_073, 1000, 3, 8), (8, 131_073, 520, 0, 4), (1, 262_145, 1638, 0, 8), (2, 200_003, 1639, 1, 8),
+         (4, 150_001, 2731, 0, 16), (2, 140_000, 20, 1, 4)]
 
 
 @pytest.mark.parametrize("kind", ["layers", "flat", "rounded", "zeros", "plateau", "levels", "two_values", "sample_large",
