@@ -893,11 +893,11 @@ __device__ __forceinline__ void tree_round_by_waves(TreeShared& sh, uint32_t pai
         tree_union<E>(sh, q, k, from, lane, (2 * k + kWave - 1) / kWave, oi, ov);
 #pragma unroll
         for (int j = 0; j < E; ++j) key[j] = oi[j] != kTomb ? ov[j] & kAbs : kNoKey;
-        // distances from a bound that k keys reach: the larger of the operands' smallest keys, unless sums cancel
-        auto reach = [&](uint32_t least) {                   // (never kNoKey)
+        // a bound that k keys reach: the larger of the operands' smallest keys, unless sums cancel
+        auto reach = [&](uint32_t least) {                   // (never kNoKey; none reach a least above kAbs, which the search may try)
             uint32_t n = 0;
 #pragma unroll
-            for (int j = 0; j < E; ++j) n += (uint32_t)__popcll(__ballot(key[j] - least <= kAbs - least));
+            for (int j = 0; j < E; ++j) n += (uint32_t)__popcll(__ballot(key[j] + 1u > least));
             return n;
         };
         uint32_t base = op_max(sh.min[turn_min][2 * q], sh.min[turn_min][2 * q + 1]);
