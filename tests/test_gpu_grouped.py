@@ -55,6 +55,10 @@ def rows(kind, P, m, k, rng):
             lo = m * w // P
             g[w, lo:lo + m // P] *= 1e4
         return g
+    if kind == "infinite":                  # fewer than k of a row, more of a pair's union
+        return np.where(rng.random((P, m)) < 0.6 * k / m, np.float32(np.inf), g).astype(np.float32)
+    if kind == "nan":
+        return np.where(rng.random((P, m)) < 0.9, np.float32(np.nan), g).astype(np.float32)
     at = sampled_positions(m, k, P)
     if kind == "sample_large":              # fewer than k keys reach the threshold
         g[:, at] *= 1e4
@@ -76,7 +80,7 @@ def rows(kind, P, m, k, rng):
 
 
 KINDS = ("zeros", "some_zero_rows", "signs", "rounded", "denormal", "cancel", "same", "plateau", "apart", "sample_large",
-         "sample_small", "sample_cancels", "sample_doubles")
+         "sample_small", "sample_cancels", "sample_doubles", "infinite", "nan")
 CASES = [
     # P, m, k, kind, elements from the end of a row to the start of the next
     (16, 128 * GROUP, 209_716, "layers", 0),            # the shortest rows, the smallest k for them
@@ -92,8 +96,9 @@ CASES = [
 
 
 # Kinds that make every worker's set miss its bracket / every pair's of the first round; none of the others' sets do
-MISS_WORKERS = ("sample_large", "sample_small", "sample_two_values", "denormal")
-MISS_PAIRS = ("sample_large", "sample_small", "sample_two_values", "sample_cancels", "sample_doubles", "signs", "plateau")
+MISS_WORKERS = ("sample_large", "sample_small", "sample_two_values", "denormal", "nan")
+MISS_PAIRS = ("sample_large", "sample_small", "sample_two_values", "sample_cancels", "sample_doubles", "signs", "plateau", "infinite",
+              "nan")
 
 
 def check_missed(kind, P, missed):

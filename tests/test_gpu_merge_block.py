@@ -22,11 +22,13 @@ def _sets(n, k, kind, overlap, seed):
         val = np.copysign(np.float32(0.25), val)
     elif kind == "wide":                        # keys over the whole range of the type, denormals and huge ones
         val = (val * np.exp2(rng.integers(-148, 120, val.shape))).astype(np.float32)
+    elif kind in ("infinite", "nan"):           # fewer than k of a set, more of a pair's union
+        val = np.where(rng.random(val.shape) < 0.7, np.float32(np.inf if kind == "infinite" else np.nan), val)
     return idx, val
 
 
 @pytest.mark.parametrize("kind,overlap", [("gauss", 0.0), ("gauss", 0.5), ("ties", 0.4), ("cancel", 1.0), ("zeros", 0.3),
-                                          ("equal", 0.5), ("wide", 0.2)])
+                                          ("equal", 0.5), ("wide", 0.2), ("infinite", 0.1), ("nan", 0.1)])
 @pytest.mark.parametrize("k", [1, 3, 511, 512, 1023, 1024, 1025, 2048, 2049, 4095, 4096, 4097, 6001, 8191, 8192, 8193])
 def test_merge_in_one_block(k, kind, overlap):
     import torch

@@ -19,7 +19,7 @@ SIZES = [(8, 30_001, 960, 0, 4), (8, 30_001, 961, 1, 8), (4, 99_999, 1984, 0, 8)
 
 
 @pytest.mark.parametrize("kind", ["layers", "flat", "rounded", "zeros", "plateau", "levels", "two_values", "sample_large",
-                                  "sample_small"])
+                                  "sample_small", "infinite", "nan"])
 @pytest.mark.parametrize("P,m,k,pad,entries", SIZES)
 def test_local_select_in_one_block(P, m, k, pad, entries, kind):
     from paper_1901_04359_amd import binding as B
