@@ -107,7 +107,8 @@ struct Bracket {
 };
 
 // Which of a group's elements stand for it in the sample of a union: of the 1024 that a wave holds, q lanes of
-// one step.  Scattered by a hash, so that no period of the data falls in with them.
+// one step.  Scattered by a hash (odd multipliers and xor-shifts, any that mix the low bits serve), so that no period of the
+// data falls in with them.
 __device__ __forceinline__ uint32_t sample_hash(uint32_t g, uint32_t wave) {
     uint32_t h = g * 0x9E3779B1u + wave * 0x85EBCA6Bu;
     h ^= h >> 15;
@@ -131,8 +132,8 @@ __device__ __forceinline__ uint32_t sample_lane(uint32_t h, uint32_t l, uint32_t
 // Blocks are half as long as k_accum_filter's, and each XCD streams one eighth of all rows from end to end instead of
 // every eighth chunk (at m = 25,557,032, P = 32, k = 6.4 M / 1.85 M: 1743 / 1715 us with blocks of 2^15 in the order of their
 // numbers, 1719 / 1699 by XCD, 1704 / 1688 with blocks of 2^14).
-// Bound by HBM as k_accum_filter is, and without its candidate lists: at m = 25,557,032, P = 32, k = 6.4 M
-// (k = 1.85 M) it writes 0.12 (0.06) GB behind the row where the lists took 1.9 (0.6) GB.
+// Bound by HBM as k_accum_filter is, and without its candidate lists: at m = 25,557,032, P = 32, k = 6.4 M it writes
+// 0.25 GB behind the rows (3.52 GB by the counters, 3.27 the rows) where the lists took 1.9 GB.
 constexpr int kGrpPassIters = 8;                        // float4 per lane and array: blocks of 2^14 elements
 constexpr uint32_t kGrpPassChunk = kGrpPassIters * 4 * kSBlock;
 __global__ __launch_bounds__(kSBlock) void k_group_pass(
@@ -1343,8 +1344,8 @@ __device__ __forceinline__ void select_pair(GroupShared& sh, const GroupSets& gs
 // Block (g, p): group g of workers 2p and 2p + 1.  Only the stretches that hold candidates are read.  bits: one bit per
 // element of a row, the worker's set (for the restore).
 // Bound by instruction issue as much as by memory (some 70 vector and 60 scalar instructions per 64 elements of the pair before
-// keys were compared as numbers and steps without candidates skipped, half of that now): 714 us for 3.4 GB = 4.8 TB/s at
-// m = 25,557,032, P = 32, k = 6.4 M.  64 registers, so that four blocks share a CU: with spills 803 us.
+// keys were compared as numbers and steps without candidates skipped, half of that now): 880 us for 4.2 GB (by the counters) =
+// 4.8 TB/s at m = 25,557,032, P = 32, k = 6.4 M; 720 us where fewer stretches hold candidates.  64 registers, so that four blocks share a CU: with spills 803 us.
 __global__ __launch_bounds__(kGrpBlock) __attribute__((amdgpu_waves_per_eu(8, 8))) void k_group_select(
         GroupSets gs, GroupNext nx, const float* __restrict__ rows, int64_t stride, uint32_t k, uint32_t* __restrict__ out_idx,
         float* __restrict__ out_val, uint64_t* __restrict__ bits) {
