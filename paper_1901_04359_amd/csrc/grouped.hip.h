@@ -584,7 +584,8 @@ __device__ inline void count_all(const GroupSets& gs, const GroupBatch& gb, uint
 #pragma unroll
             for (int j = 0; j < kU; ++j) {
                 const uint32_t i = i0 + j * kWave + lane_id();
-                key[j] = i < gs.m ? present_key(__float_as_uint(row[i])) : kAbsent;
+                const uint32_t x = __float_as_uint(row[i < gs.m ? i : 0u]);      // (in flight together, see finish_set)
+                key[j] = i < gs.m ? present_key(x) : kAbsent;
             }
 #pragma unroll
             for (int j = 0; j < kU; ++j) count(key[j]);
@@ -646,7 +647,7 @@ __global__ __launch_bounds__(kGrpWalkBlock) void k_group_walk(GroupSets gs, Grou
     const uint32_t g0 = ((blockIdx.x - 1u) * kWaves + wave) * kGrpWalkRuns;
     const uint32_t* keys = gb.keys + (size_t)blockIdx.y * gb.key_stride;
     // (the runs' first keys are fetched in front of the pick, which hides their latency)
-    constexpr int kU = 4;
+    constexpr int kU = 4, kBatch = 16;
     uint4 runs[kGrpWalkRuns];
     uint32_t ahead[kGrpWalkRuns][kU];
 #pragma unroll
@@ -683,7 +684,15 @@ __global__ __launch_bounds__(kGrpWalkBlock) void k_group_walk(GroupSets gs, Grou
         const uint4 run = runs[q];
         uint32_t gt = run.z, mx = 0, mn = kAbs, in = 0, own_gt = 0;
         const bool plain = run.w == kPlainRun;
-        auto key_at = [&](uint32_t i) { return i < run.y ? keys[run.x + i] : kAbsent; };
+        // keys [i0, i0 + 64 kBatch) of the run, a lane's in step
+        uint32_t key[kBatch];
+        auto load = [&](uint32_t i0) {
+#pragma unroll
+            for (int u = 0; u < kBatch; ++u) {
+                const uint32_t i = i0 + u * kWave + lane, x = keys[run.x + (i < run.y ? i : 0u)];
+                key[u] = i < run.y ? x : kAbsent;
+            }
+        };
         // (the row's last elements on v belong to this group: up to three keys of their own)
         uint32_t tk = kAbsent;
         if (head && lane < 3u && ((uint64_t)(g + 1u) << kGroupLog2) < (uint64_t)gs.m + head)
@@ -697,21 +706,22 @@ __global__ __launch_bounds__(kGrpWalkBlock) void k_group_walk(GroupSets gs, Grou
             }
         }
         if (plain) {
-            for (uint32_t i0 = 0; i0 < run.y; i0 += kWave * kU) {
-                uint32_t key[kU];
-#pragma unroll
-                for (int u = 0; u < kU; ++u) key[u] = i0 == 0u ? ahead[q][u] : key_at(i0 + u * kWave + lane);
-#pragma unroll
-                for (int u = 0; u < kU; ++u) {
-                    if (key[u] == kAbsent) continue;
-                    const uint32_t b = bk.bin(key[u]);
-                    if (b > d1) ++own_gt;
-                    else if (b == d1) {
-                        ++in;
-                        mx = key[u] > mx ? key[u] : mx;
-                        mn = key[u] < mn ? key[u] : mn;
-                    }
+            auto see = [&](uint32_t x) {
+                if (x == kAbsent) return;
+                const uint32_t b = bk.bin(x);
+                if (b > d1) ++own_gt;
+                else if (b == d1) {
+                    ++in;
+                    mx = x > mx ? x : mx;
+                    mn = x < mn ? x : mn;
                 }
+            };
+#pragma unroll
+            for (int u = 0; u < kU; ++u) see(ahead[q][u]);
+            for (uint32_t i0 = kWave * kU; i0 < run.y; i0 += kWave * kBatch) {
+                load(i0);
+#pragma unroll
+                for (int u = 0; u < kBatch; ++u) see(key[u]);
             }
         } else if (lane == 0) {
             const uint32_t b = bk.bin(run.w);
@@ -759,9 +769,10 @@ __global__ __launch_bounds__(kGrpWalkBlock) void k_group_walk(GroupSets gs, Grou
         };
         put(tail_in, tk, 1u);
         if (plain) {
-            for (uint32_t i0 = 0; i0 < run.y; i0 += kWave) {
-                const uint32_t key = key_at(i0 + lane);
-                put(key != kAbsent && bk.bin(key) == d1, key, 1u);
+            for (uint32_t i0 = 0; i0 < run.y; i0 += kWave * kBatch) {
+                load(i0);
+#pragma unroll
+                for (int u = 0; u < kBatch; ++u) put(key[u] != kAbsent && bk.bin(key[u]) == d1, key[u], 1u);
             }
         } else {
             put(lane == 0 && run_in, run.w, run.y);
@@ -818,7 +829,8 @@ __device__ inline void collect_missed(const GroupSets& gs, const GroupBatch& gb,
 #pragma unroll
             for (int j = 0; j < kU; ++j) {
                 const uint32_t i = turn * (kWave * kU) + j * kWave + lane;
-                key[j] = i < count ? present_key(from[i]) : kAbsent;
+                const uint32_t x = from[i < count ? i : 0u];
+                key[j] = i < count ? present_key(x) : kAbsent;
             }
         };
         // (all wave-uniform) keys above, entries; turns with any, turns whose keys agree
@@ -963,7 +975,8 @@ __device__ __forceinline__ void finish_set(FinishShared& sh, const GroupSets& gs
 #pragma unroll
                     for (int j = 0; j < kU; ++j) {
                         const uint32_t i = i0 + j * kWave + lane_id();
-                        x[j] = i < count ? present_key(from[i]) : kAbsent;
+                        const uint32_t y = from[i < count ? i : 0u];
+                        x[j] = i < count ? present_key(y) : kAbsent;
                     }
 #pragma unroll
                     for (int j = 0; j < kU; ++j) f(x[j], g, 1u);
