@@ -442,7 +442,10 @@ GroupWs carve_grouped(const StepWs& s, int64_t m, uint32_t k, uint32_t P) {
 // of one magnitude 188 / 4.7 ms, values rounded to integers 52.8 / 5.7 ms.)
 static bool grouped_step(int64_t m, uint32_t k, uint32_t P, const StepWs& s) {
     const uint64_t n = (uint64_t)m;
-    const bool size = (n >= (1u << 22) && 8ull * k >= n) || (n >= (1u << 20) && n * P >= (1u << 24) && 5ull * k >= n);
+    uint32_t rounds = 0;
+    while (2u << rounds <= P) ++rounds;
+    const bool entries = 5ull * P * k >= (uint64_t)(rounds + 2) << 22;
+    const bool size = (n >= (1u << 22) && 8ull * k >= n) || (n >= (1u << 20) && 5ull * k >= n && entries);
     return P >= 2 && size && 3ull * k <= n && carve_grouped(s, m, k, P).fits;
 }
 

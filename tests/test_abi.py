@@ -228,8 +228,11 @@ def test_debug_routes():
     assert r(25_557_032, 6_389_258, 32)["index_groups"] == 3120
     assert r(4_194_304, 524_288, 2)["index_groups"] == 512 and r(4_194_304, 524_287, 2)["index_groups"] == 0
     assert r(4_194_303, 524_288, 2)["index_groups"] == 0
-    assert r(1_048_576, 209_716, 16)["index_groups"] == 128 and r(1_048_576, 209_715, 16)["index_groups"] == 0
-    assert r(1_048_575, 209_716, 16)["index_groups"] == 0 and r(1_048_576, 209_716, 8)["index_groups"] == 0
+    assert r(1_048_576, 209_716, 32)["index_groups"] == 128 and r(1_048_576, 209_715, 32)["index_groups"] == 0
+    assert r(1_048_575, 209_716, 32)["index_groups"] == 0 and r(1_048_576, 209_716, 16)["index_groups"] == 0
+    # .. rows below 2^22 elements: entries of all workers, by the number of rounds
+    assert r(1_048_576, 314_573, 16)["index_groups"] == 128 and r(1_048_576, 314_572, 16)["index_groups"] == 0
+    assert r(2_097_152, 524_288, 8)["index_groups"] == 256 and r(2_097_152, 524_287, 8)["index_groups"] == 0
     assert r(3_000_000, 1_000_000, 8)["index_groups"] == 367 and r(3_000_000, 1_000_001, 8)["index_groups"] == 0
     assert r(25_557_032, 6_389_258, 1)["index_groups"] == 0
     assert r(8192 * 8192, 8_388_608, 2)["index_groups"] == 8192 and r(8192 * 8192 + 1, 8_388_609, 2)["index_groups"] == 0

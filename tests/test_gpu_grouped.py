@@ -83,16 +83,17 @@ KINDS = ("zeros", "some_zero_rows", "signs", "rounded", "denormal", "cancel", "s
          "sample_small", "sample_cancels", "sample_doubles", "infinite", "nan")
 CASES = [
     # P, m, k, kind, elements from the end of a row to the start of the next
-    (16, 128 * GROUP, 209_716, "layers", 0),            # the shortest rows, the smallest k for them
+    (32, 128 * GROUP, 209_716, "layers", 0),            # the shortest rows, the smallest k for them
+    (16, 128 * GROUP, 314_573, "layers", 0),            # the fewest entries of all workers
     (16, 128 * GROUP + 1, 349_525, "flat", 0),          # the largest k
-    (16, 129 * GROUP - 1, 264_191, "layers", 2),
+    (16, 129 * GROUP - 1, 330_001, "layers", 2),
     (32, 128 * GROUP + 255, 262_000, "layers", 258),
-    (8, 256 * GROUP + 3, 500_001, "layers", 0),
+    (8, 256 * GROUP + 3, 530_001, "layers", 0),
     (2, 512 * GROUP + 1, 524_289, "layers", 0),         # one round; the smallest density
     (4, 520 * GROUP - 3, 532_480, "flat", 1),
-] + [(16, 1_050_003, 262_000, kind, pad) for pad, kind in enumerate(KINDS)] + [
+] + [(16, 1_050_003, 316_000, kind, pad) for pad, kind in enumerate(KINDS)] + [
     (2, 4_200_001, 530_000, kind, 0) for kind in ("zeros", "sample_large", "sample_small", "sample_cancels")] + [
-    (16, 1_050_003, 262_000, "sample_two_values", 1)]
+    (16, 1_050_003, 316_000, "sample_two_values", 1)]
 
 
 # Kinds that make every worker's set miss its bracket / every pair's of the first round; none of the others' sets do

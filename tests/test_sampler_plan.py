@@ -87,7 +87,7 @@ def _edges(sampled, lo_rank, hi_rank):
 
 @pytest.mark.parametrize("nseg", [1, 8, 54, 400])
 @pytest.mark.parametrize("m,k,P", [
-    (1_048_579, 209_720, 16),                 # the shortest rows, the smallest density for them
+    (1_048_579, 209_720, 32),                 # the shortest rows, the smallest density for them
     (1_500_003, 500_000, 16),                 # the largest
     (4_200_001, 525_001, 2),
 ])
