@@ -525,7 +525,9 @@ __device__ __forceinline__ uint32_t select_held(TeamShared<1>& team, const uint3
 // Worker s = blockIdx.x.  The items are the worker's candidate list, or, if the
 // speculative threshold left fewer than k candidates or more than the list holds, its
 // dense row (select_row).  A candidate list of at most
-// 1024 E entries is held in registers and selected from by the block as one team.  A longer one takes
+// 1024 E entries is held in registers and selected from by the block as one team, as few entries per thread as the list
+// takes (gtopk_local_select in us, E entries for the first threads, loaded one after the other / this: m = 400,000, P = 4, k = 4000
+// 45 / 38; m = 200,000, P = 8, k = 2000 46 / 37, three kernels 41; m = 524,288, P = 1, k = 1000 33 / 29).  A longer one takes
 // three stages, each a walk over it:
 //   1. LDS histogram of the first digit -> the bin d1 of the k-th key;
 //   2. up to three LDS radix passes over the keys inside bin d1 -> the exact key T and the
@@ -607,26 +609,29 @@ __global__ __launch_bounds__(kSmallBlock) void k_small_select(
         if (t < nruns) { s_rx[t] = run.x; s_roff[t + 1] = incl; }
         if (t == 0) s_roff[0] = 0u;
         __syncthreads();
-        constexpr int kPer = E;
-        uint32_t idx[kPer], bits[kPer], key[kPer];
+        // (as few entries per thread as the list takes, so that all waves share it; their loads in flight together)
+        const uint32_t ept = (n + kT - 1) / kT;                // <= E
+        const uint32_t entry = t * ept < n ? t * ept : n - 1u; // (k <= n; a thread without any entry repeats the last)
+        uint32_t idx[E], bits[E], key[E];
         uint32_t r = 0;
         {
-            uint32_t hi = nruns;                               // the run r with roff[r] <= first entry < roff[r+1]
+            uint32_t hi = nruns;                               // the run r with roff[r] <= entry < roff[r+1]
             while (hi - r > 1) {
                 const uint32_t mid = (r + hi) >> 1;
-                if (s_roff[mid] <= t * kPer) r = mid; else hi = mid;
+                if (s_roff[mid] <= entry) r = mid; else hi = mid;
             }
         }
 #pragma unroll
-        for (int c = 0; c < kPer; ++c) {
-            const uint32_t lp = t * kPer + c;
-            idx[c] = 0u; bits[c] = 0u; key[c] = kNoKey;
-            if (lp < n) {
+        for (int c = 0; c < E; ++c) {
+            idx[c] = 0u; bits[c] = 0u;
+            if ((uint32_t)c < ept) {                           // block-uniform
+                const uint32_t lp = entry + c < n ? entry + c : n - 1u;
                 while (s_roff[r + 1] <= lp) ++r;               // (r + 1 <= nruns: the last run ends at n)
                 src.fetch_phys(s, false, s_rx[r] + (lp - s_roff[r]), idx[c], bits[c]);
-                key[c] = bits[c] & kAbs;
             }
         }
+#pragma unroll
+        for (int c = 0; c < E; ++c) key[c] = (uint32_t)c < ept && t * ept + c < n ? bits[c] & kAbs : kNoKey;
         const uint32_t T = select_held(s_team, idx, bits, key, src.tspec[s], k, out_idx + (size_t)s * k, out_val + (size_t)s * k);
         if (T_out && t == 0) {
             T_out[s] = T;
