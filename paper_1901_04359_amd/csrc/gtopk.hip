@@ -835,7 +835,8 @@ inline void launch_union_cuts(const uint32_t* a_idx, const uint32_t* b_idx, uint
 // Longer ones, with 32 slots per thread, lose: k = 12,000 63.0 / 102, 24.6 / 34.3 | 33.5 / 34.5.
 // More pairs gain more: k = 1000 256 | 4096 pairs  34.7 / 9.9 | 227 / 64.1   k = 8192 64 | 1024 pairs  80.3 / 31.6 | 358 / 99.1.
 // Sets of one magnitude, whose keys all fall into one bin, take longer either way: k = 1000, 1 pair  30.6 / 13.9   k = 8192, 1 | 16
-// pairs 63.5 / 57.3 | 103 / 57.4.  The one slower kind found: a tree of 8 sets of 8192 that lie behind one another, 61.0 / 63.8.
+// pairs 63.5 / 57.3 | 103 / 57.4.  The one slower kind found: trees of sets that lie behind one another, 8 of 6000 |
+// 8192 entries 58 / 60 | 59 / 67.
 inline bool merge_in_block(uint32_t k) { return k <= kMergeBlockMaxK; }
 template <bool DIVIDE>
 void launch_merge_block(const uint32_t* a_idx, const float* a_val, const uint32_t* b_idx, const float* b_val, uint32_t k,
