@@ -137,8 +137,8 @@ int gtopk_residual_restore(float* residual, int64_t m, int64_t stride, int32_t P
  * speculative threshold of a worker in one block, the streaming pass, the exact local
  * selection of a worker in one block, the whole tree with the average and the extra
  * residual in one block.
- * Large densities (P >= 2; k from m/8 on for m >= 2^22, from m/5 on for m >= 2^20 and m*P >= 2^24; k up to m/3;
- * m <= 2^26) go by index groups of the rows instead of candidate lists, which is some 1.1 to 1.6 times as fast.
+ * Large densities (P >= 2; k from m/8 on for m >= 2^22, from m/5 on for m >= 2^20 and
+ * 5*P*k >= (2 + log2 P) * 2^22; k up to m/3; m <= 2^26) go by index groups of the rows instead of candidate lists, which is some 1.1 to 1.6 times as fast.
  * gtopk_step_carry and the three calls in sequence keep the lists there, with the same results: at these
  * densities a step with carried thresholds is the slower one.
  *   m : 1 .. 2^31;  k : 1 .. m (and <= 2^30 if P > 1);  P : a power of two, 1 .. 32768;

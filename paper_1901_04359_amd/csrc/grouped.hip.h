@@ -23,11 +23,14 @@
 // Every list is written once and read once per round, no merged set is ever stored, and no cut point is
 // searched for: the sub-lists of a group are known from the groups' output positions.
 // A set whose k-th key lies outside its bracket (the sample misled) is counted whole by k_group_walk and gets another
-// bracket from that, whose keys several blocks of k_group_finish collect.  A step whose rows are made to mislead the sampler, in
-// us (lists / one block of k_group_finish reads all keys / now; without such rows 690 and 4750):
-//   m = 25.6 M  P = 4   k = m/4   one row of the four 1990 .. 2970 / 43,300 / 2520   all 3920 .. 6570 / 55,500 / 2770
-//   m = 25.6 M  P = 32  k = m/4   one row             8140 .. 9010 / 49,400 / 9530   all 26,900 .. 43,300 / 67,800 / 13,100
-//   m = 4.2 M   P = 4   k = m/8   one row               320 .. 440 / 6200 / 690      all     580 .. 850 / 6200 / 680
+// bracket from that, whose keys several blocks of k_group_finish collect.  A step whose rows all mislead the sampler, of 24
+// layers, in us (lists / this; with one block of k_group_finish that reads all keys 6200 at the third of these sizes, 55,500 and
+// 67,800 at the first two):
+//   m = 25.6 M  P = 4   k = m/4   2260 .. 2890 / 1760      m = 25.6 M  P = 32  k = m/4     15,000 .. 18,600 / 9600
+//   m = 4.2 M   P = 4   k = m/8     390 .. 475 / 530       m = 4.2 M   P = 2   k = 0.31 m       277 .. 315 / 467
+// So short rows lose to the lists there: without such rows the last two take 220 / 201 and 186 / 138.  (The walk reads its
+// keys with sixteen loads in flight per lane; as long as each was changed inside its own condition, one after the other, the
+// walk of two rows of 4.2 M took 147 us instead of 49.)
 #pragma once
 #include "common.hip.h"
 
@@ -630,6 +633,8 @@ __device__ inline void count_all(const GroupSets& gs, const GroupBatch& gb, uint
 // Block 0 of row p: the next round's pair p; blocks from 1 on: sixteen waves with kGrpWalkRuns groups each of set p.
 // The list is short (tens of keys to a few thousand): the keys of a run that are all one key are one entry.
 // Two groups per wave: 69 us for the 32 workers' sets at m = 25,557,032, k = 6.4 M; one 97, four 88 (the longest runs bound it).
+// Long runs (hot layers that hold most of the bracket's keys) are read sixteen loads at a time: m = 1.05 M, P = 16, k = m / 4, ten
+// layers 33 .. 26 -> 23 .. 18 us a launch (four loads, and one in the second walk, before).
 __global__ __launch_bounds__(kGrpWalkBlock) void k_group_walk(GroupSets gs, GroupBatch gb, GroupSample sm) {
     constexpr int kWaves = kGrpWalkBlock / kWave;
     constexpr uint32_t kStash = 64;                          // entries a wave parks
