@@ -28,7 +28,7 @@
 // 67,800 at the first two):
 //   m = 25.6 M  P = 4   k = m/4   2260 .. 2890 / 1760      m = 25.6 M  P = 32  k = m/4     15,000 .. 18,600 / 9600
 //   m = 4.2 M   P = 4   k = m/8     390 .. 475 / 530       m = 4.2 M   P = 2   k = 0.31 m       277 .. 315 / 467
-// So short rows lose to the lists there: without such rows the last two take 220 / 201 and 186 / 138.  (The walk reads its
+// So short rows lose to the lists there: without such rows the last two take 221 / 206 and 186 / 145.  (The walk reads its
 // keys with sixteen loads in flight per lane; as long as each was changed inside its own condition, one after the other, the
 // walk of two rows of 4.2 M took 147 us instead of 49.)
 #pragma once

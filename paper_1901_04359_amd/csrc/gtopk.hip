@@ -432,8 +432,8 @@ GroupWs carve_grouped(const StepWs& s, int64_t m, uint32_t k, uint32_t P) {
 // on.  Its tree has no fewer launches, so short rows stay with the other one but for the highest densities (up to a
 // third: above that a bracket has little room) and where all workers together have some 0.8 M entries per round of the tree,
 // two added: with fewer, rows whose bracket's keys crowd into a few layers lose.  Those, in us, lists / groups, ten layers |
-// 24 equal ones:  m = 1.05 M  P = 16  k = m/4  309 / 332 | 316 / 309   m = 2.1 M  P = 8  k = m/5  263 / 263 | 257 / 234 (left out)
-// m = 1.05 M  P = 16  k = m/3  340 / 322 | 348 / 326   m = 1.9 M  P = 16  k = m/5  0.96 | 0.91 of the lists' time (taken).
+// 24 equal ones:  m = 1.05 M  P = 16  k = m/4  309 / 332 | 316 / 309   m = 2.1 M  P = 8  k = m/5  263 / 263 | 268 / 244 (left out)
+// m = 1.05 M  P = 16  k = m/3  340 / 322 | 348 / 326   m = 1.9 M  P = 16  k = m/5  369 / 355 | 382 / 346 (taken).
 // Lower lines in general; a step in us, lists / groups, rows of 20 layers | of one:
 //   m = 25.6 M  P = 32  k = m/4   6434 / 4488 | 7199 / 5576     m/8  4813 / 3955 | 5129 / 4545     m/10  4293 / 3785 | 4482 / 4308
 //   m = 25.6 M  P = 8   k = m/4   1856 / 1386 | 1933 / 1479     m/8  1280 / 1097 | 1306 / 1269     m/10  1129 / 1065 | 1175 / 1221
